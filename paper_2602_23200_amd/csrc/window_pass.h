@@ -16,37 +16,6 @@ typedef float w_float4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 w_half4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t w_u32x2 __attribute__((ext_vector_type(2)));
 
-// Element (token t, channel c) of one tensor of sequence-head bh, decoded per Eq. hybrid_dequant.
-__device__ inline float fetch_element(const TensorView& tv, const AttnArgs& a, long long bh, long long t, int c) {
-  constexpr int D = kHeadDim;
-  if (tv.newest && t == a.n_tokens - 1) return __half2float(tv.newest[bh * D + c]);
-  if (t < tv.n_sink) return __half2float(tv.sink[(bh * a.w_sink + t) * D + c]);
-  const long long row = t - a.w_sink;
-  if (row >= tv.n_quant) return __half2float(tv.ring[(bh * tv.slots + (t % tv.slots)) * D + c]);
-  const long long lin = store_row(a.pages, a.n_kv_heads, a.capacity, bh, row);     // (contiguous: bh * capacity + row)
-  if (tv.form == kFp16) return __half2float(reinterpret_cast<const __half*>(tv.codes)[lin * D + c]);
-  const int bits = tv.bits, G = a.group;
-  long long si;
-  unsigned field;
-  // field i of a packed run of n fields that starts at byte address p (3-bit: a plane of 2-bit
-  // low parts, n/4 bytes, then a plane of high bits)
-  auto field_of = [&](const uint8_t* p, int i, int n) -> unsigned {
-    if (bits == 3) return ((p[i / 4] >> (2 * (i % 4))) & 3u) | (((p[n / 4 + i / 8] >> (i % 8)) & 1u) << 2);
-    return (p[(i * bits) / 8] >> ((i * bits) % 8)) & ((1u << bits) - 1u);
-  };
-  if (tv.form == kPerToken) {
-    field = field_of(tv.codes + (lin * D * bits) / 8, c, D);
-    si = lin * (D / G) + c / G;
-  } else {
-    si = (store_row(a.pages, a.n_kv_heads, a.capacity, bh, row - row % G) / G) * D + c;
-    field = field_of(tv.codes + si * ((G * bits) / 8), (int)(row % G), G);
-  }
-  const float s = __half2float(tv.scales[si]);
-  const bool asym = __float_as_uint(s) >> 31;
-  const float S = fabsf(s);
-  return asym ? S * (float)field + __half2float(tv.zeros[si]) : S * (float)((int)field - (1 << (bits - 1)));
-}
-
 // fp16 row of token t if that tensor keeps it in fp16 (sink window, recent ring, fp16 store, or the
 // not yet appended newest token), else null.  For the contiguous store only (the fused kernels whose store is
 // fp16 do not take paged caches).  Written for a caller that asks for many rows per
