@@ -216,10 +216,8 @@ int innerq_quantize_append(const innerq_config_t *cfg, innerq_cache_t *cache, co
  * Eq. kv_cache_init_quantized_window).  Same arguments as those two calls; the cache must be empty
  * (n_tokens == 0, else INNERQ_E_ARG); norm_out / inv_norm_out are written as by
  * innerq_calibrate_key_norm and the cache contents are bit-identical to the two separate calls.
- * What it saves: the maximum over the keys runs in the same launch as everything that does not
- * depend on it (quantising the values, filling the value windows), so the prompt's keys are read
- * twice and its values once in three launches instead of four, and the memory-bound maximum hides
- * behind the arithmetic-bound value quantisation. */
+ * It is three launches (clear, maximum over the keys, quantisation), and the prompt's keys are read twice, its values
+ * once. */
 int innerq_prefill(const innerq_config_t *cfg, innerq_cache_t *cache, const void *k_fp16,
                    const void *v_fp16, int64_t n_tokens, int per_head, float *norm_out,
                    float *inv_norm_out, void *hip_stream);

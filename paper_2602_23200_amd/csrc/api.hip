@@ -107,6 +107,11 @@ PageMap pages_of(const innerq_config_t& c, const innerq_cache_t& k) {
   return pm;
 }
 
+thread_local hipEvent_t g_prof_start = nullptr, g_prof_stop = nullptr;
+
+}  // namespace
+
+namespace innerq {
 // Compute units of the current device (queried once per device; a host-side attribute read).
 int compute_units() {
   static CachedInt cached[64];
@@ -118,10 +123,7 @@ int compute_units() {
     return n;
   });
 }
-
-thread_local hipEvent_t g_prof_start = nullptr, g_prof_stop = nullptr;
-
-}  // namespace
+}  // namespace innerq
 
 extern "C" {
 
@@ -246,10 +248,6 @@ static QuantArgs quant_args(const innerq_config_t* cfg, const innerq_cache_t* ca
     j.row_end = partition_of(*cfg, w, to).n_quant;
     // new tokens from this index on stay in the recent ring at the end of this call
     j.ring_from = cfg->w_sink + partition_of(*cfg, w, n1).n_quant;
-    // per-token form: eight lanes share a group when the call is short (a decode step: the
-    // dependent chain is what costs), one lane takes a whole group when there is bulk to fill the chip
-    const long long groups = (long long)cfg->batch * cfg->n_kv_heads * (j.row_end - j.row_begin) * (kHeadDim / cfg->group);
-    j.lanes = groups >= 4096 ? 1 : 8;
     j.normalise = (w == 0 && k_inv_norm) ? 1 : 0;
   }
   return a;
@@ -298,9 +296,11 @@ int innerq_prefill(const innerq_config_t* cfg, innerq_cache_t* cache, const void
   if (misaligned(k_fp16) || misaligned(v_fp16) || misaligned(norm_out) || misaligned(inv_norm_out)) return INNERQ_E_ALIGN;
   if (n_tokens < 1 || (per_head != 0 && per_head != 1) || cache->n_tokens != 0) return INNERQ_E_ARG;
   if (n_tokens > cfg->capacity_tokens) return INNERQ_E_CAPACITY;
+  hipError_t e = launch_calibrate(static_cast<const __half*>(k_fp16), cfg->batch, cfg->n_kv_heads, n_tokens, per_head,
+                                  norm_out, inv_norm_out, static_cast<hipStream_t>(hip_stream));
+  if (e != hipSuccess) return INNERQ_E_HIP;
   const QuantArgs a = quant_args(cfg, cache, k_fp16, v_fp16, n_tokens, inv_norm_out, 0, n_tokens);
-  const hipError_t e = launch_prefill(a, static_cast<const __half*>(k_fp16), n_tokens, per_head, norm_out, inv_norm_out,
-                                      static_cast<hipStream_t>(hip_stream));
+  e = launch_quantize(a, static_cast<hipStream_t>(hip_stream));
   if (e != hipSuccess) return INNERQ_E_HIP;
   cache->n_tokens = n_tokens;
   cache->store_ahead_tokens = n_tokens;
@@ -583,7 +583,6 @@ int innerq_decode_step_ragged(const innerq_config_t* cfg, const innerq_cache_t* 
     j.row_begin = 0;
     j.row_end = j.form == kPerChannel ? cfg->group : 1;
     j.ring_from = 0;
-    j.lanes = 8;
   }
   return launch_quantize(a, static_cast<hipStream_t>(hip_stream), &merge) == hipSuccess ? INNERQ_OK : INNERQ_E_HIP;
 }

@@ -110,7 +110,6 @@ struct QuantTensorJob {
   uint8_t* codes; __half* scales; __half* zeros; __half* sink; __half* ring;
   const __half* x_new;       // [B][Hk][t_new][d]
   int form, mode, slots, bits;
-  int lanes;                      // per-token form: lanes that share one group (8: short calls, 1: bulk)
   long long row_begin, row_end;   // store rows to quantise in this call (token = w_sink + row)
   long long ring_from;            // new tokens with index >= ring_from go to the ring
   int normalise;                  // apply k_inv_norm to tokens taken from x_new
@@ -134,9 +133,9 @@ struct AttnArgs;
 // merge (may be null): the log-sum-exp merge of an attention call whose partials are complete on
 // this stream rides in the same launch (or, for the rare two-launch appends, goes first).
 hipError_t launch_quantize(const QuantArgs& a, hipStream_t stream, const AttnArgs* merge = nullptr);
-// Calibration and bulk append of one prompt into an empty cache in three launches (zero, maxima + values, keys).
-hipError_t launch_prefill(const QuantArgs& a, const __half* k, long long n_tokens, int per_head, float* norm_out,
-                          float* inv_out, hipStream_t stream);
+// The same append for calls with enough groups to fill the chip (quantize_bulk.hip); launch_quantize routes to it.
+bool bulk_append_supported(const QuantArgs& a);
+hipError_t launch_quantize_bulk(const QuantArgs& a, hipStream_t stream);
 hipError_t launch_calibrate(const __half* k, int batch, int n_kv_heads, long long n_tokens, int per_head,
                             float* norm_out, float* inv_out, hipStream_t stream);
 
@@ -207,6 +206,8 @@ struct CachedInt {
     return x;
   }
 };
+
+int compute_units();   // of the current device
 
 // Comparison kernel over an unquantised fp16 store, same launch shape.
 bool attention_fp16_supported(const AttnArgs& a);

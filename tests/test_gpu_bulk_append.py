@@ -1,0 +1,77 @@
+"""The bulk quantiser (one launch for a chunk: rows that leave the ring, new rows, window copies) against the oracle.
+
+Every byte is compared.  The sizes cross the edges of its units: rows per wavefront (16 at G = 32, 32 at G = 64), groups
+per wavefront of a ring slice, chunks shorter and longer than the windows, a chunk that ends inside a group.
+"""
+import numpy as np
+import pytest
+
+from oracle import innerq_oracle as orc
+from paper_2602_23200_amd import workloads as wl
+from tests.helpers import assert_cache_equal, gpu_config, oracle_config
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    import torch
+    from paper_2602_23200_amd import binding as iq
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    iq.lib()
+    return torch, iq
+
+
+def values(rng, shape, dist):
+    x = rng.standard_normal(shape).astype(np.float32)
+    if dist == "ties":                                    # quarters: codes on exact halves, both signs of zero
+        x = np.round(x * 6) / 4
+    elif dist == "denormal":                              # scales that are fp16 denormals: codes are clamped
+        x = x * 2.0 ** -17
+    elif dist == "wide":                                  # 2^-20 .. 2^14 side by side: differences that fp32 rounds
+        x = x * np.exp2(rng.integers(-20, 14, shape))
+    return x.clip(-60000, 60000).astype(np.float16)
+
+
+@pytest.mark.parametrize("dist", ["normal", "ties", "denormal", "wide"])
+@pytest.mark.parametrize("kind,bits,group,modes,literal,recent,chunks", [
+    (orc.KIND_INNER, 2, 32, (orc.HYBRID, orc.HYBRID), 0, 128, (133, 2, 64, 501, 17, 300)),
+    (orc.KIND_INNER, 4, 64, (orc.SYM, orc.ASYM), 0, 32, (300, 65, 64, 63)),
+    (orc.KIND_INNER, 3, 32, (orc.HYBRID, orc.HYBRID), 1, 48, (1037, 50, 33)),
+    (orc.KIND_INNER, 2, 64, (orc.SYM, orc.HYBRID), 1, 100, (700, 129)),
+    (orc.KIND_OUTER, 3, 64, (orc.HYBRID, orc.SYM), 0, 64, (400, 100, 257)),
+    (orc.KIND_OUTER, 4, 32, (orc.HYBRID, orc.HYBRID), 0, 300, (1500, 31, 700)),
+])
+@pytest.mark.parametrize("norm", [False, True])
+def test_bulk_append_bit_exact(env, kind, bits, group, modes, literal, recent, chunks, norm, dist):
+    torch, iq = env
+    n = sum(chunks)
+    w = wl.Workload("b", 2, 3, 3, 128, n, bits, group, 4, recent, k_mode=modes[0], v_mode=modes[1])
+    o = oracle_config(w, kind=kind, sym_denominator=literal)
+    rng = np.random.default_rng(n + bits)
+    K, V = values(rng, (2, 3, n, 128), dist), values(rng, (2, 3, n, 128), dist)
+    inv = rng.uniform(0.3, 1.0, (3, 128)).astype(np.float32) if norm else None
+    want = orc.cache_init_prefill(o, K, V, k_inv_norm=inv)
+    g = iq.allocate_cache(gpu_config(o))
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    at = 0
+    for c in chunks:
+        iq.innerq_quantize_append(g, dev(K[:, :, at:at + c]), dev(V[:, :, at:at + c]), None if inv is None else dev(inv))
+        at += c
+    assert_cache_equal(g, want, o)
+
+
+@pytest.mark.parametrize("batch,heads,n_tokens", [(1, 1, 1), (2, 3, 255), (1, 5, 257), (3, 2, 1100), (1, 33, 600)])
+@pytest.mark.parametrize("per_head", [False, True])
+def test_calibration_exact(env, batch, heads, n_tokens, per_head):
+    """Slices of one and several passes, fewer and more heads than the finishing threads take at once."""
+    torch, iq = env
+    rng = np.random.default_rng(heads)
+    K = (rng.standard_normal((batch, heads, n_tokens, 128)) * 30).astype(np.float16)
+    K[:, :, :, 5] = 0
+    w = wl.Workload("c", batch, heads, heads, 128, n_tokens, 2, 32, 4, 32)
+    for _ in range(3):
+        norm, inv = iq.innerq_calibrate_key_norm(gpu_config(oracle_config(w)), torch.from_numpy(K).cuda(), per_head=per_head)
+        norm_o, inv_o = orc.calibrate_key_norm(K, per_head=per_head)
+        assert np.array_equal(norm.cpu().numpy(), norm_o.astype(np.float32))
+        assert np.array_equal(inv.cpu().numpy(), inv_o.astype(np.float32))
