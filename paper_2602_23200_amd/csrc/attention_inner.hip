@@ -14,16 +14,19 @@
 // fields and one multiply per group applies the scale.
 //
 // Mapping to CDNA4:
-//   * inner sums run on the matrix cores with v_mfma_f32_4x4x4_16B_f16: 16
-//     independent 4x4x4 blocks per instruction, A = 4 query heads x 4 inner
-//     indices (shared by all blocks), B = 4 inner indices x 4 lanes.  In the score
-//     pass a lane owns one token, in the value pass two channels, and the result
-//     lands in the lane that holds that token's / channel's scale: no cross-lane
-//     traffic.
+//   * inner sums run on the matrix cores with v_mfma_f32_16x16x32_f16 as four 4 x 8 x 16 products side by side: the
+//     A operand (4 query heads x 8 inner indices) stands on the diagonal of 16 x 32, and lane l's four results are its
+//     own column (8 inner indices of its token or channel) for the four heads.  In the score pass a lane owns one
+//     token, in the value pass two channels, and the result lands in the lane that holds that token's / channel's
+//     scale: no cross-lane traffic.  (The 4x4x4 form has the same multiply rate at twice the instructions; a tile
+//     takes 36 instead of 82, since the normaliser needs one with all A rows alike instead of a chain.)
 //   * a b-bit field becomes an fp16 operand with ONE and per two fields: masked in
-//     place inside a 16-bit half it is the fp16 denormal u * 2^(b*pos) * 2^-24
-//     (the matrix cores keep fp16 denormals); the position factor is folded into
+//     place inside a 16-bit half it is an fp16 denormal u * 2^(off - 24) (the matrix cores keep fp16
+//     denormals; see Fields for the offsets); the offset's factor is folded into
 //     the A operand (query / probabilities), the constant into the group scale.
+//     Measured, 8 x 8 heads x 32k tokens, 2-bit, step: 41.2 us -> 39.8 (3-bit 59.3 -> 56.9; 8 query heads per kv head,
+//     16k tokens, 3-bit keys 31.7 -> 27.5; sequences of 1k to 16k tokens 39.3 -> 36.6), error against fp64 2.8e-4 -> 2.3e-4
+//     (4-bit, 4k tokens 5.5e-4 -> 2.9e-4; 128k tokens 1.9e-4 -> 0.8e-4).
 //   * 3-bit fields are stored as a plane of 2-bit low parts followed by a plane of
 //     high bits; the high bits are 1-bit fields of the same kind (2^(pos - 24)) and
 //     join the same MFMA chains through operand tables that carry their weight 4.
@@ -52,6 +55,7 @@ constexpr bool kPagedStore = INNERQ_PAGED_STORE != 0;
 
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -67,18 +71,27 @@ __device__ inline _Float16 half_of(uint32_t w, int hi) {
   return __builtin_bit_cast(_Float16, (unsigned short)(hi ? (w >> 16) : (w & 0xffffu)));
 }
 
+// Where the fields of a 32-bit word are masked out: after an optional shift of the whole word, field f of a 16-bit
+// half sits at bit off(f) of it.  The offsets are kept high in the 10 mantissa bits: the matrix cores line products
+// up by the operands' exponent fields, and a denormal's is that of 2^-14 however many leading zeros it has, so a
+// field at offset 0 loses about ten bits of its product's sum (measured: 1e-6 relative, rounded towards zero,
+// with the fields of a word at offsets 0 .. 8; nothing lost with the offsets below).
 template <int BITS>
 struct Fields {
   static constexpr int FPW = 32 / BITS;        // fields per 32-bit word
   static constexpr int HALF = FPW / 2;         // fields per 16-bit half
-  static constexpr int MPW = HALF / 2;         // MFMAs per word (each eats two field positions x two halves)
-  static constexpr int SH = BITS == 2 ? 10 : 8;        // one shift brings the upper fields of both halves down
-  static constexpr int NDIRECT = BITS == 2 ? 5 : (BITS == 1 ? 8 : 2);   // field positions used unshifted
-  static __host__ __device__ constexpr int pos(int f) { return f < NDIRECT ? f : f - NDIRECT; }
-  static __host__ __device__ constexpr uint32_t mask(int f) {
-    return (uint32_t)(((1u << BITS) - 1u) * 0x00010001u) << (BITS * pos(f));
+  static constexpr int MPW = HALF / 2;         // groups of two field positions x two halves (two groups a matrix instruction)
+  // shift of the word that field position f is read from: 0, 1 (left by SHL) or 2 (right by SHR)
+  static constexpr int SHL = BITS == 2 ? 4 : BITS == 4 ? 2 : 8;
+  static constexpr int SHR = BITS == 1 ? 8 : 6;
+  static __host__ __device__ constexpr int from(int f) {
+    return BITS == 2 ? (f < 2 ? 1 : f < 5 ? 0 : 2) : BITS == 4 ? (f < 2 ? 1 : 2) : (f < 2 ? 1 : f < 10 ? 0 : 2);
   }
-  static __host__ __device__ constexpr uint32_t ones(int f) { return 0x00010001u << (BITS * pos(f)); }
+  static __host__ __device__ constexpr int off(int f) { return BITS * f + (from(f) == 1 ? SHL : from(f) == 2 ? -SHR : 0); }
+  static __host__ __device__ constexpr uint32_t mask(int f) {
+    return (uint32_t)(((1u << BITS) - 1u) * 0x00010001u) << off(f);
+  }
+  static __host__ __device__ constexpr uint32_t ones(int f) { return 0x00010001u << off(f); }
   // index of inner position e (0..FPW) inside its word's operand table: [mfma][slot]
   static __host__ __device__ constexpr int slot(int e) {
     const int hi = e / HALF, f = e % HALF;
@@ -86,23 +99,44 @@ struct Fields {
   }
 };
 
+// A word and its two shifted copies.
 template <int BITS>
-__device__ inline half4_t operand(uint32_t w, uint32_t w_shifted, int m) {
+struct Shifted {
+  uint32_t w[3];
+  __device__ __forceinline__ explicit Shifted(uint32_t v) {
+    w[0] = v;
+    w[1] = v << Fields<BITS>::SHL;
+    w[2] = v >> Fields<BITS>::SHR;
+  }
+  __device__ __forceinline__ Shifted() {}
+};
+
+// B operand of one matrix instruction: the fields of positions 2 m .. 2 m + 3 of both halves (m even).
+template <int BITS>
+__device__ inline half8_t operand(const Shifted<BITS>& w, int m) {
   using F = Fields<BITS>;
-  const int f0 = 2 * m, f1 = 2 * m + 1;
-  u32x2 r;
-  r.x = (f0 < F::NDIRECT ? w : w_shifted) & F::mask(f0);
-  r.y = (f1 < F::NDIRECT ? w : w_shifted) & F::mask(f1);
-  return __builtin_bit_cast(half4_t, r);
+  uint32_t r[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int f = 2 * m + i;
+    r[i] = w.w[F::from(f)] & F::mask(f);
+  }
+  return __builtin_bit_cast(half8_t, u32x4{r[0], r[1], r[2], r[3]});
 }
 
+// 1 in the place of every field: eight consecutive entries of an operand table, from entry 8 kb on.
 template <int BITS>
-__device__ inline half4_t ones_operand(int m) {
+__device__ inline half8_t ones_operand(int kb) {
   using F = Fields<BITS>;
-  u32x2 r;
-  r.x = F::ones(2 * m);
-  r.y = F::ones(2 * m + 1);
-  return __builtin_bit_cast(half4_t, r);
+  constexpr int PER = F::FPW / 8;              // eights per word
+  uint32_t r[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    r[i] = F::ones(i);
+#pragma unroll
+    for (int e = 1; e < PER; ++e) r[i] = kb % PER == e ? F::ones(4 * e + i) : r[i];
+  }
+  return __builtin_bit_cast(half8_t, u32x4{r[0], r[1], r[2], r[3]});
 }
 
 __device__ inline float wave_max(float x) {
@@ -170,6 +204,10 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   constexpr int WPGK = G / FK::FPW, WPGV = G / FV::FPW;   // words per group (key: channels; value: tokens)
   constexpr int MPWK = FK::MPW, MPWV = FV::MPW;
   constexpr int HALFK = 1 << (KB - 1), HALFV = 1 << (VB - 1);
+  // A field of value u at offset `off` is the fp16 number u 2^(off - 24); the table entries of the other operand carry
+  // 2^(CK - off) (queries) and 2^(CV - off) (probabilities), 4 times that in the plane of high bits.  CK, CV: as large
+  // as fp16 allows with queries below 2^9, probabilities up to 2^kSlack and offsets from 4 (2-bit) or 2 on.
+  constexpr int CK = KB == 2 ? 10 : KB == 4 ? 8 : 6, CV = VB == 2 ? 13 : VB == 4 ? 11 : 10;
   constexpr int NH = NH4 * 4;
 
   // No division on the way to the first load: the grid is (splits, kv heads, batch), and the
@@ -229,12 +267,15 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     t1 = t0 + base_t + (j < rem_t ? 1 : 0);
   }
 
-  __shared__ __attribute__((aligned(16))) _Float16 qA[NH * D];          // query operand table [head][word][mfma][slot]
-  __shared__ __attribute__((aligned(16))) float qsum[NH4][NG][4];       // log2e/sqrt(d) * sum of q over each key group
-  __shared__ __attribute__((aligned(16))) _Float16 pA[NH * TILE];       // probability operand table [head][word][mfma][slot]
+  // Operand tables, a head's row padded by 16 bytes (four heads' rows then start in different banks).
+  constexpr int QS = D + 8, PS = TILE + 8;
+  __shared__ __attribute__((aligned(16))) _Float16 tables[NH * QS + NH * PS + D + (HIK ? NH * QS : 0) + (HIV ? NH * PS : 0)];
+  constexpr int QA = 0;                       // query operand table [head][word][mfma][slot]
+  constexpr int PA = QA + NH * QS;            // probability operand table [head][word][mfma][slot]
+  constexpr int ZERO = PA + NH * PS;          // zeros, as long as a row of either
   // the same two tables for the plane of high bits (1-bit fields, weight 4): [head][word][mfma][slot]
-  __shared__ __attribute__((aligned(16))) _Float16 qA1[HIK ? NH * D : 8];
-  __shared__ __attribute__((aligned(16))) _Float16 pA1[HIV ? NH * TILE : 8];
+  constexpr int QA1 = ZERO + D, PA1 = QA1 + (HIK ? NH * QS : 0);
+  __shared__ __attribute__((aligned(16))) float qsum[NH4][NG][4];       // log2e/sqrt(d) * sum of q over each key group
 
   // A wavefront without a tile (a launch with more wavefronts than tiles gives the window chunks
   // wavefronts of their own) skips all of the tile machinery, query tables included.
@@ -349,7 +390,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   if (t1 > t0) load_tile(t0, bufA);
 
   float q_coef[NH];
-  // ---- query: fp16 (optionally rescaled), position factors folded in.  A lane takes 8
+  // ---- query: fp16 (optionally rescaled), offset factors folded in.  A lane takes 8
   // consecutive channels of one head (one 16-byte load); the channels of one key group sit in
   // G/8 neighbouring lanes, so the group sums of q come from a few DPP adds.
 #pragma unroll
@@ -366,9 +407,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       part += qv[e];
       mx = __builtin_fmaxf(mx, __builtin_fabsf(qv[e]));
     }
-    // power of two that brings the head's largest |q| into [2^8, 2^9): the position factors span
-    // up to 2^-10 .. 2^6, so the table entries stay normal fp16 numbers down to 2^-13 of the
-    // head's maximum whatever the magnitude of the queries (a head is D/8 = 16 neighbouring lanes)
+    // power of two that brings the head's largest |q| into [2^8, 2^9): with factors of 2^-2 and more the
+    // table entries stay normal fp16 numbers down to 2^-20 of the head's maximum whatever the magnitude of the
+    // queries (a head is D/8 = 16 neighbouring lanes)
     static_assert(D / 8 == 16, "a head is one 16-lane row of the cross-lane operations below");
     mx = __builtin_fmaxf(mx, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, mx), 0xB1, 0xF, 0xF, true)));    // lane ^ 1
     mx = __builtin_fmaxf(mx, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, mx), 0x4E, 0xF, 0xF, true)));    // lane ^ 2
@@ -376,9 +417,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     mx = __builtin_fmaxf(mx, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, mx), 0x140, 0xF, 0xF, true)));   // mirror within 16
     const int q_exp = mx > 0.f ? (int)((__float_as_uint(mx) >> 23) & 0xffu) - 127 : 8;
     const float q_pow = __uint_as_float((uint32_t)(127 + 8 - q_exp) << 23);
-    // per-head constant of the score, log2e/sqrt(d) * 2^20 / (the head's factor): wave-uniform, so it
+    // per-head constant of the score, log2e/sqrt(d) * 2^(24 - CK) / (the head's factor): wave-uniform, so it
     // goes to scalar registers straight from the first lane of each head's row
-    const float coef = (kSmScale * kLog2e * 1048576.0f) * __uint_as_float((uint32_t)(127 - 8 + q_exp) << 23);
+    const float coef = (kSmScale * kLog2e * (float)(1 << (24 - CK))) * __uint_as_float((uint32_t)(127 - 8 + q_exp) << 23);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       q_coef[rnd * 4 + j] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, coef), 16 * j));
@@ -387,13 +428,12 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       const int c = c0 + e;
       const int word = c / FK::FPW, ep = c % FK::FPW;
       const int f = ep % FK::HALF;
-      const float factor = (float)(1 << (4 + LBK * 4)) / (float)(1 << (LBK * FK::pos(f) + LBK * 4));   // 2^(4 - b*pos)
-      qA[(h * NW + word) * (MPWK * 4) + FK::slot(ep)] = (_Float16)(qv[e] * q_pow * factor);
+      const float factor = (float)(1 << CK) / (float)(1 << FK::off(f));
+      tables[QA + h * QS + word * (MPWK * 4) + FK::slot(ep)] = (_Float16)(qv[e] * q_pow * factor);
       if constexpr (HIK) {
-        // 1-bit field at position pos of its half: 2^(pos - 24); weight 4 -> q * 2^(6 - pos)
         const int word1 = c / 32, ep1 = c % 32;
-        const float factor1 = 64.0f / (float)(1 << F1::pos(ep1 % 16));
-        qA1[(h * (D / 32) + word1) * (F1::MPW * 4) + F1::slot(ep1)] = (_Float16)(qv[e] * q_pow * factor1);
+        const float factor1 = (float)(4 << CK) / (float)(1 << F1::off(ep1 % 16));
+        tables[QA1 + h * QS + word1 * (F1::MPW * 4) + F1::slot(ep1)] = (_Float16)(qv[e] * q_pow * factor1);
       }
     }
     // sum over the G/8 lanes of the group (4 lanes: one quad; 8 lanes: two quads)
@@ -403,6 +443,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       part += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, part), 0x141, 0xF, 0xF, true));
     if ((idx % (G / 8)) == 0) qsum[h / 4][c0 / G][h % 4] = part * (kSmScale * kLog2e);
   }
+  *reinterpret_cast<uint32_t*>(&tables[ZERO + 2 * lane]) = 0u;
   __syncthreads();
 
   // ---- A operands of the zero-point term: sum over groups of Zeff_g * (sum of q over group g) is a
@@ -427,24 +468,54 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // ---- running softmax state (log2 domain) and output accumulators.
   // m_run is a reference level, not the exact running maximum: it is raised (and l, o rescaled)
   // only when some score exceeds it by more than kSlack, so the common tile pays no wave-wide
-  // reduction and no rescale.  Probabilities are then at most 2^kSlack, times the position
-  // factor 2^8: still inside fp16.  l_run and o are kept divided by 2^16 (the raw MFMA scale).
+  // reduction and no rescale.  Probabilities are then at most 2^kSlack, times a factor of at most
+  // 2^(CV - 2): still inside fp16.  l_run and o are kept in the raw scale of the matrix results.
   // The first tile sets the level to its exact maximum.
-  constexpr float kSlack = HIV ? 5.0f : 6.0f;           // (the high-bit plane's factors reach 2^10)
+  constexpr float kSlack = HIV ? 5.0f : 6.0f;           // (the high-bit plane's factors reach 2^CV)
   float m_run[NH], l_run[NH], o[NH][2];
 #pragma unroll
   for (int h = 0; h < NH; ++h) { m_run[h] = 0.f; l_run[h] = 0.f; o[h][0] = 0.f; o[h][1] = 0.f; }
 
-  // where this lane's token sits in the probability operand table, and its position factor
+  // where this lane's token sits in the probability operand table, and its offset factor
   const int p_e = lane % FV::FPW;
   const int p_index = (lane / FV::FPW) * (MPWV * 4) + FV::slot(p_e);
-  const float p_shift = (float)(8 - LBV * FV::pos(p_e % FV::HALF));        // p is stored as p * 2^(8 - b*pos)
-  // the same token in the high-bit plane's table: p * 4 * 2^(8 - pos), as a factor on the stored p
+  const float p_shift = (float)(CV - FV::off(p_e % FV::HALF));              // p is stored as p * 2^(CV - off)
+  // the same token in the high-bit plane's table: p * 4 * 2^(CV - off), as a factor on the stored p
   const int p1_e = lane % 32;
   const int p1_index = (lane / 32) * (F1::MPW * 4) + F1::slot(p1_e);
-  const float p1_factor = __builtin_amdgcn_exp2f((float)(10 - F1::pos(p1_e % 16)) - p_shift);
-  const int qa_lane = (lane & 3) * D;                                   // this lane supplies head (lane & 3) to A
-  const int pa_lane = (lane & 3) * TILE;
+  const float p1_factor = __builtin_amdgcn_exp2f((float)(CV + 2 - F1::off(p1_e % 16)) - p_shift);
+  // A operand of the 16x16x32 instructions: row l % 16, entries 8 (l / 16) .. + 7 of the contraction.  The matrix is
+  // block diagonal -- rows 4 j .. 4 j + 3 are the four heads, with entries only where block j of the contraction is
+  // -- so that lane l's result is its own column's product with its own eight B entries for the four heads (block
+  // j = l / 16 of rows 4 j ..).  Lanes off the diagonal read the zeros.
+  const bool diagonal = ((lane >> 2) & 3) == (lane >> 4);
+  int qa[NH4], pa[NH4], qa1[NH4], pa1[NH4];
+#pragma unroll
+  for (int n = 0; n < NH4; ++n) {
+    const int h = 4 * n + (lane & 3);
+    qa[n] = diagonal ? QA + h * QS : ZERO;
+    pa[n] = diagonal ? PA + h * PS : ZERO;
+    qa1[n] = diagonal ? QA1 + h * QS : ZERO;
+    pa1[n] = diagonal ? PA1 + h * PS : ZERO;
+  }
+  // the same instruction with all rows alike (row r = head r % 4) sums 32 table entries for every lane at once
+  const int pl_lane = PA + (lane & 3) * PS + 8 * (lane >> 4);
+  const half8_t ones = ones_operand<LBV>(lane >> 4);
+  auto a_operand = [&](int base, int entry) -> half8_t { return *reinterpret_cast<const half8_t*>(&tables[base + entry]); };
+
+  // The query operands stay in registers where they fit (64 for four heads): read from the table tile by tile, each
+  // matrix instruction of the score pass waits for its own LDS read.
+  constexpr bool QREG = NH4 == 1;
+  constexpr int KOPS = D / FK::FPW * MPWK / 2;           // matrix instructions per four heads and key row
+  half8_t q_op[QREG ? KOPS : 1];
+  if constexpr (QREG) {
+#pragma unroll
+    for (int i = 0; i < KOPS; ++i) {
+      u32x4 v = __builtin_bit_cast(u32x4, a_operand(qa[0], 8 * i));
+      asm volatile("" : "+v"(v));                        // (not to be read again)
+      q_op[i] = __builtin_bit_cast(half8_t, v);
+    }
+  }
 
   auto process = [&](const Regs& cur, int tile, bool first) {
     // sparse value zero-points: the lanes whose scale pair carries a flag fetch theirs now; they are
@@ -471,24 +542,19 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       for (int n = 0; n < NH4; ++n) acc[g][n] = float4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int wd = 0; wd < WPGK; ++wd) {
-      uint32_t w[NG], wsft[NG];
+      Shifted<LBK> w[NG];
 #pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        const int word = g * WPGK + wd;
-        w[g] = cur.k_word(word);
-        wsft[g] = w[g] >> FK::SH;
-      }
+      for (int g = 0; g < NG; ++g) w[g] = Shifted<LBK>(cur.k_word(g * WPGK + wd));
 #pragma unroll
-      for (int m = 0; m < MPWK; ++m) {
+      for (int m = 0; m < MPWK; m += 2) {
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
           const int word = g * WPGK + wd;
-          const half4_t bop = operand<LBK>(w[g], wsft[g], m);
+          const half8_t bop = operand<LBK>(w[g], m);
 #pragma unroll
-          for (int n = 0; n < NH4; ++n) {
-            const half4_t aop = *reinterpret_cast<const half4_t*>(&qA[n * 4 * D + qa_lane + (word * MPWK + m) * 4]);
-            acc[g][n] = __builtin_amdgcn_mfma_f32_4x4x4f16(aop, bop, acc[g][n], 0, 0, 0);
-          }
+          for (int n = 0; n < NH4; ++n)
+            acc[g][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                QREG ? q_op[QREG ? (word * MPWK + m) / 2 : 0] : a_operand(qa[n], (word * MPWK + m) * 4), bop, acc[g][n], 0, 0, 0);
         }
       }
     }
@@ -496,29 +562,23 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       // the plane of high bits joins the same chains: its query table carries the weight 4
 #pragma unroll
       for (int j = 0; j < HWG; ++j) {
-        uint32_t w[NG], wsft[NG];
+        Shifted<1> w[NG];
 #pragma unroll
-        for (int g = 0; g < NG; ++g) {
-          w[g] = cur.k_high(g * HWG + j);
-          wsft[g] = w[g] >> F1::SH;
-        }
+        for (int g = 0; g < NG; ++g) w[g] = Shifted<1>(cur.k_high(g * HWG + j));
 #pragma unroll
-        for (int m = 0; m < F1::MPW; ++m) {
+        for (int m = 0; m < F1::MPW; m += 2) {
 #pragma unroll
           for (int g = 0; g < NG; ++g) {
             const int word = g * HWG + j;
-            const half4_t bop = operand<1>(w[g], wsft[g], m);
+            const half8_t bop = operand<1>(w[g], m);
 #pragma unroll
-            for (int n = 0; n < NH4; ++n) {
-              const half4_t aop =
-                  *reinterpret_cast<const half4_t*>(&qA1[n * 4 * D + qa_lane + (word * F1::MPW + m) * 4]);
-              acc[g][n] = __builtin_amdgcn_mfma_f32_4x4x4f16(aop, bop, acc[g][n], 0, 0, 0);
-            }
+            for (int n = 0; n < NH4; ++n)
+              acc[g][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_operand(qa1[n], (word * F1::MPW + m) * 4), bop, acc[g][n], 0, 0, 0);
           }
         }
       }
     }
-    // e[h] = score (log2 domain) + position shift - reference level: the exponent of the stored probability.
+    // e[h] = score (log2 domain) + offset shift - reference level: the exponent of the stored probability.
     // Per group: |S| * (raw inner sum) + Zeff * (sum of q).  The scale sign bit marks an asymmetric
     // group, so max(s, 0) is |S| for a symmetric group and 0 for an asymmetric one, and
     // Zeff = Z - 2^(b-1) * max(s, 0) needs no select (Z is stored as +0 for symmetric groups).
@@ -558,7 +618,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     }
 #pragma unroll
     for (int h = 0; h < NH; ++h)
-      e[h] = __builtin_fmaf(q_coef[h], t[h], e[h]);   // undoes the operand factors (2^20) and the head's query factor
+      e[h] = __builtin_fmaf(q_coef[h], t[h], e[h]);   // undoes the operand factors and the head's query factor
 
     // ================= running softmax (Eq. att:2), probabilities to the operand table =================
     if (tile * TILE + (TILE - 1) > last_row) {         // ragged last tile: lanes past the end weigh nothing
@@ -586,8 +646,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
       const float p = __builtin_amdgcn_exp2f(e[h]);
-      pA[h * TILE + p_index] = (_Float16)p;
-      if constexpr (HIV) pA1[h * TILE + p1_index] = (_Float16)(p * p1_factor);
+      tables[PA + h * PS + p_index] = (_Float16)p;
+      if constexpr (HIV) tables[PA1 + h * PS + p1_index] = (_Float16)(p * p1_factor);
     }
     __syncthreads();
 
@@ -603,38 +663,37 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       }
 #pragma unroll
       for (int wd = 0; wd < WPGV; ++wd) {
-        const uint32_t wa = cur.v_word(gi, 0, wd), wb = cur.v_word(gi, 1, wd);
-        const uint32_t was = wa >> FV::SH, wbs = wb >> FV::SH;
+        const Shifted<LBV> wa(cur.v_word(gi, 0, wd)), wb(cur.v_word(gi, 1, wd));
 #pragma unroll
-        for (int m = 0; m < MPWV; ++m) {
-          const half4_t b0 = operand<LBV>(wa, was, m);
-          const half4_t b1 = operand<LBV>(wb, wbs, m);
-          const half4_t b1s = ones_operand<LBV>(m);
+        for (int m = 0; m < MPWV; m += 2) {
+          const half8_t b0 = operand<LBV>(wa, m);
+          const half8_t b1 = operand<LBV>(wb, m);
 #pragma unroll
           for (int n = 0; n < NH4; ++n) {
-            const half4_t aop =
-                *reinterpret_cast<const half4_t*>(&pA[n * 4 * TILE + pa_lane + ((gi * WPGV + wd) * MPWV + m) * 4]);
-            acc0[n] = __builtin_amdgcn_mfma_f32_4x4x4f16(aop, b0, acc0[n], 0, 0, 0);
-            acc1[n] = __builtin_amdgcn_mfma_f32_4x4x4f16(aop, b1, acc1[n], 0, 0, 0);
-            accl[n] = __builtin_amdgcn_mfma_f32_4x4x4f16(aop, b1s, accl[n], 0, 0, 0);
+            const half8_t aop = a_operand(pa[n], ((gi * WPGV + wd) * MPWV + m) * 4);
+            acc0[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop, b0, acc0[n], 0, 0, 0);
+            acc1[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop, b1, acc1[n], 0, 0, 0);
           }
         }
       }
+#pragma unroll
+      for (int e = 0; e < G; e += 32)
+#pragma unroll
+        for (int n = 0; n < NH4; ++n)
+          accl[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_operand(pl_lane + n * 4 * PS, gi * G + e), ones, accl[n], 0, 0, 0);
       if constexpr (HIV) {
 #pragma unroll
         for (int j = 0; j < HWG; ++j) {
-          const uint32_t wa = cur.v_high(gi, 0, j), wb = cur.v_high(gi, 1, j);
-          const uint32_t was = wa >> F1::SH, wbs = wb >> F1::SH;
+          const Shifted<1> wa(cur.v_high(gi, 0, j)), wb(cur.v_high(gi, 1, j));
 #pragma unroll
-          for (int m = 0; m < F1::MPW; ++m) {
-            const half4_t b0 = operand<1>(wa, was, m);
-            const half4_t b1 = operand<1>(wb, wbs, m);
+          for (int m = 0; m < F1::MPW; m += 2) {
+            const half8_t b0 = operand<1>(wa, m);
+            const half8_t b1 = operand<1>(wb, m);
 #pragma unroll
             for (int n = 0; n < NH4; ++n) {
-              const half4_t aop = *reinterpret_cast<const half4_t*>(
-                  &pA1[n * 4 * TILE + pa_lane + ((gi * HWG + j) * F1::MPW + m) * 4]);
-              acc0[n] = __builtin_amdgcn_mfma_f32_4x4x4f16(aop, b0, acc0[n], 0, 0, 0);
-              acc1[n] = __builtin_amdgcn_mfma_f32_4x4x4f16(aop, b1, acc1[n], 0, 0, 0);
+              const half8_t aop = a_operand(pa1[n], ((gi * HWG + j) * F1::MPW + m) * 4);
+              acc0[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop, b0, acc0[n], 0, 0, 0);
+              acc1[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop, b1, acc1[n], 0, 0, 0);
             }
           }
         }
@@ -652,7 +711,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
         z0 = S0 * (float)(-HALFV);
         z1 = S1 * (float)(-HALFV);
       }
-      // accl = 2^-16 * (sum of the fp16 probabilities of this group); l and o stay in that scale
+      // accl = 2^(CV - 24) * (sum of the fp16 probabilities of this group); l and o stay in that scale
 #pragma unroll
       for (int n = 0; n < NH4; ++n) {
 #pragma unroll
@@ -696,10 +755,10 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // ---- partial (m, l, o) of every real head, kept in registers over the window pass
 #pragma unroll
   for (int h = 0; h < NH; ++h) {
-    part_o[h].x = o[h][0] * 65536.0f;                  // 2^16 undoes the operand factors of the value pass
-    part_o[h].y = o[h][1] * 65536.0f;
+    part_o[h].x = o[h][0] * (float)(1 << (24 - CV));   // undoes the operand factors of the value pass
+    part_o[h].y = o[h][1] * (float)(1 << (24 - CV));
     part_m[h] = m_run[h] * kLn2;
-    part_l[h] = l_run[h] * 65536.0f;
+    part_l[h] = l_run[h] * (float)(1 << (24 - CV));
   }
   }
 
