@@ -152,6 +152,18 @@ __device__ inline float wave_max(float x) {
   return fmaxf(fmaxf(a, b), fmaxf(c, d));
 }
 
+// Inclusive sums over the lanes.
+struct Scan { int upto, total; };
+__device__ inline Scan wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);     // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);     // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);     // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);     // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);     // row_bcast:15 into rows 1, 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);     // row_bcast:31 into rows 2, 3
+  return {x, __builtin_amdgcn_readlane(x, 63)};
+}
+
 template <typename T>
 __device__ inline T stream_load(const T* p) { return __builtin_nontemporal_load(p); }
 
@@ -213,40 +225,83 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // No division on the way to the first load: the grid is (splits, kv heads, batch), and the
   // host passes the quotients (heads per kv head; tiles per plain wavefront and their remainder).
   const int lane = threadIdx.x;
-  const int hk = (int)blockIdx.y, b = (int)blockIdx.z;
+  const int hk = (int)blockIdx.y;
+  int b = (int)blockIdx.z, s_idx = (int)blockIdx.x;      // sequence; wavefront of its (b, hk)
   // The host's plan holds for every sequence -- unless the token counts live on the device
   // (a.n_dev: one count per sequence, the tokens cached BEFORE this step; attention runs over them
-  // plus the new token).  Then the launch shape (wavefronts, window chunks, partial slots) is the
+  // plus the new token).  Then the launch shape and the window chunks are the
   // host's, planned for the longest sequence allowed, and everything that depends on the length is
   // recomputed here for this wavefront's sequence: the partition of Eq. kv_cache_init_quantized_window,
-  // the window set and the split of the tiles over the wavefronts.  Wavefronts left without a tile
-  // write an empty partial.
+  // the window set and the split of the tiles over the wavefronts.  With one grid plane (BALANCED below) the wavefronts
+  // of a kv head are shared out over the sequences by their lengths; n_splits is then the most one sequence may get
+  // (its partial slots).  Wavefronts left without a tile write an empty partial, or nothing beyond their sequences.
   AttnArgs a = a_in;
   int n_both = n_both_in, win_tiles = win_tiles_in, base_t = base_t_in, rem_t = rem_t_in;
   WindowSet win = win_in;
   if (a_in.n_dev) {
-    long long N = (long long)a_in.n_dev[b] + 1;
-    N = N < 1 ? 1 : (N > a.capacity ? a.capacity : N);
-    if (a.n_copy && blockIdx.x == 0 && hk == 0 && lane == 0) a.n_copy[b] = (int)(N - 1);   // for the append that follows
     const int w_recent = a.k.slots - 1;                  // (the per-token key ring has w_recent + 1 slots)
-    const long long kq = quantised_rows(a.w_sink, w_recent, a.group, kPerToken, N);
-    const long long vq = quantised_rows(a.w_sink, w_recent, a.group, kPerChannel, N);
-    const int n_sink = (int)(N < a.w_sink ? N : a.w_sink);
-    a.n_tokens = N;
-    a.k.n_sink = n_sink; a.v.n_sink = n_sink;
-    a.k.n_quant = kq; a.v.n_quant = vq;
-    n_both = (int)vq;
-    win.na = n_sink;
-    win.b0 = a.w_sink + vq;
-    win.nb = N > win.b0 ? N - win.b0 : 0;
-    const int tiles = (n_both + TILE - 1) / TILE;
-    const int cost = win.n_chunks > 0 ? window_cost((win.na + win.nb + win.n_chunks - 1) / win.n_chunks, G) : 0;
-    const int quota = (tiles + win.n_chunks * cost + n_splits - 1) / n_splits;
-    win_tiles = quota > cost ? quota - cost : 0;
-    if (win.n_chunks > 0 && win_tiles > tiles / win.n_chunks) win_tiles = tiles / win.n_chunks;
-    const int rest = tiles - win.n_chunks * win_tiles, others = n_splits - win.n_chunks;
-    base_t = rest / others;
-    rem_t = rest % others;
+    const int n_chunks = win.n_chunks;
+    // counts fit 24 bits (capacity * head_dim <= 2^31); outside their bounds they are clamped
+    auto clamped = [&](int n) { return n + 1 < 1 ? 1 : ((long long)n + 1 > a.capacity ? (int)a.capacity : n + 1); };
+    struct Length { int n, n_sink, vq, win, tiles, cost; };
+    auto length = [&](int n) -> Length {
+      Length x;
+      x.n = n;
+      x.n_sink = n < a.w_sink ? n : a.w_sink;
+      int mid = n - a.w_sink - w_recent;
+      mid = mid < 0 ? 0 : mid;
+      x.vq = mid - mid % G;
+      const int b0 = a.w_sink + x.vq;
+      x.win = x.n_sink + (n > b0 ? n - b0 : 0);
+      x.tiles = (x.vq + TILE - 1) / TILE;
+      x.cost = n_chunks > 0 ? window_cost((uint32_t)(x.win + n_chunks - 1) / (uint32_t)n_chunks, G) : 0;
+      return x;
+    };
+    if (gridDim.z == 1 && a.batch > 1) {
+      // BALANCED (at most 64 sequences, a lane each): the smallest number of tiles per wavefront, window chunks counted
+      // in tiles, with which the sequences' wavefronts fit the launch.  No fewer than four tiles (a wavefront pays
+      // its query set-up once).
+      const int total = (int)gridDim.x;
+      const Length x = length(clamped(lane < a.batch ? a_in.n_dev[lane] : 0));
+      const int work = lane < a.batch ? x.tiles + n_chunks * x.cost : 0;
+      int quota = (wave_scan(work).total + total - 1) / total;
+      quota = quota < 4 ? 4 : quota;
+      int mine;
+      Scan sc;
+      for (;;) {
+        mine = (work + quota - 1) / quota;
+        mine = mine < n_chunks + 1 ? n_chunks + 1 : mine;
+        mine = mine > n_splits ? n_splits : mine;
+        mine = lane < a.batch ? mine : 0;
+        sc = wave_scan(mine);
+        if (sc.total <= total) break;                    // (the host: batch * (n_chunks + 1) <= total)
+        quota += 1 + (quota >> 3);
+      }
+      b = __popcll(__builtin_amdgcn_ballot_w64(lane < a.batch && s_idx >= sc.upto));
+      if (b >= a.batch) return;                            // (wave-uniform)
+      n_splits = __builtin_amdgcn_readlane(mine, b);
+      s_idx -= __builtin_amdgcn_readlane(sc.upto, b) - n_splits;
+    }
+    const Length x = length(clamped(a_in.n_dev[b]));
+    if (s_idx == 0 && hk == 0 && lane == 0) {
+      if (a.n_copy) a.n_copy[b] = x.n - 1;                 // for the append that follows
+      a.n_valid[b] = n_splits + n_chunks;                  // partial results of this sequence's heads
+    }
+    a.n_tokens = x.n;
+    a.k.n_sink = x.n_sink; a.v.n_sink = x.n_sink;
+    a.k.n_quant = x.n - a.w_sink - w_recent > 0 ? x.n - a.w_sink - w_recent : 0;
+    a.v.n_quant = x.vq;
+    n_both = x.vq;
+    win.na = x.n_sink;
+    win.b0 = a.w_sink + x.vq;
+    win.nb = x.win - x.n_sink;
+    const int quota = (int)((uint32_t)(x.tiles + n_chunks * x.cost + n_splits - 1) / (uint32_t)n_splits);
+    win_tiles = quota > x.cost ? quota - x.cost : 0;
+    const int most = n_chunks > 0 ? (int)((uint32_t)x.tiles / (uint32_t)n_chunks) : win_tiles;
+    win_tiles = win_tiles > most ? most : win_tiles;
+    const int rest = x.tiles - n_chunks * win_tiles, others = n_splits - n_chunks;
+    base_t = (int)((uint32_t)rest / (uint32_t)others);
+    rem_t = rest - base_t * others;
   }
   const long long bh = (long long)b * a.n_kv_heads + hk;
   constexpr bool has_kz = ZK, has_vz = ZV != 0;  // zero-point arrays exist unless the tensor is symmetric-only
@@ -256,7 +311,6 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // also serve one chunk of the fp16 windows each (after their tiles) and get win_tiles tiles;
   // the others share the remaining tiles evenly.
   const int n_tiles = (n_both + TILE - 1) / TILE;
-  const int s_idx = (int)blockIdx.x;
   int t0, t1;
   if (s_idx < win.n_chunks) {
     t0 = s_idx * win_tiles;
@@ -798,6 +852,7 @@ hipError_t launch_z(const AttnArgs& a, int n_both, int n_splits, const WindowSet
   const int rest = n_tiles - win.n_chunks * win_tiles, others = n_splits - win.n_chunks;
   const int base_t = rest / others, rem_t = rest % others;
   dim3 grid((unsigned)n_splits, (unsigned)a.n_kv_heads, (unsigned)a.batch);
+  if (a.shared_waves > 0) grid = dim3((unsigned)a.shared_waves, (unsigned)a.n_kv_heads, 1u);
   // (the launch with dispatch events only when events were asked for: the plain launch is the one a
   // stream capture is sure to record)
   const bool timed = L.ev_start || L.ev_stop;

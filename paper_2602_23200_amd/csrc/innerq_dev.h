@@ -154,6 +154,8 @@ struct AttnArgs {
   // kernel leaves a copy of them for the append that follows in the same step (workspace, [B])
   const int* n_dev;
   int* n_copy;
+  int* n_valid;             // with n_dev: partial results per head of every sequence (workspace, [B]), left by the fused kernel for the merge; else null
+  int shared_waves;         // with n_dev: wavefronts of a kv head that the sequences share by their lengths; 0: the same number each
   PageMap pages;
 };
 

@@ -39,9 +39,9 @@ struct MergeBatch {
 // together with the loads of (m, l): one memory round trip for the usual 30 to 50 partials.
 __device__ inline void merge_head(const AttnArgs& a, long long bhq, int lane) {
   constexpr int D = kHeadDim;
-  const int P = a.n_partials;
-  const float* ml = a.ws_ml + bhq * P * 2;
-  const float* po = a.ws_o + bhq * P * D + 2 * lane;
+  const float* ml = a.ws_ml + bhq * a.n_partials * 2;
+  const float* po = a.ws_o + bhq * a.n_partials * D + 2 * lane;
+  const int P = a.n_valid ? a.n_valid[(uint32_t)bhq / (uint32_t)a.n_q_heads] : a.n_partials;
   float n0 = 0.f, n1 = 0.f, den = 0.f;
   // (m, l) of partial 64 i + lane, for the first two chunks (the rest is re-read below)
   float2 mlv0 = {-INFINITY, 0.f}, mlv1 = {-INFINITY, 0.f};
