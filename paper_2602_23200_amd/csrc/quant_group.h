@@ -34,84 +34,8 @@ __device__ inline float code_quotient(float num, float S, float r) {
 // is the code the formula assigns when the scale is 0.
 __device__ inline float group_reciprocal(float S) { return S == 0.f ? 0.f : 1.0f / S; }
 
-// One pass over a group held in registers: packed fields and L1 error of the asymmetric and of
-// the symmetric variant (each only if the mode can choose it).
-template <int G, int BITS, typename X>
-__device__ inline void group_codes(X x, int mode, float mn, float Saf, float Ssf,
-                                   uint32_t (&wa)[G * BITS / 32], uint32_t (&ws)[G * BITS / 32], float& ea,
-                                   float& es) {
-  constexpr int W = G * BITS / 32;
-  constexpr int QMAX = (1 << BITS) - 1;
-  constexpr int HALF = 1 << (BITS - 1);
-#pragma unroll
-  for (int i = 0; i < W; ++i) { wa[i] = 0u; ws[i] = 0u; }
-  ea = 0.f; es = 0.f;
-  if (mode != INNERQ_SYM) {
-    const float rS = group_reciprocal(Saf);
-#pragma unroll
-    for (int i = 0; i < G; ++i) {
-      const float ca = __builtin_amdgcn_fmed3f(rintf(code_quotient(x(i) - mn, Saf, rS)), 0.f, (float)QMAX);
-      const float ra = Saf * ca + mn;
-      ea = ea + fabsf(x(i) - ra);
-      const uint32_t ua = (uint32_t)(int)ca;
-      if constexpr (BITS == 3) {
-        // a plane of 2-bit low parts (G/16 words), then a plane of high bits
-        wa[(i * 2) / 32] |= (ua & 3u) << ((i * 2) % 32);
-        wa[G / 16 + i / 32] |= (ua >> 2) << (i % 32);
-      } else {
-        wa[(i * BITS) / 32] |= ua << ((i * BITS) % 32);
-      }
-    }
-  }
-  if (mode != INNERQ_ASYM) {
-    const float rS = group_reciprocal(Ssf);
-#pragma unroll
-    for (int i = 0; i < G; ++i) {
-      const float cs = __builtin_amdgcn_fmed3f(rintf(code_quotient(x(i), Ssf, rS)), (float)(-HALF), (float)(HALF - 1));
-      const float rs = Ssf * cs;
-      es = es + fabsf(x(i) - rs);
-      const uint32_t us = (uint32_t)((int)cs + HALF);
-      if constexpr (BITS == 3) {
-        ws[(i * 2) / 32] |= (us & 3u) << ((i * 2) % 32);
-        ws[G / 16 + i / 32] |= (us >> 2) << (i % 32);
-      } else {
-        ws[(i * BITS) / 32] |= us << ((i * BITS) % 32);
-      }
-    }
-  }
-}
-
-// x(i), i = 0 .. G-1 with i a compile-time constant after unrolling, returns element i of the group
-// (a register array of floats, or packed fp16 pairs for groups too large to hold as floats).
-template <int G, int BITS, typename X>
-__device__ inline void quantize_group(X x, int mode, int sym_den_literal,
-                                      uint32_t (&words)[G * BITS / 32], __half& scale, __half& zero) {
-  constexpr int W = G * BITS / 32;
-  constexpr int QMAX = (1 << BITS) - 1;
-  constexpr int HALF = 1 << (BITS - 1);
-  float mn = x(0), mx = mn, am = fabsf(mn);
-#pragma unroll
-  for (int i = 1; i < G; ++i) {
-    const float v = x(i);
-    mn = fminf(mn, v);
-    mx = fmaxf(mx, v);
-    am = fmaxf(am, fabsf(v));
-  }
-  const float den = sym_den_literal ? (float)QMAX : (float)(HALF - 1);
-  const __half Sa = __float2half_rn((mx - mn) / (float)QMAX);
-  const __half Ss = __float2half_rn(am / den);
-  const float Saf = h2f(Sa), Ssf = h2f(Ss);
-  uint32_t wa[W], ws[W];
-  float ea, es;
-  group_codes<G, BITS>(x, mode, mn, Saf, Ssf, wa, ws, ea, es);
-  const bool asym = (mode == INNERQ_ASYM) || (mode == INNERQ_HYBRID && ea < es);
-#pragma unroll
-  for (int i = 0; i < W; ++i) words[i] = asym ? wa[i] : ws[i];
-  scale = asym ? __hneg(Sa) : Ss;
-  zero = asym ? __float2half_rn(mn) : __float2half_rn(0.f);
-}
-
-// ---- bulk form of the same quantiser, for launches that are bound by vector instructions.
+// ---- a group in one lane: the form of bulk launches, which are bound by vector instructions, and of the per-channel
+// groups of a decode step.
 //
 // It uses three facts, each exact, so that codes, flags and scales keep every bit:
 //   * rint(fl(num / S)) is the exact quotient rounded to nearest-even.  A tie k + 1/2 of the quotient is
@@ -327,13 +251,6 @@ __device__ inline uint32_t scaled_pair(uint32_t w, float lo, float hi) {
   uint32_t d;
   asm("v_cvt_pk_f16_f32 %0, %1, %2" : "=v"(d) : "v"(half_times(HalfRef{w, false}, lo)), "v"(half_times(HalfRef{w, true}, hi)));
   return d;
-}
-
-// Element i of a group kept as packed fp16 pairs.
-template <int N>
-__device__ inline float packed_half(const uint32_t (&xp)[N], int i) {
-  const uint32_t w = xp[i / 2];
-  return h2f(__ushort_as_half((unsigned short)((i & 1) ? (w >> 16) : (w & 0xffffu))));
 }
 
 // Index arithmetic of one launch is 32-bit: the host refuses launches of 2^32 or more threads, token

@@ -11,11 +11,11 @@
 namespace innerq {
 namespace {
 
-// The same group quantiser spread over 8 neighbouring lanes (lane `sub` of the group holds the
+// The group quantiser spread over 8 neighbouring lanes (lane `sub` of the group holds the
 // G/8 consecutive values x): the per-element divisions run in parallel, minimum / maximum are
 // exact in any order, and the two error sums are still taken one element after the other in
 // index order (every lane adds the whole chain from shuffled copies), so codes and flag are
-// bit-identical to quantize_group.  Returns this lane's share of the packed fields, shifted to
+// bit-identical to the form in one lane.  Returns this lane's share of the packed fields, shifted to
 // its place inside its 32-bit word and OR-ed over the lanes that share that word.
 template <int CTRL>
 __device__ inline float lane_swap(float v) {
@@ -185,43 +185,24 @@ __device__ __forceinline__ void quantize_rows(const QuantArgs& a, const QuantTen
     if (a.n_dev && !sequence_rows(a, j, bh, n_old, row_begin)) return;
     const long long tg = row_begin / G + (idx / kHeadDim - bh * n_groups);   // token-group index in the store
     const float inv = j.normalise ? a.inv_norm[mod32(bh, a.n_kv_heads) * kHeadDim + c] : 1.f;
-    uint32_t words[W];
-    __half s, z;
-    auto run = [&](auto fetch) {
-      if constexpr (G <= 32) {
-        float x[G];
-#pragma unroll
-        for (int i = 0; i < G; ++i) x[i] = h2f(fetch(i));
-        quantize_group<G, BITS>([&](int i) { return x[i]; }, j.mode, a.sym_den_literal, words, s, z);
-      } else {
-        // 64 floats do not fit the register file next to the rest: the group stays packed as fp16 pairs
-        uint32_t xp[G / 2];
-#pragma unroll
-        for (int p = 0; p < G / 2; ++p) {
-          const uint32_t lo = __half_as_ushort(fetch(2 * p)), hi = __half_as_ushort(fetch(2 * p + 1));
-          xp[p] = lo | (hi << 16);
-        }
-        quantize_group<G, BITS>([&](int i) { return packed_half(xp, i); }, j.mode, a.sym_den_literal, words, s, z);
-      }
-    };
     const long long t0 = a.w_sink + tg * G;              // first token of the group
-    if (t0 >= n_old) {
-      // the whole group comes from x_new (bulk calls): one base address, a fixed stride
-      const __half* src0 = j.x_new + ((bh * a.t_new) + (t0 - n_old)) * kHeadDim + c;
-      run([&](int i) -> __half {
-        __half v = src0[i * kHeadDim];
-        if (j.normalise) v = scaled_half(h2f(v), inv);
-        return v;
-      });
-    } else {
-      run([&](int i) -> __half {
-        bool from_new;
-        const __half* src = token_row(j, a, n_old, bh, t0 + i, from_new);
-        __half v = src[c];
-        if (from_new && j.normalise) v = scaled_half(h2f(v), inv);
-        return v;
-      });
+    const __half* fresh = j.x_new + ((bh * a.t_new) + (t0 - n_old)) * kHeadDim + c;     // (meaningful from token n_old on)
+    const __half* ring = j.ring + bh * j.slots * kHeadDim + c;
+    uint32_t slot = mod32(t0, j.slots);
+    uint32_t x[G];                                       // a value each, in the low half
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+      const bool from_new = t0 + i >= n_old;
+      __half v = *(from_new ? fresh + i * kHeadDim : ring + slot * kHeadDim);
+      if (from_new && j.normalise) v = scaled_half(h2f(v), inv);
+      x[i] = __half_as_ushort(v);
+      slot = slot + 1u == (uint32_t)j.slots ? 0u : slot + 1u;
     }
+    uint32_t mn, mx, words[W];
+    pair_range(x, mn, mx);
+    __half s, z;
+    quantize_group_bulk<G, BITS>([&](int i) { return HalfRef{x[i], false}; }, half_lo(mn), half_lo(mx), j.mode,
+                                 a.sym_den_literal, words, s, z);
     const long long go = (store_row(a.pages, a.n_kv_heads, a.capacity, bh, tg * G) / G) * kHeadDim + c;
     uint32_t* dst = reinterpret_cast<uint32_t*>(j.codes) + go * W;
 #pragma unroll
