@@ -308,8 +308,9 @@ __global__ void __launch_bounds__(1024 / ROWS) attention_generic_kernel(AttnArgs
   }
 }
 
-__global__ void __launch_bounds__(64) attention_merge_kernel(AttnArgs a) {
-  merge_head(a, blockIdx.x, threadIdx.x);
+template <int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) attention_merge_kernel(AttnArgs a) {
+  merge_head<WAVES>(a, blockIdx.x, threadIdx.x >> 6, threadIdx.x & 63);
 }
 
 }  // namespace
@@ -347,7 +348,9 @@ hipError_t launch_attention_generic(const AttnArgs& a, long long a0, long long a
 }
 
 hipError_t launch_attention_merge(const AttnArgs& a, hipStream_t stream) {
-  attention_merge_kernel<<<(unsigned)(a.batch * a.n_q_heads), 64, 0, stream>>>(a);
+  const unsigned heads = (unsigned)(a.batch * a.n_q_heads);
+  if (merge_is_shared(a)) attention_merge_kernel<4><<<heads, 256, 0, stream>>>(a);
+  else attention_merge_kernel<1><<<heads, 64, 0, stream>>>(a);
   return hipGetLastError();
 }
 

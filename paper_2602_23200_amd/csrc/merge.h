@@ -34,54 +34,74 @@ struct MergeBatch {
 };
 
 // out[b][hq][:] = sum_p w_p o_p / sum_p w_p l_p,  w_p = exp(m_p - max_p m_p).
-// One wavefront per query head, a lane per channel pair; the partial index is wave-uniform.
-// The partial outputs do not depend on the weights, so the loads of up to 64 of them go out
-// together with the loads of (m, l): one memory round trip for the usual 30 to 50 partials.
-__device__ inline void merge_head(const AttnArgs& a, long long bhq, int lane) {
+// WAVES wavefronts of a work-group (1: any single wavefront) per query head, a lane per channel pair; the
+// wavefronts take a contiguous share of the partials each and meet in LDS.  The partial outputs do not depend on the
+// weights, so the loads of up to 32 of them per wavefront go out together with the loads of (m, l): one memory round
+// trip for up to 32 (128 with four wavefronts) partials.
+struct MergeShare { float m, den, n0, n1; };
+
+template <int WAVES>
+__device__ inline void merge_head(const AttnArgs& a, long long bhq, int wave, int lane) {
   constexpr int D = kHeadDim;
-  const float* ml = a.ws_ml + bhq * a.n_partials * 2;
-  const float* po = a.ws_o + bhq * a.n_partials * D + 2 * lane;
-  const int P = a.n_valid ? a.n_valid[(uint32_t)bhq / (uint32_t)a.n_q_heads] : a.n_partials;
-  float n0 = 0.f, n1 = 0.f, den = 0.f;
-  // (m, l) of partial 64 i + lane, for the first two chunks (the rest is re-read below)
-  float2 mlv0 = {-INFINITY, 0.f}, mlv1 = {-INFINITY, 0.f};
-  if (lane < P) mlv0 = *reinterpret_cast<const float2*>(ml + 2 * lane);
-  if (64 + lane < P) mlv1 = *reinterpret_cast<const float2*>(ml + 2 * (64 + lane));
-  MergeBatch<32> first;                                  // partials 0 .. 31 of the first chunk
-  MergeBatch<16> second;                                 // partials 32 .. 47
-  const int n_first = P < 32 ? P : 32, n_second = P <= 32 ? 0 : (P < 48 ? P - 32 : 16);
-  first.load(po, 0, n_first);
-  if (n_second > 0) second.load(po, 32, n_second);
-  float mloc = fmaxf(mlv0.x, mlv1.x);
-  for (int p = 128 + lane; p < P; p += 64) mloc = fmaxf(mloc, ml[2 * p]);
-  const float M = window_wave_max(mloc);
-  for (int base = 0; base < P; base += 64) {
-    const int p_l = base + lane;
-    float2 mlv = base == 0 ? mlv0 : mlv1;
-    if (base >= 128 && p_l < P) mlv = *reinterpret_cast<const float2*>(ml + 2 * p_l);
-    float w_l = 0.f, l_l = 0.f;
-    if (p_l < P) {
-      w_l = mlv.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mlv.x - M) * 1.4426950408889634f);           // an empty partial has m = -inf
-      l_l = mlv.y;
-    }
-    float wl = w_l * l_l;
-    asm("" : "+v"(wl));                                 // keeps the product out of a fused add in the reduction
-    den += window_wave_sum(wl);
-    const int n = P - base < 64 ? P - base : 64;
-    int p0 = 0;
-    if (base == 0) {
-      first.add(w_l, n_first, n0, n1);
-      if (n_second > 0) {
-        const float w_s = __shfl(w_l, (lane + 32) & 63);  // weight of partial 32 + k in lane k
-        second.add(w_s, n_second, n0, n1);
+  const int n_all = a.n_valid ? a.n_valid[(uint32_t)bhq / (uint32_t)a.n_q_heads] : a.n_partials;
+  const int share = (n_all + WAVES - 1) / WAVES, from = WAVES == 1 ? 0 : wave * share;
+  const int P = WAVES == 1 ? n_all : (n_all - from < share ? n_all - from : share);     // (0 or less: nothing left)
+  const float* ml = a.ws_ml + (bhq * a.n_partials + from) * 2;
+  const float* po = a.ws_o + (bhq * a.n_partials + from) * D + 2 * lane;
+  float n0 = 0.f, n1 = 0.f, den = 0.f, M = -INFINITY;
+  if (WAVES == 1 || P > 0) {
+    // (m, l) of partial 64 i + lane, for the first two chunks (the rest is re-read below)
+    float2 mlv0 = {-INFINITY, 0.f}, mlv1 = {-INFINITY, 0.f};
+    if (lane < P) mlv0 = *reinterpret_cast<const float2*>(ml + 2 * lane);
+    if (64 + lane < P) mlv1 = *reinterpret_cast<const float2*>(ml + 2 * (64 + lane));
+    MergeBatch<32> first;                                // partials 0 .. 31 of the first chunk
+    const int n_first = P < 32 ? P : 32;
+    first.load(po, 0, n_first);
+    float mloc = fmaxf(mlv0.x, mlv1.x);
+    for (int p = 128 + lane; p < P; p += 64) mloc = fmaxf(mloc, ml[2 * p]);
+    M = window_wave_max(mloc);
+    for (int base = 0; base < P; base += 64) {
+      const int p_l = base + lane;
+      float2 mlv = base == 0 ? mlv0 : mlv1;
+      if (base >= 128 && p_l < P) mlv = *reinterpret_cast<const float2*>(ml + 2 * p_l);
+      float w_l = 0.f, l_l = 0.f;
+      if (p_l < P) {
+        w_l = mlv.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mlv.x - M) * 1.4426950408889634f);           // an empty partial has m = -inf
+        l_l = mlv.y;
       }
-      p0 = 48;
+      float wl = w_l * l_l;
+      asm("" : "+v"(wl));                               // keeps the product out of a fused add in the reduction
+      den += window_wave_sum(wl);
+      const int n = P - base < 64 ? P - base : 64;
+      int p0 = 0;
+      if (base == 0) {
+        first.add(w_l, n_first, n0, n1);
+        p0 = 32;
+      }
+      for (; p0 < n; p0 += 16) {
+        MergeBatch<16> more;
+        more.load(po, base + p0, n - p0 < 16 ? n - p0 : 16);
+        const float w_s = __shfl(w_l, (lane + p0) & 63);
+        more.add(w_s, n - p0 < 16 ? n - p0 : 16, n0, n1);
+      }
     }
-    for (; p0 < n; p0 += 16) {
-      MergeBatch<16> more;
-      more.load(po, base + p0, n - p0 < 16 ? n - p0 : 16);
-      const float w_s = __shfl(w_l, (lane + p0) & 63);
-      more.add(w_s, n - p0 < 16 ? n - p0 : 16, n0, n1);
+  }
+  if constexpr (WAVES > 1) {
+    __shared__ MergeShare part[WAVES][64];
+    part[wave][lane] = MergeShare{M, den, n0, n1};
+    __syncthreads();
+    if (wave != 0) return;
+    float top = M;
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) top = fmaxf(top, part[w][lane].m);
+    den = n0 = n1 = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+      const MergeShare s = part[w][lane];
+      const float f = s.m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((s.m - top) * 1.4426950408889634f);
+      den = __builtin_fmaf(f, s.den, den);
+      n0 = __builtin_fmaf(f, s.n0, n0);
+      n1 = __builtin_fmaf(f, s.n1, n1);
     }
   }
   const float inv = 1.0f / den;
@@ -96,5 +116,13 @@ __device__ inline void merge_head(const AttnArgs& a, long long bhq, int lane) {
   }
 }
 
+// Whether a head's partials are shared by four wavefronts: where there are many and work-groups are few.  (One rule for both
+// launches that merge, so that both give the same bits.)  Per step: 1 sequence x 4 heads x 512 partials 34.4 us -> 17.1,
+// 128 heads x 68 74.1 -> 73.1, 32 heads x 35 13.4 -> 13.1; 512 x 36 28.0 -> 29.5 and 1024 x 12 41.7 -> 44.7 (too many work-groups),
+// and in the attention call's own launch 256 x 35 34.0 -> 35.0.
+inline bool merge_is_shared(const AttnArgs& a) {
+  const long long heads = (long long)a.batch * a.n_q_heads;
+  return (a.n_partials >= 17 && heads <= 64) || (a.n_partials >= 49 && heads <= 256);
+}
 
 }  // namespace innerq

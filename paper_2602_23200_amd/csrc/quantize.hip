@@ -249,15 +249,16 @@ __global__ void __launch_bounds__(256) quantize_kernel(QuantArgs a, long long co
 }
 
 // The same launch with the log-sum-exp merge of an attention call riding along: the last
-// merge_blocks work-groups (of job 0) merge four query heads each, the ones before them are
+// work-groups (of job 0) merge four query heads each, or one where it has many partials (SHARED); the ones before them are
 // quantize_kernel (the longer dependent chain, so it is dispatched first).  The two jobs touch
 // disjoint memory (partials and output against store rows and window slots).
-template <int G>
+template <int G, bool SHARED>
 __global__ void __launch_bounds__(256) quantize_merge_kernel(QuantArgs a, long long copy_from, AttnArgs m,
                                                              int quant_blocks) {
   if ((int)blockIdx.x >= quant_blocks) {
-    const long long bhq = (long long)(blockIdx.x - quant_blocks) * 4 + (threadIdx.x >> 6);
-    if (blockIdx.y == 0 && bhq < (long long)m.batch * m.n_q_heads) merge_head(m, bhq, threadIdx.x & 63);
+    const int wave = threadIdx.x >> 6;
+    const long long bhq = SHARED ? (long long)blockIdx.x - quant_blocks : (long long)(blockIdx.x - quant_blocks) * 4 + wave;
+    if (blockIdx.y == 0 && bhq < (long long)m.batch * m.n_q_heads) merge_head<SHARED ? 4 : 1>(m, bhq, wave, threadIdx.x & 63);
     return;
   }
   const QuantTensorJob j = pick_job(a, (int)blockIdx.y);
@@ -308,10 +309,13 @@ hipError_t launch_quantize_t(const QuantArgs& a, hipStream_t stream, const AttnA
   if (merge && disjoint) {
     // one launch: the quantise threads, the window-copy threads, then the merge blocks
     const long long qthreads = ((threads + 255) / 256) * 256;
-    const int merge_blocks = (int)(((long long)merge->batch * merge->n_q_heads + 3) / 4);
+    const long long heads = (long long)merge->batch * merge->n_q_heads;
+    const bool shared = merge_is_shared(*merge);
+    const int merge_blocks = (int)(shared ? heads : (heads + 3) / 4);
     const int quant_blocks = (int)((qthreads + cthreads + 255) / 256);
     dim3 grid((unsigned)(quant_blocks + merge_blocks), 2);
-    quantize_merge_kernel<G><<<grid, 256, 0, stream>>>(a, qthreads, *merge, quant_blocks);
+    if (shared) quantize_merge_kernel<G, true><<<grid, 256, 0, stream>>>(a, qthreads, *merge, quant_blocks);
+    else quantize_merge_kernel<G, false><<<grid, 256, 0, stream>>>(a, qthreads, *merge, quant_blocks);
     return hipGetLastError();
   }
   if (merge) {
