@@ -119,10 +119,10 @@ __device__ inline void merge_head(const AttnArgs& a, long long bhq, int wave, in
 // Whether a head's partials are shared by four wavefronts: where there are many and work-groups are few.  (One rule for both
 // launches that merge, so that both give the same bits.)  Per step: 1 sequence x 4 heads x 512 partials 34.4 us -> 17.1,
 // 128 heads x 68 74.1 -> 73.1, 32 heads x 35 13.4 -> 13.1; 512 x 36 28.0 -> 29.5 and 1024 x 12 41.7 -> 44.7 (too many work-groups),
-// and in the attention call's own launch 256 x 35 34.0 -> 35.0.
+// 4 heads x 18 merge 3.4 -> 4.0, and in the attention call's own launch 256 x 35 34.0 -> 35.0.
 inline bool merge_is_shared(const AttnArgs& a) {
   const long long heads = (long long)a.batch * a.n_q_heads;
-  return (a.n_partials >= 17 && heads <= 64) || (a.n_partials >= 49 && heads <= 256);
+  return (a.n_partials >= 25 && heads <= 64) || (a.n_partials >= 49 && heads <= 256);
 }
 
 }  // namespace innerq
