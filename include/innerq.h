@@ -328,7 +328,7 @@ int innerq_decode_step(const innerq_config_t *cfg, innerq_cache_t *cache, const 
  *                 kernels; the second launch adds one to every entry.  cache->n_tokens and
  *                 cache->store_ahead_tokens (host) are neither read nor written.
  *   max_tokens    host: a bound, n_tokens_dev[b] + 1 <= max_tokens <= capacity_tokens for every b.
- *                 It only sizes the launch: wavefronts are planned for that length, and a batch of up to 64
+ *                 It only sizes the launch: wavefronts are planned for that length, and a batch of up to 32
  *                 sequences shares them by its lengths (larger ones get the same number each), so a
  *                 loose bound costs idle wavefronts, never correctness.  A count outside the bound
  *                 is clamped on the device (that sequence's result is then unspecified; no buffer

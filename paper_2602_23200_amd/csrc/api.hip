@@ -28,9 +28,12 @@ inline int split_cap(const innerq_config_t& c) {
   return (int)s;
 }
 
-// Bytes at the start of the workspace for two ints per sequence: the fused kernel of a ragged step leaves
-// the sequences' token counts there for the append that follows it, and how many partial results each has for the merge.
-inline size_t seq_bytes(const innerq_config_t& c) { return (((size_t)c.batch * 2 * sizeof(int) + 255) / 256) * 256; }
+// Bytes at the start of the workspace for one int per sequence: the fused kernel of a ragged step leaves
+// the sequences' token counts there for the append that follows it -- and, for batches that share the launch's
+// wavefronts by length, behind them how many partial results each sequence has (these fit the first 256 bytes).
+constexpr int kSharedBatchMost = 32;
+inline size_t seq_bytes(const innerq_config_t& c) { return (((size_t)c.batch * sizeof(int) + 255) / 256) * 256; }
+static_assert(2 * kSharedBatchMost * sizeof(int) <= 256, "both counts of a sequence in the first 256 bytes");
 
 int check_config(const innerq_config_t* c) {
   if (!c) return INNERQ_E_NULL;
@@ -358,7 +361,7 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
   a.sparse_zeros = c.sparse_zeros;
   a.n_dev = n_dev;
   a.n_copy = n_dev ? static_cast<int*>(workspace) : nullptr;
-  a.n_valid = n_dev ? static_cast<int*>(workspace) + c.batch : nullptr;
+  a.n_valid = nullptr;
   a.shared_waves = 0;
   a.pages = pages_of(c, *cache);
 
@@ -443,8 +446,9 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
     // their lengths (16 sequences of 1k to 16k tokens: 35.3 us per step with the same number each, 29.9 shared), as
     // many to one as it has partial slots.
     const long long shared = (long long)n_splits * c.batch;
-    if (n_dev && c.batch > 1 && c.batch <= 64 && (n_win_chunks + 1) * c.batch <= shared) {
+    if (n_dev && c.batch > 1 && c.batch <= kSharedBatchMost && (n_win_chunks + 1) * c.batch <= shared) {
       a.shared_waves = (int)shared;
+      a.n_valid = static_cast<int*>(workspace) + c.batch;
       n_splits = split_cap(c);
     }
   } else if (n_both > 0) {

@@ -232,7 +232,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // plus the new token).  Then the launch shape and the window chunks are the
   // host's, planned for the longest sequence allowed, and everything that depends on the length is
   // recomputed here for this wavefront's sequence: the partition of Eq. kv_cache_init_quantized_window,
-  // the window set and the split of the tiles over the wavefronts.  With one grid plane (BALANCED below) the wavefronts
+  // the window set and the split of the tiles over the wavefronts.  With shared_waves (BALANCED below) the wavefronts
   // of a kv head are shared out over the sequences by their lengths; n_splits is then the most one sequence may get
   // (its partial slots).  Wavefronts left without a tile write an empty partial, or nothing beyond their sequences.
   AttnArgs a = a_in;
@@ -257,8 +257,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       x.cost = n_chunks > 0 ? window_cost((uint32_t)(x.win + n_chunks - 1) / (uint32_t)n_chunks, G) : 0;
       return x;
     };
-    if (gridDim.z == 1 && a.batch > 1) {
-      // BALANCED (at most 64 sequences, a lane each): the smallest number of tiles per wavefront, window chunks counted
+    if (a.shared_waves > 0) {
+      // BALANCED (a sequence a lane): the smallest number of tiles per wavefront, window chunks counted
       // in tiles, with which the sequences' wavefronts fit the launch.  No fewer than four tiles (a wavefront pays
       // its query set-up once).
       const int total = (int)gridDim.x;
@@ -285,7 +285,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const Length x = length(clamped(a_in.n_dev[b]));
     if (s_idx == 0 && hk == 0 && lane == 0) {
       if (a.n_copy) a.n_copy[b] = x.n - 1;                 // for the append that follows
-      a.n_valid[b] = n_splits + n_chunks;                  // partial results of this sequence's heads
+      if (a.n_valid) a.n_valid[b] = n_splits + n_chunks;   // partial results of this sequence's heads
     }
     a.n_tokens = x.n;
     a.k.n_sink = x.n_sink; a.v.n_sink = x.n_sink;

@@ -1,6 +1,6 @@
 """innerq_decode_step_ragged: the wavefronts of a launch shared over the sequences by their lengths.
 
-Batches at the edges of the plan: two sequences, 64 (a lane each) and 65 (every sequence the same number), one long
+Batches at the edges of the plan: two sequences, 32 (the most that share) and 33 and 65 (every sequence the same number), one long
 sequence among short ones (as many wavefronts as it has partial slots), all short (none has a tile), equal lengths, and
 a loose bound.  Every sequence against the oracle on its own.
 """
@@ -17,7 +17,8 @@ TOL = 2e-3
 
 @pytest.mark.parametrize("name,lengths,heads,group,bound", [
     ("two", [3000, 17], (4, 1), 32, 0),
-    ("64", [5 + 37 * i % 1500 for i in range(64)], (2, 1), 32, 0),
+    ("32", [5 + 37 * i % 1500 for i in range(32)], (2, 1), 32, 0),
+    ("33", [5 + 41 * i % 1500 for i in range(33)], (4, 1), 32, 0),
     ("65", [5 + 37 * i % 900 for i in range(65)], (2, 1), 64, 0),
     ("one long", [40, 12000, 300, 5, 64], (8, 2), 32, 0),
     ("all short", [1, 5, 130, 60, 164, 163], (4, 1), 64, 0),
