@@ -270,8 +270,8 @@ bool bulk_append_supported(const QuantArgs& a) {
     const QuantTensorJob& j = a.job[w];
     if (j.form == kFp16) return false;
     const long long groups = (long long)a.batch * a.n_kv_heads * (j.row_end - j.row_begin) * (D / a.group);
-    // (a launch's index arithmetic is 32-bit; thousands of ring rows would make long work-groups)
-    if (groups + 64 >= (1LL << 32) || j.row_end >= (1LL << 31) || a.n_old + a.t_new >= (1LL << 31) || j.slots > 8192) return false;
+    // (a launch's index arithmetic is 32-bit)
+    if (groups + 64 >= (1LL << 32) || j.row_end >= (1LL << 31) || a.n_old + a.t_new >= (1LL << 31)) return false;
     most = groups > most ? groups : most;
     shared = shared || ring_slots_shared(a, j);
   }

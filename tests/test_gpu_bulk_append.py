@@ -41,6 +41,7 @@ def values(rng, shape, dist):
     (orc.KIND_INNER, 2, 64, (orc.SYM, orc.HYBRID), 1, 100, (700, 129)),
     (orc.KIND_OUTER, 3, 64, (orc.HYBRID, orc.SYM), 0, 64, (400, 100, 257)),
     (orc.KIND_OUTER, 4, 32, (orc.HYBRID, orc.HYBRID), 0, 300, (1500, 31, 700)),
+    (orc.KIND_INNER, 2, 32, (orc.HYBRID, orc.HYBRID), 0, 1500, (1400, 900, 40, 2500)),     # a long ring
 ])
 @pytest.mark.parametrize("norm", [False, True])
 def test_bulk_append_bit_exact(env, kind, bits, group, modes, literal, recent, chunks, norm, dist):
