@@ -348,6 +348,7 @@ struct AbsmaxPlan {
   uint32_t blocks_per_head;           // work-groups of one kv head (over the batch)
   uint32_t* table;                    // [Hk][d], aliases inv_out
   uint32_t* done;                     // [Hk][d], aliases norm_out: entry 0 of a head counts its work-groups; entry 1 of head 0 the heads
+                                      // (null where the two outputs share memory: the factors are then a launch of their own)
   float* norm_out;
   float* inv_out;
 };
@@ -356,7 +357,41 @@ __global__ void calibrate_zero_kernel(uint32_t* table, uint32_t* done, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) {
     table[i] = 0u;
-    done[i] = 0u;
+    if (done) done[i] = 0u;
+  }
+}
+
+// The factors from the maxima: one work-group, four threads a channel, every fourth head each; a thread reads its
+// entries before it overwrites them.
+constexpr int kCalibThreads = 512;
+__device__ __forceinline__ void write_factors(const AbsmaxPlan& m) {
+  constexpr int kShare = kCalibThreads / kHeadDim;
+  const int c = threadIdx.x % kHeadDim, share = threadIdx.x / kHeadDim;
+  auto entry = [&](int h) {
+    return __uint_as_float(__hip_atomic_load(m.table + h * kHeadDim + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  };
+  __shared__ float part[kShare][kHeadDim];
+  float all = 0.f;
+  if (!m.per_head) {
+    for (int h0 = share; h0 < m.n_kv_heads; h0 += 8 * kShare) {
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = entry(h0 + kShare * i < m.n_kv_heads ? h0 + kShare * i : h0);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) all = fmaxf(all, v[i]);
+    }
+    part[share][c] = all;
+  }
+  __syncthreads();                                       // (every entry has been read)
+  if (!m.per_head) {
+#pragma unroll
+    for (int i = 0; i < kShare; ++i) all = fmaxf(all, part[i][c]);
+  }
+  for (int h = share; h < m.n_kv_heads; h += kShare) {
+    const float v = m.per_head ? entry(h) : all;
+    const float n = v == 0.f ? 1.f : sqrtf(v);
+    m.norm_out[h * kHeadDim + c] = n;
+    m.inv_out[h * kHeadDim + c] = 1.0f / n;
   }
 }
 
@@ -366,7 +401,6 @@ __global__ void calibrate_zero_kernel(uint32_t* table, uint32_t* done, int n) {
 // plain read of the keys is what it takes (8 x 8 heads x 32k tokens: 82 us, 6.5 TB/s; 91 without the non-temporal
 // loads; 101 before, one row a thread in flight).  Few, large work-groups: the atomics of a head meet in the same
 // 128 entries, about 20 ns each, and so do the counts.
-constexpr int kCalibThreads = 512;
 constexpr int kCalibRows = kCalibThreads / 16;   // token rows per pass of a work-group
 constexpr int kCalibPasses = 8;                  // passes in flight
 __global__ void __launch_bounds__(kCalibThreads) absmax_kernel(AbsmaxPlan m) {
@@ -412,6 +446,7 @@ __global__ void __launch_bounds__(kCalibThreads) absmax_kernel(AbsmaxPlan m) {
     seen = atomicMax(m.table + hk * kHeadDim + threadIdx.x, __float_as_uint(__half2float(__ushort_as_half((unsigned short)v))));
   }
   if (__syncthreads_or(seen == 0xffffffffu)) return;     // (never true: a maximum of |fp16| is finite)
+  if (!m.done) return;                                   // (uniform)
   __shared__ uint32_t last;
   if (threadIdx.x == 0) {
     last = 0u;
@@ -420,37 +455,10 @@ __global__ void __launch_bounds__(kCalibThreads) absmax_kernel(AbsmaxPlan m) {
   }
   __syncthreads();
   if (!last) return;
-  // ---- the last work-group: four threads a channel, every fourth head each; a thread reads its entries before it
-  // overwrites them
-  constexpr int kShare = kCalibThreads / kHeadDim;
-  const int c = threadIdx.x % kHeadDim, share = threadIdx.x / kHeadDim;
-  auto entry = [&](int h) {
-    return __uint_as_float(__hip_atomic_load(m.table + h * kHeadDim + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-  };
-  __shared__ float part[kShare][kHeadDim];
-  float all = 0.f;
-  if (!m.per_head) {
-    for (int h0 = share; h0 < m.n_kv_heads; h0 += 8 * kShare) {
-      float v[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = entry(h0 + kShare * i < m.n_kv_heads ? h0 + kShare * i : h0);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) all = fmaxf(all, v[i]);
-    }
-    part[share][c] = all;
-  }
-  __syncthreads();                                       // (every entry has been read)
-  if (!m.per_head) {
-#pragma unroll
-    for (int i = 0; i < kShare; ++i) all = fmaxf(all, part[i][c]);
-  }
-  for (int h = share; h < m.n_kv_heads; h += kShare) {
-    const float v = m.per_head ? entry(h) : all;
-    const float n = v == 0.f ? 1.f : sqrtf(v);
-    m.norm_out[h * kHeadDim + c] = n;
-    m.inv_out[h * kHeadDim + c] = 1.0f / n;
-  }
+  write_factors(m);
 }
+
+__global__ void __launch_bounds__(kCalibThreads) factors_kernel(AbsmaxPlan m) { write_factors(m); }
 
 }  // namespace
 
@@ -468,9 +476,12 @@ hipError_t launch_calibrate(const __half* k, int batch, int n_kv_heads, long lon
   AbsmaxPlan m;
   m.k = k; m.n_tokens = n_tokens; m.n_kv_heads = n_kv_heads; m.per_head = per_head;
   m.table = reinterpret_cast<uint32_t*>(inv_out);
-  m.done = reinterpret_cast<uint32_t*>(norm_out);
   m.norm_out = norm_out; m.inv_out = inv_out;
   const int n = n_kv_heads * kHeadDim;
+  // counts and maxima in one place would spoil each other: a caller that wants one of the two vectors may pass its
+  // buffer for both (1 / norm, written last, is what stays)
+  const bool apart = norm_out + n <= inv_out || inv_out + n <= norm_out;
+  m.done = apart ? reinterpret_cast<uint32_t*>(norm_out) : nullptr;
   calibrate_zero_kernel<<<(n + 255) / 256, 256, 0, stream>>>(m.table, m.done, n);   // (a kernel: safe inside a captured graph)
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
@@ -482,6 +493,9 @@ hipError_t launch_calibrate(const __half* k, int batch, int n_kv_heads, long lon
   dim3 grid((unsigned)((n_tokens + m.tokens_per_block - 1) / m.tokens_per_block), (unsigned)bh);
   m.blocks_per_head = grid.x * (unsigned)batch;
   absmax_kernel<<<grid, kCalibThreads, 0, stream>>>(m);
+  e = hipGetLastError();
+  if (e != hipSuccess || apart) return e;
+  factors_kernel<<<1, kCalibThreads, 0, stream>>>(m);
   return hipGetLastError();
 }
 

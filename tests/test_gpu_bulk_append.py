@@ -76,3 +76,19 @@ def test_calibration_exact(env, batch, heads, n_tokens, per_head):
         norm_o, inv_o = orc.calibrate_key_norm(K, per_head=per_head)
         assert np.array_equal(norm.cpu().numpy(), norm_o.astype(np.float32))
         assert np.array_equal(inv.cpu().numpy(), inv_o.astype(np.float32))
+
+
+@pytest.mark.parametrize("per_head", [False, True])
+def test_calibration_into_one_buffer(env, per_head):
+    """A caller that wants 1 / norm only may pass its buffer for both outputs: 1 / norm is what stays in it."""
+    import ctypes
+    torch, iq = env
+    rng = np.random.default_rng(9)
+    K = (rng.standard_normal((2, 3, 700, 128)) * 30).astype(np.float16)
+    Kd = torch.from_numpy(K).cuda()
+    inv = torch.full((3, 128), 7.0, device="cuda")
+    cfg = gpu_config(oracle_config(wl.Workload("c", 2, 3, 3, 128, 700, 2, 32, 4, 32)))
+    st = iq.lib().innerq_calibrate_key_norm(ctypes.byref(cfg), Kd.data_ptr(), 700, int(per_head), inv.data_ptr(), inv.data_ptr(),
+                                            iq._stream(None))
+    assert st == iq.OK
+    assert np.array_equal(inv.cpu().numpy(), orc.calibrate_key_norm(K, per_head=per_head)[1].astype(np.float32))
