@@ -397,10 +397,11 @@ __device__ __forceinline__ void write_factors(const AbsmaxPlan& m) {
 
 // max |K| per (kv head, channel): each work-group scans a slice of tokens of one (b, hk), eight rows a thread in
 // flight, and folds its 128 channel maxima into the table with an unsigned atomic max on the float bits (monotone
-// for non-negative floats).  Maxima are taken on the fp16 bits without the sign, two channels an instruction; a
-// plain read of the keys is what it takes (8 x 8 heads x 32k tokens: 82 us, 6.5 TB/s; 91 without the non-temporal
-// loads; 101 before, one row a thread in flight).  Few, large work-groups: the atomics of a head meet in the same
-// 128 entries, about 20 ns each, and so do the counts.
+// for non-negative floats).  The maxima of x and -x are packed fp16 ones, two channels an instruction, and pass a NaN
+// over (a maximum of the bits would put one NaN key in the place of its channel's maximum); a plain read of the keys
+// is what it takes (8 x 8 heads x 32k tokens: 82 us, 6.5 TB/s; 91 without the non-temporal loads; 101 before, one row a
+// thread in flight).  Few, large work-groups: the atomics of a head meet in the same 128 entries, about 20 ns each, and
+// so do the counts.
 constexpr int kCalibRows = kCalibThreads / 16;   // token rows per pass of a work-group
 constexpr int kCalibPasses = 8;                  // passes in flight
 __global__ void __launch_bounds__(kCalibThreads) absmax_kernel(AbsmaxPlan m) {
@@ -411,8 +412,8 @@ __global__ void __launch_bounds__(kCalibThreads) absmax_kernel(AbsmaxPlan m) {
   const long long t0 = (long long)blockIdx.x * m.tokens_per_block;
   const long long t1 = t0 + m.tokens_per_block < m.n_tokens ? t0 + m.tokens_per_block : m.n_tokens;
   const u32x4* rows = reinterpret_cast<const u32x4*>(m.k + bh * m.n_tokens * kHeadDim + ch * 8);
-  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-  u16x2 mx[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
+  typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+  f16x2 mx[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
   for (long long t = t0 + r; t < t1; t += kCalibRows * kCalibPasses) {
     u32x4 raw[kCalibPasses];
 #pragma unroll
@@ -424,12 +425,15 @@ __global__ void __launch_bounds__(kCalibThreads) absmax_kernel(AbsmaxPlan m) {
     for (int p = 0; p < kCalibPasses; ++p) {
       const uint32_t w[4] = {raw[p].x, raw[p].y, raw[p].z, raw[p].w};
 #pragma unroll
-      for (int e = 0; e < 4; ++e) mx[e] = __builtin_elementwise_max(mx[e], __builtin_bit_cast(u16x2, w[e] & 0x7fff7fffu));
+      for (int e = 0; e < 4; ++e) {
+        const f16x2 x = __builtin_bit_cast(f16x2, w[e]);
+        mx[e] = __builtin_elementwise_max(mx[e], __builtin_elementwise_max(x, -x));
+      }
     }
   }
   __shared__ uint32_t red[kCalibRows][kHeadDim / 2];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) red[r][ch * 4 + e] = __builtin_bit_cast(uint32_t, mx[e]);
+  for (int e = 0; e < 4; ++e) red[r][ch * 4 + e] = __builtin_bit_cast(uint32_t, mx[e]) & 0x7fff7fffu;
   __syncthreads();
   // Table and counts are only ever touched by device-scope atomics (performed at the memory side, past the caches),
   // so no cache has to be written back or invalidated: a work-group counts itself done once its own atomic maxima

@@ -92,3 +92,24 @@ def test_calibration_into_one_buffer(env, per_head):
                                             iq._stream(None))
     assert st == iq.OK
     assert np.array_equal(inv.cpu().numpy(), orc.calibrate_key_norm(K, per_head=per_head)[1].astype(np.float32))
+
+
+@pytest.mark.parametrize("per_head", [False, True])
+def test_calibration_passes_over_nan(env, per_head):
+    """A NaN among the keys does not count towards its channel's maximum, nor does it hide the others (a channel of
+    nothing but NaN is like one of zeros)."""
+    torch, iq = env
+    rng = np.random.default_rng(11)
+    K = (rng.standard_normal((2, 3, 900, 128)) * 30).astype(np.float16)
+    K[:, 1, 400, 7] = 6000.0                              # (the maximum of all heads is in the head that has the NaN)
+    at = (rng.random(K.shape) < 0.01).astype(bool)
+    at[:, 1, 400, 7] = False
+    at[:, 2, :, 9] = True
+    bad, good = K.copy(), K.copy()
+    bad[at] = rng.integers(0x7C01, 0x8000, int(at.sum()), dtype=np.uint16).view(np.float16)    # signalling ones among them
+    good[at] = 0
+    cfg = gpu_config(oracle_config(wl.Workload("c", 2, 3, 3, 128, 900, 2, 32, 4, 32)))
+    norm, inv = iq.innerq_calibrate_key_norm(cfg, torch.from_numpy(bad).cuda(), per_head=per_head)
+    norm_o, inv_o = orc.calibrate_key_norm(good, per_head=per_head)
+    assert np.array_equal(norm.cpu().numpy(), norm_o.astype(np.float32))
+    assert np.array_equal(inv.cpu().numpy(), inv_o.astype(np.float32))
