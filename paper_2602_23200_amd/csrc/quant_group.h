@@ -205,19 +205,36 @@ __device__ __forceinline__ void quantize_group_bulk(X x, float mn, float mx, int
                                                     uint32_t (&words)[G * BITS / 32], __half& scale, __half& zero) {
   constexpr int QMAX = (1 << BITS) - 1;
   constexpr int HALF = 1 << (BITS - 1);
-  const __half Sa = __float2half_rn((mx - mn) / (float)QMAX);
-  const __half Ss = __float2half_rn(fmaxf(fabsf(mn), fabsf(mx)) / (sym_den_literal ? (float)QMAX : (float)(HALF - 1)));
-  // a scale that is an fp16 denormal but not 0 (for 2-bit symmetric groups it is max |x| itself: exact), or
-  // infinite (keys that overflowed in their normalisation)
+  auto asym_scale = [&] { return __float2half_rn((mx - mn) / (float)QMAX); };
+  auto sym_scale = [&] {
+    return __float2half_rn(fmaxf(fabsf(mn), fabsf(mx)) / (sym_den_literal ? (float)QMAX : (float)(HALF - 1)));
+  };
+  __half Sa = asym_scale(), Ss = sym_scale();
+  // a scale that is an fp16 denormal but not 0 (for 2-bit symmetric groups it is max |x| itself: exact),
+  // infinite (keys that overflowed in their normalisation) or NaN (a NaN among the values)
   auto coarse = [](__half S, bool denormal) {
     const uint32_t u = __half_as_ushort(S);
     return (denormal && u != 0u && u < 0x400u) || u >= 0x7c00u;
   };
   bool clamp = (mode != INNERQ_SYM && coarse(Sa, true)) || (mode != INNERQ_ASYM && coarse(Ss, BITS != 2));
   if (sym_den_literal && mode != INNERQ_ASYM) clamp = true;
-  if (__builtin_amdgcn_ballot_w64(clamp) != 0)            // (wave-uniform)
+  if (__builtin_amdgcn_ballot_w64(clamp) != 0) {          // (wave-uniform)
+    if (__builtin_amdgcn_ballot_w64(mn != mn) != 0) {
+      // the packed minimum and maximum hand a NaN on; the form of eight lanes passes it over, and a token's bytes
+      // do not depend on the call it came with
+      mn = mx = value_of(x(0));
+#pragma unroll
+      for (int i = 1; i < G; ++i) {
+        HalfRef v = x(i);
+        asm volatile("" : "+v"(v.w));                      // (a conversion of its own: shared with the codes below it would hold a register)
+        mn = fminf(mn, value_of(v));
+        mx = fmaxf(mx, value_of(v));
+      }
+      Sa = asym_scale();
+      Ss = sym_scale();
+    }
     bulk_codes<G, BITS, INNERQ_HYBRID, true>(x, mn, Sa, Ss, mode, words, scale, zero);
-  else if (mode == INNERQ_HYBRID) bulk_codes<G, BITS, INNERQ_HYBRID, false>(x, mn, Sa, Ss, mode, words, scale, zero);
+  } else if (mode == INNERQ_HYBRID) bulk_codes<G, BITS, INNERQ_HYBRID, false>(x, mn, Sa, Ss, mode, words, scale, zero);
   else if (mode == INNERQ_SYM) bulk_codes<G, BITS, INNERQ_SYM, false>(x, mn, Sa, Ss, mode, words, scale, zero);
   else bulk_codes<G, BITS, INNERQ_ASYM, false>(x, mn, Sa, Ss, mode, words, scale, zero);
 }

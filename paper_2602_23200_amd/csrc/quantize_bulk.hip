@@ -68,8 +68,10 @@ __device__ __forceinline__ void per_token_unit(const QuantArgs& a, const QuantTe
   pair_range(x, mn, mx);
   uint32_t words[W];
   __half s, z;
-  quantize_group_bulk<G, BITS>([&](int i) { return HalfRef{x[i / 2], (i & 1) != 0}; }, fminf(half_lo(mn), half_hi(mn)),
-                               fmaxf(half_lo(mx), half_hi(mx)), j.mode, a.sym_den_literal, words, s, z);
+  mn = pair_min(mn, mn >> 16, mn >> 16);                 // (fminf would lose the NaN of one half and that half with it)
+  mx = pair_max(mx, mx >> 16, mx >> 16);
+  quantize_group_bulk<G, BITS>([&](int i) { return HalfRef{x[i / 2], (i & 1) != 0}; }, half_lo(mn), half_lo(mx), j.mode,
+                               a.sym_den_literal, words, s, z);
   // a row is one plane of LB-bit fields over all channels (3-bit: followed by the plane of high bits)
   constexpr int LB = BITS == 3 ? 2 : BITS;
   constexpr int WL = G * LB / 32;                        // words of the (low) plane of one group

@@ -113,3 +113,26 @@ def test_calibration_passes_over_nan(env, per_head):
     norm_o, inv_o = orc.calibrate_key_norm(good, per_head=per_head)
     assert np.array_equal(norm.cpu().numpy(), norm_o.astype(np.float32))
     assert np.array_equal(inv.cpu().numpy(), inv_o.astype(np.float32))
+
+
+@pytest.mark.parametrize("kind,bits,group,mode", [(orc.KIND_INNER, 2, 32, orc.HYBRID), (orc.KIND_OUTER, 4, 64, orc.HYBRID),
+                                                  (orc.KIND_INNER, 3, 64, orc.ASYM), (orc.KIND_OUTER, 2, 32, orc.SYM)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_bytes_do_not_depend_on_the_call(env, kind, bits, group, mode, bad):
+    """NaN and infinite values leave the bytes of a group unspecified, but the same in a chunk and token by token."""
+    torch, iq = env
+    n = 1500                                              # (more than 16384 groups: the bulk form)
+    w = wl.Workload("n", 2, 3, 3, 128, n, bits, group, 4, 32, k_mode=mode, v_mode=mode)
+    rng = np.random.default_rng(bits)
+    KV = []
+    for x in wl.kv_full(w):
+        x[rng.random(x.shape) < 0.002] = bad
+        KV.append(torch.from_numpy(x).cuda())
+    cfg = gpu_config(oracle_config(w, kind=kind))
+    chunk, steps = iq.allocate_cache(cfg), iq.allocate_cache(cfg)
+    iq.innerq_quantize_append(chunk, *KV)
+    for t in range(n):
+        iq.innerq_quantize_append(steps, *(x[:, :, t:t + 1].contiguous() for x in KV))
+    for name, buf in chunk.buffers.items():
+        if buf is not None and not name.endswith("recent"):               # (a ring's spare slots hold older tokens)
+            assert torch.equal(buf, steps.buffers[name]), name
