@@ -62,6 +62,27 @@ def test_bulk_append_bit_exact(env, kind, bits, group, modes, literal, recent, c
     assert_cache_equal(g, want, o)
 
 
+@pytest.mark.parametrize("kind,bits,group", [(orc.KIND_INNER, 2, 32), (orc.KIND_INNER, 4, 64), (orc.KIND_OUTER, 3, 32)])
+@pytest.mark.parametrize("norm", [False, True])
+@pytest.mark.parametrize("chunks", [(300,), (20, 300), (140, 2, 40, 1, 200), (3, 133)])
+def test_short_append_bit_exact(env, kind, bits, group, chunks, norm):
+    """Calls of few groups: groups of new tokens only, of ring tokens only and of both."""
+    torch, iq = env
+    n = sum(chunks)
+    w = wl.Workload("s", 2, 3, 3, 128, n, bits, group, 4, 32)
+    o = oracle_config(w, kind=kind)
+    rng = np.random.default_rng(n + bits)
+    K, V = values(rng, (2, 3, n, 128), "normal"), values(rng, (2, 3, n, 128), "normal")
+    inv = rng.uniform(0.3, 1.0, (3, 128)).astype(np.float32) if norm else None
+    g = iq.allocate_cache(gpu_config(o))
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    at = 0
+    for c in chunks:
+        iq.innerq_quantize_append(g, dev(K[:, :, at:at + c]), dev(V[:, :, at:at + c]), None if inv is None else dev(inv))
+        at += c
+    assert_cache_equal(g, orc.cache_init_prefill(o, K, V, k_inv_norm=inv), o)
+
+
 @pytest.mark.parametrize("batch,heads,n_tokens", [(1, 1, 1), (2, 3, 255), (1, 5, 257), (3, 2, 1100), (1, 33, 600)])
 @pytest.mark.parametrize("per_head", [False, True])
 def test_calibration_exact(env, batch, heads, n_tokens, per_head):
