@@ -16,8 +16,8 @@ COMMON = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17",
 SOURCES = {
     "api.hip": [],
     "quantize.hip": ["-ffp-contract=off"],
-    "quantize_bulk.hip": ["-ffp-contract=off"],
-    "quantize_bulk_g64.hip": ["-ffp-contract=off"],
+    "quantize_owners.hip": ["-ffp-contract=off"],
+    "quantize_owners_g64.hip": ["-ffp-contract=off"],
     "attention_generic.hip": [],
     "stream_probe.hip": [],
     "attention_fp16.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],

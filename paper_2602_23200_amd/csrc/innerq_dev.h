@@ -133,9 +133,15 @@ struct AttnArgs;
 // merge (may be null): the log-sum-exp merge of an attention call whose partials are complete on
 // this stream rides in the same launch (or, for the rare two-launch appends, goes first).
 hipError_t launch_quantize(const QuantArgs& a, hipStream_t stream, const AttnArgs* merge = nullptr);
-// The same append for calls with enough groups to fill the chip (quantize_bulk.hip); launch_quantize routes to it.
-bool bulk_append_supported(const QuantArgs& a);
-hipError_t launch_quantize_bulk(const QuantArgs& a, hipStream_t stream);
+// How an append runs (the rule: append_form in quantize_owners.hip; launch_quantize routes by it):
+//   kLanes8      a per-token group spread over eight lanes (a decode step, short calls); the window copies in the same
+//                launch, or in a second one where a new token lands in a ring slot that the call still reads
+//   kLane        the same launches with a group a lane (prompts and large chunks)
+//   kRingOwners  a group a lane, and a work-group that owns a slice of a ring reads what leaves it and then writes what
+//                enters: one launch although slots are shared
+enum class AppendForm { kLanes8, kLane, kRingOwners };
+AppendForm append_form(const QuantArgs& a);
+hipError_t launch_quantize_owners(const QuantArgs& a, hipStream_t stream);
 hipError_t launch_calibrate(const __half* k, int batch, int n_kv_heads, long long n_tokens, int per_head,
                             float* norm_out, float* inv_out, hipStream_t stream);
 

@@ -34,8 +34,8 @@ __device__ inline float code_quotient(float num, float S, float r) {
 // is the code the formula assigns when the scale is 0.
 __device__ inline float group_reciprocal(float S) { return S == 0.f ? 0.f : 1.0f / S; }
 
-// ---- a group in one lane: the form of bulk launches, which are bound by vector instructions, and of the per-channel
-// groups of a decode step.
+// ---- a group in one lane: the form of prompts and chunks, which are bound by vector instructions, and of all
+// per-channel groups.
 //
 // It uses three facts, each exact, so that codes, flags and scales keep every bit:
 //   * rint(fl(num / S)) is the exact quotient rounded to nearest-even.  A tie k + 1/2 of the quotient is
@@ -324,6 +324,17 @@ inline bool ring_slots_shared(const QuantArgs& a, const QuantTensorJob& j) {
   return j.row_end > j.row_begin && a.w_sink + j.row_begin < a.n_old && a.n_old + a.t_new - (a.w_sink + j.row_begin) > j.slots;
 }
 
+// Threads the window copies of the larger of the two tensors take.
+inline long long copy_threads(const QuantArgs& a) {
+  long long most = 0;
+  for (int w = 0; w < 2; ++w) {
+    const CopySpan sp = copy_span(a, a.job[w]);
+    const long long n = (long long)a.batch * a.n_kv_heads * (sp.n_a + (a.t_new - sp.i_b)) * (kHeadDim / 8);
+    most = n > most ? n : most;
+  }
+  return most;
+}
+
 // New tokens join the fp16 windows: the sink window while it has room, otherwise the recent
 // ring -- unless this same call already moved them on to the quantised store.
 __device__ __forceinline__ void window_copy(const QuantArgs& a, const QuantTensorJob& j, long long idx) {
@@ -359,6 +370,48 @@ __device__ __forceinline__ void window_copy(const QuantArgs& a, const QuantTenso
     for (int e = 0; e < 8; ++e) h[e] = scaled_half(h2f(h[e]), inv[e]);
   }
   *reinterpret_cast<uint4*>(dst + ch * 8) = raw;
+}
+
+// Group g of one row of the per-token form in one lane: its values at src (scaled if they are new ones and the job
+// says so), its packed fields, scale and zero-point to store row lin + dr (dr apart: lin may be uniform).
+template <int G, int BITS>
+__device__ __forceinline__ void per_token_group(const QuantArgs& a, const QuantTensorJob& j, const __half* src, bool fresh,
+                                                uint32_t bh, uint32_t g, long long lin, uint32_t dr) {
+  constexpr int GPR = kHeadDim / G, W = G * BITS / 32;
+  uint32_t x[G / 2];
+#pragma unroll
+  for (int i = 0; i < G / 8; ++i) {
+    const uint4 raw = reinterpret_cast<const uint4*>(src)[i];
+    x[4 * i] = raw.x; x[4 * i + 1] = raw.y; x[4 * i + 2] = raw.z; x[4 * i + 3] = raw.w;
+  }
+  if (j.normalise) {
+    const float* inv = a.inv_norm + (bh % (uint32_t)a.n_kv_heads) * kHeadDim + g * G;
+#pragma unroll
+    for (int i = 0; i < G / 2; ++i) {
+      const uint32_t y = scaled_pair(x[i], inv[2 * i], inv[2 * i + 1]);
+      x[i] = fresh ? y : x[i];                           // (ring rows already are)
+    }
+  }
+  uint32_t mn, mx;
+  pair_range(x, mn, mx);
+  mn = pair_min(mn, mn >> 16, mn >> 16);                 // (fminf would lose the NaN of one half and that half with it)
+  mx = pair_max(mx, mx >> 16, mx >> 16);
+  uint32_t words[W];
+  __half s, z;
+  quantize_group_bulk<G, BITS>([&](int i) { return HalfRef{x[i / 2], (i & 1) != 0}; }, half_lo(mn), half_lo(mx), j.mode,
+                               a.sym_den_literal, words, s, z);
+  // a row is one plane of LB-bit fields over all channels (3-bit: followed by the plane of high bits)
+  constexpr int LB = BITS == 3 ? 2 : BITS;
+  constexpr int WL = G * LB / 32;                        // words of the (low) plane of one group
+  uint32_t* rowp = reinterpret_cast<uint32_t*>(j.codes + lin * (kHeadDim * BITS / 8)) + dr * (kHeadDim * BITS / 32);
+#pragma unroll
+  for (int i = 0; i < WL; i += 2) *reinterpret_cast<uint2*>(rowp + g * WL + i) = uint2{words[i], words[i + 1]};
+  if constexpr (BITS == 3) {
+#pragma unroll
+    for (int i = 0; i < G / 32; ++i) rowp[kHeadDim * 2 / 32 + g * (G / 32) + i] = words[WL + i];
+  }
+  (j.scales + lin * GPR)[dr * GPR + g] = s;
+  if (j.zeros) (j.zeros + lin * GPR)[dr * GPR + g] = z;
 }
 
 // Job y (0: keys, 1: values) of a launch, field by field: indexing the by-value kernel argument

@@ -119,16 +119,27 @@ __global__ void __launch_bounds__(256) window_copy_kernel(QuantArgs a) {
   window_copy(a, j, (long long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
-// The quantise work of thread idx of tensor job j (keys and values may have different widths).  STEP: of a call with at
-// most one new token.
-template <int G, int BITS, bool STEP>
+// The quantise work of thread idx of tensor job j (keys and values may have different widths).  LANES: that share a
+// per-token group (8, or 1).  STEP: of a call with at most one new token.
+template <int G, int BITS, int LANES, bool STEP>
 __device__ __forceinline__ void quantize_rows(const QuantArgs& a, const QuantTensorJob& j, long long idx) {
   const long long n_rows = j.row_end - j.row_begin;
   if (n_rows <= 0) return;
   const long long BH = (long long)a.batch * a.n_kv_heads;
   constexpr int W = G * BITS / 32;
 
-  if (j.form == kPerToken) {
+  if (LANES == 1 && j.form == kPerToken) {
+    // A lane per group, its G channels 2 G contiguous bytes; consecutive groups in consecutive lanes, over all rows and
+    // sequence-heads (units of one sequence-head with scalar addresses, built first: 8 x 8 heads x 32k tokens 259 us
+    // against 261 here at 2 bits, G = 32, but 325 against 277 at 4 bits, G = 64, and nothing to spread short rows over).
+    constexpr int GPR = kHeadDim / G;                    // groups per row
+    if (idx >= BH * n_rows * GPR) return;
+    const uint32_t g = (uint32_t)idx % GPR;
+    const long long bh = div32(idx / GPR, n_rows), row = j.row_begin + (idx / GPR - bh * n_rows);
+    bool from_new;
+    const __half* src = token_row(j, a, a.n_old, bh, a.w_sink + row, from_new) + g * G;
+    per_token_group<G, BITS>(a, j, src, from_new, (uint32_t)bh, g, store_row(a.pages, a.n_kv_heads, a.capacity, bh, row), 0u);
+  } else if (j.form == kPerToken) {
     // 8 lanes per group, G/8 consecutive channels each
     constexpr int GPR = kHeadDim / G;                    // groups per row
     constexpr int E = G / 8;
@@ -245,7 +256,7 @@ __device__ __forceinline__ void quantize_rows(const QuantArgs& a, const QuantTen
   }
 }
 
-template <int G>
+template <int G, int LANES>
 __global__ void __launch_bounds__(256) quantize_kernel(QuantArgs a, long long copy_from) {
   // Thread indices below copy_from quantise evicted tokens, those from copy_from on write the
   // new tokens into the windows (one launch; only used when no new token lands in a ring slot
@@ -256,9 +267,9 @@ __global__ void __launch_bounds__(256) quantize_kernel(QuantArgs a, long long co
     window_copy(a, j, idx - copy_from);
     return;
   }
-  if (j.bits == 2) quantize_rows<G, 2, false>(a, j, idx);
-  else if (j.bits == 3) quantize_rows<G, 3, false>(a, j, idx);
-  else quantize_rows<G, 4, false>(a, j, idx);
+  if (j.bits == 2) quantize_rows<G, 2, LANES, false>(a, j, idx);
+  else if (j.bits == 3) quantize_rows<G, 3, LANES, false>(a, j, idx);
+  else quantize_rows<G, 4, LANES, false>(a, j, idx);
 }
 
 // The same launch with the log-sum-exp merge of an attention call riding along: the last
@@ -280,42 +291,34 @@ __global__ void __launch_bounds__(256) quantize_merge_kernel(QuantArgs a, long l
     window_copy(a, j, idx - copy_from);
     return;
   }
-  if (j.bits == 2) quantize_rows<G, 2, true>(a, j, idx);
-  else if (j.bits == 3) quantize_rows<G, 3, true>(a, j, idx);
-  else quantize_rows<G, 4, true>(a, j, idx);
+  if (j.bits == 2) quantize_rows<G, 2, 8, true>(a, j, idx);
+  else if (j.bits == 3) quantize_rows<G, 3, 8, true>(a, j, idx);
+  else quantize_rows<G, 4, 8, true>(a, j, idx);
 }
 
-// Threads the quantise work / the window copies of one tensor job need.
-template <int G>
+// Threads the quantise work of one tensor job needs.
+template <int G, int LANES>
 long long quantize_threads(const QuantArgs& a, const QuantTensorJob& j) {
   const long long BH = (long long)a.batch * a.n_kv_heads;
   const long long rows = j.row_end - j.row_begin;
   if (rows <= 0) return 0;
-  if (j.form == kPerToken) return BH * rows * (kHeadDim / G) * 8;
+  if (j.form == kPerToken) return BH * rows * (kHeadDim / G) * LANES;
   if (j.form == kPerChannel) return BH * (rows / G) * kHeadDim;
   return BH * rows * (kHeadDim / 8);
 }
-inline long long copy_threads(const QuantArgs& a, const QuantTensorJob& j) {
-  const CopySpan sp = copy_span(a, j);
-  return (long long)a.batch * a.n_kv_heads * (sp.n_a + (a.t_new - sp.i_b)) * (kHeadDim / 8);
-}
 
 hipError_t window_copies(const QuantArgs& a, hipStream_t stream) {
-  const long long k = copy_threads(a, a.job[0]), v = copy_threads(a, a.job[1]), n = k > v ? k : v;
+  const long long n = copy_threads(a);
   if (n == 0) return hipSuccess;
   dim3 grid((unsigned)((n + 255) / 256), 2);
   window_copy_kernel<<<grid, 256, 0, stream>>>(a);
   return hipGetLastError();
 }
 
-template <int G>
+template <int G, int LANES>
 hipError_t launch_quantize_t(const QuantArgs& a, hipStream_t stream, const AttnArgs* merge) {
-  long long threads = 0, cthreads = 0;
-  for (int w = 0; w < 2; ++w) {
-    const long long n = quantize_threads<G>(a, a.job[w]), c = copy_threads(a, a.job[w]);
-    threads = n > threads ? n : threads;
-    cthreads = c > cthreads ? c : cthreads;
-  }
+  const long long kthreads = quantize_threads<G, LANES>(a, a.job[0]), vthreads = quantize_threads<G, LANES>(a, a.job[1]);
+  const long long threads = kthreads > vthreads ? kthreads : vthreads, cthreads = copy_threads(a);
   if (threads >= (1LL << 32)) return hipErrorInvalidValue;   // (device index arithmetic is 32-bit)
   // no ring slot shared by an evicted and a new token: one launch does both jobs
   const bool disjoint = !ring_slots_shared(a, a.job[0]) && !ring_slots_shared(a, a.job[1]);
@@ -338,12 +341,12 @@ hipError_t launch_quantize_t(const QuantArgs& a, hipStream_t stream, const AttnA
   if (threads > 0 && disjoint) {
     const long long qthreads = ((threads + 255) / 256) * 256;
     dim3 grid((unsigned)((qthreads + cthreads + 255) / 256), 2);
-    quantize_kernel<G><<<grid, 256, 0, stream>>>(a, qthreads);
+    quantize_kernel<G, LANES><<<grid, 256, 0, stream>>>(a, qthreads);
     return hipGetLastError();
   }
   if (threads > 0) {
     dim3 grid((unsigned)((threads + 255) / 256), 2);
-    quantize_kernel<G><<<grid, 256, 0, stream>>>(a, -1);
+    quantize_kernel<G, LANES><<<grid, 256, 0, stream>>>(a, -1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -482,10 +485,11 @@ __global__ void __launch_bounds__(kCalibThreads) factors_kernel(AbsmaxPlan m) { 
 hipError_t launch_quantize(const QuantArgs& a, hipStream_t stream, const AttnArgs* merge) {
   for (int w = 0; w < 2; ++w)
     if (a.job[w].form != kFp16 && (a.job[w].bits < 2 || a.job[w].bits > 4)) return hipErrorInvalidValue;
-  if (!merge && bulk_append_supported(a)) return launch_quantize_bulk(a, stream);
-  if (a.group == 32) return launch_quantize_t<32>(a, stream, merge);
-  if (a.group == 64) return launch_quantize_t<64>(a, stream, merge);
-  return hipErrorInvalidValue;
+  if (a.group != 32 && a.group != 64) return hipErrorInvalidValue;
+  const AppendForm form = merge ? AppendForm::kLanes8 : append_form(a);
+  if (form == AppendForm::kRingOwners) return launch_quantize_owners(a, stream);
+  if (form == AppendForm::kLane) return a.group == 32 ? launch_quantize_t<32, 1>(a, stream, nullptr) : launch_quantize_t<64, 1>(a, stream, nullptr);
+  return a.group == 32 ? launch_quantize_t<32, 8>(a, stream, merge) : launch_quantize_t<64, 8>(a, stream, merge);
 }
 
 hipError_t launch_calibrate(const __half* k, int batch, int n_kv_heads, long long n_tokens, int per_head,

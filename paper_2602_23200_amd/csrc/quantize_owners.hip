@@ -1,32 +1,28 @@
-// Bulk appends (a prompt or a chunk of one): quantise, pack and copy into the windows in one launch.
+// Chunks onto a filled cache in one launch: quantise, pack and copy into the windows, where a new token lands in a
+// ring slot that the same call still has to read.
 //
-// What bounds it: vector instructions, with memory close behind (2-bit hybrid groups: 14 instructions and 2.4
-// bytes moved per element).  So everything that is the same for a wavefront is kept out of the lanes:
-//   * a wavefront of the per-token form takes 64 consecutive groups of one sequence-head, one a lane: its G
-//     channels are 2 G contiguous bytes, and the 64 lanes' loads and packed stores are contiguous too;
-//   * a wavefront of the per-channel form takes one group of G tokens, a lane a pair of channels: a token's row
-//     is one coalesced 256-byte load.
-// One wavefront, one such unit; four wavefronts per SIMD hide the loads.  (Resident wavefronts that walk over
-// the units with the next unit's loads in flight were built first: 317 us against 301 for one unit each, with
-// the same arithmetic, on 8 x 8 heads x 32k tokens: copies and spills cost more than the latency they hid.)
-// Tokens that leave the recent ring are read by the same work-group that afterwards writes the new tokens
-// into it, one work-group per sequence-head, tensor and slice of G channels, so a call needs no second launch.
+// A work-group owns a slice of G channels of one ring (of one sequence-head and tensor): it quantises the tokens that
+// leave the slice and, behind a barrier, writes the tokens that enter it, so no second launch has to wait for the first.
+// New tokens that do not stay in a window are units of one wavefront each:
+//   * per-token form: 64 consecutive groups of one sequence-head, one a lane (its G channels are 2 G contiguous bytes,
+//     and the 64 lanes' loads and packed stores are contiguous too);
+//   * per-channel form: one group of G tokens, a lane a pair of channels (a token's row is one coalesced 256-byte load).
 //
-// Measured against one group a lane in a kernel of all forms (quotients in three operations, values converted
-// first, copies in a second launch): 8 x 8 heads x 32k tokens, 2-bit hybrid, G = 32, append 364 us -> 262, with key
-// factors 383 -> 278; G = 64, 16k tokens 191 -> 142; 3-bit, 16k tokens 243 -> 182; a 512-token chunk onto 500 tokens of
-// 8 heads 10.2 -> 7.7.
+// What bounds it is the chain of an owner: the rounds of loads of the rows that leave, one lane's whole group, the
+// rounds of copies.  It pays while the owners fit the chip and their rings are short (append_form): 512 tokens onto 500
+// of 8 heads, G = 32, 7.9 us against 8.7 in two launches; 32 heads 9.0 against 10.5; but with a window of 1024 tokens
+// 19 against 10, and 157 against 13 with 8192 (1 head, G = 64): a ring's rows are one work-group's serial rounds.
 #include "innerq_dev.h"
 #include "quant_group.h"
 
-#ifndef INNERQ_BULK_GROUP
-#define INNERQ_BULK_GROUP 32
+#ifndef INNERQ_OWNERS_GROUP
+#define INNERQ_OWNERS_GROUP 32
 #endif
 
 namespace innerq {
 namespace {
 
-constexpr int G = INNERQ_BULK_GROUP;
+constexpr int G = INNERQ_OWNERS_GROUP;
 constexpr int D = kHeadDim;
 
 // ---- per-token form ------------------------------------------------------------------------
@@ -50,46 +46,13 @@ __device__ __forceinline__ void per_token_unit(const QuantArgs& a, const QuantTe
     const __half* old = j.ring + ((long long)bh * j.slots + (uint32_t)t % (uint32_t)j.slots) * D + g * G;
     src = fresh ? src : old;
   }
-  uint32_t x[G / 2];
-#pragma unroll
-  for (int i = 0; i < G / 8; ++i) {
-    const uint4 raw = reinterpret_cast<const uint4*>(src)[i];
-    x[4 * i] = raw.x; x[4 * i + 1] = raw.y; x[4 * i + 2] = raw.z; x[4 * i + 3] = raw.w;
-  }
-  if (j.normalise) {
-    const float* inv = a.inv_norm + (bh % (uint32_t)a.n_kv_heads) * D + g * G;
-#pragma unroll
-    for (int i = 0; i < G / 2; ++i) {
-      const uint32_t y = scaled_pair(x[i], inv[2 * i], inv[2 * i + 1]);
-      x[i] = !RING || fresh ? y : x[i];                  // (ring rows already are)
-    }
-  }
-  uint32_t mn, mx;
-  pair_range(x, mn, mx);
-  uint32_t words[W];
-  __half s, z;
-  mn = pair_min(mn, mn >> 16, mn >> 16);                 // (fminf would lose the NaN of one half and that half with it)
-  mx = pair_max(mx, mx >> 16, mx >> 16);
-  quantize_group_bulk<G, BITS>([&](int i) { return HalfRef{x[i / 2], (i & 1) != 0}; }, half_lo(mn), half_lo(mx), j.mode,
-                               a.sym_den_literal, words, s, z);
-  // a row is one plane of LB-bit fields over all channels (3-bit: followed by the plane of high bits)
-  constexpr int LB = BITS == 3 ? 2 : BITS;
-  constexpr int WL = G * LB / 32;                        // words of the (low) plane of one group
   long long lin = (long long)bh * a.capacity + row0;     // first row of the unit (uniform), then the lane's from it
   uint32_t dr = r;
   if (a.pages.table) {
     lin = store_row(a.pages, a.n_kv_heads, a.capacity, bh, row0 + r);
     dr = 0u;
   }
-  uint32_t* rowp = reinterpret_cast<uint32_t*>(j.codes + lin * (D * BITS / 8)) + dr * (D * BITS / 32);
-#pragma unroll
-  for (int i = 0; i < WL; i += 2) *reinterpret_cast<uint2*>(rowp + g * WL + i) = uint2{words[i], words[i + 1]};
-  if constexpr (BITS == 3) {
-#pragma unroll
-    for (int i = 0; i < G / 32; ++i) rowp[D * 2 / 32 + g * (G / 32) + i] = words[WL + i];
-  }
-  (j.scales + lin * GPR)[dr * GPR + g] = s;
-  if (j.zeros) (j.zeros + lin * GPR)[dr * GPR + g] = z;
+  per_token_group<G, BITS>(a, j, src, !RING || fresh, bh, g, lin, dr);
 }
 
 // ---- per-channel form ----------------------------------------------------------------------
@@ -206,7 +169,7 @@ __device__ __forceinline__ void copy_slice(const QuantArgs& a, const QuantTensor
 constexpr uint32_t kSlices = D / G;                      // channel slices, and groups per row
 constexpr uint32_t kUnitRows = 64u / kSlices;            // rows of a per-token unit
 
-struct BulkPlan {
+struct OwnersPlan {
   uint32_t ring_groups;                                  // work-groups in front that own a ring slice each: 2 BH kSlices
   uint32_t per_bh_t, per_bh_c;                           // units per sequence-head of the per-token / per-channel tensor
 };
@@ -225,7 +188,7 @@ __device__ __forceinline__ void ring_units(const QuantArgs& a, const QuantTensor
 }
 
 template <bool INNER>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 32 ? 4 : 3))) quantize_bulk_kernel(QuantArgs a, BulkPlan p) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 32 ? 4 : 3))) quantize_owners_kernel(QuantArgs a, OwnersPlan p) {
   if (blockIdx.x < p.ring_groups) {
     // ---- a ring slice: what leaves it, then what enters
     const uint32_t slice = blockIdx.x % kSlices, tensor = (blockIdx.x / kSlices) & 1u, bh = blockIdx.x / (2u * kSlices);
@@ -263,34 +226,57 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 3
 
 }  // namespace
 
-#if INNERQ_BULK_GROUP == 32
-bool bulk_append_supported(const QuantArgs& a) {
-  if (a.n_dev || a.t_new < 2) return false;
-  long long most = 0;
-  bool shared = false;                                   // a new token lands in a ring slot that this call reads
+#if INNERQ_OWNERS_GROUP == 32
+// One chunk measured in all forms, 2800 shapes of 1 to 2048 sequence-heads, 2 to 32768 tokens, windows of 32 to 16384, both
+// group sizes: the rule is 0.7 % (geometric mean) behind the best form of each.
+AppendForm append_form(const QuantArgs& a) {
+  if (a.n_dev || a.t_new < 2) return AppendForm::kLanes8;
+  long long most = 0, slice_rows = 0;
+  bool shared = false, values = false, ring_values = false, hybrid = false;
+  bool narrow = a.n_old + a.t_new < (1LL << 31);         // (the owners' row arithmetic is 32-bit)
   for (int w = 0; w < 2; ++w) {
     const QuantTensorJob& j = a.job[w];
-    if (j.form == kFp16) return false;
-    const long long groups = (long long)a.batch * a.n_kv_heads * (j.row_end - j.row_begin) * (D / a.group);
-    // (a launch's index arithmetic is 32-bit)
-    if (groups + 64 >= (1LL << 32) || j.row_end >= (1LL << 31) || a.n_old + a.t_new >= (1LL << 31)) return false;
+    if (j.form == kFp16) return AppendForm::kLanes8;
+    const long long rows = j.row_end - j.row_begin, groups = (long long)a.batch * a.n_kv_heads * rows * (D / a.group);
+    narrow = narrow && groups + 64 < (1LL << 32);
     most = groups > most ? groups : most;
     shared = shared || ring_slots_shared(a, j);
+    hybrid = hybrid || j.mode == INNERQ_HYBRID;
+    if (j.form == kPerChannel) {
+      values = rows > 0;
+      ring_values = rows > 0 && a.w_sink + j.row_begin < a.n_old;
+    }
+    // rows that an owner reads from its ring, tokens that it writes
+    long long old = a.n_old - a.w_sink - j.row_begin;
+    old = old < 0 ? 0 : old > rows ? rows : old;
+    const CopySpan sp = copy_span(a, j);
+    const long long in = sp.n_a + (a.t_new - sp.i_b);
+    slice_rows = old > slice_rows ? old : slice_rows;
+    slice_rows = in > slice_rows ? in : slice_rows;
   }
-  // The other form (launch_quantize_t) spreads a group over eight lanes, which is the shorter chain while the chip is
-  // idle, but needs a second launch when ring slots are shared.  Per call, 8 kv heads: 128 tokens onto 500 cached
-  // ones 7.5 us against 10.0; a first 400 tokens (12800 groups) 5.1 against 5.1, a first 1000 (32000 groups) 5.2
-  // against 7.2.  With more ring work-groups than fit at once the second launch is the cheaper one: 32 sequences, 8
-  // tokens each (8192 groups) 9.5 against 6.5.
-  const bool few_rings = 2LL * a.batch * a.n_kv_heads * (D / a.group) <= 4LL * compute_units();
-  return most >= 16384 || (most > 0 && shared && few_rings);
+  // Owners of ring slices: where per-channel groups leave a ring (a chunk that only moves keys on is a short chain in
+  // either form: 16 heads, 8 tokens 5.0 us in two launches of eight lanes a group, 5.3 here), at most two owners a
+  // compute unit (64 x 8 heads, 8 tokens 17 us here, 7.7 there) and rings of up to 448 rows (above).  At G = 64 one
+  // lane's chain through both variants of a group is longer than the second launch it saves while the chip has room
+  // (8 heads, 512 tokens 12.5 us against 11.3; 32 heads 13.2 against 13.1), and behind a large chunk it is the tail
+  // (128 heads, 3000 tokens 75 against 60): hybrid groups from 32 sequence-heads on and up to 131072 groups only.
+  const long long heads = (long long)a.batch * a.n_kv_heads, owners = 2 * heads * (D / a.group);
+  if (narrow && shared && ring_values && owners <= 2LL * compute_units() && slice_rows <= 448 &&
+      (a.group == 32 || !hybrid || (heads >= 32 && most <= 131072)))
+    return AppendForm::kRingOwners;
+  // A group a lane, or spread over eight: the chain of a lane's group is the longer one, but the per-channel groups
+  // beside it are in one lane each anyway, so eight lanes only pay while the chip is nearly empty (a first prompt of 8
+  // heads, 133 tokens 3.3 us against 3.9; 700 (18176 groups) 5.5 against 4.9; 4000 15.8 against 7.7), or, with nothing
+  // but keys, as long as there are wavefronts to spare (2048 heads, 2 tokens (16384 groups) 7.5 against 9; 8 tokens
+  // 10.2 against 10.5).
+  return most < (values ? 4096 : 65536) ? AppendForm::kLanes8 : AppendForm::kLane;
 }
 
-hipError_t launch_quantize_bulk_g64(const QuantArgs& a, hipStream_t stream);
-hipError_t launch_quantize_bulk(const QuantArgs& a, hipStream_t stream) {
-  if (a.group == 64) return launch_quantize_bulk_g64(a, stream);
+hipError_t launch_quantize_owners_g64(const QuantArgs& a, hipStream_t stream);
+hipError_t launch_quantize_owners(const QuantArgs& a, hipStream_t stream) {
+  if (a.group == 64) return launch_quantize_owners_g64(a, stream);
 #else
-hipError_t launch_quantize_bulk_g64(const QuantArgs& a, hipStream_t stream) {
+hipError_t launch_quantize_owners_g64(const QuantArgs& a, hipStream_t stream) {
 #endif
   if (a.group != G) return hipErrorInvalidValue;
   const bool inner = a.job[0].form == kPerToken;
@@ -298,10 +284,10 @@ hipError_t launch_quantize_bulk_g64(const QuantArgs& a, hipStream_t stream) {
   const QuantTensorJob &jt = a.job[inner ? 0 : 1], &jc = a.job[inner ? 1 : 0];
   const long long per_bh_t = (split_rows(a, jt).fresh + kUnitRows - 1) / kUnitRows, per_bh_c = split_rows(a, jc).fresh / G;
   const long long ring_groups = 2 * BH * kSlices, blocks = (BH * (per_bh_t + per_bh_c) + 3) / 4;
-  const BulkPlan p = {(uint32_t)ring_groups, (uint32_t)per_bh_t, (uint32_t)per_bh_c};
+  const OwnersPlan p = {(uint32_t)ring_groups, (uint32_t)per_bh_t, (uint32_t)per_bh_c};
   const unsigned grid = (unsigned)(ring_groups + blocks);
-  if (inner) quantize_bulk_kernel<true><<<grid, 256, 0, stream>>>(a, p);
-  else quantize_bulk_kernel<false><<<grid, 256, 0, stream>>>(a, p);
+  if (inner) quantize_owners_kernel<true><<<grid, 256, 0, stream>>>(a, p);
+  else quantize_owners_kernel<false><<<grid, 256, 0, stream>>>(a, p);
   return hipGetLastError();
 }
 

@@ -1,7 +1,9 @@
-"""The bulk quantiser (one launch for a chunk: rows that leave the ring, new rows, window copies) against the oracle.
+"""Appends of prompts and chunks, in each form they run in (a group a lane, a group on eight lanes, owners of ring
+slices), against the oracle.
 
-Every byte is compared.  The sizes cross the edges of its units: rows per wavefront (16 at G = 32, 32 at G = 64), groups
-per wavefront of a ring slice, chunks shorter and longer than the windows, a chunk that ends inside a group.
+Every byte is compared.  The sizes cross the edges of the forms' units (rows per wavefront: 16 at G = 32, 32 at G = 64;
+groups per wavefront of a ring slice), chunks shorter and longer than the windows, a chunk that ends inside a group, and
+the lines between the forms.
 """
 import numpy as np
 import pytest
@@ -60,6 +62,73 @@ def test_bulk_append_bit_exact(env, kind, bits, group, modes, literal, recent, c
         iq.innerq_quantize_append(g, dev(K[:, :, at:at + c]), dev(V[:, :, at:at + c]), None if inv is None else dev(inv))
         at += c
     assert_cache_equal(g, want, o)
+
+
+@pytest.mark.parametrize("heads,group,recent,chunks", [
+    (33, 64, 64, (200, 140, 300)),                        # owners of hybrid groups of 64: from 32 sequence-heads on
+    (31, 64, 64, (200, 140, 300)),                        # ... below it two launches
+    (2, 32, 416, (900, 448, 449, 447, 480)),              # rings of 448 rows and more
+    (40, 32, 32, (70, 2, 3, 130, 27, 4)),                 # keys only, few groups, 4096 groups and more
+])
+def test_lines_between_the_forms(env, heads, group, recent, chunks):
+    torch, iq = env
+    n = sum(chunks)
+    w = wl.Workload("l", 1, heads, heads, 128, n, 2, group, 4, recent)
+    o = oracle_config(w)
+    rng = np.random.default_rng(n)
+    K, V = values(rng, (1, heads, n, 128), "normal"), values(rng, (1, heads, n, 128), "ties")
+    g = iq.allocate_cache(gpu_config(o))
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    at = 0
+    for c in chunks:
+        iq.innerq_quantize_append(g, dev(K[:, :, at:at + c]), dev(V[:, :, at:at + c]))
+        at += c
+    assert_cache_equal(g, orc.cache_init_prefill(o, K, V), o)
+
+
+def append_us(torch, iq, heads, group, recent, cached, t):
+    """GPU time of one append of t tokens onto `cached` ones, from a replayed graph of ten."""
+    cfg = iq.make_config(1, heads, heads, 128, 2, group, 4, recent, capacity_tokens=-(-(cached + t) // 64) * 64)
+    c = iq.allocate_cache(cfg)
+    x = torch.randn(1, heads, max(cached, t), 128, device="cuda").half()
+    iq.innerq_quantize_append(c, x[:, :, :cached].contiguous(), x[:, :, :cached].contiguous())
+    x = x[:, :, :t].contiguous()
+
+    def again():
+        c.c.n_tokens = c.c.store_ahead_tokens = cached
+        iq.innerq_quantize_append(c, x, x)
+
+    again()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(10):
+            again()
+    best = []
+    for _ in range(6):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        graph.replay()
+        b.record()
+        b.synchronize()
+        best.append(a.elapsed_time(b) * 100)
+    return min(best)
+
+
+@pytest.mark.parametrize("group", [32, 64])
+def test_long_windows_use_the_whole_chip(env, group):
+    """The rows of a long ring are no work for one work-group: with a window of 8192 tokens instead of 128 a chunk of
+    16384 has to read and copy as much again (12 and 17 us), not 86 (G = 32) and 158 us (G = 64)."""
+    torch, iq = env
+    short, long = (append_us(torch, iq, 1, group, recent, recent + 1000, 16384) for recent in (128, 8192))
+    assert long < 4 * short, (short, long)
+
+
+def test_many_heads_use_the_whole_chip(env):
+    """Two tokens of 2048 heads have work for a few thousand wavefronts: 8 us, where 256 heads take 6; a work-group for
+    every slice of every ring took 52."""
+    torch, iq = env
+    few, many = append_us(torch, iq, 256, 32, 128, 1000, 2), append_us(torch, iq, 2048, 32, 128, 1000, 2)
+    assert many < 3 * few, (few, many)
 
 
 @pytest.mark.parametrize("kind,bits,group", [(orc.KIND_INNER, 2, 32), (orc.KIND_INNER, 4, 64), (orc.KIND_OUTER, 3, 32)])
