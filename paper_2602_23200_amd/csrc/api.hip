@@ -443,10 +443,14 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
     // comparison kernels run the window chunks as extra wavefronts of the same launch
     n_splits = (int)(fused_kind == 1 ? best_plain + n_win_chunks : best_plain);
     // Token counts on the device: the wavefronts planned for sequences of the bound's length go to the sequences by
-    // their lengths (16 sequences of 1k to 16k tokens: 35.3 us per step with the same number each, 29.9 shared), as
-    // many to one as it has partial slots.
+    // their lengths, as many to one as it has partial slots, where there is something to gain: 16 sequences of 1k to
+    // 16k tokens, 35.3 us per step with the same number each, 29.9 shared.  The sharing itself costs 1 to 1.7 us in
+    // front of the first load, and packs the wavefronts of short sequences onto fewer compute units, so it wants
+    // several tiles per wavefront (8 sequences x 8 heads, bound 2000 tokens: 13.8 against 14.9 shared; 8000 tokens,
+    // lengths spread 16-fold: 18.2 against 15.9) and several wavefronts per head (16 x 32 heads, bound 4000: 28.8 against 38.2).
     const long long shared = (long long)n_splits * c.batch;
-    if (n_dev && c.batch > 1 && c.batch <= kSharedBatchMost && (n_win_chunks + 1) * c.batch <= shared) {
+    if (n_dev && c.batch > 1 && c.batch <= kSharedBatchMost && (n_win_chunks + 1) * c.batch <= shared &&
+        n_tiles >= 6 * per_head && per_head >= 10) {
       a.shared_waves = (int)shared;
       a.n_valid = static_cast<int*>(workspace) + c.batch;
       n_splits = split_cap(c);

@@ -257,12 +257,15 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       x.cost = n_chunks > 0 ? window_cost((uint32_t)(x.win + n_chunks - 1) / (uint32_t)n_chunks, G) : 0;
       return x;
     };
+    int n;
     if (a.shared_waves > 0) {
-      // BALANCED (a sequence a lane): the smallest number of tiles per wavefront, window chunks counted
-      // in tiles, with which the sequences' wavefronts fit the launch.  No fewer than four tiles (a wavefront pays
-      // its query set-up once).
+      // BALANCED (a sequence a lane): a number of tiles per wavefront, window chunks counted in tiles, with which the
+      // sequences' wavefronts fit the launch: the smallest one below 8, at most an eighth above it beyond (every try is a
+      // scan of the lengths, in front of the first load).  No fewer than four tiles (a wavefront pays its query set-up
+      // once).
       const int total = (int)gridDim.x;
-      const Length x = length(clamped(lane < a.batch ? a_in.n_dev[lane] : 0));
+      const int n_lane = clamped(lane < a.batch ? a_in.n_dev[lane] : 0);
+      const Length x = length(n_lane);
       const int work = lane < a.batch ? x.tiles + n_chunks * x.cost : 0;
       int quota = (wave_scan(work).total + total - 1) / total;
       quota = quota < 4 ? 4 : quota;
@@ -281,8 +284,11 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       if (b >= a.batch) return;                            // (wave-uniform)
       n_splits = __builtin_amdgcn_readlane(mine, b);
       s_idx -= __builtin_amdgcn_readlane(sc.upto, b) - n_splits;
+      n = __builtin_amdgcn_readlane(n_lane, b);            // (not read again: a memory round trip)
+    } else {
+      n = clamped(a_in.n_dev[b]);
     }
-    const Length x = length(clamped(a_in.n_dev[b]));
+    const Length x = length(n);
     if (s_idx == 0 && hk == 0 && lane == 0) {
       if (a.n_copy) a.n_copy[b] = x.n - 1;                 // for the append that follows
       if (a.n_valid) a.n_valid[b] = n_splits + n_chunks;   // partial results of this sequence's heads

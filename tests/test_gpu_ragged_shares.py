@@ -2,7 +2,8 @@
 
 Batches at the edges of the plan: two sequences, 32 (the most that share) and 33 and 65 (every sequence the same number), one long
 sequence among short ones (as many wavefronts as it has partial slots), all short (none has a tile), equal lengths, and
-a loose bound.  Every sequence against the oracle on its own.
+a loose bound; bounds on both sides of the line from which on wavefronts are shared (six tiles for each, ten for a
+sequence's kv head).  Every sequence against the oracle on its own.
 """
 import numpy as np
 import pytest
@@ -26,14 +27,33 @@ TOL = 2e-3
     ("loose bound", [700, 90, 2100], (8, 1), 64, 9000),
 ])
 def test_every_sequence_of_a_shared_launch(name, lengths, heads, group, bound):
+    run(name, lengths, heads, group, bound)
+
+
+# (several tiles for every wavefront of the bound and at least ten wavefronts per sequence and kv head, so these share)
+@pytest.mark.parametrize("name,lengths,heads,group,bound,more", [
+    ("two", [3000, 17], (64, 64), 32, 7000, {}),
+    ("32", [5 + 37 * i % 1500 for i in range(32)], (16, 4), 32, 7000, dict(half=True)),
+    ("one long", [40, 6800] + [5 + 50 * i for i in range(14)], (32, 8), 32, 7000, dict(scaled=True)),
+    ("all short", [1, 5, 130, 60, 164, 163, 132, 131] * 3, (12, 6), 64, 9000, dict(bits=4)),
+    ("equal", [1000] * 17, (8, 8), 64, 8000, dict(bits=3)),
+    ("a spill in each", [100 + 61 * i for i in range(16)], (8, 8), 32, 7000, dict(bits=3, v_bits=2, steps=33, half=True)),
+    ("just below the line", [900 + 61 * i for i in range(16)], (8, 8), 32, 6200, {}),
+    ("just above the line", [900 + 61 * i for i in range(16)], (8, 8), 32, 6400, {}),
+])
+def test_shared_launch_over_widths_and_options(name, lengths, heads, group, bound, more):
+    run(name, lengths, heads, group, bound, **more)
+
+
+def run(name, lengths, heads, group, bound, steps=3, bits=2, v_bits=0, scaled=False, half=False):
     import torch
     from paper_2602_23200_amd import binding as iq
     assert torch.cuda.is_available(), "these tests need the MI355X"
-    B, steps = len(lengths), 3
+    B = len(lengths)
     n_most = max(lengths) + steps
-    w = wl.Workload("r", B, heads[0], heads[1], 128, n_most, 2, group, 4, 128, seed=7)
+    w = wl.Workload("r", B, heads[0], heads[1], 128, n_most, bits, group, 4, 128, seed=7)
     cap = -(-max(n_most, bound) // group) * group + group
-    o, o1 = oracle_config(w, capacity=cap), oracle_config(w.with_(batch=1), capacity=cap)
+    o, o1 = oracle_config(w, capacity=cap, v_bits=v_bits), oracle_config(w.with_(batch=1), capacity=cap, v_bits=v_bits)
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
     g = iq.allocate_cache(gpu_config(o))
     want, kv = [], []
@@ -45,18 +65,66 @@ def test_every_sequence_of_a_shared_launch(name, lengths, heads, group, bound):
         iq.innerq_quantize_ahead(view)
         want.append(orc.cache_init_prefill(o1, K[:, :, :n], V[:, :, :n]))
         kv.append((K, V))
+    norm = np.random.default_rng(3).uniform(0.5, 2.0, (heads[1], 128)).astype(np.float32) if scaled else None
     counts = torch.tensor(lengths, dtype=torch.int32, device="cuda")
     ws = iq.allocate_workspace(g.cfg)
     ws.fill_(0xA5)                                        # (its contents must not matter)
+    out = torch.empty(B, heads[0], 128, dtype=torch.float16 if half else torch.float32, device="cuda")
     for i in range(steps):
         k1 = np.concatenate([K[:, :, n + i:n + i + 1] for (K, _), n in zip(kv, lengths)])
         v1 = np.concatenate([V[:, :, n + i:n + i + 1] for (_, V), n in zip(kv, lengths)])
         q = wl.query(w, step=i)
-        out = iq.innerq_decode_step_ragged(g, counts, bound or n_most, dev(k1), dev(v1), dev(q), ws).cpu().numpy()
+        iq.innerq_decode_step_ragged(g, counts, bound or n_most, dev(k1), dev(v1), dev(q), ws, out=out,
+                                     q_scale=None if norm is None else dev(norm))
+        got = out.float().cpu().numpy()
         assert counts.cpu().tolist() == [n + i + 1 for n in lengths]
         for b in range(B):
             orc.quantize_append(o1, want[b], k1[b:b + 1], v1[b:b + 1])
-            if B < 20 or b % 7 == 0:
-                assert max_rel_err(out[b:b + 1], orc.decode_attention(o1, want[b], q[b:b + 1])) <= TOL, f"{name} {i} {b}"
+            if (B < 20 or b % 7 == 0) and (steps < 10 or i % 8 == 0):
+                ref = orc.decode_attention(o1, want[b], q[b:b + 1], q_scale=norm)
+                assert max_rel_err(got[b:b + 1], ref) <= TOL, f"{name} {i} {b}"
     for b in range(B):
         assert_cache_equal(g, want[b], o1, bsel=slice(b, b + 1), what=f"{name} sequence {b}", per_sequence=True)
+
+
+def test_short_sequences_keep_their_wavefronts():
+    """Four sequences of 750 tokens behind a bound of 1500 have a wavefront per tile, as in a plain step: a few
+    tenths longer for reading the counts, not half as long again for sharing wavefronts (12.5 and 18.5 us, plain 10.5)."""
+    import torch
+    from paper_2602_23200_amd import binding as iq
+    B, n, bound = 4, 750, 1500
+    cfg = iq.make_config(B, 4, 1, 128, 2, 32, 4, 128, capacity_tokens=2048)
+    g, ws = iq.allocate_cache(cfg), iq.allocate_workspace(cfg)
+    x = torch.randn(B, 1, n, 128, device="cuda").half()
+    iq.innerq_quantize_append(g, x, x)
+    iq.innerq_quantize_ahead(g)
+    q, one = torch.randn(B, 4, 128, device="cuda").half(), x[:, :, :1].contiguous()
+    counts = torch.full((B,), n, dtype=torch.int32, device="cuda")
+    first, out = counts.clone(), torch.empty(B, 4, 128, device="cuda")
+
+    def plain():
+        g.c.n_tokens, g.c.store_ahead_tokens = n, n + 1
+        counts.copy_(first)                               # (in both, for its time)
+        iq.innerq_decode_step(g, one, one, q, ws, out=out)
+
+    def ragged():
+        counts.copy_(first)
+        iq.innerq_decode_step_ragged(g, counts, bound, one, one, q, ws, out=out)
+
+    def us(call):
+        call()
+        graph, best = torch.cuda.CUDAGraph(), []
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                call()
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            graph.replay()
+            b.record()
+            b.synchronize()
+            best.append(a.elapsed_time(b) * 50)
+        return min(best)
+
+    t_plain, t_ragged = us(plain), us(ragged)
+    assert t_ragged < 1.4 * t_plain, (t_plain, t_ragged)
