@@ -156,8 +156,8 @@ __device__ __forceinline__ void add_row_groups(const float (&o)[RT][8], float (&
 // fp16 row each, coalesced), ROWS rows a thread, and a tile's key and value loads all go out before the
 // first is used.  On the short caches this kernel is there for, a launch is one tile per work-group and
 // its time is a memory round trip and the instructions of one thread, so 1024 threads take a row each
-// (ROWS = 1); with several tiles per work-group 256 threads take four (ROWS = 4).  The kernel before this
-// one decoded element by element: 2 x 8 heads x 165 tokens, kernel trace, 27 us (100 tokens) and 36 us
+// (ROWS = 1); with several tiles per work-group, or more work-groups than compute units, 256 threads take four
+// (ROWS = 4).  The kernel before this one decoded element by element: 2 x 8 heads x 165 tokens, kernel trace, 27 us (100 tokens) and 36 us
 // (packed key rows among them) against 6.2 and 6.7; four rows a thread 7.6 and 8.4.  Attention call on
 // longer caches (4 sequences, 8 kv heads, 4k tokens, 4-bit keys with 2-bit values): 146 us against 66.
 template <int KF, int VF, int ROWS>
@@ -328,9 +328,13 @@ hipError_t launch_attention_generic(const AttnArgs& a, long long a0, long long a
   };
   const int kf = packed_form(a.k), vf = packed_form(a.v);
   const long long tokens = (a1 - a0) + (b1 - b0);
-  const bool one_tile = (tokens + n_chunks - 1) / n_chunks <= TILE;
+  // A row a thread while every work-group has a compute unit to itself (16 x 8 heads, 70 tokens, 256 work-groups: step
+  // 9.3 us against 9.9); beyond, work-groups of 1024 threads wait for one another (129 tokens, 384 of them: 13.3 against
+  // 11.1; 256 x 8 heads, one token: 35.8 against 20.7).
+  const bool one_row_each =
+      (tokens + n_chunks - 1) / n_chunks <= TILE && (long long)grid.x * grid.y * grid.z <= (long long)compute_units();
   auto go = [&](auto one_row, auto four_rows) {
-    if (one_tile) one_row<<<grid, 1024, 0, stream>>>(a, a0, a1, b0, b1, n_chunks, first_slot);
+    if (one_row_each) one_row<<<grid, 1024, 0, stream>>>(a, a0, a1, b0, b1, n_chunks, first_slot);
     else four_rows<<<grid, 256, 0, stream>>>(a, a0, a1, b0, b1, n_chunks, first_slot);
     return hipGetLastError();
   };

@@ -56,3 +56,19 @@ def test_fp32_attention(env, kind, bits, v_bits, group, heads, n_tokens, scaled)
     out = iq.innerq_decode_attention(g, dev(q), iq.allocate_workspace(g.cfg),
                                      q_scale=None if norm is None else dev(norm.astype(np.float32)))
     assert max_rel_err(out.cpu().numpy(), want) <= TOL
+
+
+@pytest.mark.parametrize("batch,n_tokens", [(128, 1), (129, 1), (128, 64), (64, 65), (65, 65), (300, 3)])
+@pytest.mark.parametrize("heads", [(2, 2), (8, 2)])
+def test_more_work_groups_than_compute_units(env, batch, n_tokens, heads):
+    """Short caches of many sequences: up to 256 work-groups take a row a thread, more take four."""
+    torch, iq = env
+    w = wl.Workload("g", batch, heads[0], heads[1], 128, n_tokens, 2, 32, 4, 128, seed=batch)
+    o = oracle_config(w)
+    K, V = wl.kv_full(w)
+    q = wl.query(w)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    g = iq.allocate_cache(gpu_config(o))
+    iq.innerq_quantize_append(g, dev(K), dev(V))
+    out = iq.innerq_decode_attention(g, dev(q), iq.allocate_workspace(g.cfg))
+    assert max_rel_err(out.cpu().numpy(), orc.decode_attention(o, orc.cache_init_prefill(o, K, V), q)) <= TOL
