@@ -116,13 +116,14 @@ __device__ inline void merge_head(const AttnArgs& a, long long bhq, int wave, in
   }
 }
 
-// Whether a head's partials are shared by four wavefronts: where there are many and work-groups are few.  (One rule for both
-// launches that merge, so that both give the same bits.)  Per step: 1 sequence x 4 heads x 512 partials 34.4 us -> 17.1,
-// 128 heads x 68 74.1 -> 73.1, 32 heads x 35 13.4 -> 13.1; 512 x 36 28.0 -> 29.5 and 1024 x 12 41.7 -> 44.7 (too many work-groups),
-// 4 heads x 18 merge 3.4 -> 4.0, and in the attention call's own launch 256 x 35 34.0 -> 35.0.
+// Whether a head's partials are shared by four wavefronts: where one wavefront would need a second round of loads and
+// work-groups are few.  (One rule for both launches that merge, so that both give the same bits.)  Per step: 4 heads, 31
+// partials 9.5 us -> 9.9, 38 10.2 -> 10.0, 512 partials 34.4 -> 17.1; 128 heads, 31 11.2 -> 11.5, 35 11.6 -> 11.2, 68 74.1 ->
+// 73.1; one head alone 9.0 -> 9.4 up to 48 partials; 256 heads, 35 13.3 -> 13.7, 49 and more 20.7 -> 20.4; 512 x 36 28.0 -> 29.5
+// and 1024 x 12 41.7 -> 44.7 (too many work-groups).
 inline bool merge_is_shared(const AttnArgs& a) {
   const long long heads = (long long)a.batch * a.n_q_heads;
-  return (a.n_partials >= 25 && heads <= 64) || (a.n_partials >= 49 && heads <= 256);
+  return (a.n_partials >= 33 && heads >= 4 && heads <= 128) || (a.n_partials >= 49 && heads <= 256);
 }
 
 }  // namespace innerq
