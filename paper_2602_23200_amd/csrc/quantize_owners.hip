@@ -230,7 +230,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 3
 // One chunk measured in all forms, 2800 shapes of 1 to 2048 sequence-heads, 2 to 32768 tokens, windows of 32 to 16384, both
 // group sizes: the rule is 0.7 % (geometric mean) behind the best form of each.
 AppendForm append_form(const QuantArgs& a) {
-  if (a.n_dev || a.t_new < 2) return AppendForm::kLanes8;
+  if (a.n_dev) return AppendForm::kLanes8;
   long long most = 0, slice_rows = 0;
   bool shared = false, values = false, ring_values = false, hybrid = false;
   bool narrow = a.n_old + a.t_new < (1LL << 31);         // (the owners' row arithmetic is 32-bit)
@@ -267,9 +267,10 @@ AppendForm append_form(const QuantArgs& a) {
   // A group a lane, or spread over eight: the chain of a lane's group is the longer one, but the per-channel groups
   // beside it are in one lane each anyway, so eight lanes only pay while the chip is nearly empty (a first prompt of 8
   // heads, 133 tokens 3.3 us against 3.9; 700 (18176 groups) 5.5 against 4.9; 4000 15.8 against 7.7), or, with nothing
-  // but keys, as long as there are wavefronts to spare (2048 heads, 2 tokens (16384 groups) 7.5 against 9; 8 tokens
-  // 10.2 against 10.5).
-  return most < (values ? 4096 : 65536) ? AppendForm::kLanes8 : AppendForm::kLane;
+  // but keys, as long as there are wavefronts to spare: a single token of 8192 heads (32768 groups) 7.0 against 5.9, of
+  // 2048 heads the same; beside the second launch of a chunk longer (2048 heads, 2 tokens (16384 groups) 7.5 against
+  // 9; 8 tokens 10.2 against 10.5).
+  return most < (values ? 4096 : shared ? 65536 : 16384) ? AppendForm::kLanes8 : AppendForm::kLane;
 }
 
 hipError_t launch_quantize_owners_g64(const QuantArgs& a, hipStream_t stream);
