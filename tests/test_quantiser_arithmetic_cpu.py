@@ -58,6 +58,104 @@ def test_reciprocal_correction_step_equals_ieee_division(kind):
         assert (frac[ok] == 0.5).mean() > 0.1                        # the exact ties are really in the sample
 
 
+def numerators_and_scales(kind, n):
+    """What a lane that holds a whole group meets: (x - min) or x, and the group's scale; also the exact ties
+    (k + 1/2) S and their fp32 neighbours."""
+    rng = np.random.default_rng({"asym": 11, "sym": 12, "ties": 13, "beside_ties": 14, "denormal_scale": 15}[kind])
+    S = fp16_values(rng, n, lo=0x0400)
+    if kind == "denormal_scale":
+        S = rng.integers(1, 0x400, n, dtype=np.uint16).view(np.float16).astype(f32)
+    if kind in ("ties", "beside_ties"):
+        k = rng.integers(-9, 17, n).astype(f32)
+        num = ((k + f32(0.5)) * S).astype(f32)                        # exact: at most 16 bits
+        if kind == "beside_ties":
+            num = np.nextafter(num, rng.choice(f32([-np.inf, np.inf]), n))
+        return num, S
+    lo = (rng.standard_normal(n) * np.exp2(rng.integers(-10, 8, n))).astype(np.float16).astype(f32)
+    with np.errstate(over="ignore"):                                  # (infinite ones are left out below)
+        x = (lo + S * (rng.random(n) * 16).astype(f32)).astype(np.float16).astype(f32)
+        return ((S * (rng.random(n) * 18 - 9)).astype(np.float16).astype(f32) if kind == "sym" else (x - lo).astype(f32)), S
+
+
+@pytest.mark.skipif(np.finfo(ld).nmant < 63, reason="needs an extended-precision long double")
+@pytest.mark.parametrize("kind", ["asym", "sym", "ties", "beside_ties", "denormal_scale"])
+def test_two_piece_reciprocal_gives_the_code_of_ieee_division(kind):
+    """A lane that holds a whole group forms its codes as rint(fma(num, r_hi, fl(num r_lo))) with r_hi = fl(1 / S) and
+    r_lo = fl((1 - S r_hi) r_hi): the same integer as rint(fl(num / S)) for every quotient that a code can come from."""
+    num, S = numerators_and_scales(kind, 2_000_000)
+    with np.errstate(all="ignore"):
+        hi = (f32(1) / S).astype(f32)
+        rem = f64(1) - S.astype(f64) * hi.astype(f64)                # 11 x 24 bits: exact in fp64
+        assert np.array_equal(rem, rem.astype(f32).astype(f64))       # and what the fused multiply-add leaves fits fp32
+        lo = (rem.astype(f32) * hi).astype(f32)
+        tail = (num * lo).astype(f32)
+        quotient = (num.astype(ld) * hi.astype(ld) + tail.astype(ld)).astype(f32)      # one rounding
+        want = (num / S).astype(f32)
+    ok = np.isfinite(num) & np.isfinite(S) & (np.abs(want) <= 64)
+    assert ok.mean() > 0.8
+    assert np.array_equal(np.rint(quotient[ok]), np.rint(want[ok]))
+    if kind == "ties":
+        assert (np.abs(want[ok] - np.trunc(want[ok])) == 0.5).all()
+
+
+@pytest.mark.skipif(np.finfo(ld).nmant < 63, reason="needs an extended-precision long double")
+def test_ternary_codes():
+    """2-bit symmetric codes (S = max |x|, so |x| <= S): x r + 1.5 2^23 with r = fl(fl(1 / S) (1 - 2^-20)) leaves
+    rint(x / S) in its low bits for every positive fp16 S: the tie S / 2 and its neighbours on both sides, S itself, small
+    and random values, and every value where S is a denormal."""
+    rng = np.random.default_rng(21)
+    bits = np.arange(1, 0x7C00, dtype=np.uint16)
+    S = bits.view(np.float16).astype(f32)
+
+    def check(x, S):
+        x, S = x.astype(f32), S.astype(f32)
+        r = ((f32(1) / S).astype(f32) * f32(1 - 2.0 ** -20)).astype(f32)
+        t = (x.astype(ld) * r.astype(ld) + ld(12582912.0)).astype(f32)
+        code = t - f32(12582912.0)
+        want = np.rint((x / S).astype(f32))
+        assert np.array_equal(code, want)
+        assert np.array_equal(t.view(np.uint32) - np.uint32(0x4B400000), want.astype(np.int32).view(np.uint32))
+
+    half = (S / 2).astype(np.float16)
+    for step in range(-3, 4):
+        x = (half.view(np.uint16).astype(np.int32) + step).clip(0, bits).astype(np.uint16).view(np.float16)
+        check(x, S)
+        check(-x, S)
+    check(S, S)
+    check(-S, S)
+    check(np.zeros_like(S), S)
+    for _ in range(20):
+        check((rng.integers(0, bits.astype(np.int64) + 1).astype(np.uint16)).view(np.float16), S)
+    for s in range(1, 0x400, 7):
+        x = np.arange(0, s + 1, dtype=np.uint16).view(np.float16)
+        check(x, np.full(x.shape, S[s - 1]))
+
+
+@pytest.mark.parametrize("bits,bias", [(2, 0), (2, 2), (3, 0), (3, 4), (4, 0), (4, 8)])
+def test_fields_collected_in_fp32(bits, bias):
+    """Sixteen bits of fields at a time are summed as c 2^(b i) in fp32 (3 bits: low parts and high bits apart, the high bit
+    taken off the low sum): every partial sum is an integer below 2^24, so the result is the packed field word."""
+    rng = np.random.default_rng(bits)
+    low_bits = 2 if bits == 3 else bits
+    per = 16 // low_bits
+    field = rng.integers(0, 1 << bits, (200_000, 16))
+    c = (field - bias).astype(f32)
+    low = np.full((field.shape[0], 16 // per), f32(sum(bias << (low_bits * i) for i in range(per))))
+    high = np.zeros(field.shape[0], dtype=f32)
+    for i in range(16):
+        low[:, i // per] += c[:, i] * f32(1 << (low_bits * (i % per)))
+        if bits == 3:
+            h = np.clip(c[:, i] + f32(bias - 3), f32(0), f32(1))
+            low[:, i // per] += h * f32(-4 * (1 << (low_bits * (i % per))))
+            high += h * f32(1 << i)
+    want_low = np.zeros(low.shape, dtype=np.int64)
+    for i in range(16):
+        want_low[:, i // per] |= (field[:, i] & ((1 << low_bits) - 1)) << (low_bits * (i % per))
+    assert np.array_equal(low.astype(np.int64), want_low)
+    if bits == 3:
+        assert np.array_equal(high.astype(np.int64), ((field >> 2) << np.arange(16)).sum(axis=1))
+
+
 def test_zero_scale_gives_code_zero_without_a_select():
     """A group whose scale is 0 gets r = 0 instead of 1 / 0: every quotient is then exactly 0."""
     num = f32([0.0, 1.5, -3.0, 65504.0])
