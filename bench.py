@@ -52,7 +52,7 @@ def parse():
                         "serial: innerq_quantize_append, then innerq_decode_attention (three launches); two-stream: "
                         "the deferred append on a side stream next to the attention")
     p.add_argument("--inner-kernel", type=int, default=0, choices=[0, 1],
-                   help="0: the default fused kernel (4x4x4 fp16 matrix instructions); 1: the fp8 x fp4 "
+                   help="0: the default fused kernel (fp16 matrix instructions); 1: the fp8 x fp4 "
                         "block-scaled kernel for 2-bit caches (comparison runs)")
     p.add_argument("--cpu-seconds", type=float, default=12.0)
     p.add_argument("--min-timed-ms", type=float, default=50.0,

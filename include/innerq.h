@@ -328,13 +328,16 @@ int innerq_decode_step(const innerq_config_t *cfg, innerq_cache_t *cache, const 
  *                 kernels; the second launch adds one to every entry.  cache->n_tokens and
  *                 cache->store_ahead_tokens (host) are neither read nor written.
  *   max_tokens    host: a bound, n_tokens_dev[b] + 1 <= max_tokens <= capacity_tokens for every b.
- *                 It only sizes the launch: wavefronts are planned for that length, and a batch of up to 32
- *                 sequences shares them by its lengths (larger ones get the same number each), so a
- *                 loose bound costs idle wavefronts, never correctness.  A count outside the bound
+ *                 It only sizes the launch: wavefronts are planned for that length, the same number for
+ *                 every sequence, or (2 to 32 sequences, a bound long enough to give every wavefront
+ *                 several tiles) shared by their lengths.  A loose bound costs idle wavefronts, never
+ *                 correctness.  A count outside the bound
  *                 is clamped on the device (that sequence's result is then unspecified; no buffer
  *                 is overrun).
  * Per sequence b the result equals innerq_decode_step on a cache of n_tokens_dev[b] tokens, bit for
- * bit in the cache; every sequence's store must have been run one step ahead (innerq_quantize_ahead
+ * bit in the cache; the output to the rounding of its sums, whose order follows from max_tokens and, where
+ * wavefronts are shared by length, from the other sequences' lengths as well (the same call on the same
+ * batch repeats itself bit for bit; a sequence in another batch need not); every sequence's store must have been run one step ahead (innerq_quantize_ahead
  * when it was filled, then this call keeps it so).  Inner-grouped caches on the fused kernel only
  * (INNERQ_E_UNSUPPORTED otherwise: outer-grouped and fp16 caches, more than 8 query heads per kv
  * head).  Other arguments and errors as innerq_decode_step. */
@@ -359,8 +362,8 @@ int innerq_profile_next_attention(void *ev_start, void *ev_stop);
 /* Measurement switch (no counterpart in the paper).  2-bit inner-grouped caches have a second
  * fused kernel that computes the same partial results: it forms the inner sums over the stored
  * fields with the block-scaled fp8 x fp4 matrix instruction (2-bit keys and values, at most 4
- * query heads per kv head) instead of 4x4x4 fp16 matrix instructions.  It is slower on the
- * measured configurations and off by default.  which = 0: every configuration on the 4x4x4 form
+ * query heads per kv head) instead of fp16 matrix instructions.  It is slower on the measured
+ * configurations and off by default.  which = 0: every configuration on the fp16 matrix form
  * (default); which = 1: the fp8 x fp4 form where it applies, for side-by-side timing and parity
  * runs.  Process-wide, host-side only; returns INNERQ_E_ARG for any other value. */
 int innerq_select_inner_kernel(int which);

@@ -360,7 +360,7 @@ def innerq_profile_next_attention(ev_start: Optional[int], ev_stop: Optional[int
 
 
 def innerq_select_inner_kernel(which: int) -> None:
-    """0: 4x4x4 fp16 fused kernel everywhere (default); 1: the fp8 x fp4 kernel for 2-bit caches where it applies."""
+    """0: the fp16 matrix form of the fused kernel everywhere (default); 1: the fp8 x fp4 kernel for 2-bit caches where it applies."""
     st = lib().innerq_select_inner_kernel(which)
     if st != OK:
         raise InnerQError(st, "innerq_select_inner_kernel")

@@ -382,7 +382,7 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
   }
   const int r = c.n_q_heads / c.n_kv_heads;
   int n_splits = 0, win_chunk_len = kWindowChunk;
-  // which fused kernel serves this cache (0 = none: element-by-element fallback)
+  // which fused kernel serves this cache (0 = none: the fp32 kernel)
   const int fused_kind =
       attention_inner_supported(a) ? 1 : attention_fp16_supported(a) ? 2 : attention_outer_supported(a) ? 3 : 0;
   const bool fused = fused_kind != 0;

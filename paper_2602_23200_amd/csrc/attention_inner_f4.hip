@@ -7,7 +7,7 @@
 // fields are formed:
 //   * a 2-bit field u, zero-extended to a nibble, IS the E2M1 number u/2 (0, 0.5, 1, 1.5).  A
 //     packed word therefore becomes two fp4 operand registers with one shift and two ANDs (16
-//     fields), against eight ANDs for the fp16-denormal form of the 4x4x4 kernel.
+//     fields), against eight ANDs for the fp16-denormal fields of attention_inner.hip.
 //   * the other operand (query; softmax weights) must then be fp8.  An fp16 query value, scaled
 //     per head by a power of two into [128, 256), is exactly a1 + a2/16 + a3/256 with three E4M3
 //     numbers (4 significant bits each; the factors 1/16 and 1/256 are the instruction's block
@@ -18,7 +18,7 @@
 //     of inner group g and zeros elsewhere, so the 16 x 16 result holds, for 16 tokens (keys) or
 //     16 channels (values), the sums of every group separately: C[(g, h), n].  Three quarters of
 //     the multiplies hit zeros; the instruction is still 4x cheaper per useful product than the
-//     4x4x4 form, and the A operands are shared by every token (keys) or channel (values) of a tile.
+//     4x4x4 fp16 one, and the A operands are shared by every token (keys) or channel (values) of a tile.
 //   * k-index layout, measured: an fp8 operand register block of lane (m, kb) holds
 //     k = 16 kb + 0..15 (registers 0-3, byte order) and k = 64 + 16 kb + 0..15 (registers 4-7);
 //     an fp4 operand of lane (n, kb) holds k = 32 kb + 0..31 (registers 0-3, nibble order).
@@ -32,10 +32,10 @@
 //     result for token group T lands in lane row T, which loaded that group's scales; each lane
 //     row accumulates its own token groups and the rows are added once, at the end.
 //
-// Status: parity-green (same tolerance as the 4x4x4 kernel) and NOT the default.  On the 32k-token
-// Llama-3-8B-shaped configuration it takes 61 us against 40 us for the 4x4x4 kernel, with or
-// without its loads.  Counters: 25 % fewer vector instructions per token than the 4x4x4 kernel,
-// but an fp8 x fp4 instruction occupies the matrix pipe for 32 cycles (the fp8 rate: 8 passes, not
+// Status: parity-green (same tolerance as the default kernel) and NOT the default.  On the 32k-token
+// Llama-3-8B-shaped configuration it takes 61 us against 37 us for the default kernel, with or
+// without its loads.  Counters, taken against the default kernel of the time (4x4x4 fp16 instructions, 40 us, 12.0 M
+// vector instructions a launch; it has 10.7 M now): 25 % fewer vector instructions per token, but an fp8 x fp4 instruction occupies the matrix pipe for 32 cycles (the fp8 rate: 8 passes, not
 // the 4 of an all-fp4 product), so the matrix-pipe time per token is 27 % higher, and with two
 // wavefronts per SIMD the longer dependent chains (three chained instructions per sum, the row
 // transposes, the three-way split of the weights) leave the SIMD idle 40 % of the time.

@@ -165,7 +165,7 @@ struct AttnArgs {
   PageMap pages;
 };
 
-// Generic (any form, element-by-element) partial attention over the token set
+// Generic (any form, fp32) partial attention over the token set
 // [a0,a1) U [b0,b1), cut into n_chunks equal chunks, written to partial slots
 // first_slot .. first_slot+n_chunks.
 hipError_t launch_attention_generic(const AttnArgs& a, long long a0, long long a1, long long b0, long long b1,
@@ -193,14 +193,14 @@ hipError_t launch_attention_inner_paged(const AttnArgs& a, long long n_both, int
                                         hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 
 // The same partial results for 2-bit codes from the block-scaled fp8 x fp4 matrix instruction
-// (128-token tiles).  Parity-green but slower than the 4x4x4 form (see the file header), so it runs
+// (128-token tiles).  Parity-green but slower than the fp16 matrix form (see the file header), so it runs
 // only on request: launch_attention_inner and attention_inner_waves_per_cu route to it when
 // g_inner_variant == 1 and it applies.
 bool attention_inner_f4_supported(const AttnArgs& a);
 int attention_inner_f4_waves_per_cu(const AttnArgs& a);
 hipError_t launch_attention_inner_f4(const AttnArgs& a, long long n_both, int n_splits, const WindowSet& win,
                                      hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
-extern std::atomic<int> g_inner_variant;   // 0: 4x4x4 fp16 form everywhere (default); 1: fp8 x fp4 form where it applies
+extern std::atomic<int> g_inner_variant;   // 0: fp16 matrix form everywhere (default); 1: fp8 x fp4 form where it applies
 
 // A host-side answer that depends on the kernel instance only (an occupancy query, a device attribute),
 // looked up once and kept: relaxed atomics, so that concurrent first callers race benignly (both store
