@@ -9,9 +9,10 @@
 //   * per-channel form: one group of G tokens, a lane a pair of channels (a token's row is one coalesced 256-byte load).
 //
 // What bounds it is the chain of an owner: the rounds of loads of the rows that leave, one lane's whole group, the
-// rounds of copies.  It pays while the owners fit the chip and their rings are short (append_form): 512 tokens onto 500
-// of 8 heads, G = 32, 7.9 us against 8.7 in two launches; 32 heads 9.0 against 10.5; but with a window of 1024 tokens
-// 19 against 10, and 157 against 13 with 8192 (1 head, G = 64): a ring's rows are one work-group's serial rounds.
+// rounds of copies.  It pays while the owners fit the chip and their rings are short, and for the longest prompts with
+// key factors (append_form): 512 tokens onto 500 of 8 heads, G = 32, 7.9 us against 8.7 in two launches; 32 heads 9.0
+// against 10.5; but with a window of 1024 tokens 19 against 10, and 157 against 13 with 8192 (1 head, G = 64): a ring's
+// rows are one work-group's serial rounds.
 #include "innerq_dev.h"
 #include "quant_group.h"
 
@@ -261,8 +262,13 @@ AppendForm append_form(const QuantArgs& a) {
   // (8 heads, 512 tokens 12.5 us against 11.3; 32 heads 13.2 against 13.1), and behind a large chunk it is the tail
   // (128 heads, 3000 tokens 75 against 60): hybrid groups from 32 sequence-heads on and up to 131072 groups only.
   const long long heads = (long long)a.batch * a.n_kv_heads, owners = 2 * heads * (D / a.group);
-  if (narrow && shared && ring_values && owners <= 2LL * compute_units() && slice_rows <= 448 &&
-      (a.group == 32 || !hybrid || (heads >= 32 && most <= 131072)))
+  const bool few_short = narrow && owners <= 2LL * compute_units() && slice_rows <= 448;
+  if (few_short && shared && ring_values && (a.group == 32 || !hybrid || (heads >= 32 && most <= 131072)))
+    return AppendForm::kRingOwners;
+  // Long prompts with key factors, G = 32: the units of new rows here take 2 to 5 % less than consecutive groups in
+  // consecutive lanes (8 heads x 131072 tokens, 2 bits 153 us against 159; 8 x 8 x 32768 294 against 302, 4 bits 317 against
+  // 327; 32 x 16384 (2 M groups) 82.4 against 82.1; 8 x 8 x 4096 38.7 against 37.2; G = 64 5 to 20 % more).
+  if (few_short && a.group == 32 && a.job[0].form == kPerToken && a.job[0].normalise && most >= (1LL << 22))
     return AppendForm::kRingOwners;
   // A group a lane, or spread over eight: the chain of a lane's group is the longer one, but the per-channel groups
   // beside it are in one lane each anyway, so eight lanes only pay while the chip is nearly empty (a first prompt of 8

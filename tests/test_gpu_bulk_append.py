@@ -86,6 +86,23 @@ def test_lines_between_the_forms(env, heads, group, recent, chunks):
     assert_cache_equal(g, orc.cache_init_prefill(o, K, V), o)
 
 
+def test_long_prompt_with_key_factors(env):
+    """From 4 M groups on a prompt runs as units of new rows; in chunks of any length it leaves the same bytes."""
+    torch, iq = env
+    n, H = 131400, 8
+    cfg = iq.make_config(1, H, H, 128, 2, 32, 4, 128, capacity_tokens=131456)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    K, V = (torch.randn(1, H, n, 128, device="cuda", generator=gen).half() for _ in range(2))
+    inv = torch.rand(H, 128, device="cuda", generator=gen) + 0.5
+    whole, parts = iq.allocate_cache(cfg), iq.allocate_cache(cfg)
+    iq.innerq_quantize_append(whole, K, V, inv)
+    for a, b in ((0, 70000), (70000, 70601), (70601, n)):
+        iq.innerq_quantize_append(parts, K[:, :, a:b].contiguous(), V[:, :, a:b].contiguous(), inv)
+    for name, buf in whole.buffers.items():
+        if buf is not None and not name.endswith("recent"):               # (a ring's spare slots hold older tokens)
+            assert torch.equal(buf, parts.buffers[name]), name
+
+
 def append_us(torch, iq, heads, group, recent, cached, t):
     """GPU time of one append of t tokens onto `cached` ones, from a replayed graph of ten."""
     cfg = iq.make_config(1, heads, heads, 128, 2, group, 4, recent, capacity_tokens=-(-(cached + t) // 64) * 64)
