@@ -26,7 +26,7 @@
 //     the A operand (query / probabilities), the constant into the group scale.
 //     Measured, 8 x 8 heads x 32k tokens, 2-bit, step: 41.2 us -> 39.8 (3-bit 59.3 -> 56.9; 8 query heads per kv head,
 //     16k tokens, 3-bit keys 31.7 -> 27.5; sequences of 1k to 16k tokens 39.3 -> 36.6), error against fp64 2.8e-4 -> 2.3e-4
-//     (4-bit, 4k tokens 5.5e-4 -> 2.9e-4; 128k tokens 1.9e-4 -> 0.8e-4).
+//     (4-bit, 4k tokens 5.4e-4 -> 2.7e-4; 128k tokens 2.5e-4 -> 1.2e-4; eight heads, 16k tokens 1.8e-4 -> 1.1e-4).
 //   * 3-bit fields are stored as a plane of 2-bit low parts followed by a plane of
 //     high bits; the high bits are 1-bit fields of the same kind (2^(pos - 24)) and
 //     join the same MFMA chains through operand tables that carry their weight 4.
