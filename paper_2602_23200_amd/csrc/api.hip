@@ -1,9 +1,13 @@
 // C ABI of libinnerq (see include/innerq.h): argument checks, the window /
 // eviction arithmetic on the host, and kernel dispatch.  No device memory is
 // allocated here and nothing synchronises.
+#include <time.h>
+#include <unistd.h>
+
 #include <mutex>
 
 #include "innerq_dev.h"
+#include "merge.h"
 
 using namespace innerq;
 
@@ -108,6 +112,21 @@ PageMap pages_of(const innerq_config_t& c, const innerq_cache_t& k) {
   pm.tiles_per_seq = (int)(c.capacity_tokens / kPageTokens);
   pm.pool_pages = (int)c.page_pool_pages;
   return pm;
+}
+
+// The tag of a launch that joins its own partial results: odd, another one for each of 2^31 launches, and from another
+// start in every process.
+uint32_t next_join_tag() {
+  static const uint32_t start = [] {
+    timespec t = {};
+    (void)clock_gettime(CLOCK_REALTIME, &t);
+    unsigned long long x = (unsigned long long)t.tv_sec * 1000000007ull + (unsigned long long)t.tv_nsec;
+    x ^= (unsigned long long)getpid() << 40;
+    x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
+    return (uint32_t)(x >> 32);
+  }();
+  static std::atomic<uint32_t> count{0};
+  return (start + count.fetch_add(1, std::memory_order_relaxed) * 0x9e3779b1u) << 1 | 1u;
 }
 
 thread_local hipEvent_t g_prof_start = nullptr, g_prof_stop = nullptr;
@@ -333,12 +352,15 @@ int innerq_append_deferred(const innerq_config_t* cfg, innerq_cache_t* cache, co
 // Attention over the first N tokens of the cache.  k_newest / v_newest (both or neither): fp16 rows
 // [B][Hk][d] of token N - 1 when that token has not been copied into its window yet.
 // defer_merge (may be null): the final merge is not launched; its arguments are returned instead.
+// append, appended (may be null): the append of the step's token but for a value group, which a launch that joins its own partials takes along
+// (*appended says whether it did).
 // n_dev (may be null): per-sequence token counts on the device (the count before this step); N is then
 // only the bound the launch is planned for.
 static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cache, long long N,
                           const void* k_newest, const void* v_newest, const void* q_fp16, const float* q_scale,
                           void* out, int out_is_fp32, void* workspace, size_t workspace_bytes, void* hip_stream,
-                          AttnArgs* defer_merge = nullptr, const int* n_dev = nullptr) {
+                          AttnArgs* defer_merge = nullptr, const int* n_dev = nullptr, const QuantArgs* append = nullptr,
+                          bool* appended = nullptr) {
   if (!q_fp16 || !out || !workspace) return INNERQ_E_NULL;
   if (misaligned(q_fp16) || misaligned(out) || misaligned(workspace) || (q_scale && misaligned(q_scale)))
     return INNERQ_E_ALIGN;
@@ -362,7 +384,9 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
   a.n_dev = n_dev;
   a.n_copy = n_dev ? static_cast<int*>(workspace) : nullptr;
   a.n_valid = nullptr;
-  a.shared_waves = 0;
+  a.shared_groups = 0;
+  a.join = nullptr;
+  a.join_tag = 0;
   a.pages = pages_of(c, *cache);
 
   // Tokens [w_sink, w_sink + n_both) are in the quantised store for both K and V: the split-K
@@ -381,11 +405,16 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
     win_tokens = N < most ? N : most;
   }
   const int r = c.n_q_heads / c.n_kv_heads;
-  int n_splits = 0, win_chunk_len = kWindowChunk;
+  int n_splits = 0, win_chunk_len = kWindowChunk, waves = 1;
   // which fused kernel serves this cache (0 = none: the fp32 kernel)
   const int fused_kind =
       attention_inner_supported(a) ? 1 : attention_fp16_supported(a) ? 2 : attention_outer_supported(a) ? 3 : 0;
   const bool fused = fused_kind != 0;
+  bool joins = fused_kind == 1 && n_both > 0 && !n_dev && attention_inner_joins(a);
+  const long long BH = (long long)c.batch * c.n_kv_heads;
+  const size_t heads = (size_t)c.batch * c.n_q_heads;
+  // Partial results a head may have where the launch joins them itself (they are larger there: kJoinBytes each).
+  const long long most_groups = (long long)(split_cap(c) + window_chunk_cap(c)) * (kHeadDim + 2) * (long long)sizeof(float) / kJoinBytes;
   if (n_both > 0 && fused) {
     // one wavefront per split; every wavefront of the launch resident at once, no tail round
     // (the window wavefronts of the same launch take their share of the slots)
@@ -399,8 +428,10 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
     // wavefronts (one per SIMD instead of two) is the faster one -- every wavefront pays its query
     // set-up once, and the launch itself costs time per wavefront (measured on the 32-head 4k-token
     // configuration: 17.8 -> 14.3 us per step; the two meet at four tiles per wavefront).
-    if (fused_kind == 1 && n_tiles < 4 * per_head && per_head >= 8) per_head /= 2;
+    const bool few_tiles = n_tiles < 4 * per_head;
+    if (fused_kind == 1 && few_tiles && per_head >= 8) per_head /= 2;
     // Window chunk length and the number of plain wavefronts.
+    bool one_group = false;
     long long best_len = kWindowChunk, best_cost = -1, best_plain = 1;
     auto plain_for = [&](long long len) {
       const long long nw = ceil_div(win_tokens, len);
@@ -424,6 +455,13 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
       const long long waves16 = (long long)c.batch * c.n_kv_heads * (plain_for(kWindowChunkMin) + ceil_div(win_tokens, kWindowChunkMin));
       best_len = waves16 * 4 <= simds ? kWindowChunkMin : (n_tiles < 48 ? 32 : kWindowChunk);
       best_plain = plain_for(best_len);
+      // A short context: one work-group per sequence-head, its wavefronts a window chunk or a tile or two each.
+      const long long chunks32 = ceil_div(win_tokens, 32);
+      if (joins && n_tiles + chunks32 <= 12 && chunks32 <= 7) {
+        one_group = true;
+        best_len = 32;
+        best_plain = plain_for(32);
+      }
     } else {
       // Comparison kernels: 64 tokens when the wavefront slots are all needed for tiles (long
       // contexts: a chunk then hides behind the tile work), shorter when slots are to spare and the
@@ -442,6 +480,38 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
     // the inner kernel's first wavefronts each carry a window chunk besides their tiles; the
     // comparison kernels run the window chunks as extra wavefronts of the same launch
     n_splits = (int)(fused_kind == 1 ? best_plain + n_win_chunks : best_plain);
+    if (joins) {
+      // Wavefronts per work-group and work-groups per sequence-head, all resident at once.
+      const long long cus = compute_units(), per_cu = BH * n_splits <= 4 * cus ? 4 : 8;
+      long long best = 0, groups = 1;
+      if (one_group) {
+        waves = n_splits < 8 ? n_splits : 8;
+      } else {
+        for (int w = per_cu; w >= 1; w /= 2) {
+          const long long fit = cus * (per_cu / w) / BH, want = ceil_div(n_splits, w), g = fit < want ? fit : want;
+          if (g * w <= n_win_chunks) continue;
+          const long long got = g * w < n_splits ? g * w : n_splits;
+          if (got * 10 > best * 11) { best = got; waves = w; groups = g; }
+        }
+        if (best == 0) {                               // more wavefronts than fit at once
+          waves = n_splits < 8 ? n_splits : 8;
+          groups = ceil_div(n_splits, waves);
+        }
+        while (groups > most_groups && waves < 8) {
+          waves = waves * 2 < 8 ? waves * 2 : 8;
+          groups = ceil_div(n_splits, waves);
+        }
+      }
+      // An attention call by itself leaves a launch of several work-groups per sequence-head that does not fill the chip to
+      // the merge.
+      if (groups > 1 && few_tiles && !append) joins = false;
+      if (!joins) {
+        waves = 1;
+      } else {
+        n_splits = (int)(groups * waves);
+        a.n_partials = (int)groups;
+      }
+    }
     // Token counts on the device: the wavefronts planned for sequences of the bound's length go to the sequences by
     // their lengths, as many to one as it has partial slots, where there is something to gain: 16 sequences of 1k to
     // 16k tokens, 35.3 us per step with the same number each, 29.9 shared.  The sharing itself costs 1 to 1.7 us in
@@ -451,7 +521,7 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
     const long long shared = (long long)n_splits * c.batch;
     if (n_dev && c.batch > 1 && c.batch <= kSharedBatchMost && (n_win_chunks + 1) * c.batch <= shared &&
         n_tiles >= 6 * per_head && per_head >= 10) {
-      a.shared_waves = (int)shared;
+      a.shared_groups = (int)shared;
       a.n_valid = static_cast<int*>(workspace) + c.batch;
       n_splits = split_cap(c);
     }
@@ -466,10 +536,13 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
   }
   const int n_win = (int)ceil_div(win_tokens, win_chunk_len);
   if (n_win > window_chunk_cap(c)) return INNERQ_E_ARG;
-  a.n_partials = n_splits + n_win;
-  const size_t heads = (size_t)c.batch * c.n_q_heads;
-  if (seq_bytes(c) + heads * (size_t)a.n_partials * (kHeadDim + 2) * sizeof(float) + 64 > workspace_bytes)
-    return INNERQ_E_WORKSPACE;
+  if (!joins) a.n_partials = n_splits + n_win;
+  const size_t partial_bytes = joins ? (size_t)kJoinBytes : (kHeadDim + 2) * sizeof(float);
+  if (seq_bytes(c) + heads * (size_t)a.n_partials * partial_bytes + 64 > workspace_bytes) return INNERQ_E_WORKSPACE;
+  if (joins) {
+    a.join = reinterpret_cast<unsigned long long*>(static_cast<char*>(workspace) + seq_bytes(c));
+    a.join_tag = next_join_tag();
+  }
   a.ws_ml = reinterpret_cast<float*>(static_cast<char*>(workspace) + seq_bytes(c));
   a.ws_o = a.ws_ml + ((heads * a.n_partials * 2 + 3) / 4) * 4;
 
@@ -480,7 +553,7 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
     if (fused) {
       // the events take the timestamps of the dispatch itself
       const WindowSet win = {n_sink, win_b0, win_b1 - win_b0, n_win};
-      e = fused_kind == 1   ? launch_attention_inner(a, n_both, n_splits, win, stream, prof_start, prof_stop)
+      e = fused_kind == 1   ? launch_attention_inner(a, n_both, n_splits, win, waves, joins ? append : nullptr, stream, prof_start, prof_stop)
           : fused_kind == 2 ? launch_attention_fp16(a, n_both, n_splits, win, stream, prof_start, prof_stop)
                             : launch_attention_outer(a, n_both, n_splits, win, stream, prof_start, prof_stop);
     } else {
@@ -494,10 +567,12 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
     e = launch_attention_generic(a, 0, n_sink, win_b0, win_b1, n_win, n_splits, stream);
     if (e != hipSuccess) return INNERQ_E_HIP;
   }
-  if (defer_merge) {
-    *defer_merge = a;
+  if (defer_merge) *defer_merge = a;
+  if (joins) {
+    if (appended) *appended = append != nullptr;
     return INNERQ_OK;
   }
+  if (defer_merge) return INNERQ_OK;
   e = launch_attention_merge(a, stream);
   return e == hipSuccess ? INNERQ_OK : INNERQ_E_HIP;
 }
@@ -602,7 +677,7 @@ int innerq_decode_step_ragged(const innerq_config_t* cfg, const innerq_cache_t* 
     j.row_end = j.form == kPerChannel ? cfg->group : 1;
     j.ring_from = 0;
   }
-  return launch_quantize(a, static_cast<hipStream_t>(hip_stream), &merge) == hipSuccess ? INNERQ_OK : INNERQ_E_HIP;
+  return launch_quantize(a, static_cast<hipStream_t>(hip_stream), merge.join ? nullptr : &merge) == hipSuccess ? INNERQ_OK : INNERQ_E_HIP;
 }
 
 int innerq_decode_step(const innerq_config_t* cfg, innerq_cache_t* cache, const void* k_new, const void* v_new,
@@ -616,14 +691,33 @@ int innerq_decode_step(const innerq_config_t* cfg, innerq_cache_t* cache, const 
   if (misaligned(k_new) || misaligned(v_new)) return INNERQ_E_ALIGN;
   if (cache->n_tokens + 1 > cfg->capacity_tokens) return INNERQ_E_CAPACITY;
   if (cache->store_ahead_tokens != cache->n_tokens + 1) return INNERQ_E_ARG;   // the store was not run one step ahead
+  // One launch where the fused inner kernel joins its own partials and no ring slot is shared by the token that enters and
+  // one that leaves (nor the new token itself among them).
+  const long long n = cache->n_tokens, to = n + 2 > cfg->capacity_tokens ? cfg->capacity_tokens : n + 2;
+  const QuantArgs append = quant_args(cfg, cache, k_new, v_new, 1, nullptr, n + 1, to);
+  const bool apart = cfg->w_recent < 2 || ring_slots_shared(append, append.job[0]) || ring_slots_shared(append, append.job[1]);
   AttnArgs merge;
-  st = attention_impl(cfg, cache, cache->n_tokens + 1, k_new, v_new, q_fp16, q_scale, out, out_is_fp32, workspace,
-                      workspace_bytes, hip_stream, &merge);
+  bool appended = false;
+  st = attention_impl(cfg, cache, n + 1, k_new, v_new, q_fp16, q_scale, out, out_is_fp32, workspace, workspace_bytes,
+                      hip_stream, &merge, nullptr, apart ? nullptr : &append, &appended);
   if (st != INNERQ_OK) return st;
+  if (appended) {
+    if (append.job[1].row_end > append.job[1].row_begin) {
+      // a value group leaves its ring
+      QuantArgs values = append;
+      values.job[0].row_end = values.job[0].row_begin;
+      values.n_old = n + 1;
+      values.t_new = 0;
+      if (launch_quantize(values, static_cast<hipStream_t>(hip_stream)) != hipSuccess) return INNERQ_E_HIP;
+    }
+    cache->n_tokens = n + 1;
+    cache->store_ahead_tokens = to;
+    return INNERQ_OK;
+  }
   // second launch: the merge of this step together with the append of its token and the
   // quantisation the next step needs
   return quantize_impl(cfg, cache, k_new, v_new, 1, nullptr, cache->n_tokens + 1, cache->n_tokens + 2, hip_stream,
-                       &merge);
+                       merge.join ? nullptr : &merge);
 }
 
 }  // extern "C"

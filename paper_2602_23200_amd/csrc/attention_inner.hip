@@ -34,18 +34,29 @@
 //   * softmax probabilities are rounded to fp16 for the value pass and the
 //     normaliser is the MFMA sum of those same rounded values (an extra all-ones B
 //     operand), so the weights stay consistent.
-//   * schedule: n_splits + n_window_chunks wavefronts per (batch, kv-head), all
-//     resident at once at two per SIMD; contiguous tile ranges; two register
-//     buffers in ping-pong; the wavefront that is behind its SIMD partner gets the
-//     higher issue priority, so both finish together.
-//   * paged store: this file is compiled twice.  attention_inner_paged.hip includes it with
-//     INNERQ_PAGED_STORE set and gets the kernels that look every tile up in the page table (a page is
-//     one 64-token tile); the build for the contiguous store carries no trace of that.
+//   * schedule: n_splits wavefronts per (batch, kv-head), all resident at once at two per SIMD, in work-groups of up to
+//     eight that share the query tables; contiguous tile ranges; two register buffers in ping-pong; the wavefront that is
+//     behind its SIMD partner gets the higher issue priority, so both finish together.
+//   * one launch: a work-group's wavefronts meet in LDS at the end, the work-groups of a (batch, kv-head) through the
+//     workspace (merge.h), and the append of a decode step's token is taken by the first wavefront that is through.  A
+//     launch for merge and append behind this one takes 3.4 us after a short kernel and 4.7 after a long one, whatever it
+//     does.  Per step, before -> now: 1 head x 512 tokens 12.2 us -> 9.4, 32 heads x 4k 12.9 -> 11.6, 8 x 8 x 32k
+//     40.3 -> 38.3, 32 x 8 x 8k 42.0 -> 39.6, 4 x 8 x 128k 72.2 -> 69.1, 3-bit 8 x 8 x 32k 56.9 -> 54.8.
+//   * paged store: this file is compiled for both stores (and, to build in parallel, for both group sizes).
+//     attention_inner_paged*.hip include it with INNERQ_PAGED_STORE set and get the kernels that look every tile up in
+//     the page table (a page is one 64-token tile); the builds for the contiguous store carry no trace of that.
 #include "innerq_dev.h"
+#define INNERQ_CONTRACTED
+#include "quantize_rows.h"
 #include "window_pass.h"
+#include "merge.h"
 
 #ifndef INNERQ_PAGED_STORE
 #define INNERQ_PAGED_STORE 0
+#endif
+#ifndef INNERQ_INNER_LAUNCH
+#define INNERQ_INNER_LAUNCH launch_inner_g32
+#define INNERQ_INNER_GROUP 32
 #endif
 
 namespace innerq {
@@ -69,6 +80,13 @@ constexpr float kSmScale = 0.08838834764831845f;   // 1/sqrt(128)
 // Half `hi` (0 or 1) of a 32-bit word as fp16.
 __device__ inline _Float16 half_of(uint32_t w, int hi) {
   return __builtin_bit_cast(_Float16, (unsigned short)(hi ? (w >> 16) : (w & 0xffffu)));
+}
+
+// max(x, 0), half by half, in one instruction (the compiler would put another before it for signalling NaNs).
+__device__ __forceinline__ half2_t positive_part(half2_t x) {
+  half2_t y;
+  asm("v_pk_max_f16 %0, %1, 0" : "=v"(y) : "v"(x));
+  return y;
 }
 
 // Where the fields of a 32-bit word are masked out: after an optional shift of the whole word, field f of a 16-bit
@@ -195,6 +213,22 @@ struct TileRegs {
 // G = 32 configuration, best at 9; best at 5 on the 8k x 32 G = 64 one, 6 % better than at 11).
 __host__ __device__ inline int window_cost(long long len, int group) { return (int)(2 + (group == 64 ? 5 : 9) * len / 64); }
 
+// LDS of a work-group, in bytes: what its wavefronts share, then OWN for each.
+template <int KB, int VB, int G, int NH4>
+struct Lds {
+  static constexpr int NH = 4 * NH4, NG = D / G;
+  static constexpr int QS = D + 8, PS = TILE + 8;                  // a head's row of the query / probability tables (halves)
+  static constexpr int ZEROS = QS + (NH4 - 1) * 4 * QS;            // a row of zeros for the first four heads' offsets, and as far on as the last four's
+  static constexpr int QSUM = (NH * QS * (KB == 3 ? 2 : 1) + ZEROS) * 2;
+  static constexpr int COEF = QSUM + NH4 * NG * 4 * 4;
+  static constexpr int COUNT = COEF + NH * 4;                      // wavefronts that have come to the end
+  static constexpr int SHARED = COUNT + 16;
+  static constexpr int most(int x, int y) { return x > y ? x : y; }
+  static constexpr int OWN = most(most(NH * PS * 2 * (VB == 3 ? 2 : 1), window_lds_bytes<NH4, G, false>()), NH * (D + 2) * 4);
+  static_assert(QSUM % 16 == 0 && SHARED % 16 == 0 && OWN % 16 == 0, "16-byte pieces");
+  static constexpr int bytes(int waves) { return SHARED + waves * OWN; }
+};
+
 // KB, VB: widths of the key and value codes.  ZK: the key zero-point array exists (the key mode is not
 // symmetric-only).  ZV: 0 = no value zero-point array; 1 = zero-points read densely, one tile ahead with
 // everything else; 2 = sparse (Section "Sparsity of M": the flag matrix is mostly zero): a lane reads the
@@ -202,8 +236,8 @@ __host__ __device__ inline int window_cost(long long len, int group) { return (i
 // sign bit of the scale it already holds), at the start of the tile that needs them, so a 128-byte line
 // of zero-points (64 channels of one token-group) that holds no asymmetric group is never fetched.
 template <int KB, int VB, int G, int NH4, bool ZK, int ZV>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) attention_inner_kernel(AttnArgs a_in, int n_both_in, int n_splits, WindowSet win_in, int win_tiles_in, int base_t_in,
-                                                                                                 int rem_t_in, int r) {
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) attention_inner_kernel(AttnArgs a_in, int n_both_in, int n_splits, WindowSet win_in, int win_tiles_in, int base_t_in,
+                                                                                                 int rem_t_in, int r, QuantArgs append, int appends) {
   constexpr int LBK = KB == 3 ? 2 : KB, LBV = VB == 3 ? 2 : VB;   // field width of the (low) plane
   constexpr bool HIK = KB == 3, HIV = VB == 3;                     // a plane of high bits follows it
   using FK = Fields<LBK>;
@@ -224,15 +258,17 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 
   // No division on the way to the first load: the grid is (splits, kv heads, batch), and the
   // host passes the quotients (heads per kv head; tiles per plain wavefront and their remainder).
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
   const int hk = (int)blockIdx.y;
-  int b = (int)blockIdx.z, s_idx = (int)blockIdx.x;      // sequence; wavefront of its (b, hk)
+  int b = (int)blockIdx.z, group = (int)blockIdx.x;      // sequence; work-group of its (b, hk)
+  int n_groups = (int)gridDim.x;
   // The host's plan holds for every sequence -- unless the token counts live on the device
   // (a.n_dev: one count per sequence, the tokens cached BEFORE this step; attention runs over them
   // plus the new token).  Then the launch shape and the window chunks are the
   // host's, planned for the longest sequence allowed, and everything that depends on the length is
   // recomputed here for this wavefront's sequence: the partition of Eq. kv_cache_init_quantized_window,
-  // the window set and the split of the tiles over the wavefronts.  With shared_waves (BALANCED below) the wavefronts
+  // the window set and the split of the tiles over the wavefronts.  With shared_groups (BALANCED below) the wavefronts
   // of a kv head are shared out over the sequences by their lengths; n_splits is then the most one sequence may get
   // (its partial slots).  Wavefronts left without a tile write an empty partial, or nothing beyond their sequences.
   AttnArgs a = a_in;
@@ -258,38 +294,39 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       return x;
     };
     int n;
-    if (a.shared_waves > 0) {
+    if (a.shared_groups > 0) {
       // BALANCED (a sequence a lane): a number of tiles per wavefront, window chunks counted in tiles, with which the
       // sequences' wavefronts fit the launch: the smallest one below 8, at most an eighth above it beyond (every try is a
       // scan of the lengths, in front of the first load).  No fewer than four tiles (a wavefront pays its query set-up
       // once).
-      const int total = (int)gridDim.x;
+      const int total = (int)gridDim.x, least = (n_chunks + waves) / waves;        // (at least one wavefront without a chunk)
       const int n_lane = clamped(lane < a.batch ? a_in.n_dev[lane] : 0);
       const Length x = length(n_lane);
       const int work = lane < a.batch ? x.tiles + n_chunks * x.cost : 0;
-      int quota = (wave_scan(work).total + total - 1) / total;
+      int quota = (wave_scan(work).total + total * waves - 1) / (total * waves);
       quota = quota < 4 ? 4 : quota;
       int mine;
       Scan sc;
       for (;;) {
-        mine = (work + quota - 1) / quota;
-        mine = mine < n_chunks + 1 ? n_chunks + 1 : mine;
+        mine = (work + quota * waves - 1) / (quota * waves);
+        mine = mine < least ? least : mine;
         mine = mine > n_splits ? n_splits : mine;
         mine = lane < a.batch ? mine : 0;
         sc = wave_scan(mine);
-        if (sc.total <= total) break;                    // (the host: batch * (n_chunks + 1) <= total)
+        if (sc.total <= total) break;                    // (the host: batch * least <= total)
         quota += 1 + (quota >> 3);
       }
-      b = __popcll(__builtin_amdgcn_ballot_w64(lane < a.batch && s_idx >= sc.upto));
+      b = __popcll(__builtin_amdgcn_ballot_w64(lane < a.batch && group >= sc.upto));
       if (b >= a.batch) return;                            // (wave-uniform)
-      n_splits = __builtin_amdgcn_readlane(mine, b);
-      s_idx -= __builtin_amdgcn_readlane(sc.upto, b) - n_splits;
+      n_groups = __builtin_amdgcn_readlane(mine, b);
+      group -= __builtin_amdgcn_readlane(sc.upto, b) - n_groups;
+      n_splits = n_groups * waves;
       n = __builtin_amdgcn_readlane(n_lane, b);            // (not read again: a memory round trip)
     } else {
       n = clamped(a_in.n_dev[b]);
     }
     const Length x = length(n);
-    if (s_idx == 0 && hk == 0 && lane == 0) {
+    if (group == 0 && hk == 0 && wave == 0 && lane == 0) {
       if (a.n_copy) a.n_copy[b] = x.n - 1;                 // for the append that follows
       if (a.n_valid) a.n_valid[b] = n_splits + n_chunks;   // partial results of this sequence's heads
     }
@@ -317,6 +354,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // also serve one chunk of the fp16 windows each (after their tiles) and get win_tiles tiles;
   // the others share the remaining tiles evenly.
   const int n_tiles = (n_both + TILE - 1) / TILE;
+  const int s_idx = wave * n_groups + group;             // (the chunks go to different work-groups first)
   int t0, t1;
   if (s_idx < win.n_chunks) {
     t0 = s_idx * win_tiles;
@@ -327,24 +365,25 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     t1 = t0 + base_t + (j < rem_t ? 1 : 0);
   }
 
-  // Operand tables, a head's row padded by 16 bytes (four heads' rows then start in different banks).
-  constexpr int QS = D + 8, PS = TILE + 8;
-  constexpr int ZEROS = QS + (NH4 - 1) * 4 * QS;       // a row of zeros for the first four heads' offsets, and as far on as the last four's
-  __shared__ __attribute__((aligned(16))) _Float16 tables[NH * QS + NH * PS + ZEROS + (HIK ? NH * QS : 0) + (HIV ? NH * PS : 0)];
+  // Operand tables, a head's row padded by 16 bytes (four heads' rows then start in different banks).  The query's, the
+  // group sums and the zeros stand once for the work-group; a wavefront's own part holds its probability tables, then the
+  // window pass's memory, then its state for the join.
+  using L = Lds<KB, VB, G, NH4>;
+  constexpr int QS = L::QS, PS = L::PS, ZEROS = L::ZEROS;
+  extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+  _Float16* tables = reinterpret_cast<_Float16*>(lds);
   constexpr int QA = 0;                       // query operand table [head][word][mfma][slot]
-  constexpr int PA = QA + NH * QS;            // probability operand table [head][word][mfma][slot]
-  constexpr int ZERO = PA + NH * PS;          // zeros, for either
-  // the same two tables for the plane of high bits (1-bit fields, weight 4): [head][word][mfma][slot]
-  constexpr int QA1 = ZERO + ZEROS, PA1 = QA1 + (HIK ? NH * QS : 0);
-  __shared__ __attribute__((aligned(16))) float qsum[NH4][NG][4];       // log2e/sqrt(d) * sum of q over each key group
+  constexpr int QA1 = QA + NH * QS;           // the same for the plane of high bits (1-bit fields, weight 4)
+  constexpr int ZERO = QA1 + (HIK ? NH * QS : 0);        // zeros, for any table
+  float* coef_lds = reinterpret_cast<float*>(lds + L::COEF);                     // [NH]
+  float (*qsum)[NG][4] = reinterpret_cast<float (*)[NG][4]>(lds + L::QSUM);      // [NH4] log2e/sqrt(d) * sum of q over each key group
+  const int own_lds = L::SHARED + wave * L::OWN;         // bytes
+  const int PA = own_lds / 2;                 // probability operand table [head][word][mfma][slot]
+  const int PA1 = PA + NH * PS;               // ... and its high bits' one
 
-  // A wavefront without a tile (a launch with more wavefronts than tiles gives the window chunks
-  // wavefronts of their own) skips all of the tile machinery, query tables included.
-  float part_m[NH], part_l[NH];
-  float2 part_o[NH];
+  WaveState<NH> part;
 #pragma unroll
-  for (int h = 0; h < NH; ++h) { part_m[h] = -INFINITY; part_l[h] = 0.f; part_o[h] = float2{0.f, 0.f}; }   // (an empty partial)
-  if (t1 > t0) {
+  for (int h = 0; h < NH; ++h) { part.m[h] = -INFINITY; part.l[h] = 0.f; part.o[h] = float2{0.f, 0.f}; }   // (an empty partial)
   // ---- per-(b, hk) base pointers
   const long long slab = kPagedStore ? 0 : bh * a.capacity;             // first store row of (b, hk); paged: see below
   const uint8_t* kcodes_slab = a.k.codes + slab * (D * KB / 8);
@@ -434,11 +473,14 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   };
 
   // ---- the query loads go out first (the set-up below waits for them), the first tile's loads
-  // right behind them: those overlap the query set-up
+  // right behind them: those overlap the query set-up.  One wavefront sets four heads up for the whole work-group (the last
+  // ones, which carry no window chunk); the others meet it at the barrier with their first tile in flight.
   u32x4 q_raw[NH4];
   float4_t q_fac[NH4][2];                              // per-channel query factors, when given
+  auto sets_up = [&](int rnd) { return wave == waves - 1 - (waves > rnd ? rnd : 0); };
 #pragma unroll
   for (int rnd = 0; rnd < NH4; ++rnd) {
+    if (!sets_up(rnd)) continue;
     const int h = (rnd * 64 + lane) / (D / 8), c0 = 8 * ((rnd * 64 + lane) % (D / 8));
     q_raw[rnd] = u32x4{0u, 0u, 0u, 0u};
     if (h < r) q_raw[rnd] = *reinterpret_cast<const u32x4*>(a.q + ((long long)b * a.n_q_heads + hk * r + h) * D + c0);
@@ -450,12 +492,12 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   Regs bufA, bufB;
   if (t1 > t0) load_tile(t0, bufA);
 
-  float q_coef[NH];
   // ---- query: fp16 (optionally rescaled), offset factors folded in.  A lane takes 8
   // consecutive channels of one head (one 16-byte load); the channels of one key group sit in
   // G/8 neighbouring lanes, so the group sums of q come from a few DPP adds.
 #pragma unroll
   for (int rnd = 0; rnd < NH4; ++rnd) {
+    if (!sets_up(rnd)) continue;
     const int idx = rnd * 64 + lane;
     const int h = idx / (D / 8), c0 = 8 * (idx % (D / 8));
     const uint32_t rw[4] = {q_raw[rnd].x, q_raw[rnd].y, q_raw[rnd].z, q_raw[rnd].w};
@@ -478,12 +520,9 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     mx = __builtin_fmaxf(mx, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, mx), 0x140, 0xF, 0xF, true)));   // mirror within 16
     const int q_exp = mx > 0.f ? (int)((__float_as_uint(mx) >> 23) & 0xffu) - 127 : 8;
     const float q_pow = __uint_as_float((uint32_t)(127 + 8 - q_exp) << 23);
-    // per-head constant of the score, log2e/sqrt(d) * 2^(24 - CK) / (the head's factor): wave-uniform, so it
-    // goes to scalar registers straight from the first lane of each head's row
+    // per-head constant of the score, log2e/sqrt(d) * 2^(24 - CK) / (the head's factor)
     const float coef = (kSmScale * kLog2e * (float)(1 << (24 - CK))) * __uint_as_float((uint32_t)(127 - 8 + q_exp) << 23);
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      q_coef[rnd * 4 + j] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, coef), 16 * j));
+    if (lane % 16 == 0) coef_lds[h] = coef;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int c = c0 + e;
@@ -504,8 +543,22 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       part += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, part), 0x141, 0xF, 0xF, true));
     if ((idx % (G / 8)) == 0) qsum[h / 4][c0 / G][h % 4] = part * (kSmScale * kLog2e);
   }
-  for (int i = 2 * lane; i < ZEROS; i += 128) *reinterpret_cast<uint32_t*>(&tables[ZERO + i]) = 0u;
-  __syncthreads();
+  int* arrivals = reinterpret_cast<int*>(lds + L::COUNT);
+  if (wave == 0) {
+    if (lane == 0) *arrivals = 0;
+    for (int i = 2 * lane; i < ZEROS; i += 128) *reinterpret_cast<uint32_t*>(&tables[ZERO + i]) = 0u;
+  }
+  // A wavefront without a tile (a launch with more wavefronts than tiles gives the window chunks wavefronts of their own)
+  // meets the others behind the loads of its window chunk.
+  const bool has_tiles = t1 > t0, has_chunk = s_idx < win.n_chunks;
+  if (has_tiles || !has_chunk) __syncthreads();
+  if (has_tiles) {
+  float q_coef[NH];                                    // (wave-uniform: scalar registers)
+  {
+    const float v = coef_lds[lane % NH];
+#pragma unroll
+    for (int h = 0; h < NH; ++h) q_coef[h] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), h));
+  }
 
   // ---- A operands of the zero-point term: sum over groups of Zeff_g * (sum of q over group g) is a
   // 4 (heads) x 4 (groups) product per token, one more matrix instruction.  The group sums of q
@@ -647,7 +700,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
       for (int gp = 0; gp < NG / 2; ++gp) {
         const half2_t sp = __builtin_bit_cast(half2_t, cur.ks[gp]);
-        const half2_t mp = __builtin_elementwise_max(sp, half2_t{(_Float16)0, (_Float16)0});
+        const half2_t mp = positive_part(sp);
         half2_t zp;
         constexpr _Float16 kNegQuarterK = (_Float16)(-HALFK / 2), kHalf = (_Float16)0.5f;
         if constexpr (has_kz)
@@ -699,14 +752,14 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
         o[h][1] *= alpha;
       }
     }
-    __syncthreads();                                   // previous tile's readers of pA are done
+    wave_fence();                                      // previous tile's readers of pA are done
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
       const float p = __builtin_amdgcn_exp2f(e[h]);
       tables[PA + h * PS + p_index] = (_Float16)p;
       if constexpr (HIV) tables[PA1 + h * PS + p1_index] = (_Float16)(p * p1_factor);
     }
-    __syncthreads();
+    wave_fence();
 
     // ================= values: lane = two channels (Eq. att:3 with Eq. hybrid_dequant fused) =================
 #pragma unroll
@@ -760,7 +813,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       float z0, z1;
       if constexpr (has_vz) {
         const uint32_t mpair = __builtin_bit_cast(
-            uint32_t, __builtin_elementwise_max(__builtin_bit_cast(half2_t, spair), half2_t{(_Float16)0, (_Float16)0}));
+            uint32_t, positive_part(__builtin_bit_cast(half2_t, spair)));
         const uint32_t zpair = late_vz ? vz_late[gi] : cur.vz[gi];
         z0 = __builtin_fmaf((float)half_of(mpair, 0), (float)(-HALFV), (float)half_of(zpair, 0));
         z1 = __builtin_fmaf((float)half_of(mpair, 1), (float)(-HALFV), (float)half_of(zpair, 1));
@@ -809,35 +862,50 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     }
   }
 
-  // ---- partial (m, l, o) of every real head, kept in registers over the window pass
+  // ---- this wavefront's state over its tiles
 #pragma unroll
   for (int h = 0; h < NH; ++h) {
-    part_o[h].x = o[h][0] * (float)(1 << (24 - CV));   // undoes the operand factors of the value pass
-    part_o[h].y = o[h][1] * (float)(1 << (24 - CV));
-    part_m[h] = m_run[h] * kLn2;
-    part_l[h] = l_run[h] * (float)(1 << (24 - CV));
+    part.o[h].x = o[h][0] * (float)(1 << (24 - CV));   // undoes the operand factors of the value pass
+    part.o[h].y = o[h][1] * (float)(1 << (24 - CV));
+    part.m[h] = m_run[h];
+    part.l[h] = l_run[h] * (float)(1 << (24 - CV));
   }
   }
 
-  // ---- the window chunk of this wavefront, with a partial slot of its own
-  if (s_idx < win.n_chunks) {
+  // ---- the window chunk of this wavefront joins it
+  if (has_chunk) {
     __builtin_amdgcn_s_setprio(0);
-    window_pass<NH4, KB, G, true, false, kPagedStore>(a, bh, win.na, win.b0, win.nb, s_idx, win.n_chunks, n_splits + s_idx);
-  }
-
-  // ---- the tile partial goes out last: nothing after these stores reuses their registers (which
-  // would have to wait for the stores to complete)
+    WaveState<NH> w;
+    const bool apart = a.join == nullptr;
+    window_pass<NH4, KB, G, true, false, kPagedStore>(a, bh, win.na, win.b0, win.nb, s_idx, win.n_chunks, 0, lds + own_lds, w,
+                                                      [&] { if (!has_tiles) __syncthreads(); });
+    if (apart) store_partial(a, w, bh, r, n_splits + s_idx, lane);
 #pragma unroll
-  for (int h = 0; h < NH; ++h) {
-    if (h < r) {
-      const long long bhq = (long long)b * a.n_q_heads + hk * r + h;
-      *reinterpret_cast<float2*>(&a.ws_o[(bhq * a.n_partials + s_idx) * D + 2 * lane]) = part_o[h];
-      if (lane == 0) {
-        a.ws_ml[(bhq * a.n_partials + s_idx) * 2 + 0] = part_m[h];
-        a.ws_ml[(bhq * a.n_partials + s_idx) * 2 + 1] = part_l[h];
-      }
+    for (int h = 0; h < NH; ++h) {
+      if (apart) continue;
+      const float top = fmaxf(part.m[h], w.m[h]);
+      const float f = level_weight(part.m[h], top), g = level_weight(w.m[h], top);
+      part.m[h] = top;
+      part.l[h] = part.l[h] * f + w.l[h] * g;
+      part.o[h].x = part.o[h].x * f + w.o[h].x * g;
+      part.o[h].y = part.o[h].y * f + w.o[h].y * g;
     }
   }
+
+  // ---- the append of the step's token: disjoint memory.  The wavefront of one work-group that is through first takes it,
+  // while the others still have tiles.
+  if (appends && group == n_groups - 1) {
+    int at = 0;
+    if (lane == 0) at = __hip_atomic_fetch_add(arrivals, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (__builtin_amdgcn_readfirstlane(at) == 0) append_keys_and_copies<G, KB>(append, bh, a.n_tokens - 1, lane);
+  }
+
+  if (!a.join) {                                         // partials for a later launch (the tiles' after the chunk's: nothing reuses its registers)
+    store_partial(a, part, bh, r, s_idx, lane);
+    return;
+  }
+  // ---- the work-group's wavefronts, and the sequence-head's work-groups, meet
+  join_and_store<NH>(a, part, reinterpret_cast<float*>(lds + L::SHARED), L::OWN / 4, wave, waves, lane, bh, r, group, n_groups);
 }
 
 template <int KB, int VB, int G, bool ZK, int ZV>
@@ -850,42 +918,35 @@ hipError_t launch_z(const AttnArgs& a, int n_both, int n_splits, const WindowSet
   const int quota = (n_tiles + win.n_chunks * cost + n_splits - 1) / n_splits;
   int win_tiles = quota > cost ? quota - cost : 0;
   if (win.n_chunks > 0 && win_tiles > n_tiles / win.n_chunks) win_tiles = n_tiles / win.n_chunks;
+  if (L.waves < 1 || L.waves > kJoinWaves || n_splits % L.waves != 0 || (!a.join && L.append)) return hipErrorInvalidValue;
   if (n_splits <= win.n_chunks) return hipErrorInvalidValue;      // the host gives at least one plain wavefront
   if (a.batch > 65535 || a.n_kv_heads > 65535) return hipErrorInvalidValue;
   const int rest = n_tiles - win.n_chunks * win_tiles, others = n_splits - win.n_chunks;
   const int base_t = rest / others, rem_t = rest % others;
-  dim3 grid((unsigned)n_splits, (unsigned)a.n_kv_heads, (unsigned)a.batch);
-  if (a.shared_waves > 0) grid = dim3((unsigned)a.shared_waves, (unsigned)a.n_kv_heads, 1u);
+  dim3 grid((unsigned)(n_splits / L.waves), (unsigned)a.n_kv_heads, (unsigned)a.batch);
+  if (a.shared_groups > 0) grid = dim3((unsigned)a.shared_groups, (unsigned)a.n_kv_heads, 1u);
+  const unsigned lds_bytes = (unsigned)(r <= 4 ? Lds<KB, VB, G, 1>::bytes(L.waves) : Lds<KB, VB, G, 2>::bytes(L.waves));
   // (the launch with dispatch events only when events were asked for: the plain launch is the one a
   // stream capture is sure to record)
   const bool timed = L.ev_start || L.ev_stop;
+  const int appends = L.append ? 1 : 0;
+  const QuantArgs q = L.append ? *L.append : QuantArgs{};
   if (r <= 4) {
     if (timed)
-      hipExtLaunchKernelGGL((attention_inner_kernel<KB, VB, G, 1, ZK, ZV>), grid, dim3(64), 0, L.stream, L.ev_start,
-                            L.ev_stop, 0, a, n_both, n_splits, win, win_tiles, base_t, rem_t, r);
+      hipExtLaunchKernelGGL((attention_inner_kernel<KB, VB, G, 1, ZK, ZV>), grid, dim3(64u * L.waves), lds_bytes, L.stream, L.ev_start,
+                            L.ev_stop, 0, a, n_both, n_splits, win, win_tiles, base_t, rem_t, r, q, appends);
     else
-      hipLaunchKernelGGL((attention_inner_kernel<KB, VB, G, 1, ZK, ZV>), grid, dim3(64), 0, L.stream, a, n_both,
-                         n_splits, win, win_tiles, base_t, rem_t, r);
+      hipLaunchKernelGGL((attention_inner_kernel<KB, VB, G, 1, ZK, ZV>), grid, dim3(64u * L.waves), lds_bytes, L.stream, a, n_both,
+                         n_splits, win, win_tiles, base_t, rem_t, r, q, appends);
   } else {
     if (timed)
-      hipExtLaunchKernelGGL((attention_inner_kernel<KB, VB, G, 2, ZK, ZV>), grid, dim3(64), 0, L.stream, L.ev_start,
-                            L.ev_stop, 0, a, n_both, n_splits, win, win_tiles, base_t, rem_t, r);
+      hipExtLaunchKernelGGL((attention_inner_kernel<KB, VB, G, 2, ZK, ZV>), grid, dim3(64u * L.waves), lds_bytes, L.stream, L.ev_start,
+                            L.ev_stop, 0, a, n_both, n_splits, win, win_tiles, base_t, rem_t, r, q, appends);
     else
-      hipLaunchKernelGGL((attention_inner_kernel<KB, VB, G, 2, ZK, ZV>), grid, dim3(64), 0, L.stream, a, n_both,
-                         n_splits, win, win_tiles, base_t, rem_t, r);
+      hipLaunchKernelGGL((attention_inner_kernel<KB, VB, G, 2, ZK, ZV>), grid, dim3(64u * L.waves), lds_bytes, L.stream, a, n_both,
+                         n_splits, win, win_tiles, base_t, rem_t, r, q, appends);
   }
   return hipGetLastError();
-}
-
-// Wavefronts of this kernel instance that one compute unit holds at once (a host-side query).
-template <int KB, int VB, int G, bool ZK, int ZV>
-int resident_z(const AttnArgs& a) {
-  const int r = a.n_q_heads / a.n_kv_heads;
-  int n = 0;
-  hipError_t e = r <= 4
-      ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, attention_inner_kernel<KB, VB, G, 1, ZK, ZV>, 64, 0)
-      : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, attention_inner_kernel<KB, VB, G, 2, ZK, ZV>, 64, 0);
-  return (e == hipSuccess && n > 0) ? n : 8;
 }
 
 // 0: no value zero-point array; 1: read densely; 2: read only where a group is flagged
@@ -905,14 +966,6 @@ hipError_t launch_t(const AttnArgs& a, int n_both, int n_splits, const WindowSet
   return launch_z<KB, VB, G, false, 0>(a, n_both, n_splits, win, L);
 }
 
-template <int KB, int VB, int G>
-int resident_t(const AttnArgs& a) {
-  const bool zk = a.k.zeros != nullptr;
-  const int zv = value_zero_mode(a);
-  if (zk) return zv == 2 ? resident_z<KB, VB, G, true, 2>(a) : zv == 1 ? resident_z<KB, VB, G, true, 1>(a) : resident_z<KB, VB, G, true, 0>(a);
-  return zv == 2 ? resident_z<KB, VB, G, false, 2>(a) : zv == 1 ? resident_z<KB, VB, G, false, 1>(a) : resident_z<KB, VB, G, false, 0>(a);
-}
-
 // Width pairs (keys, values) the fused kernel is built for: equal widths, and the paper's
 // Hybrid / Small presets (3-bit keys, 2-bit values).
 inline int width_pair(const AttnArgs& a) {
@@ -921,57 +974,22 @@ inline int width_pair(const AttnArgs& a) {
   return -1;
 }
 
-// Calls f.template operator()<KB, VB, G>() for the configuration's widths and group size.
-template <typename Fn>
-auto for_widths(const AttnArgs& a, Fn f) {
-  const int wp = width_pair(a);
-  if (a.group == 32) {
-    if (wp == 0) return f.template operator()<2, 2, 32>();
-    if (wp == 1) return f.template operator()<3, 3, 32>();
-    if (wp == 2) return f.template operator()<4, 4, 32>();
-    return f.template operator()<3, 2, 32>();
-  }
-  if (wp == 0) return f.template operator()<2, 2, 64>();
-  if (wp == 1) return f.template operator()<3, 3, 64>();
-  if (wp == 2) return f.template operator()<4, 4, 64>();
-  return f.template operator()<3, 2, 64>();
-}
-
-struct ResidentFn {
-  const AttnArgs& a;
-  template <int KB, int VB, int G>
-  int operator()() const { return resident_t<KB, VB, G>(a); }
-};
-struct LaunchFn {
-  const AttnArgs& a; int n_both, n_splits; const WindowSet& win; const Launch& L;
-  template <int KB, int VB, int G>
-  hipError_t operator()() const { return launch_t<KB, VB, G>(a, n_both, n_splits, win, L); }
-};
-
-// cached per (widths, group, zero flags, head tile): the answer depends on the kernel instance only
-int waves_per_cu_of_this_build(const AttnArgs& a) {
-  static CachedInt cache[4][2][2][3][2];
-  const int r = a.n_q_heads / a.n_kv_heads;
-  const int wp = width_pair(a);
-  if (wp < 0) return 8;
-  return cache[wp][a.group == 64][a.k.zeros != nullptr][value_zero_mode(a)][r > 4].get(
-      [&] { return for_widths(a, ResidentFn{a}); });
-}
-
 }  // namespace
 
-#if INNERQ_PAGED_STORE
-
-int attention_inner_paged_waves_per_cu(const AttnArgs& a) { return waves_per_cu_of_this_build(a); }
-
-hipError_t launch_attention_inner_paged(const AttnArgs& a, long long n_both_ll, int n_splits, const WindowSet& win,
-                                        hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  if (!a.pages.table || !attention_inner_supported(a)) return hipErrorInvalidValue;
-  const Launch L = {stream, ev_start, ev_stop};
-  return for_widths(a, LaunchFn{a, (int)n_both_ll, n_splits, win, L});
+// The launch of this build (contiguous or paged store, one group size).
+hipError_t INNERQ_INNER_LAUNCH(const AttnArgs& a, int n_both, int n_splits, const WindowSet& win, const Launch& L) {
+  constexpr int G = INNERQ_INNER_GROUP;
+  if (a.group != G || (a.pages.table != nullptr) != kPagedStore) return hipErrorInvalidValue;
+  switch (width_pair(a)) {
+    case 0: return launch_t<2, 2, G>(a, n_both, n_splits, win, L);
+    case 1: return launch_t<3, 3, G>(a, n_both, n_splits, win, L);
+    case 2: return launch_t<4, 4, G>(a, n_both, n_splits, win, L);
+    case 3: return launch_t<3, 2, G>(a, n_both, n_splits, win, L);
+    default: return hipErrorInvalidValue;
+  }
 }
 
-#else
+#if !INNERQ_PAGED_STORE && INNERQ_INNER_GROUP == 32
 
 bool attention_inner_supported(const AttnArgs& a) {
   const int r = a.n_q_heads / a.n_kv_heads;
@@ -982,21 +1000,23 @@ bool attention_inner_supported(const AttnArgs& a) {
 
 std::atomic<int> g_inner_variant{0};
 
-int attention_inner_waves_per_cu(const AttnArgs& a) {
-  if (a.pages.table) return attention_inner_paged_waves_per_cu(a);
-  if (g_inner_variant.load(std::memory_order_relaxed) == 1 && attention_inner_f4_supported(a))
-    return attention_inner_f4_waves_per_cu(a);
-  return waves_per_cu_of_this_build(a);
+bool attention_inner_joins(const AttnArgs& a) {
+  return a.pages.table || g_inner_variant.load(std::memory_order_relaxed) != 1 || !attention_inner_f4_supported(a);
 }
 
-hipError_t launch_attention_inner(const AttnArgs& a, long long n_both_ll, int n_splits, const WindowSet& win,
-                                  hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
+int attention_inner_waves_per_cu(const AttnArgs& a) {
+  if (!attention_inner_joins(a)) return attention_inner_f4_waves_per_cu(a);
+  return 8;                                            // two per SIMD, by the kernel's register bound
+}
+
+hipError_t launch_attention_inner(const AttnArgs& a, long long n_both, int n_splits, const WindowSet& win, int waves,
+                                  const QuantArgs* append, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
   if (!attention_inner_supported(a)) return hipErrorInvalidValue;
-  if (a.pages.table) return launch_attention_inner_paged(a, n_both_ll, n_splits, win, stream, ev_start, ev_stop);
-  if (g_inner_variant.load(std::memory_order_relaxed) == 1 && attention_inner_f4_supported(a))
-    return launch_attention_inner_f4(a, n_both_ll, n_splits, win, stream, ev_start, ev_stop);
-  const Launch L = {stream, ev_start, ev_stop};
-  return for_widths(a, LaunchFn{a, (int)n_both_ll, n_splits, win, L});
+  if (!attention_inner_joins(a)) return launch_attention_inner_f4(a, n_both, n_splits, win, stream, ev_start, ev_stop);
+  const Launch L = {stream, ev_start, ev_stop, waves, append};
+  if (a.pages.table)
+    return a.group == 32 ? launch_inner_paged_g32(a, (int)n_both, n_splits, win, L) : launch_inner_paged_g64(a, (int)n_both, n_splits, win, L);
+  return a.group == 32 ? launch_inner_g32(a, (int)n_both, n_splits, win, L) : launch_inner_g64(a, (int)n_both, n_splits, win, L);
 }
 
 #endif

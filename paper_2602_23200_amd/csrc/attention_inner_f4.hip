@@ -563,7 +563,7 @@ attention_inner_f4_kernel(AttnArgs a, int n_both, int n_splits, WindowSet win, i
   // ---- the window chunk of this wavefront, with a partial slot of its own
   if (s_idx < win.n_chunks) {
     __syncthreads();
-    window_pass<1, 2, G, true, false>(a, bh, win.na, win.b0, win.nb, s_idx, win.n_chunks, n_splits + s_idx);
+    window_partial<1, 2, G, true, false>(a, bh, win.na, win.b0, win.nb, s_idx, win.n_chunks, n_splits + s_idx);
   }
 }
 

@@ -1,5 +1,5 @@
-// The fused inner-grouped decode-attention kernels built for a paged store: the same source as the kernels
-// for the contiguous store, compiled with the page-table lookup in (one entry per 64-token tile, fetched a
-// tile ahead).  Exports launch_attention_inner_paged and attention_inner_paged_waves_per_cu.
+// The fused inner-grouped kernels for a paged store, groups of 32 (see attention_inner.hip).
 #define INNERQ_PAGED_STORE 1
+#define INNERQ_INNER_LAUNCH launch_inner_paged_g32
+#define INNERQ_INNER_GROUP 32
 #include "attention_inner.hip"

@@ -129,6 +129,12 @@ struct QuantArgs {
   PageMap pages;
 };
 
+// A new token may overwrite a ring slot only after the old token in it has been read.  If every token from the
+// oldest one evicted in this call to the newest one appended fits the ring at once, no slot is shared.
+inline bool ring_slots_shared(const QuantArgs& a, const QuantTensorJob& j) {
+  return j.row_end > j.row_begin && a.w_sink + j.row_begin < a.n_old && a.n_old + a.t_new - (a.w_sink + j.row_begin) > j.slots;
+}
+
 struct AttnArgs;
 // merge (may be null): the log-sum-exp merge of an attention call whose partials are complete on
 // this stream rides in the same launch (or, for the rare two-launch appends, goes first).
@@ -161,7 +167,11 @@ struct AttnArgs {
   const int* n_dev;
   int* n_copy;
   int* n_valid;             // with n_dev: partial results per head of every sequence (workspace, [B]), left by the fused kernel for the merge; else null
-  int shared_waves;         // with n_dev: wavefronts of a kv head that the sequences share by their lengths; 0: the same number each
+  int shared_groups;        // with n_dev: work-groups of a kv head that the sequences share by their lengths; 0: the same number each
+  // a launch that joins its own partial results (merge.h): where its work-groups publish them (workspace) and its tag
+  // (odd); null: the partials are joined by a later launch
+  unsigned long long* join;
+  uint32_t join_tag;
   PageMap pages;
 };
 
@@ -181,16 +191,19 @@ hipError_t launch_attention_merge(const AttnArgs& a, hipStream_t stream);
 struct WindowSet { long long na, b0, nb; int n_chunks; };
 bool attention_inner_supported(const AttnArgs& a);
 int attention_inner_waves_per_cu(const AttnArgs& a);   // resident wavefronts per compute unit
+bool attention_inner_joins(const AttnArgs& a);         // the launch writes the output itself (not on the fp8 x fp4 form)
+// append (may be null; only where the launch joins): the append of the step's token rides in the launch, but for a value
+// group that leaves its ring.
 // ev_start / ev_stop (may be null) take the begin and end timestamps of the kernel dispatch itself.
-struct Launch { hipStream_t stream; hipEvent_t ev_start, ev_stop; };
-hipError_t launch_attention_inner(const AttnArgs& a, long long n_both, int n_splits, const WindowSet& win,
-                                  hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
+struct Launch { hipStream_t stream; hipEvent_t ev_start, ev_stop; int waves; const QuantArgs* append; };   // waves: per work-group
+hipError_t launch_attention_inner(const AttnArgs& a, long long n_both, int n_splits, const WindowSet& win, int waves,
+                                  const QuantArgs* append, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 
-// The same kernels compiled for a paged store (a.pages.table set); launch_attention_inner and
-// attention_inner_waves_per_cu route there.
-int attention_inner_paged_waves_per_cu(const AttnArgs& a);
-hipError_t launch_attention_inner_paged(const AttnArgs& a, long long n_both, int n_splits, const WindowSet& win,
-                                        hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
+// One build of the kernel each: contiguous or paged store (a.pages.table set), groups of 32 or 64.
+hipError_t launch_inner_g32(const AttnArgs& a, int n_both, int n_splits, const WindowSet& win, const Launch& L);
+hipError_t launch_inner_g64(const AttnArgs& a, int n_both, int n_splits, const WindowSet& win, const Launch& L);
+hipError_t launch_inner_paged_g32(const AttnArgs& a, int n_both, int n_splits, const WindowSet& win, const Launch& L);
+hipError_t launch_inner_paged_g64(const AttnArgs& a, int n_both, int n_splits, const WindowSet& win, const Launch& L);
 
 // The same partial results for 2-bit codes from the block-scaled fp8 x fp4 matrix instruction
 // (128-token tiles).  Parity-green but slower than the fp16 matrix form (see the file header), so it runs

@@ -126,4 +126,205 @@ inline bool merge_is_shared(const AttnArgs& a) {
   return (a.n_partials >= 33 && heads >= 4 && heads <= 128) || (a.n_partials >= 49 && heads <= 256);
 }
 
+// ---- one launch: the work-groups of a sequence-head publish their partials and the last one to do so joins them.
+//
+// Every number is published as a 64-bit word together with a tag of this launch, so data and flag are one store.  A
+// wavefront publishes its 64 channels of a head, waits until its stores have been performed, and then reads the words
+// of all work-groups: of the wavefronts with the same channels, the one whose stores were performed last finds every
+// word there, and whoever does joins them (should two find them all, both write the same bits).  Nobody waits for
+// anybody.  The joiner clears the words, so a launch that is replayed from a graph with its tag finds none to begin
+// with; what else the caller's workspace may hold carries the tags of no launch (31 bits, varied by lane, 66 words at a
+// time).  Words are only touched by device-scope accesses (performed past the per-XCD caches), so nothing has to be
+// written back or invalidated.
+//
+// From the barrier in front of it to the output (time stamps, 8 x 8 heads x 32k tokens): 1.1 us for the wavefronts'
+// states and publishing, 0.3 until the stores are performed, 1.3 for the words, 0.5 for the sums -- against 4.7 us for a
+// launch of any size behind one that fills the chip.  Arrivals counted in a word per sequence-head, the last one
+// joining, take a third memory round trip and contend (32 heads x 4k tokens, attention and append 16.7 us against 14.5).
+constexpr int kJoinWaves = 8;            // most wavefronts of a work-group that joins its own
+// bytes of one partial of one head: 128 channels, and level and sum for each half of them
+constexpr int kJoinBytes = (kHeadDim + 4) * 8;
+
+typedef unsigned long long join_word;
+__device__ __forceinline__ void publish(join_word* p, float x, uint32_t tag) {
+  __hip_atomic_store(p, (join_word)tag << 32 | __float_as_uint(x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ join_word look(const join_word* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void clear_word(join_word* p) { __hip_atomic_store(p, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float word_value(join_word w) { return __uint_as_float((uint32_t)w); }
+__device__ __forceinline__ uint32_t word_tag(join_word w) { return (uint32_t)(w >> 32); }
+
+// This wavefront's stores have been performed.
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// w = 2^(x - top) of a partial whose level is x, both in the log2 domain (an empty partial has x = -inf).
+__device__ __forceinline__ float level_weight(float x, float top) {
+  return x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(x - top);
+}
+
+__device__ __forceinline__ void store_output(const AttnArgs& a, long long bhq, int c, float x) {
+  if (a.out_is_fp32) reinterpret_cast<float*>(a.out)[bhq * kHeadDim + c] = x;
+  else reinterpret_cast<__half*>(a.out)[bhq * kHeadDim + c] = __float2half_rn(x);
+}
+
+// The words of one half (64 channels) of one head: channels [n_partials][64], then levels and sums [n_partials] each.
+__device__ __forceinline__ join_word* join_words(const AttnArgs& a, long long bhq, int half) {
+  return a.join + (bhq * 2 + half) * (long long)(a.n_partials * (kHeadDim / 2 + 2));
+}
+
+// Maximum / sum over the eight neighbouring lanes, in all of them.
+template <int CTRL>
+__device__ __forceinline__ float lane_moved(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float max_of_eight(float x) {
+  x = fmaxf(x, lane_moved<0xB1>(x));
+  x = fmaxf(x, lane_moved<0x4E>(x));
+  return fmaxf(x, lane_moved<0x141>(x));
+}
+__device__ __forceinline__ float sum_of_eight(float x) {
+  x += lane_moved<0xB1>(x);
+  x += lane_moved<0x4E>(x);
+  return x + lane_moved<0x141>(x);
+}
+__device__ __forceinline__ float from_lane(float x, int k) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), k));
+}
+
+// The published partials of UNITS half heads, if all are there (false for the whole wavefront else); half head u is half
+// u & 1 of head u >> 1.  Up to eight of each, so that one round of loads brings everything.
+template <int UNITS>
+__device__ __forceinline__ void join_few(const AttnArgs& a, long long head0, int unit, int step, int lane, int n, uint32_t tag) {
+  constexpr int H = kHeadDim / 2, NB = 8;
+  const uint32_t mine = tag ^ (uint32_t)(lane << 1);
+  join_word lv[UNITS], sv[UNITS], w[UNITS][NB];
+#pragma unroll
+  for (int i = 0; i < UNITS; ++i) {
+    const int u = unit + i * step;
+    const join_word* words = join_words(a, head0 + (u >> 1), u & 1);
+    const join_word* levels = words + a.n_partials * H + (lane < n ? lane : n - 1);
+    lv[i] = look(levels);
+    sv[i] = look(levels + a.n_partials);
+#pragma unroll
+    for (int k = 0; k < NB; ++k) w[i][k] = look(words + (k < n ? k : n - 1) * H + lane);
+  }
+#pragma unroll
+  for (int i = 0; i < UNITS; ++i) {
+    const int u = unit + i * step;
+    bool bad = lane < n && (word_tag(lv[i]) != mine || word_tag(sv[i]) != mine);
+#pragma unroll
+    for (int k = 0; k < NB; ++k) bad |= word_tag(w[i][k]) != mine;
+    if (__builtin_amdgcn_ballot_w64(bad) != 0) continue;
+    const float level = lane < n ? word_value(lv[i]) : -INFINITY;
+    const float f = level_weight(level, max_of_eight(level));
+    const float den = sum_of_eight(f * (lane < n ? word_value(sv[i]) : 0.f));
+    float num = 0.f;
+#pragma unroll
+    for (int k = 0; k < NB; ++k) num = __builtin_fmaf(from_lane(f, k), word_value(w[i][k]), num);
+    store_output(a, head0 + (u >> 1), (u & 1) * H + lane, num / from_lane(den, 0));
+    join_word* words = join_words(a, head0 + (u >> 1), u & 1);
+    for (int p = 0; p < n; ++p) clear_word(words + p * H + lane);
+    if (lane < n) {
+      clear_word(words + a.n_partials * H + lane);
+      clear_word(words + a.n_partials * (H + 1) + lane);
+    }
+  }
+}
+
+// The same for one half head and any number of partials.
+__device__ __forceinline__ void join_many(const AttnArgs& a, long long bhq, int half, int lane, int n, uint32_t tag) {
+  constexpr int H = kHeadDim / 2, NB = 8;
+  join_word* words = join_words(a, bhq, half);
+  join_word* levels = words + (long long)a.n_partials * H;
+  const uint32_t mine = tag ^ (uint32_t)(lane << 1);
+  float top = -INFINITY, den = 0.f, num = 0.f;
+  for (int base = 0; base < n; base += 64) {
+    const int here = n - base < 64 ? n - base : 64;
+    const bool some = lane < here;
+    // levels and sums of partial base + lane; the first channels' words go out with them
+    join_word lv = 0, sv = 0, w[NB];
+    if (some) {
+      lv = look(levels + base + lane);
+      sv = look(levels + a.n_partials + base + lane);
+    }
+#pragma unroll
+    for (int k = 0; k < NB; ++k) w[k] = look(words + (long long)(base + (k < here ? k : here - 1)) * H + lane);
+    if (__builtin_amdgcn_ballot_w64(some && (word_tag(lv) != mine || word_tag(sv) != mine)) != 0) return;
+    const float level = some ? word_value(lv) : -INFINITY;
+    const float up = fmaxf(top, window_wave_max(level));
+    const float f = level_weight(level, up), f0 = level_weight(top, up);
+    den = den * f0 + window_wave_sum(some ? f * word_value(sv) : 0.f);
+    num *= f0;
+    top = up;
+    for (int p0 = 0;;) {
+      bool bad = false;
+#pragma unroll
+      for (int k = 0; k < NB; ++k) {
+        bad |= word_tag(w[k]) != mine;
+        const float fk = from_lane(f, p0 + k < here ? p0 + k : here - 1);
+        num = __builtin_fmaf(p0 + k < here ? fk : 0.f, word_value(w[k]), num);
+      }
+      if (__builtin_amdgcn_ballot_w64(bad) != 0) return;
+      p0 += NB;
+      if (p0 >= here) break;
+#pragma unroll
+      for (int k = 0; k < NB; ++k) w[k] = look(words + (long long)(base + (p0 + k < here ? p0 + k : here - 1)) * H + lane);
+    }
+  }
+  store_output(a, bhq, half * H + lane, num / den);
+  for (int p = 0; p < n; ++p) clear_word(words + (long long)p * H + lane);
+  for (int p = lane; p < n; p += 64) {
+    clear_word(levels + p);
+    clear_word(levels + a.n_partials + p);
+  }
+}
+
+// The end of a work-group of `waves` wavefronts (all of them here): their states meet in LDS (each wavefront's own
+// `stride` floats of `lds`), a wavefront for every half head; then the output goes out where the sequence-head has one
+// work-group, and else the partial is published and the last one joins.  Levels are in the log2 domain.
+template <int NH>
+__device__ __forceinline__ void join_and_store(const AttnArgs& a, const WaveState<NH>& st, float* lds, int stride, int wave,
+                                               int waves, int lane, long long bh, int r, int group, int n_groups) {
+  constexpr int D = kHeadDim, H = D / 2;
+  static_assert(kJoinWaves == 8, "the wavefronts' levels are eight neighbouring lanes below");
+  float* mine = lds + wave * stride;                     // [NH][D] outputs, then [NH][2] levels and sums
+#pragma unroll
+  for (int h = 0; h < NH; ++h) {
+    *reinterpret_cast<float2*>(mine + h * D + 2 * lane) = st.o[h];
+    if (lane == 0) *reinterpret_cast<float2*>(mine + NH * D + 2 * h) = float2{st.m[h], st.l[h]};
+  }
+  __syncthreads();
+  const uint32_t tag = a.join_tag;
+  for (int u = wave; u < 2 * r; u += waves) {
+    const int h = u >> 1, c = (u & 1) * H + lane;
+    float2 ml = *reinterpret_cast<const float2*>(lds + (lane < waves ? lane : 0) * stride + NH * D + 2 * h);
+    float ov[kJoinWaves], num = 0.f;
+#pragma unroll
+    for (int w = 0; w < kJoinWaves; ++w) ov[w] = lds[(w < waves ? w : 0) * stride + h * D + c];
+    if (lane >= waves) ml = float2{-INFINITY, 0.f};
+    const float top = max_of_eight(ml.x), f = level_weight(ml.x, top);
+    const float den = sum_of_eight(f * ml.y);
+#pragma unroll
+    for (int w = 0; w < kJoinWaves; ++w) num = __builtin_fmaf(from_lane(f, w), ov[w], num);
+    const long long bhq = bh * r + h;
+    if (n_groups == 1) {
+      store_output(a, bhq, c, num / from_lane(den, 0));
+    } else {
+      join_word* words = join_words(a, bhq, u & 1);
+      publish(words + (long long)group * H + lane, num, tag ^ (uint32_t)(lane << 1));
+      if (lane < 2)
+        publish(words + (long long)a.n_partials * (H + lane) + group, lane == 0 ? top : den, tag ^ (uint32_t)((group & 63) << 1));
+    }
+  }
+  if (n_groups == 1) return;
+  stores_done();
+  if (n_groups <= 8) {
+    int u = wave;
+    for (; u + waves < 2 * r; u += 2 * waves) join_few<2>(a, bh * r, u, waves, lane, n_groups, tag);
+    if (u < 2 * r) join_few<1>(a, bh * r, u, waves, lane, n_groups, tag);
+  } else {
+    for (int u = wave; u < 2 * r; u += waves) join_many(a, bh * r + (u >> 1), u & 1, lane, n_groups, tag);
+  }
+}
+
 }  // namespace innerq

@@ -318,12 +318,6 @@ __host__ __device__ inline CopySpan copy_span(const QuantArgs& a, const QuantTen
   return copy_span(a, a.n_old, j.ring_from);
 }
 
-// A new token may overwrite a ring slot only after the old token in it has been read.  If every token from the
-// oldest one evicted in this call to the newest one appended fits the ring at once, no slot is shared.
-inline bool ring_slots_shared(const QuantArgs& a, const QuantTensorJob& j) {
-  return j.row_end > j.row_begin && a.w_sink + j.row_begin < a.n_old && a.n_old + a.t_new - (a.w_sink + j.row_begin) > j.slots;
-}
-
 // Threads the window copies of the larger of the two tensors take.
 inline long long copy_threads(const QuantArgs& a) {
   long long most = 0;

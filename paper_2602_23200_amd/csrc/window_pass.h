@@ -73,6 +73,37 @@ __device__ inline float window_wave_sum(float x) {
 __device__ inline float window_half_lo(uint32_t w) { return __half2float(__ushort_as_half((unsigned short)(w & 0xffffu))); }
 __device__ inline float window_half_hi(uint32_t w) { return __half2float(__ushort_as_half((unsigned short)(w >> 16))); }
 
+// Orders LDS accesses among the lanes of one wavefront (a wavefront's LDS operations execute in order; the compiler must
+// keep them so).  What follows shares LDS inside a wavefront only, whatever the size of its work-group.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Running softmax state of one wavefront's share of the tokens: reference level (log2 domain), sum of the weights and
+// weighted sums of the lane's two channels for every head.
+template <int NH>
+struct WaveState {
+  float m[NH], l[NH];
+  float2 o[NH];
+};
+
+// ... as partial result `slot` of the sequence-head's r heads, for a later launch to join.
+template <int NH>
+__device__ __forceinline__ void store_partial(const AttnArgs& a, const WaveState<NH>& st, long long bh, int r, int slot, int lane) {
+#pragma unroll
+  for (int h = 0; h < NH; ++h) {
+    if (h < r) {
+      const long long at = (bh * r + h) * a.n_partials + slot;
+      *reinterpret_cast<float2*>(&a.ws_o[at * kHeadDim + 2 * lane]) = st.o[h];
+      if (lane == 0) {
+        a.ws_ml[at * 2 + 0] = st.m[h] * 0.6931471805599453f;
+        a.ws_ml[at * 2 + 1] = st.l[h];
+      }
+    }
+  }
+}
+
 // Window token set: virtual index v in [0, na + nb) -> token v (v < na) or b0 + v - na.
 // Chunk `chunk` of `n_chunks` equal chunks of that set; partial written to `slot`.
 //
@@ -92,9 +123,17 @@ __device__ inline float window_half_hi(uint32_t w) { return __half2float(__ushor
 // packed value rows (VQ): 16 lanes share a row, four rows per load, summed across the lane groups at
 // the end.
 // PAGED: the packed rows are looked up through the page table (else the table is never consulted).
-template <int NH4, int BITS, int G, bool KQ, bool VQ, bool PAGED = false>
+// lds: window_lds_bytes<...>() bytes, 16-byte aligned, of this wavefront's own.  The chunk's state is left in `state` (!VQ), or
+// written to partial slot `slot` of the workspace (VQ).
+// loads_out() is called once, behind the loads of the first step.
+template <int NH4, int G, bool VQ>
+__host__ __device__ constexpr int window_lds_bytes() {
+  return 4 * NH4 * kHeadDim * 2 + kHeadDim / G * 4 * NH4 * 4 + (VQ ? 64 * 4 * NH4 * 4 : 4 * NH4 * 64 * 2);
+}
+template <int NH4, int BITS, int G, bool KQ, bool VQ, bool PAGED, typename Hook>
 __device__ __forceinline__ void window_pass(const AttnArgs& a, long long bh, long long na, long long b0,
-                                            long long nb, int chunk, int n_chunks, int slot) {
+                                            long long nb, int chunk, int n_chunks, int slot, unsigned char* lds,
+                                            WaveState<4 * NH4>& state, Hook loads_out) {
   constexpr int D = kHeadDim;
   constexpr int NH = NH4 * 4;
   constexpr int NG = D / G;
@@ -111,11 +150,10 @@ __device__ __forceinline__ void window_pass(const AttnArgs& a, long long bh, lon
   const long long v0 = chunk * chunk_len;
   const long long v1 = v0 + chunk_len < total ? v0 + chunk_len : total;
 
-  __shared__ __attribute__((aligned(16))) _Float16 wq[NH][D];       // query, fp16 (exact)
-  __shared__ __attribute__((aligned(16))) float wqs[NG][NH];        // their sums over each key group
-  __shared__ __attribute__((aligned(16))) float wp[VQ ? 64 : 1][NH];   // probabilities of the current 64 tokens
-  // the same, rounded to fp16, as matrix operands: [head][token]
-  __shared__ __attribute__((aligned(16))) _Float16 wp16[VQ ? 4 : NH * 64];
+  _Float16 (*wq)[D] = reinterpret_cast<_Float16 (*)[D]>(lds);                               // [NH][D] query, fp16 (exact)
+  float (*wqs)[NH] = reinterpret_cast<float (*)[NH]>(lds + NH * D * 2);                     // [NG][NH] their sums over each key group
+  float (*wp)[NH] = reinterpret_cast<float (*)[NH]>(lds + NH * D * 2 + NG * NH * 4);        // (VQ) [64][NH] probabilities of the current 64 tokens
+  _Float16* wp16 = reinterpret_cast<_Float16*>(lds + NH * D * 2 + NG * NH * 4);             // (!VQ) the same, rounded to fp16, as matrix operands: [head][token]
 
   const int cg = lane & 15, tg = lane >> 4;
   // (every index here is below 2^24: 32-bit arithmetic per lane)
@@ -159,6 +197,7 @@ __device__ __forceinline__ void window_pass(const AttnArgs& a, long long bh, lon
     }
   }
 
+  if (v0 >= v1) loads_out();
   for (long long base = v0; base < v1; base += 64) {
     // ---- all loads of this step
     w_u32x4 kreg[16], vreg[VQ ? 16 : 1];
@@ -241,6 +280,7 @@ __device__ __forceinline__ void window_pass(const AttnArgs& a, long long bh, lon
     }
 
     if (base == v0) {
+      loads_out();
       // ---- query: a lane takes 8 consecutive channels of one head (one 16-byte load)
 #pragma unroll
       for (int rnd = 0; rnd < NH4; ++rnd) {
@@ -266,7 +306,7 @@ __device__ __forceinline__ void window_pass(const AttnArgs& a, long long bh, lon
         }
       }
     }
-    __syncthreads();
+    wave_fence();
 
     // ---- packed key rows (KQ): the stored fields take the place of the fp16 row, as the fp16
     // integers they are (0x6400 | u is 1024 + u; minus 1024, exact), so that one pass through the
@@ -343,7 +383,7 @@ __device__ __forceinline__ void window_pass(const AttnArgs& a, long long bh, lon
         }
       }
     }
-    __syncthreads();
+    wave_fence();
     // ---- running softmax
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
@@ -369,7 +409,7 @@ __device__ __forceinline__ void window_pass(const AttnArgs& a, long long bh, lon
         for (int e = 0; e < 2; ++e) oq[e][h / 4][h % 4] *= alpha;
       }
     }
-    __syncthreads();
+    wave_fence();
     // ---- values: 16 lanes share one token row (8 channels = 16 bytes each), 4 rows per load
     // instruction; a lane keeps o[head][8 channels] of the tokens (4k + lane/16) and the four
     // lane groups are summed at the end.  Rows past the end carry probability 0.
@@ -426,24 +466,17 @@ __device__ __forceinline__ void window_pass(const AttnArgs& a, long long bh, lon
       }
     }
     }
-    __syncthreads();
+    wave_fence();
   }
 
   if constexpr (!VQ) {
     // ---- every lane holds its two channels, complete
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
-      if (h < r) {
-        const long long bhq = (long long)b * a.n_q_heads + hk * r + h;
-        float2 ov;
-        ov.x = oq[0][h / 4][h % 4];
-        ov.y = oq[1][h / 4][h % 4];
-        *reinterpret_cast<float2*>(&a.ws_o[(bhq * a.n_partials + slot) * D + 2 * lane]) = ov;
-        if (lane == 0) {
-          a.ws_ml[(bhq * a.n_partials + slot) * 2 + 0] = m_run[h] * 0.6931471805599453f;
-          a.ws_ml[(bhq * a.n_partials + slot) * 2 + 1] = l_run[h];
-        }
-      }
+      state.m[h] = m_run[h];
+      state.l[h] = l_run[h];
+      state.o[h].x = oq[0][h / 4][h % 4];
+      state.o[h].y = oq[1][h / 4][h % 4];
     }
   } else {
   // ---- sum the four lane groups; lanes 0..15 then hold channels 8*lane .. 8*lane+7
@@ -470,6 +503,17 @@ __device__ __forceinline__ void window_pass(const AttnArgs& a, long long bh, lon
     }
   }
   }
+}
+
+// The same for a kernel of one wavefront per work-group: the partial goes to slot `slot` of the workspace.
+template <int NH4, int BITS, int G, bool KQ, bool VQ, bool PAGED = false>
+__device__ __forceinline__ void window_partial(const AttnArgs& a, long long bh, long long na, long long b0,
+                                               long long nb, int chunk, int n_chunks, int slot) {
+  constexpr int NH = 4 * NH4;
+  __shared__ __attribute__((aligned(16))) unsigned char lds[window_lds_bytes<NH4, G, VQ>()];
+  WaveState<NH> st;
+  window_pass<NH4, BITS, G, KQ, VQ, PAGED>(a, bh, na, b0, nb, chunk, n_chunks, slot, lds, st, [] {});
+  if constexpr (!VQ) store_partial(a, st, bh, a.n_q_heads / a.n_kv_heads, slot, threadIdx.x & 63);
 }
 
 }  // namespace innerq

@@ -1,0 +1,78 @@
+"""Launches that join their own partial results: one work-group per sequence-head and several (up to eight, and more than
+eight, which take another path), work-groups of few and of eight wavefronts, more of them than fit the chip at once, and
+windows of many chunks; steps at which a value group leaves its ring; a workspace of any content; replays from a graph.
+"""
+import numpy as np
+import pytest
+
+from oracle import innerq_oracle as orc
+from paper_2602_23200_amd import workloads as wl
+from tests.helpers import assert_cache_equal, gpu_config, max_rel_err, oracle_config
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-3
+
+
+@pytest.mark.parametrize("batch,q_heads,kv_heads,tokens,recent,group,bits", [
+    (1, 4, 1, 200, 32, 32, 4), (2, 8, 2, 440, 48, 64, 2),                             # one work-group
+    (1, 3, 1, 900, 32, 32, 2), (1, 32, 8, 1500, 128, 32, 4), (2, 16, 2, 3000, 128, 64, 2), (3, 15, 3, 2000, 48, 32, 3),
+    (1, 4, 1, 9000, 128, 32, 2),                                                      # more than eight
+    (1, 4, 1, 1500, 900, 32, 2), (300, 1, 1, 700, 32, 32, 2), (2100, 2, 1, 250, 40, 32, 2),
+])
+def test_steps(batch, q_heads, kv_heads, tokens, recent, group, bits):
+    import torch
+    from paper_2602_23200_amd import binding as iq
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    steps = 3
+    n = tokens - (tokens - 4 - recent) % group + group - 3       # a value group leaves its ring within the steps
+    # (sequences of a large batch are copies of one, which the oracle follows)
+    one = batch > 8
+    w = wl.Workload("j", 1 if one else batch, q_heads, kv_heads, 128, n + steps, bits, group, 4, recent, seed=tokens)
+    o = oracle_config(w)
+    K, V = wl.kv_full(w)
+    spread = lambda a: torch.from_numpy(np.ascontiguousarray(np.broadcast_to(a, (batch,) + a.shape[1:]) if one else a)).cuda()  # noqa: E731
+    g = iq.allocate_cache(gpu_config(oracle_config(w.with_(batch=batch))))
+    iq.innerq_quantize_append(g, spread(K[:, :, :n]), spread(V[:, :, :n]))
+    iq.innerq_quantize_ahead(g)
+    want = orc.cache_init_prefill(o, K[:, :, :n], V[:, :, :n])
+    ws = iq.allocate_workspace(g.cfg)
+    for i in range(steps):
+        ws.fill_((0xFF, 0x00, 0x3F)[i])
+        q = wl.query(w, 0, i)
+        out = iq.innerq_decode_step(g, spread(K[:, :, n + i:n + i + 1]), spread(V[:, :, n + i:n + i + 1]), spread(q), ws).cpu().numpy()
+        orc.quantize_append(o, want, K[:, :, n + i:n + i + 1], V[:, :, n + i:n + i + 1])
+        ref = orc.decode_attention(o, want, q)
+        for b in range(0, batch, max(1, batch // 7)):
+            assert max_rel_err(out[b:b + 1], ref[:1] if one else ref[b:b + 1]) <= TOL, f"step {i} sequence {b}"
+        again = iq.innerq_decode_attention(g, spread(q), ws).cpu().numpy()      # the same tokens, now appended
+        assert max_rel_err(again, out) <= TOL
+    assert_cache_equal(g, want, o, bsel=slice(0, 1) if one else slice(None))
+
+
+def test_replays_from_a_graph_start_from_nothing():
+    """A recorded launch keeps its tag: what a replay publishes must not be taken for the next one's."""
+    import torch
+    from paper_2602_23200_amd import binding as iq
+    w = wl.Workload("g", 16, 32, 8, 128, 4600, 2, 32, 4, 128, seed=5)            # fills the chip: joined by the call itself
+    cfg = gpu_config(oracle_config(w))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    rows = lambda *s: torch.randn(*s, generator=gen, device="cuda").half()  # noqa: E731
+    g = iq.allocate_cache(cfg)
+    iq.innerq_quantize_append(g, rows(16, 8, 4600, 128), rows(16, 8, 4600, 128))
+    ws, other = iq.allocate_workspace(cfg), iq.allocate_workspace(cfg)
+    q, out = rows(16, 32, 128), torch.empty(16, 32, 128, device="cuda")
+    iq.innerq_decode_attention(g, q, ws, out=out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        iq.innerq_decode_attention(g, q, ws, out=out)
+    for i in range(12):
+        q.copy_(rows(16, 32, 128))
+        out.fill_(float("nan"))
+        graph.replay()
+        if i % 3 == 0:
+            graph.replay()
+        ref = iq.innerq_decode_attention(g, q, ws if i % 2 else other)
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref), f"replay {i}"
