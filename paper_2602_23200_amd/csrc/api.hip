@@ -36,6 +36,7 @@ inline int split_cap(const innerq_config_t& c) {
 // the sequences' token counts there for the append that follows it -- and, for batches that share the launch's
 // wavefronts by length, behind them how many partial results each sequence has (these fit the first 256 bytes).
 constexpr int kSharedBatchMost = 32;
+constexpr int kRaggedWaves = 1;          // wavefronts of a work-group there (20 heads x 25k tokens 21.9 us, with two 24.3)
 inline size_t seq_bytes(const innerq_config_t& c) { return (((size_t)c.batch * sizeof(int) + 255) / 256) * 256; }
 static_assert(2 * kSharedBatchMost * sizeof(int) <= 256, "both counts of a sequence in the first 256 bytes");
 
@@ -481,35 +482,73 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
     // comparison kernels run the window chunks as extra wavefronts of the same launch
     n_splits = (int)(fused_kind == 1 ? best_plain + n_win_chunks : best_plain);
     if (joins) {
-      // Wavefronts per work-group and work-groups per sequence-head, all resident at once.
-      const long long cus = compute_units(), per_cu = BH * n_splits <= 4 * cus ? 4 : 8;
-      long long best = 0, groups = 1;
+      // Wavefronts per work-group and work-groups per sequence-head, all resident at once.  The join costs the same for
+      // two work-groups and for eight, and more beyond (another round of loads, and more that arrive at once).
+      const long long cus = compute_units();
+      const bool heavy = a.bits == 3 || a.v_bits == 3;
+      long long groups = 1, most_joining = r <= 4 ? 16 : 8;
       if (one_group) {
         waves = n_splits < 8 ? n_splits : 8;
+      } else if (few_tiles) {
+        // A chip that is not full, up to 192 tiles: eight work-groups at most, wavefronts with one to three tiles each (us per
+        // step, with the merge -> now; kv heads x tokens: 1 x 4k 11.3 -> 9.6, 8 x 4k 12.6 -> 10.2, 8 x 8k 13.6 -> 10.9,
+        // 16 x 8k 13.1 -> 11.1, 32 x 8k 13.6 -> 12.5, 64 x 3k 13.2 -> 11.6).  More tiles want more wavefronts a head than
+        // that: 8 x 16k 13.6 with the merge, 13.7 with eight work-groups, 8 x 32k 13.7 against 16.7 with sixteen.
+        // 3-bit codes are bound by issue: a wavefront a SIMD and a tile each (8 x 8 heads x 8k tokens 23.1 with the merge,
+        // 25.1 with two wavefronts a SIMD).
+        const long long full = slots / BH, half = 4 * cus / BH;
+        long long most = full < 64 ? full : 64;
+        if (heavy && half < most) most = half;
+        long long want = (heavy ? n_tiles : n_tiles * 2 / 3) + n_win_chunks;
+        if (want > most) want = most;
+        if (want <= n_win_chunks) want = n_win_chunks + 1;
+        waves = 8;
+        // (a wavefront a SIMD where that is two and a half tiles each at most: 32 x 4k tokens at 4 bits 11.4, with more 12.2; 8k 13.8, 12.5)
+        if (half <= 32 && n_win_chunks < half && 2 * n_tiles <= 5 * half) want = want < half ? want : half;
+        if (want <= 32 && (BH * want <= 4 * cus || want / 4 * 4 > want / 8 * 8)) waves = 4;
+        if (waves > want) waves = (int)want;
+        groups = ceil_div(want, waves);
+        while (groups > 1 && groups * waves > most && (groups - 1) * waves > n_win_chunks) --groups;
+        if (n_tiles > 192 || (n_tiles > 96 && a.bits + a.v_bits > 4) || (n_tiles > 48 && heavy)) {
+          // ... but for a few heads (1 x 32k 15.4 with the merge, 13.8; 4 x 32k 14.7, 14.4)
+          joins = BH <= 4 && n_tiles > 192 && n_tiles <= 512 && r <= 4 && a.bits + a.v_bits == 4;
+          waves = 8;
+          groups = ceil_div(n_tiles / 2, 8);
+          most_joining = 32;
+        } else if (r > 4 && n_tiles < 48 && BH < 32) {
+          joins = false;                               // (eight heads' outputs are twice the join: 8 x 2k tokens 13.7, 14.3)
+        }
       } else {
-        for (int w = per_cu; w >= 1; w /= 2) {
-          const long long fit = cus * (per_cu / w) / BH, want = ceil_div(n_splits, w), g = fit < want ? fit : want;
+        long long best = 0;
+        for (int w = 8; w >= 4; w /= 2) {                // (of fewer, every one of the launch would take part in the join)
+          const long long fit = cus * (8 / w) / BH, all = ceil_div(n_splits, w), g = fit < all ? fit : all;
           if (g * w <= n_win_chunks) continue;
           const long long got = g * w < n_splits ? g * w : n_splits;
           if (got * 10 > best * 11) { best = got; waves = w; groups = g; }
         }
-        if (best == 0) {                               // more wavefronts than fit at once
+        if (best == 0) {
+          // more wavefronts than fit at once: in rounds, where they are many (1024 heads x 4k tokens 85.3 -> 75.2; 320 heads x 3k
+          // tokens 35.8 and 52.2) and the window chunks not most of it (1024 x 1k 39.8 and 50.1)
           waves = n_splits < 8 ? n_splits : 8;
           groups = ceil_div(n_splits, waves);
+          if (n_tiles < 32 || BH < 4 * cus) joins = false;
+          best = n_splits;
         }
-        while (groups > most_groups && waves < 8) {
-          waves = waves * 2 < 8 ? waves * 2 : 8;
-          groups = ceil_div(n_splits, waves);
-        }
+        // Work-groups of several wavefronts may leave slots empty: not where that is two fifths of a tile more for each of them (208
+        // heads, eight wavefronts a head instead of nine: 16k tokens, 3.4 tiles more, 51.9 us -> 59.3; 112 heads, 16 instead of
+        // 18: 6.5k tokens, 0.7 more, 18.5 -> 19.5).
+        if (10 * n_tiles * (n_splits - best) > 4 * best * n_splits) joins = false;
       }
-      // An attention call by itself leaves a launch of several work-groups per sequence-head that does not fill the chip to
-      // the merge.
-      if (groups > 1 && few_tiles && !append) joins = false;
-      if (!joins) {
-        waves = 1;
-      } else {
+      if (groups > most_joining || groups > most_groups) joins = false;
+      // An attention call by itself gains less (there is no append to save) and keeps the merge on a chip that is not full
+      // (4 heads x 9k tokens 11.7 us, joined 12.5) and with work-groups of four (160 heads x 3.6k tokens 18.8, 20.2).
+      if (groups > 1 && (few_tiles || waves < 8) && !append) joins = false;
+      if (joins) {
         n_splits = (int)(groups * waves);
         a.n_partials = (int)groups;
+      } else {
+        // (sharing the query tables is worth it for eight heads, 8 x 32k tokens 18.3 us -> 17.0, where all work-groups fit at once)
+        waves = r > 4 && BH * ceil_div(n_splits, 4) <= 2 * cus ? 4 : 1;
       }
     }
     // Token counts on the device: the wavefronts planned for sequences of the bound's length go to the sequences by
@@ -518,12 +557,12 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
     // front of the first load, and packs the wavefronts of short sequences onto fewer compute units, so it wants
     // several tiles per wavefront (8 sequences x 8 heads, bound 2000 tokens: 13.8 against 14.9 shared; 8000 tokens,
     // lengths spread 16-fold: 18.2 against 15.9) and several wavefronts per head (16 x 32 heads, bound 4000: 28.8 against 38.2).
-    const long long shared = (long long)n_splits * c.batch;
-    if (n_dev && c.batch > 1 && c.batch <= kSharedBatchMost && (n_win_chunks + 1) * c.batch <= shared &&
-        n_tiles >= 6 * per_head && per_head >= 10) {
+    const long long shared = (long long)n_splits * c.batch / kRaggedWaves, least = ceil_div(n_win_chunks + 1, kRaggedWaves);
+    if (n_dev && c.batch > 1 && c.batch <= kSharedBatchMost && least * c.batch <= shared && n_tiles >= 6 * per_head && per_head >= 10) {
+      waves = kRaggedWaves;
       a.shared_groups = (int)shared;
       a.n_valid = static_cast<int*>(workspace) + c.batch;
-      n_splits = split_cap(c);
+      n_splits = split_cap(c) / waves * waves;
     }
   } else if (n_both > 0) {
     const long long blocks_per_split = (long long)c.batch * c.n_kv_heads * ceil_div(r, kHeadTile);

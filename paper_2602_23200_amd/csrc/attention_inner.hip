@@ -170,6 +170,16 @@ __device__ inline float wave_max(float x) {
   return fmaxf(fmaxf(a, b), fmaxf(c, d));
 }
 
+// Maximum over the lanes of the same row parity (rows of 16 lanes).
+__device__ inline float parity_max(float x, int par) {
+  x = fmaxf(x, lane_moved<0xB1>(x));
+  x = fmaxf(x, lane_moved<0x4E>(x));
+  x = fmaxf(x, lane_moved<0x141>(x));
+  x = fmaxf(x, lane_moved<0x140>(x));
+  const float even = fmaxf(from_lane(x, 0), from_lane(x, 32)), odd = fmaxf(from_lane(x, 16), from_lane(x, 48));
+  return par ? odd : even;
+}
+
 // Inclusive sums over the lanes.
 struct Scan { int upto, total; };
 __device__ inline Scan wave_scan(int x) {
@@ -218,7 +228,7 @@ template <int KB, int VB, int G, int NH4>
 struct Lds {
   static constexpr int NH = 4 * NH4, NG = D / G;
   static constexpr int QS = D + 8, PS = TILE + 8;                  // a head's row of the query / probability tables (halves)
-  static constexpr int ZEROS = QS + (NH4 - 1) * 4 * QS;            // a row of zeros for the first four heads' offsets, and as far on as the last four's
+  static constexpr int ZEROS = QS;                                 // a row of zeros
   static constexpr int QSUM = (NH * QS * (KB == 3 ? 2 : 1) + ZEROS) * 2;
   static constexpr int COEF = QSUM + NH4 * NG * 4 * 4;
   static constexpr int COUNT = COEF + NH * 4;                      // wavefronts that have come to the end
@@ -235,7 +245,10 @@ struct Lds {
 // zero-points of its two channels only if one of the two groups is flagged asymmetric (the flag is the
 // sign bit of the scale it already holds), at the start of the tile that needs them, so a 128-byte line
 // of zero-points (64 channels of one token-group) that holds no asymmetric group is never fetched.
-template <int KB, int VB, int G, int NH4, bool ZK, int ZV>
+// JOIN: the launch joins its own partial results and may append a step's token; else it leaves them to the merge, and the token
+// counts may live on the device.  (One kernel for both had worse code in the tile loop: 3-bit keys, 8 x 8 heads x 8k tokens,
+// attention call 19.7 us before, 21.1, 19.9 with the two apart.)
+template <int KB, int VB, int G, int NH4, bool ZK, int ZV, bool JOIN>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) attention_inner_kernel(AttnArgs a_in, int n_both_in, int n_splits, WindowSet win_in, int win_tiles_in, int base_t_in,
                                                                                                  int rem_t_in, int r, QuantArgs append, int appends) {
   constexpr int LBK = KB == 3 ? 2 : KB, LBV = VB == 3 ? 2 : VB;   // field width of the (low) plane
@@ -255,6 +268,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   // as fp16 allows with queries below 2^9, probabilities up to 2^kSlack and offsets from 4 (2-bit) or 2 on.
   constexpr int CK = KB == 2 ? 10 : KB == 4 ? 8 : 6, CV = VB == 2 ? 13 : VB == 4 ? 11 : 10;
   constexpr int NH = NH4 * 4;
+  constexpr int CH = NH4;                              // chains of matrix instructions, each over 64 / CH of the columns
+  // Field positions of a 16-bit half of a high plane's word that one lane takes (eight heads and groups of 32: a word is a
+  // whole group's, and two lanes share it).
+  constexpr int F1PER = NH4 == 2 && G == 32 ? 8 : 16;
 
   // No division on the way to the first load: the grid is (splits, kv heads, batch), and the
   // host passes the quotients (heads per kv head; tiles per plain wavefront and their remainder).
@@ -274,7 +291,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   AttnArgs a = a_in;
   int n_both = n_both_in, win_tiles = win_tiles_in, base_t = base_t_in, rem_t = rem_t_in;
   WindowSet win = win_in;
-  if (a_in.n_dev) {
+  if (!JOIN && a_in.n_dev) {
     const int w_recent = a.k.slots - 1;                  // (the per-token key ring has w_recent + 1 slots)
     const int n_chunks = win.n_chunks;
     // counts fit 24 bits (capacity * head_dim <= 2^31); outside their bounds they are clamped
@@ -299,7 +316,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
       // sequences' wavefronts fit the launch: the smallest one below 8, at most an eighth above it beyond (every try is a
       // scan of the lengths, in front of the first load).  No fewer than four tiles (a wavefront pays its query set-up
       // once).
-      const int total = (int)gridDim.x, least = (n_chunks + waves) / waves;        // (at least one wavefront without a chunk)
+      const int total = (int)gridDim.x, most = n_splits / waves, least = (n_chunks + waves) / waves;   // (at least one wavefront without a chunk)
       const int n_lane = clamped(lane < a.batch ? a_in.n_dev[lane] : 0);
       const Length x = length(n_lane);
       const int work = lane < a.batch ? x.tiles + n_chunks * x.cost : 0;
@@ -310,7 +327,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
       for (;;) {
         mine = (work + quota * waves - 1) / (quota * waves);
         mine = mine < least ? least : mine;
-        mine = mine > n_splits ? n_splits : mine;
+        mine = mine > most ? most : mine;
         mine = lane < a.batch ? mine : 0;
         sc = wave_scan(mine);
         if (sc.total <= total) break;                    // (the host: batch * least <= total)
@@ -355,8 +372,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   // the others share the remaining tiles evenly.
   const int n_tiles = (n_both + TILE - 1) / TILE;
   const int s_idx = wave * n_groups + group;             // (the chunks go to different work-groups first)
-  int t0, t1;
-  if (s_idx < win.n_chunks) {
+  int t0 = 0, t1 = 0;
+  if (s_idx >= n_splits) {                               // (a launch that leaves its partials to the merge: beyond the plan)
+  } else if (s_idx < win.n_chunks) {
     t0 = s_idx * win_tiles;
     t1 = t0 + win_tiles;
   } else {
@@ -475,38 +493,41 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   // ---- the query loads go out first (the set-up below waits for them), the first tile's loads
   // right behind them: those overlap the query set-up.  One wavefront sets four heads up for the whole work-group (the last
   // ones, which carry no window chunk); the others meet it at the barrier with their first tile in flight.
-  u32x4 q_raw[NH4];
-  float4_t q_fac[NH4][2];                              // per-channel query factors, when given
+  struct Query {
+    u32x4 raw[NH4];
+    float4_t fac[NH4][2];                              // per-channel query factors, when given
+  };
   auto sets_up = [&](int rnd) { return wave == waves - 1 - (waves > rnd ? rnd : 0); };
+  auto load_query = [&](Query& q) {
 #pragma unroll
   for (int rnd = 0; rnd < NH4; ++rnd) {
     if (!sets_up(rnd)) continue;
     const int h = (rnd * 64 + lane) / (D / 8), c0 = 8 * ((rnd * 64 + lane) % (D / 8));
-    q_raw[rnd] = u32x4{0u, 0u, 0u, 0u};
-    if (h < r) q_raw[rnd] = *reinterpret_cast<const u32x4*>(a.q + ((long long)b * a.n_q_heads + hk * r + h) * D + c0);
+    q.raw[rnd] = u32x4{0u, 0u, 0u, 0u};
+    if (h < r) q.raw[rnd] = *reinterpret_cast<const u32x4*>(a.q + ((long long)b * a.n_q_heads + hk * r + h) * D + c0);
     if (a.q_scale) {
-      q_fac[rnd][0] = *reinterpret_cast<const float4_t*>(a.q_scale + hk * D + c0);
-      q_fac[rnd][1] = *reinterpret_cast<const float4_t*>(a.q_scale + hk * D + c0 + 4);
+      q.fac[rnd][0] = *reinterpret_cast<const float4_t*>(a.q_scale + hk * D + c0);
+      q.fac[rnd][1] = *reinterpret_cast<const float4_t*>(a.q_scale + hk * D + c0 + 4);
     }
   }
-  Regs bufA, bufB;
-  if (t1 > t0) load_tile(t0, bufA);
+  };
 
   // ---- query: fp16 (optionally rescaled), offset factors folded in.  A lane takes 8
   // consecutive channels of one head (one 16-byte load); the channels of one key group sit in
   // G/8 neighbouring lanes, so the group sums of q come from a few DPP adds.
+  auto set_up = [&](const Query& q) {
 #pragma unroll
   for (int rnd = 0; rnd < NH4; ++rnd) {
     if (!sets_up(rnd)) continue;
     const int idx = rnd * 64 + lane;
     const int h = idx / (D / 8), c0 = 8 * (idx % (D / 8));
-    const uint32_t rw[4] = {q_raw[rnd].x, q_raw[rnd].y, q_raw[rnd].z, q_raw[rnd].w};
+    const uint32_t rw[4] = {q.raw[rnd].x, q.raw[rnd].y, q.raw[rnd].z, q.raw[rnd].w};
     float qv[8], part = 0.f, mx = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const uint32_t hb = (e & 1) ? (rw[e / 2] >> 16) : (rw[e / 2] & 0xffffu);
       qv[e] = __half2float(__ushort_as_half((unsigned short)hb));
-      if (a.q_scale) qv[e] = __half2float(scaled_half(qv[e], q_fac[rnd][e / 4][e % 4]));
+      if (a.q_scale) qv[e] = __half2float(scaled_half(qv[e], q.fac[rnd][e / 4][e % 4]));
       part += qv[e];
       mx = __builtin_fmaxf(mx, __builtin_fabsf(qv[e]));
     }
@@ -532,7 +553,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
       tables[QA + h * QS + word * (MPWK * 4) + FK::slot(ep)] = (_Float16)(qv[e] * q_pow * factor);
       if constexpr (HIK) {
         const int word1 = c / 32, ep1 = c % 32;
-        const float factor1 = (float)(4 << CK) / (float)(1 << F1::off(ep1 % 16));
+        const float factor1 = (float)(4 << CK) / (float)(1 << F1::off(ep1 % 16 % F1PER));
         tables[QA1 + h * QS + word1 * (F1::MPW * 4) + F1::slot(ep1)] = (_Float16)(qv[e] * q_pow * factor1);
       }
     }
@@ -543,6 +564,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
       part += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, part), 0x141, 0xF, 0xF, true));
     if ((idx % (G / 8)) == 0) qsum[h / 4][c0 / G][h % 4] = part * (kSmScale * kLog2e);
   }
+  };
   int* arrivals = reinterpret_cast<int*>(lds + L::COUNT);
   if (wave == 0) {
     if (lane == 0) *arrivals = 0;
@@ -551,13 +573,28 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   // A wavefront without a tile (a launch with more wavefronts than tiles gives the window chunks wavefronts of their own)
   // meets the others behind the loads of its window chunk.
   const bool has_tiles = t1 > t0, has_chunk = s_idx < win.n_chunks;
-  if (has_tiles || !has_chunk) __syncthreads();
-  if (has_tiles) {
-  float q_coef[NH];                                    // (wave-uniform: scalar registers)
-  {
-    const float v = coef_lds[lane % NH];
+  Query query;
+  if (!has_tiles) {
+    if (waves > 1) {                                     // (alone, it needs no tables)
+      load_query(query);
+      set_up(query);
+    }
+    if (!has_chunk) __syncthreads();
+  } else {
+  // (the first tile's loads and their use in one branch: brought together from two, they were waited for at the barrier,
+  // 0.9 us of a launch of 1024 wavefronts with a few tiles each)
+  Regs bufA, bufB;
+  load_query(query);
+  load_tile(t0, bufA);
+  set_up(query);
+  __syncthreads();
+  // Four results a lane: heads 4 par .. 4 par + 3 (see CH below); their constants of the score.
+  const int par = NH4 == 2 ? (lane >> 4) & 1 : 0;
+  float q_coef[4];
 #pragma unroll
-    for (int h = 0; h < NH; ++h) q_coef[h] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), h));
+  for (int i = 0; i < 4; ++i) {
+    q_coef[i] = coef_lds[4 * par + i];
+    if constexpr (NH4 == 1) q_coef[i] = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, q_coef[i])));
   }
 
   // ---- A operands of the zero-point term: sum over groups of Zeff_g * (sum of q over group g) is a
@@ -567,16 +604,13 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   // operands carry 2 * qsum and Zeff / 2: S is at most 65504 / (2^(b-1) - 1), so 2^(b-2) S is
   // finite in fp16 for every finite cache where 2^(b-1) S is not; Z / 2 is exact unless Z is an fp16
   // denormal with an odd last bit (2^-25 off).
-  half4_t qs_hi[NH4], qs_lo[NH4];
+  half4_t qs_hi, qs_lo;
 #pragma unroll
-  for (int n = 0; n < NH4; ++n) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const float v = g < NG ? 2.f * qsum[n][g][lane & 3] : 0.f;
-      const _Float16 hi = (_Float16)v;
-      qs_hi[n][g] = hi;
-      qs_lo[n][g] = (_Float16)(v - (float)hi);
-    }
+  for (int g = 0; g < 4; ++g) {
+    const float v = g < NG ? 2.f * qsum[par][g][lane & 3] : 0.f;
+    const _Float16 hi = (_Float16)v;
+    qs_hi[g] = hi;
+    qs_lo[g] = (_Float16)(v - (float)hi);
   }
 
   // ---- running softmax state (log2 domain) and output accumulators.
@@ -586,42 +620,72 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   // 2^(CV - 2): still inside fp16.  l_run and o are kept in the raw scale of the matrix results.
   // The first tile sets the level to its exact maximum.
   constexpr float kSlack = HIV ? 5.0f : 6.0f;           // (the high-bit plane's factors reach 2^CV)
-  float m_run[NH], l_run[NH], o[NH][2];
+  float m_run[4], l_run[4], o[CH][2][4];
 #pragma unroll
-  for (int h = 0; h < NH; ++h) { m_run[h] = 0.f; l_run[h] = 0.f; o[h][0] = 0.f; o[h][1] = 0.f; }
+  for (int i = 0; i < 4; ++i) {
+    m_run[i] = 0.f;
+    l_run[i] = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) o[c][0][i] = o[c][1][i] = 0.f;
+  }
 
-  // where this lane's token sits in the probability operand table, and its offset factor
-  const int p_e = lane % FV::FPW;
-  const int p_index = (lane / FV::FPW) * (MPWV * 4) + FV::slot(p_e);
+  // Column (token, or channel pair) of chain c in this lane.
+  auto column = [&](int c) { return CH == 1 ? lane : (lane & ~16) + 16 * c; };
+  // where the lane's tokens sit in the probability operand table, and their offset factor (the same for both chains)
+  const int p_e = column(0) % FV::FPW;
   const float p_shift = (float)(CV - FV::off(p_e % FV::HALF));              // p is stored as p * 2^(CV - off)
-  // the same token in the high-bit plane's table: p * 4 * 2^(CV - off), as a factor on the stored p
-  const int p1_e = lane % 32;
-  const int p1_index = (lane / 32) * (F1::MPW * 4) + F1::slot(p1_e);
-  const float p1_factor = __builtin_amdgcn_exp2f((float)(CV + 2 - F1::off(p1_e % 16)) - p_shift);
-  // A operand of the 16x16x32 instructions: row l % 16, entries 8 (l / 16) .. + 7 of the contraction.  The matrix is
-  // block diagonal -- rows 4 j .. 4 j + 3 are the four heads, with entries only where block j of the contraction is
-  // -- so that lane l's result is its own column's product with its own eight B entries for the four heads (block
-  // j = l / 16 of rows 4 j ..).  Lanes off the diagonal read the zeros.  (One base a table for both halves of eight heads:
-  // with a base each, reloads of spilled registers in the tile loop waited for the tile in flight; 4-bit, 8 heads per kv
-  // head, 16k tokens: step 32.3 us against 30.6.)
-  const bool diagonal = ((lane >> 2) & 3) == (lane >> 4);
-  const int h4 = lane & 3;
-  const int qa = diagonal ? QA + h4 * QS : ZERO, pa = diagonal ? PA + h4 * PS : ZERO;
-  const int qa1 = diagonal ? QA1 + h4 * QS : ZERO, pa1 = diagonal ? PA1 + h4 * PS : ZERO;
-  // the same instruction with all rows alike (row r = head r % 4) sums 32 table entries for every lane at once
-  const int pl_lane = PA + (lane & 3) * PS + 8 * (lane >> 4);
+  auto p_index = [&](int c) { const int t = column(0); return t / FV::FPW * (MPWV * 4) + FV::slot(t % FV::FPW) + 16 * c; };
+  // the same in the high-bit plane's table: p * 4 * 2^(CV - off), as a factor on the stored p
+  const int p1_e = column(0) % 32;
+  const float p1_factor = __builtin_amdgcn_exp2f((float)(CV + 2 - F1::off(p1_e % 16 % F1PER)) - p_shift);
+  auto p1_index = [&](int c) { const int t = column(0); return t / 32 * (F1::MPW * 4) + F1::slot(t % 32) + c; };   // (16 tokens on: the other half of the word)
+  // A operand of the 16x16x32 instructions: row l % 16, entries 8 (l / 16) .. + 7 of the contraction.
+  // Four heads: the matrix is block diagonal -- rows 4 j .. 4 j + 3 are the four heads, with entries only where block j of
+  // the contraction is -- so that lane l's result is its own column's product with its own eight B entries for the four
+  // heads (block j = l / 16 of rows 4 j ..).
+  // Eight heads: two blocks, rows 8 j .. 8 j + 7 the eight heads, 16 contraction indices each: a column's B entries stand in
+  // the lanes l and l + 16 (the first half of a group's indices in the first), a chain of instructions takes 32 columns,
+  // and lane l's result are heads 4 par .. 4 par + 3 of its chain's column.  Half the matrix instructions of eight
+  // heads as twice four, and a quarter of the operand reads; the halves of two columns change places by one lane swap a word.
+  // (Eight query heads per kv head, step before -> now: 8 x 8 x 32k tokens, 2-bit 51.8 us -> 45.5, 4-bit 86.3 -> 77.1; 32 x 8 x
+  // 8k, G = 64 51.6 -> 39.9; 4 x 8 x 16k, 3-bit keys 28.1 -> 26.4.)
+  // Lanes off the diagonal read the zeros.
+  const bool diagonal = CH == 1 ? ((lane >> 2) & 3) == (lane >> 4) : ((lane >> 3) & 1) == (lane >> 5);
+  const int head_row = lane & (NH - 1), half_at = CH == 1 ? 0 : par * (G / 2);
+  const int qa = diagonal ? QA + head_row * QS + half_at : ZERO, pa = diagonal ? PA + head_row * PS + half_at : ZERO;
+  const int qa1 = diagonal ? QA1 + head_row * QS + half_at : ZERO, pa1 = diagonal ? PA1 + head_row * PS + half_at : ZERO;
+  // the same instruction with all blocks alike (row r = head r % NH) sums 32 table entries for every lane at once
+  const int pl_lane = PA + head_row * PS + 8 * (lane >> 4);
   const half8_t ones = ones_operand<LBV>(lane >> 4);
   auto a_operand = [&](int base, int entry) -> half8_t { return *reinterpret_cast<const half8_t*>(&tables[base + entry]); };
 
-  // The query operands stay in registers where they fit (64 for four heads): read from the table tile by tile, each
-  // matrix instruction of the score pass waits for its own LDS read.
-  constexpr bool QREG = NH4 == 1;
-  constexpr int KOPS = D / FK::FPW * MPWK / 2;           // matrix instructions per four heads and key row
+  // A word of each chain's column: of this lane's column (four heads); from words `lo` and `hi` of the lane's own column,
+  // the half that this lane takes of both chains' columns (eight heads).
+  struct Chains { uint32_t w[CH]; };
+  auto chains = [&](uint32_t lo, uint32_t hi) -> Chains {
+    if constexpr (CH == 1) {
+      return Chains{{lo}};
+    } else {
+      const u32x2 r = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(lo, hi, false, false));
+      return Chains{{r.x, r.y}};
+    }
+  };
+  // ... the same word of both chains' columns
+  auto both = [&](uint32_t w) -> Chains {
+    uint32_t copy = w;
+    if constexpr (CH == 2) asm volatile("" : "+v"(copy));   // (a register of its own)
+    return chains(w, copy);
+  };
+
+  // The query operands stay in registers where they fit (64 for four heads, 32 for 2-bit keys and eight): read from the
+  // table tile by tile, each matrix instruction of the score pass waits for its own LDS read.
+  constexpr bool QREG = CH == 1 || KB == 2;
+  constexpr int KOPS = D / 8 / CH;                       // matrix instructions per chain and (low) plane of a key row
   half8_t q_op[QREG ? KOPS : 1];
   if constexpr (QREG) {
 #pragma unroll
     for (int i = 0; i < KOPS; ++i) {
-      u32x4 v = __builtin_bit_cast(u32x4, a_operand(qa, 8 * i));
+      u32x4 v = __builtin_bit_cast(u32x4, a_operand(qa, CH == 1 ? 8 * i : 8 * i / (G / 2) * G + 8 * i % (G / 2)));
       asm volatile("" : "+v"(v));                        // (not to be read again)
       q_op[i] = __builtin_bit_cast(half8_t, v);
     }
@@ -644,191 +708,225 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
       }
     }
     // ================= scores: lane = token (Eq. att:1 with Eq. hybrid_dequant fused) =================
-    // one MFMA chain per key group, the chains interleaved so that consecutive MFMAs are independent
-    float4_t acc[NG][NH4];
+    // one MFMA chain per key group (and columns), the chains interleaved so that consecutive MFMAs are independent
+    float4_t acc[NG][CH];
 #pragma unroll
     for (int g = 0; g < NG; ++g)
 #pragma unroll
-      for (int n = 0; n < NH4; ++n) acc[g][n] = float4_t{0.f, 0.f, 0.f, 0.f};
+      for (int c = 0; c < CH; ++c) acc[g][c] = float4_t{0.f, 0.f, 0.f, 0.f};
+    constexpr int HWK = WPGK / CH;                       // words of a group that a lane takes
 #pragma unroll
-    for (int wd = 0; wd < WPGK; ++wd) {
-      Shifted<LBK> w[NG];
+    for (int wd = 0; wd < HWK; ++wd) {
+      Shifted<LBK> w[NG][CH];
 #pragma unroll
-      for (int g = 0; g < NG; ++g) w[g] = Shifted<LBK>(cur.k_word(g * WPGK + wd));
+      for (int g = 0; g < NG; ++g) {
+        const Chains x = chains(cur.k_word(g * WPGK + wd), cur.k_word(g * WPGK + (CH - 1) * HWK + wd));
+#pragma unroll
+        for (int c = 0; c < CH; ++c) w[g][c] = Shifted<LBK>(x.w[c]);
+      }
 #pragma unroll
       for (int m = 0; m < MPWK; m += 2) {
 #pragma unroll
-        for (int g = 0; g < NG; ++g) {
-          const int word = g * WPGK + wd;
-          const half8_t bop = operand<LBK>(w[g], m);
+        for (int g = 0; g < NG; ++g)
 #pragma unroll
-          for (int n = 0; n < NH4; ++n)
-            acc[g][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                QREG ? q_op[QREG ? (word * MPWK + m) / 2 : 0] : a_operand(qa, 4 * n * QS + (word * MPWK + m) * 4), bop, acc[g][n], 0, 0, 0);
-        }
+          for (int c = 0; c < CH; ++c)
+            acc[g][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                QREG ? q_op[QREG ? (g * (G / CH) + wd * FK::FPW + 4 * m) / 8 : 0] : a_operand(qa, g * G + wd * FK::FPW + 4 * m),
+                operand<LBK>(w[g][c], m), acc[g][c], 0, 0, 0);
       }
     }
     if constexpr (HIK) {
       // the plane of high bits joins the same chains: its query table carries the weight 4
+      constexpr int HW1 = HWG / CH > 0 ? HWG / CH : 1, M1 = HWG >= CH ? F1::MPW : F1::MPW / 2;
 #pragma unroll
-      for (int j = 0; j < HWG; ++j) {
-        Shifted<1> w[NG];
+      for (int j = 0; j < HW1; ++j) {
+        Shifted<1> w[NG][CH];
 #pragma unroll
-        for (int g = 0; g < NG; ++g) w[g] = Shifted<1>(cur.k_high(g * HWG + j));
+        for (int g = 0; g < NG; ++g) {
+          const Chains x = HWG >= CH ? chains(cur.k_high(g * HWG + j), cur.k_high(g * HWG + (CH - 1) * HW1 + j)) : both(cur.k_high(g * HWG + j));
 #pragma unroll
-        for (int m = 0; m < F1::MPW; m += 2) {
+          for (int c = 0; c < CH; ++c) w[g][c] = Shifted<1>(HWG >= CH ? x.w[c] : x.w[c] >> (8 * par));
+        }
 #pragma unroll
-          for (int g = 0; g < NG; ++g) {
-            const int word = g * HWG + j;
-            const half8_t bop = operand<1>(w[g], m);
+        for (int m = 0; m < M1; m += 2) {
 #pragma unroll
-            for (int n = 0; n < NH4; ++n)
-              acc[g][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_operand(qa1, 4 * n * QS + (word * F1::MPW + m) * 4), bop, acc[g][n], 0, 0, 0);
-          }
+          for (int g = 0; g < NG; ++g)
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+              acc[g][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                  a_operand(qa1, (g * HWG + j) * 32 + 4 * m), operand<1>(w[g][c], m), acc[g][c], 0, 0, 0);
         }
       }
     }
-    // e[h] = score (log2 domain) + offset shift - reference level: the exponent of the stored probability.
+    // e[c][i] = score (log2 domain) + offset shift - reference level: the exponent of the stored probability.
     // Per group: |S| * (raw inner sum) + Zeff * (sum of q).  The scale sign bit marks an asymmetric
     // group, so max(s, 0) is |S| for a symmetric group and 0 for an asymmetric one, and
     // Zeff = Z - 2^(b-1) * max(s, 0) needs no select (Z is stored as +0 for symmetric groups).
     // Scales and zero-points enter the FMAs as fp16 sources; the constant factor is applied once.
-    float e[NH], t[NH];
+    float e[CH][4];
+    uint32_t ks[NG / 2][CH];
+#pragma unroll
+    for (int gp = 0; gp < NG / 2; ++gp) {
+      const Chains x = both(cur.ks[gp]);
+#pragma unroll
+      for (int c = 0; c < CH; ++c) ks[gp][c] = x.w[c];
+    }
     {
-      // Zeff / 2 of this token's groups as fp16: Z / 2 - 2^(b-2) max(s, 0) (one of the two terms is 0)
-      u32x2 zw = {0u, 0u};
+      // Zeff / 2 of the lane's own token's groups as fp16: Z / 2 - 2^(b-2) max(s, 0) (one of the two terms is 0)
+      u32x2 zw[CH];
 #pragma unroll
-      for (int gp = 0; gp < NG / 2; ++gp) {
-        const half2_t sp = __builtin_bit_cast(half2_t, cur.ks[gp]);
-        const half2_t mp = positive_part(sp);
-        half2_t zp;
-        constexpr _Float16 kNegQuarterK = (_Float16)(-HALFK / 2), kHalf = (_Float16)0.5f;
-        if constexpr (has_kz)
-          zp = mp * half2_t{kNegQuarterK, kNegQuarterK} + __builtin_bit_cast(half2_t, cur.kz[gp]) * half2_t{kHalf, kHalf};
-        else zp = sp * half2_t{kNegQuarterK, kNegQuarterK};
-        zw[gp] = __builtin_bit_cast(uint32_t, zp);
+      for (int gp = 0; gp < 2; ++gp) {
+        Chains x = {};
+        if (gp < NG / 2) {
+          const half2_t sp = __builtin_bit_cast(half2_t, cur.ks[gp < NG / 2 ? gp : 0]);
+          half2_t zp;
+          constexpr _Float16 kNegQuarterK = (_Float16)(-HALFK / 2), kHalf = (_Float16)0.5f;
+          if constexpr (has_kz)
+            zp = positive_part(sp) * half2_t{kNegQuarterK, kNegQuarterK} + __builtin_bit_cast(half2_t, cur.kz[gp < NG / 2 ? gp : 0]) * half2_t{kHalf, kHalf};
+          else zp = sp * half2_t{kNegQuarterK, kNegQuarterK};
+          x = both(__builtin_bit_cast(uint32_t, zp));
+        }
+#pragma unroll
+        for (int c = 0; c < CH; ++c) zw[c][gp] = x.w[c];
       }
-      const half4_t zop = __builtin_bit_cast(half4_t, zw);
 #pragma unroll
-      for (int n = 0; n < NH4; ++n) {
-        float4_t ez = float4_t{p_shift - m_run[4 * n], p_shift - m_run[4 * n + 1], p_shift - m_run[4 * n + 2],
-                               p_shift - m_run[4 * n + 3]};
-        ez = __builtin_amdgcn_mfma_f32_4x4x4f16(qs_hi[n], zop, ez, 0, 0, 0);
-        ez = __builtin_amdgcn_mfma_f32_4x4x4f16(qs_lo[n], zop, ez, 0, 0, 0);
-        e[4 * n] = ez.x; e[4 * n + 1] = ez.y; e[4 * n + 2] = ez.z; e[4 * n + 3] = ez.w;
+      for (int c = 0; c < CH; ++c) {
+        const half4_t zop = __builtin_bit_cast(half4_t, zw[c]);
+        float4_t ez = float4_t{p_shift - m_run[0], p_shift - m_run[1], p_shift - m_run[2], p_shift - m_run[3]};
+        ez = __builtin_amdgcn_mfma_f32_4x4x4f16(qs_hi, zop, ez, 0, 0, 0);
+        ez = __builtin_amdgcn_mfma_f32_4x4x4f16(qs_lo, zop, ez, 0, 0, 0);
+        e[c][0] = ez.x; e[c][1] = ez.y; e[c][2] = ez.z; e[c][3] = ez.w;
       }
     }
 #pragma unroll
-    for (int h = 0; h < NH; ++h) t[h] = 0.f;
+    for (int c = 0; c < CH; ++c) {
+      float t[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      const float S = __builtin_fabsf((float)half_of(cur.ks[g / 2], g & 1));
+      for (int g = 0; g < NG; ++g) {
+        const float S = __builtin_fabsf((float)half_of(ks[g / 2][c], g & 1));
 #pragma unroll
-      for (int h = 0; h < NH; ++h) t[h] = __builtin_fmaf(S, acc[g][h / 4][h % 4], t[h]);
+        for (int i = 0; i < 4; ++i) t[i] = __builtin_fmaf(S, acc[g][c][i], t[i]);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) e[c][i] = __builtin_fmaf(q_coef[i], t[i], e[c][i]);   // undoes the operand factors and the head's query factor
     }
-#pragma unroll
-    for (int h = 0; h < NH; ++h)
-      e[h] = __builtin_fmaf(q_coef[h], t[h], e[h]);   // undoes the operand factors and the head's query factor
 
     // ================= running softmax (Eq. att:2), probabilities to the operand table =================
-    if (tile * TILE + (TILE - 1) > last_row) {         // ragged last tile: lanes past the end weigh nothing
-      const bool valid = tile * TILE + lane <= last_row;
+    if (tile * TILE + (TILE - 1) > last_row) {         // ragged last tile: columns past the end weigh nothing
 #pragma unroll
-      for (int h = 0; h < NH; ++h) e[h] = valid ? e[h] : -INFINITY;
+      for (int c = 0; c < CH; ++c) {
+        const bool valid = tile * TILE + column(c) <= last_row;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) e[c][i] = valid ? e[c][i] : -INFINITY;
+      }
     }
     bool raise = false;
 #pragma unroll
-    for (int h = 0; h < NH; ++h) raise |= e[h] > kSlack + p_shift;
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) raise |= e[c][i] > kSlack + p_shift;
     if (first || __builtin_amdgcn_ballot_w64(raise) != 0) {   // rare after the first tiles
 #pragma unroll
-      for (int h = 0; h < NH; ++h) {
-        const float mx = wave_max(e[h] - p_shift);           // largest score relative to the current level
+      for (int i = 0; i < 4; ++i) {
+        // largest score relative to the current level
+        const float mx = CH == 1 ? wave_max(e[0][i] - p_shift) : parity_max(fmaxf(e[0][i], e[CH - 1][i]) - p_shift, par);
         const float d = first ? mx : fmaxf(mx, 0.f);         // the level only rises, except when it is first set
         const float alpha = first ? 1.f : __builtin_amdgcn_exp2f(-d);
-        m_run[h] += d;
-        e[h] -= d;
-        l_run[h] *= alpha;
-        o[h][0] *= alpha;
-        o[h][1] *= alpha;
+        m_run[i] += d;
+        l_run[i] *= alpha;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+          e[c][i] -= d;
+          o[c][0][i] *= alpha;
+          o[c][1][i] *= alpha;
+        }
       }
     }
     wave_fence();                                      // previous tile's readers of pA are done
 #pragma unroll
-    for (int h = 0; h < NH; ++h) {
-      const float p = __builtin_amdgcn_exp2f(e[h]);
-      tables[PA + h * PS + p_index] = (_Float16)p;
-      if constexpr (HIV) tables[PA1 + h * PS + p1_index] = (_Float16)(p * p1_factor);
-    }
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float p = __builtin_amdgcn_exp2f(e[c][i]);
+        tables[PA + (4 * par + i) * PS + p_index(c)] = (_Float16)p;
+        if constexpr (HIV) tables[PA1 + (4 * par + i) * PS + p1_index(c)] = (_Float16)(p * p1_factor);
+      }
     wave_fence();
 
     // ================= values: lane = two channels (Eq. att:3 with Eq. hybrid_dequant fused) =================
 #pragma unroll
     for (int gi = 0; gi < GPT; ++gi) {
-      float4_t acc0[NH4], acc1[NH4], accl[NH4];
+      float4_t av[CH][2], accl = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int n = 0; n < NH4; ++n) {
-        acc0[n] = float4_t{0.f, 0.f, 0.f, 0.f};
-        acc1[n] = acc0[n];
-        accl[n] = acc0[n];
-      }
+      for (int c = 0; c < CH; ++c) av[c][0] = av[c][1] = float4_t{0.f, 0.f, 0.f, 0.f};
+      constexpr int HWV = WPGV / CH;
 #pragma unroll
-      for (int wd = 0; wd < WPGV; ++wd) {
-        const Shifted<LBV> wa(cur.v_word(gi, 0, wd)), wb(cur.v_word(gi, 1, wd));
+      for (int wd = 0; wd < HWV; ++wd) {
+        Shifted<LBV> w[2][CH];
+#pragma unroll
+        for (int ch = 0; ch < 2; ++ch) {
+          const Chains x = chains(cur.v_word(gi, ch, wd), cur.v_word(gi, ch, (CH - 1) * HWV + wd));
+#pragma unroll
+          for (int c = 0; c < CH; ++c) w[ch][c] = Shifted<LBV>(x.w[c]);
+        }
 #pragma unroll
         for (int m = 0; m < MPWV; m += 2) {
-          const half8_t b0 = operand<LBV>(wa, m);
-          const half8_t b1 = operand<LBV>(wb, m);
+          const half8_t aop = a_operand(pa, gi * G + wd * FV::FPW + 4 * m);
 #pragma unroll
-          for (int n = 0; n < NH4; ++n) {
-            const half8_t aop = a_operand(pa, 4 * n * PS + ((gi * WPGV + wd) * MPWV + m) * 4);
-            acc0[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop, b0, acc0[n], 0, 0, 0);
-            acc1[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop, b1, acc1[n], 0, 0, 0);
-          }
+          for (int ch = 0; ch < 2; ++ch)
+#pragma unroll
+            for (int c = 0; c < CH; ++c)
+              av[c][ch] = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop, operand<LBV>(w[ch][c], m), av[c][ch], 0, 0, 0);
         }
       }
 #pragma unroll
-      for (int e = 0; e < G; e += 32)
-#pragma unroll
-        for (int n = 0; n < NH4; ++n)
-          accl[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_operand(pl_lane + n * 4 * PS, gi * G + e), ones, accl[n], 0, 0, 0);
+      for (int x = 0; x < G; x += 32)
+        accl = __builtin_amdgcn_mfma_f32_16x16x32_f16(a_operand(pl_lane, gi * G + x), ones, accl, 0, 0, 0);
       if constexpr (HIV) {
+        constexpr int HW1 = HWG / CH > 0 ? HWG / CH : 1, M1 = HWG >= CH ? F1::MPW : F1::MPW / 2;
 #pragma unroll
-        for (int j = 0; j < HWG; ++j) {
-          const Shifted<1> wa(cur.v_high(gi, 0, j)), wb(cur.v_high(gi, 1, j));
+        for (int j = 0; j < HW1; ++j) {
+          Shifted<1> w[2][CH];
 #pragma unroll
-          for (int m = 0; m < F1::MPW; m += 2) {
-            const half8_t b0 = operand<1>(wa, m);
-            const half8_t b1 = operand<1>(wb, m);
+          for (int ch = 0; ch < 2; ++ch) {
+            const Chains x = HWG >= CH ? chains(cur.v_high(gi, ch, j), cur.v_high(gi, ch, (CH - 1) * HW1 + j)) : both(cur.v_high(gi, ch, j));
 #pragma unroll
-            for (int n = 0; n < NH4; ++n) {
-              const half8_t aop = a_operand(pa1, 4 * n * PS + ((gi * HWG + j) * F1::MPW + m) * 4);
-              acc0[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop, b0, acc0[n], 0, 0, 0);
-              acc1[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop, b1, acc1[n], 0, 0, 0);
-            }
+            for (int c = 0; c < CH; ++c) w[ch][c] = Shifted<1>(HWG >= CH ? x.w[c] : x.w[c] >> (8 * par));
+          }
+#pragma unroll
+          for (int m = 0; m < M1; m += 2) {
+            const half8_t aop = a_operand(pa1, (gi * HWG + j) * 32 + 4 * m);
+#pragma unroll
+            for (int ch = 0; ch < 2; ++ch)
+#pragma unroll
+              for (int c = 0; c < CH; ++c)
+                av[c][ch] = __builtin_amdgcn_mfma_f32_16x16x32_f16(aop, operand<1>(w[ch][c], m), av[c][ch], 0, 0, 0);
           }
         }
-      }
-      const uint32_t spair = cur.vs[gi];
-      const float S0 = __builtin_fabsf((float)half_of(spair, 0)), S1 = __builtin_fabsf((float)half_of(spair, 1));
-      float z0, z1;
-      if constexpr (has_vz) {
-        const uint32_t mpair = __builtin_bit_cast(
-            uint32_t, positive_part(__builtin_bit_cast(half2_t, spair)));
-        const uint32_t zpair = late_vz ? vz_late[gi] : cur.vz[gi];
-        z0 = __builtin_fmaf((float)half_of(mpair, 0), (float)(-HALFV), (float)half_of(zpair, 0));
-        z1 = __builtin_fmaf((float)half_of(mpair, 1), (float)(-HALFV), (float)half_of(zpair, 1));
-      } else {
-        z0 = S0 * (float)(-HALFV);
-        z1 = S1 * (float)(-HALFV);
       }
       // accl = 2^(CV - 24) * (sum of the fp16 probabilities of this group); l and o stay in that scale
 #pragma unroll
-      for (int n = 0; n < NH4; ++n) {
+      for (int i = 0; i < 4; ++i) l_run[i] += accl[i];
+      const Chains sx = both(cur.vs[gi]);
+      Chains zx = {};
+      if constexpr (has_vz) zx = both(late_vz ? vz_late[gi] : cur.vz[gi]);
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        const uint32_t spair = sx.w[c];
+        const float S0 = __builtin_fabsf((float)half_of(spair, 0)), S1 = __builtin_fabsf((float)half_of(spair, 1));
+        float z0, z1;
+        if constexpr (has_vz) {
+          const uint32_t mpair = __builtin_bit_cast(uint32_t, positive_part(__builtin_bit_cast(half2_t, spair)));
+          z0 = __builtin_fmaf((float)half_of(mpair, 0), (float)(-HALFV), (float)half_of(zx.w[c], 0));
+          z1 = __builtin_fmaf((float)half_of(mpair, 1), (float)(-HALFV), (float)half_of(zx.w[c], 1));
+        } else {
+          z0 = S0 * (float)(-HALFV);
+          z1 = S1 * (float)(-HALFV);
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          l_run[n * 4 + i] += accl[n][i];
-          o[n * 4 + i][0] = __builtin_fmaf(S0, acc0[n][i], __builtin_fmaf(z0, accl[n][i], o[n * 4 + i][0]));
-          o[n * 4 + i][1] = __builtin_fmaf(S1, acc1[n][i], __builtin_fmaf(z1, accl[n][i], o[n * 4 + i][1]));
+          o[c][0][i] = __builtin_fmaf(S0, av[c][0][i], __builtin_fmaf(z0, accl[i], o[c][0][i]));
+          o[c][1][i] = __builtin_fmaf(S1, av[c][1][i], __builtin_fmaf(z1, accl[i], o[c][1][i]));
         }
       }
     }
@@ -862,13 +960,25 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
   }
 
-  // ---- this wavefront's state over its tiles
+  // ---- this wavefront's state over its tiles: every head of the lane's own channels
+  constexpr float kUndo = (float)(1 << (24 - CV));     // the operand factors of the value pass
 #pragma unroll
-  for (int h = 0; h < NH; ++h) {
-    part.o[h].x = o[h][0] * (float)(1 << (24 - CV));   // undoes the operand factors of the value pass
-    part.o[h].y = o[h][1] * (float)(1 << (24 - CV));
-    part.m[h] = m_run[h];
-    part.l[h] = l_run[h] * (float)(1 << (24 - CV));
+  for (int i = 0; i < 4; ++i) {
+    if constexpr (CH == 1) {
+      part.o[i].x = o[0][0][i] * kUndo;
+      part.o[i].y = o[0][1][i] * kUndo;
+      part.m[i] = m_run[i];
+      part.l[i] = l_run[i] * kUndo;
+    } else {
+      const Chains x = chains(__float_as_uint(o[0][0][i] * kUndo), __float_as_uint(o[CH - 1][0][i] * kUndo));
+      const Chains y = chains(__float_as_uint(o[0][1][i] * kUndo), __float_as_uint(o[CH - 1][1][i] * kUndo));
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        part.o[4 * c + i] = float2{__uint_as_float(x.w[c]), __uint_as_float(y.w[c])};
+        part.m[4 * c + i] = from_lane(m_run[i], 16 * c);
+        part.l[4 * c + i] = from_lane(l_run[i] * kUndo, 16 * c);
+      }
+    }
   }
   }
 
@@ -876,13 +986,12 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   if (has_chunk) {
     __builtin_amdgcn_s_setprio(0);
     WaveState<NH> w;
-    const bool apart = a.join == nullptr;
     window_pass<NH4, KB, G, true, false, kPagedStore>(a, bh, win.na, win.b0, win.nb, s_idx, win.n_chunks, 0, lds + own_lds, w,
                                                       [&] { if (!has_tiles) __syncthreads(); });
-    if (apart) store_partial(a, w, bh, r, n_splits + s_idx, lane);
+    if (!JOIN) store_partial(a, w, bh, r, n_splits + s_idx, lane);
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
-      if (apart) continue;
+      if (!JOIN) continue;
       const float top = fmaxf(part.m[h], w.m[h]);
       const float f = level_weight(part.m[h], top), g = level_weight(w.m[h], top);
       part.m[h] = top;
@@ -894,18 +1003,18 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
 
   // ---- the append of the step's token: disjoint memory.  The wavefront of one work-group that is through first takes it,
   // while the others still have tiles.
-  if (appends && group == n_groups - 1) {
+  if (JOIN && appends && group == n_groups - 1) {
     int at = 0;
     if (lane == 0) at = __hip_atomic_fetch_add(arrivals, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (__builtin_amdgcn_readfirstlane(at) == 0) append_keys_and_copies<G, KB>(append, bh, a.n_tokens - 1, lane);
   }
 
-  if (!a.join) {                                         // partials for a later launch (the tiles' after the chunk's: nothing reuses its registers)
-    store_partial(a, part, bh, r, s_idx, lane);
-    return;
+  if constexpr (!JOIN) {                                 // partials for a later launch (the tiles' after the chunk's: nothing reuses its registers)
+    if (s_idx < n_splits) store_partial(a, part, bh, r, s_idx, lane);
+  } else {
+    // ---- the work-group's wavefronts, and the sequence-head's work-groups, meet
+    join_and_store<NH>(a, part, reinterpret_cast<float*>(lds + L::SHARED), L::OWN / 4, wave, waves, lane, bh, r, group, n_groups);
   }
-  // ---- the work-group's wavefronts, and the sequence-head's work-groups, meet
-  join_and_store<NH>(a, part, reinterpret_cast<float*>(lds + L::SHARED), L::OWN / 4, wave, waves, lane, bh, r, group, n_groups);
 }
 
 template <int KB, int VB, int G, bool ZK, int ZV>
@@ -918,12 +1027,12 @@ hipError_t launch_z(const AttnArgs& a, int n_both, int n_splits, const WindowSet
   const int quota = (n_tiles + win.n_chunks * cost + n_splits - 1) / n_splits;
   int win_tiles = quota > cost ? quota - cost : 0;
   if (win.n_chunks > 0 && win_tiles > n_tiles / win.n_chunks) win_tiles = n_tiles / win.n_chunks;
-  if (L.waves < 1 || L.waves > kJoinWaves || n_splits % L.waves != 0 || (!a.join && L.append)) return hipErrorInvalidValue;
+  if (L.waves < 1 || L.waves > kJoinWaves || (a.join && n_splits > kJoinGroups * L.waves) || (!a.join && L.append)) return hipErrorInvalidValue;
   if (n_splits <= win.n_chunks) return hipErrorInvalidValue;      // the host gives at least one plain wavefront
   if (a.batch > 65535 || a.n_kv_heads > 65535) return hipErrorInvalidValue;
   const int rest = n_tiles - win.n_chunks * win_tiles, others = n_splits - win.n_chunks;
   const int base_t = rest / others, rem_t = rest % others;
-  dim3 grid((unsigned)(n_splits / L.waves), (unsigned)a.n_kv_heads, (unsigned)a.batch);
+  dim3 grid((unsigned)((n_splits + L.waves - 1) / L.waves), (unsigned)a.n_kv_heads, (unsigned)a.batch);
   if (a.shared_groups > 0) grid = dim3((unsigned)a.shared_groups, (unsigned)a.n_kv_heads, 1u);
   const unsigned lds_bytes = (unsigned)(r <= 4 ? Lds<KB, VB, G, 1>::bytes(L.waves) : Lds<KB, VB, G, 2>::bytes(L.waves));
   // (the launch with dispatch events only when events were asked for: the plain launch is the one a
@@ -931,20 +1040,20 @@ hipError_t launch_z(const AttnArgs& a, int n_both, int n_splits, const WindowSet
   const bool timed = L.ev_start || L.ev_stop;
   const int appends = L.append ? 1 : 0;
   const QuantArgs q = L.append ? *L.append : QuantArgs{};
-  if (r <= 4) {
+  auto go = [&](auto kernel) {
     if (timed)
-      hipExtLaunchKernelGGL((attention_inner_kernel<KB, VB, G, 1, ZK, ZV>), grid, dim3(64u * L.waves), lds_bytes, L.stream, L.ev_start,
-                            L.ev_stop, 0, a, n_both, n_splits, win, win_tiles, base_t, rem_t, r, q, appends);
+      hipExtLaunchKernelGGL(kernel, grid, dim3(64u * L.waves), lds_bytes, L.stream, L.ev_start, L.ev_stop, 0, a, n_both, n_splits, win,
+                            win_tiles, base_t, rem_t, r, q, appends);
     else
-      hipLaunchKernelGGL((attention_inner_kernel<KB, VB, G, 1, ZK, ZV>), grid, dim3(64u * L.waves), lds_bytes, L.stream, a, n_both,
-                         n_splits, win, win_tiles, base_t, rem_t, r, q, appends);
+      hipLaunchKernelGGL(kernel, grid, dim3(64u * L.waves), lds_bytes, L.stream, a, n_both, n_splits, win, win_tiles, base_t, rem_t, r, q,
+                         appends);
+  };
+  if (a.join) {
+    if (r <= 4) go(attention_inner_kernel<KB, VB, G, 1, ZK, ZV, true>);
+    else go(attention_inner_kernel<KB, VB, G, 2, ZK, ZV, true>);
   } else {
-    if (timed)
-      hipExtLaunchKernelGGL((attention_inner_kernel<KB, VB, G, 2, ZK, ZV>), grid, dim3(64u * L.waves), lds_bytes, L.stream, L.ev_start,
-                            L.ev_stop, 0, a, n_both, n_splits, win, win_tiles, base_t, rem_t, r, q, appends);
-    else
-      hipLaunchKernelGGL((attention_inner_kernel<KB, VB, G, 2, ZK, ZV>), grid, dim3(64u * L.waves), lds_bytes, L.stream, a, n_both,
-                         n_splits, win, win_tiles, base_t, rem_t, r, q, appends);
+    if (r <= 4) go(attention_inner_kernel<KB, VB, G, 1, ZK, ZV, false>);
+    else go(attention_inner_kernel<KB, VB, G, 2, ZK, ZV, false>);
   }
   return hipGetLastError();
 }
@@ -1000,19 +1109,22 @@ bool attention_inner_supported(const AttnArgs& a) {
 
 std::atomic<int> g_inner_variant{0};
 
-bool attention_inner_joins(const AttnArgs& a) {
-  return a.pages.table || g_inner_variant.load(std::memory_order_relaxed) != 1 || !attention_inner_f4_supported(a);
+// Whether the fp8 x fp4 form was asked for and applies.
+static bool uses_f4(const AttnArgs& a) {
+  return !a.pages.table && g_inner_variant.load(std::memory_order_relaxed) == 1 && attention_inner_f4_supported(a);
 }
 
+bool attention_inner_joins(const AttnArgs& a) { return !uses_f4(a); }
+
 int attention_inner_waves_per_cu(const AttnArgs& a) {
-  if (!attention_inner_joins(a)) return attention_inner_f4_waves_per_cu(a);
+  if (uses_f4(a)) return attention_inner_f4_waves_per_cu(a);
   return 8;                                            // two per SIMD, by the kernel's register bound
 }
 
 hipError_t launch_attention_inner(const AttnArgs& a, long long n_both, int n_splits, const WindowSet& win, int waves,
                                   const QuantArgs* append, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
   if (!attention_inner_supported(a)) return hipErrorInvalidValue;
-  if (!attention_inner_joins(a)) return launch_attention_inner_f4(a, n_both, n_splits, win, stream, ev_start, ev_stop);
+  if (uses_f4(a)) return launch_attention_inner_f4(a, n_both, n_splits, win, stream, ev_start, ev_stop);
   const Launch L = {stream, ev_start, ev_stop, waves, append};
   if (a.pages.table)
     return a.group == 32 ? launch_inner_paged_g32(a, (int)n_both, n_splits, win, L) : launch_inner_paged_g64(a, (int)n_both, n_splits, win, L);

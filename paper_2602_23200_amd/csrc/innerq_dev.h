@@ -191,7 +191,7 @@ hipError_t launch_attention_merge(const AttnArgs& a, hipStream_t stream);
 struct WindowSet { long long na, b0, nb; int n_chunks; };
 bool attention_inner_supported(const AttnArgs& a);
 int attention_inner_waves_per_cu(const AttnArgs& a);   // resident wavefronts per compute unit
-bool attention_inner_joins(const AttnArgs& a);         // the launch writes the output itself (not on the fp8 x fp4 form)
+bool attention_inner_joins(const AttnArgs& a);         // the launch can write the output itself (not the fp8 x fp4 form)
 // append (may be null; only where the launch joins): the append of the step's token rides in the launch, but for a value
 // group that leaves its ring.
 // ev_start / ev_stop (may be null) take the begin and end timestamps of the kernel dispatch itself.

@@ -142,6 +142,7 @@ inline bool merge_is_shared(const AttnArgs& a) {
 // launch of any size behind one that fills the chip.  Arrivals counted in a word per sequence-head, the last one
 // joining, take a third memory round trip and contend (32 heads x 4k tokens, attention and append 16.7 us against 14.5).
 constexpr int kJoinWaves = 8;            // most wavefronts of a work-group that joins its own
+constexpr int kJoinGroups = 64;          // most work-groups of a sequence-head that join
 // bytes of one partial of one head: 128 channels, and level and sum for each half of them
 constexpr int kJoinBytes = (kHeadDim + 4) * 8;
 
@@ -231,51 +232,38 @@ __device__ __forceinline__ void join_few(const AttnArgs& a, long long head0, int
   }
 }
 
-// The same for one half head and any number of partials.
+// The same for one half head and more of them: the levels first (most work-groups are not the last one), then the
+// channels, 32 partials a round of loads.
 __device__ __forceinline__ void join_many(const AttnArgs& a, long long bhq, int half, int lane, int n, uint32_t tag) {
-  constexpr int H = kHeadDim / 2, NB = 8;
+  constexpr int H = kHeadDim / 2, NB = 32;
   join_word* words = join_words(a, bhq, half);
-  join_word* levels = words + (long long)a.n_partials * H;
+  join_word* levels = words + a.n_partials * H;
   const uint32_t mine = tag ^ (uint32_t)(lane << 1);
-  float top = -INFINITY, den = 0.f, num = 0.f;
-  for (int base = 0; base < n; base += 64) {
-    const int here = n - base < 64 ? n - base : 64;
-    const bool some = lane < here;
-    // levels and sums of partial base + lane; the first channels' words go out with them
-    join_word lv = 0, sv = 0, w[NB];
-    if (some) {
-      lv = look(levels + base + lane);
-      sv = look(levels + a.n_partials + base + lane);
+  // (n <= 64: a lane each)
+  const int at = lane < n ? lane : n - 1;
+  const join_word lv = look(levels + at), sv = look(levels + a.n_partials + at);
+  if (__builtin_amdgcn_ballot_w64(lane < n && (word_tag(lv) != mine || word_tag(sv) != mine)) != 0) return;
+  const float level = lane < n ? word_value(lv) : -INFINITY;
+  const float f = level_weight(level, window_wave_max(level));
+  const float den = window_wave_sum(f * (lane < n ? word_value(sv) : 0.f));
+  float num = 0.f;
+  for (int p0 = 0; p0 < n; p0 += NB) {
+    join_word w[NB];
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < NB; ++k) w[k] = look(words + (p0 + k < n ? p0 + k : n - 1) * H + lane);
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      bad |= word_tag(w[k]) != mine;
+      num = __builtin_fmaf(from_lane(f, p0 + k), word_value(w[k]), num);       // (weight 0 beyond the last)
     }
-#pragma unroll
-    for (int k = 0; k < NB; ++k) w[k] = look(words + (long long)(base + (k < here ? k : here - 1)) * H + lane);
-    if (__builtin_amdgcn_ballot_w64(some && (word_tag(lv) != mine || word_tag(sv) != mine)) != 0) return;
-    const float level = some ? word_value(lv) : -INFINITY;
-    const float up = fmaxf(top, window_wave_max(level));
-    const float f = level_weight(level, up), f0 = level_weight(top, up);
-    den = den * f0 + window_wave_sum(some ? f * word_value(sv) : 0.f);
-    num *= f0;
-    top = up;
-    for (int p0 = 0;;) {
-      bool bad = false;
-#pragma unroll
-      for (int k = 0; k < NB; ++k) {
-        bad |= word_tag(w[k]) != mine;
-        const float fk = from_lane(f, p0 + k < here ? p0 + k : here - 1);
-        num = __builtin_fmaf(p0 + k < here ? fk : 0.f, word_value(w[k]), num);
-      }
-      if (__builtin_amdgcn_ballot_w64(bad) != 0) return;
-      p0 += NB;
-      if (p0 >= here) break;
-#pragma unroll
-      for (int k = 0; k < NB; ++k) w[k] = look(words + (long long)(base + (p0 + k < here ? p0 + k : here - 1)) * H + lane);
-    }
+    if (__builtin_amdgcn_ballot_w64(bad) != 0) return;
   }
   store_output(a, bhq, half * H + lane, num / den);
-  for (int p = 0; p < n; ++p) clear_word(words + (long long)p * H + lane);
-  for (int p = lane; p < n; p += 64) {
-    clear_word(levels + p);
-    clear_word(levels + a.n_partials + p);
+  for (int p = 0; p < n; ++p) clear_word(words + p * H + lane);
+  if (lane < n) {
+    clear_word(levels + lane);
+    clear_word(levels + a.n_partials + lane);
   }
 }
 
