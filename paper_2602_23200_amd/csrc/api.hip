@@ -277,8 +277,7 @@ static QuantArgs quant_args(const innerq_config_t* cfg, const innerq_cache_t* ca
 }
 
 static int quantize_impl(const innerq_config_t* cfg, innerq_cache_t* cache, const void* k_new, const void* v_new,
-                         int64_t t_new, const float* k_inv_norm, long long from, long long to, void* hip_stream,
-                         const AttnArgs* merge = nullptr) {
+                         int64_t t_new, const float* k_inv_norm, long long from, long long to, void* hip_stream) {
   if (t_new > 0 && (!k_new || !v_new)) return INNERQ_E_NULL;
   if ((k_new && misaligned(k_new)) || (v_new && misaligned(v_new)) || (k_inv_norm && misaligned(k_inv_norm)))
     return INNERQ_E_ALIGN;
@@ -287,7 +286,7 @@ static int quantize_impl(const innerq_config_t* cfg, innerq_cache_t* cache, cons
   if (to > cfg->capacity_tokens) to = cfg->capacity_tokens;
   if (from > to) from = to;
   const QuantArgs a = quant_args(cfg, cache, k_new, v_new, t_new, k_inv_norm, from, to);
-  const hipError_t e = launch_quantize(a, static_cast<hipStream_t>(hip_stream), merge);
+  const hipError_t e = launch_quantize(a, static_cast<hipStream_t>(hip_stream));
   if (e != hipSuccess) return INNERQ_E_HIP;
   cache->n_tokens = n1;
   cache->store_ahead_tokens = to;
@@ -458,7 +457,7 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
       best_plain = plain_for(best_len);
       // A short context: one work-group per sequence-head, its wavefronts a window chunk or a tile or two each.
       const long long chunks32 = ceil_div(win_tokens, 32);
-      if (joins && n_tiles + chunks32 <= 12 && chunks32 <= 7) {
+      if (joins && n_tiles + chunks32 <= 12 && chunks32 <= 7 && BH <= compute_units()) {
         one_group = true;
         best_len = 32;
         best_plain = plain_for(32);
@@ -486,7 +485,7 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
       // two work-groups and for eight, and more beyond (another round of loads, and more that arrive at once).
       const long long cus = compute_units();
       const bool heavy = a.bits == 3 || a.v_bits == 3;
-      long long groups = 1, most_joining = r <= 4 ? 16 : 8;
+      long long groups = 1, most_joining = 8;
       if (one_group) {
         waves = n_splits < 8 ? n_splits : 8;
       } else if (few_tiles) {
@@ -494,12 +493,9 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
         // step, with the merge -> now; kv heads x tokens: 1 x 4k 11.3 -> 9.6, 8 x 4k 12.6 -> 10.2, 8 x 8k 13.6 -> 10.9,
         // 16 x 8k 13.1 -> 11.1, 32 x 8k 13.6 -> 12.5, 64 x 3k 13.2 -> 11.6).  More tiles want more wavefronts a head than
         // that: 8 x 16k 13.6 with the merge, 13.7 with eight work-groups, 8 x 32k 13.7 against 16.7 with sixteen.
-        // 3-bit codes are bound by issue: a wavefront a SIMD and a tile each (8 x 8 heads x 8k tokens 23.1 with the merge,
-        // 25.1 with two wavefronts a SIMD).
         const long long full = slots / BH, half = 4 * cus / BH;
-        long long most = full < 64 ? full : 64;
-        if (heavy && half < most) most = half;
-        long long want = (heavy ? n_tiles : n_tiles * 2 / 3) + n_win_chunks;
+        const long long most = full < 64 ? full : 64;
+        long long want = n_tiles * 2 / 3 + n_win_chunks;
         if (want > most) want = most;
         if (want <= n_win_chunks) want = n_win_chunks + 1;
         waves = 8;
@@ -509,14 +505,18 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
         if (waves > want) waves = (int)want;
         groups = ceil_div(want, waves);
         while (groups > 1 && groups * waves > most && (groups - 1) * waves > n_win_chunks) --groups;
-        if (n_tiles > 192 || (n_tiles > 96 && a.bits + a.v_bits > 4) || (n_tiles > 48 && heavy)) {
+        if (n_tiles > 192 || (n_tiles > 96 && a.bits + a.v_bits > 4)) {
           // ... but for a few heads (1 x 32k 15.4 with the merge, 13.8; 4 x 32k 14.7, 14.4)
           joins = BH <= 4 && n_tiles > 192 && n_tiles <= 512 && r <= 4 && a.bits + a.v_bits == 4;
           waves = 8;
           groups = ceil_div(n_tiles / 2, 8);
           most_joining = 32;
-        } else if (r > 4 && n_tiles < 48 && BH < 32) {
-          joins = false;                               // (eight heads' outputs are twice the join: 8 x 2k tokens 13.7, 14.3)
+        } else if (BH * groups > cus * (8 / waves) || (a.bits + a.v_bits > 4 && BH * groups * waves > 4 * cus) ||
+                   (groups > 1 && (heavy || r > 4))) {
+          // Not where a second round would begin, nor for wider codes two wavefronts a SIMD (96 heads x 1.3k at 4 bits 13.6 with
+          // the merge, 16.1).  Eight heads' outputs are twice the join (72 heads x 2k tokens 17.3, 19.8; 96 x 0.9k 16.8,
+          // 19.0); 3-bit tiles want a SIMD to themselves (10 heads x 0.9k 12.2, 14.8; 64 heads x 8k 23.1, 25.1).
+          joins = false;
         }
       } else {
         long long best = 0;
@@ -547,8 +547,9 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
         n_splits = (int)(groups * waves);
         a.n_partials = (int)groups;
       } else {
-        // (sharing the query tables is worth it for eight heads, 8 x 32k tokens 18.3 us -> 17.0, where all work-groups fit at once)
-        waves = r > 4 && BH * ceil_div(n_splits, 4) <= 2 * cus ? 4 : 1;
+        // (sharing the query tables is worth it for eight heads, 8 x 32k tokens 18.3 us -> 17.0, while every work-group has a
+        // compute unit to itself)
+        waves = r > 4 && BH * ceil_div(n_splits, 4) <= cus ? 4 : 1;
       }
     }
     // Token counts on the device: the wavefronts planned for sequences of the bound's length go to the sequences by
@@ -733,7 +734,7 @@ int innerq_decode_step(const innerq_config_t* cfg, innerq_cache_t* cache, const 
   // One launch where the fused inner kernel joins its own partials and no ring slot is shared by the token that enters and
   // one that leaves (nor the new token itself among them).
   const long long n = cache->n_tokens, to = n + 2 > cfg->capacity_tokens ? cfg->capacity_tokens : n + 2;
-  const QuantArgs append = quant_args(cfg, cache, k_new, v_new, 1, nullptr, n + 1, to);
+  const QuantArgs append = quant_args(cfg, cache, k_new, v_new, 1, nullptr, n + 1 < to ? n + 1 : to, to);
   const bool apart = cfg->w_recent < 2 || ring_slots_shared(append, append.job[0]) || ring_slots_shared(append, append.job[1]);
   AttnArgs merge;
   bool appended = false;
@@ -755,8 +756,10 @@ int innerq_decode_step(const innerq_config_t* cfg, innerq_cache_t* cache, const 
   }
   // second launch: the merge of this step together with the append of its token and the
   // quantisation the next step needs
-  return quantize_impl(cfg, cache, k_new, v_new, 1, nullptr, cache->n_tokens + 1, cache->n_tokens + 2, hip_stream,
-                       merge.join ? nullptr : &merge);
+  if (launch_quantize(append, static_cast<hipStream_t>(hip_stream), merge.join ? nullptr : &merge) != hipSuccess) return INNERQ_E_HIP;
+  cache->n_tokens = n + 1;
+  cache->store_ahead_tokens = to;
+  return INNERQ_OK;
 }
 
 }  // extern "C"

@@ -245,12 +245,17 @@ struct Lds {
 // zero-points of its two channels only if one of the two groups is flagged asymmetric (the flag is the
 // sign bit of the scale it already holds), at the start of the tile that needs them, so a 128-byte line
 // of zero-points (64 channels of one token-group) that holds no asymmetric group is never fetched.
+// (a launch that cannot append has no use for its arguments)
+template <bool JOIN> struct AppendArgsOf { typedef int type; };
+template <> struct AppendArgsOf<true> { typedef QuantArgs type; };
+template <bool JOIN> using AppendArgs = typename AppendArgsOf<JOIN>::type;
+
 // JOIN: the launch joins its own partial results and may append a step's token; else it leaves them to the merge, and the token
 // counts may live on the device.  (One kernel for both had worse code in the tile loop: 3-bit keys, 8 x 8 heads x 8k tokens,
 // attention call 19.7 us before, 21.1, 19.9 with the two apart.)
 template <int KB, int VB, int G, int NH4, bool ZK, int ZV, bool JOIN>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) attention_inner_kernel(AttnArgs a_in, int n_both_in, int n_splits, WindowSet win_in, int win_tiles_in, int base_t_in,
-                                                                                                 int rem_t_in, int r, QuantArgs append, int appends) {
+                                                                                                 int rem_t_in, int r, int waves, int groups_in, int appends, AppendArgs<JOIN> append) {
   constexpr int LBK = KB == 3 ? 2 : KB, LBV = VB == 3 ? 2 : VB;   // field width of the (low) plane
   constexpr bool HIK = KB == 3, HIV = VB == 3;                     // a plane of high bits follows it
   using FK = Fields<LBK>;
@@ -276,10 +281,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   // No division on the way to the first load: the grid is (splits, kv heads, batch), and the
   // host passes the quotients (heads per kv head; tiles per plain wavefront and their remainder).
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // (waves, groups: of a work-group / launch, as arguments: the built-in sizes are loads of their own)
   const int hk = (int)blockIdx.y;
   int b = (int)blockIdx.z, group = (int)blockIdx.x;      // sequence; work-group of its (b, hk)
-  int n_groups = (int)gridDim.x;
+  int n_groups = groups_in;
   // The host's plan holds for every sequence -- unless the token counts live on the device
   // (a.n_dev: one count per sequence, the tokens cached BEFORE this step; attention runs over them
   // plus the new token).  Then the launch shape and the window chunks are the
@@ -316,7 +321,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
       // sequences' wavefronts fit the launch: the smallest one below 8, at most an eighth above it beyond (every try is a
       // scan of the lengths, in front of the first load).  No fewer than four tiles (a wavefront pays its query set-up
       // once).
-      const int total = (int)gridDim.x, most = n_splits / waves, least = (n_chunks + waves) / waves;   // (at least one wavefront without a chunk)
+      const int total = groups_in, most = n_splits / waves, least = (n_chunks + waves) / waves;   // (at least one wavefront without a chunk)
       const int n_lane = clamped(lane < a.batch ? a_in.n_dev[lane] : 0);
       const Length x = length(n_lane);
       const int work = lane < a.batch ? x.tiles + n_chunks * x.cost : 0;
@@ -1003,7 +1008,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
 
   // ---- the append of the step's token: disjoint memory.  The wavefront of one work-group that is through first takes it,
   // while the others still have tiles.
-  if (JOIN && appends && group == n_groups - 1) {
+  if constexpr (JOIN) if (appends && group == n_groups - 1) {
     int at = 0;
     if (lane == 0) at = __hip_atomic_fetch_add(arrivals, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (__builtin_amdgcn_readfirstlane(at) == 0) append_keys_and_copies<G, KB>(append, bh, a.n_tokens - 1, lane);
@@ -1039,21 +1044,20 @@ hipError_t launch_z(const AttnArgs& a, int n_both, int n_splits, const WindowSet
   // stream capture is sure to record)
   const bool timed = L.ev_start || L.ev_stop;
   const int appends = L.append ? 1 : 0;
-  const QuantArgs q = L.append ? *L.append : QuantArgs{};
-  auto go = [&](auto kernel) {
+  auto go = [&](auto kernel, auto q) {
     if (timed)
       hipExtLaunchKernelGGL(kernel, grid, dim3(64u * L.waves), lds_bytes, L.stream, L.ev_start, L.ev_stop, 0, a, n_both, n_splits, win,
-                            win_tiles, base_t, rem_t, r, q, appends);
+                            win_tiles, base_t, rem_t, r, L.waves, (int)grid.x, appends, q);
     else
-      hipLaunchKernelGGL(kernel, grid, dim3(64u * L.waves), lds_bytes, L.stream, a, n_both, n_splits, win, win_tiles, base_t, rem_t, r, q,
-                         appends);
+      hipLaunchKernelGGL(kernel, grid, dim3(64u * L.waves), lds_bytes, L.stream, a, n_both, n_splits, win, win_tiles, base_t, rem_t, r,
+                         L.waves, (int)grid.x, appends, q);
   };
   if (a.join) {
-    if (r <= 4) go(attention_inner_kernel<KB, VB, G, 1, ZK, ZV, true>);
-    else go(attention_inner_kernel<KB, VB, G, 2, ZK, ZV, true>);
+    if (r <= 4) go(attention_inner_kernel<KB, VB, G, 1, ZK, ZV, true>, L.append ? *L.append : QuantArgs{});
+    else go(attention_inner_kernel<KB, VB, G, 2, ZK, ZV, true>, L.append ? *L.append : QuantArgs{});
   } else {
-    if (r <= 4) go(attention_inner_kernel<KB, VB, G, 1, ZK, ZV, false>);
-    else go(attention_inner_kernel<KB, VB, G, 2, ZK, ZV, false>);
+    if (r <= 4) go(attention_inner_kernel<KB, VB, G, 1, ZK, ZV, false>, 0);
+    else go(attention_inner_kernel<KB, VB, G, 2, ZK, ZV, false>, 0);
   }
   return hipGetLastError();
 }
