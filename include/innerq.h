@@ -17,9 +17,10 @@
  *     keep, process-wide and host-side only: the kernel choice set by
  *     innerq_select_inner_kernel, the one-shot per-thread request of
  *     innerq_profile_next_attention, remembered answers of occupancy / device-attribute
- *     queries (atomics; set once), and the device address of the static workspace of
+ *     queries (atomics; set once), a count of launches (every launch that joins its partial
+ *     results gets a tag of its own) and the device address of the static workspace of
  *     innerq_decode_attention_static.
- *   - The exception to "on error nothing has been launched": innerq_decode_step makes two
+ *   - The exception to "on error nothing has been launched": innerq_decode_step may make two
  *     launches, and INNERQ_E_HIP from the second one arrives after the first was enqueued
  *     (every argument check is done before the first).
  *   - Inputs are assumed finite; NaN/Inf in K, V or q give unspecified output.
@@ -308,13 +309,17 @@ int innerq_decode_attention_next(const innerq_config_t *cfg, const innerq_cache_
 int innerq_append_deferred(const innerq_config_t *cfg, innerq_cache_t *cache, const void *k_new,
                            const void *v_new, void *hip_stream);
 
-/* One decode step in two launches instead of three: innerq_decode_attention_next followed by
- * innerq_append_deferred on the same stream, with the log-sum-exp merge of the attention call
- * and the append sharing one launch (they touch disjoint memory).  Same preconditions, results
- * and errors as those two calls (INNERQ_E_ARG unless store_ahead_tokens == n_tokens + 1); on
- * success n_tokens += 1 and the store already holds what the next step evicts.  Every argument is
- * checked before the first launch; only INNERQ_E_HIP of the second launch can follow an enqueued
- * first one. */
+/* One decode step in one or two launches instead of three: innerq_decode_attention_next followed by
+ * innerq_append_deferred on the same stream (they touch disjoint memory).  Where the fused inner kernel
+ * joins its partial results itself, the append rides in the same launch, but for the value group that
+ * leaves its ring in one step of G; else the log-sum-exp merge and the append share the second launch.
+ * Same preconditions and errors as those two calls (INNERQ_E_ARG unless store_ahead_tokens ==
+ * n_tokens + 1), the same cache bit for bit, the same output to the rounding of its sums, whose order
+ * follows from how the launch is cut; on success n_tokens += 1 and the store already holds what the next
+ * step evicts.  Every argument is checked before the first launch; only INNERQ_E_HIP of the second launch
+ * can follow an enqueued first one.
+ *   workspace  its content may be anything before a call; two calls that may run at the same time need one
+ *              each. */
 int innerq_decode_step(const innerq_config_t *cfg, innerq_cache_t *cache, const void *k_new,
                        const void *v_new, const void *q_fp16, const float *q_scale, void *out,
                        int out_is_fp32, void *workspace, size_t workspace_bytes, void *hip_stream);

@@ -288,7 +288,7 @@ def innerq_decode_attention_next(cache: Cache, k_new, v_new, q, workspace, out=N
 
 
 def innerq_decode_step(cache: Cache, k_new, v_new, q, workspace, out=None, q_scale=None, stream=None):
-    """innerq_decode_attention_next + innerq_append_deferred in two launches (merge and append share one)."""
+    """innerq_decode_attention_next + innerq_append_deferred in one launch, or in two (merge and append share the second)."""
     import torch
     for t in (k_new, v_new, q):
         assert t.dtype == torch.float16 and t.is_contiguous() and t.is_cuda
