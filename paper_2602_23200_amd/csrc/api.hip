@@ -7,38 +7,13 @@
 #include <mutex>
 
 #include "innerq_dev.h"
-#include "merge.h"
+#include "plan.h"
 
 using namespace innerq;
 
 namespace {
 
 inline bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
-
-inline long long ceil_div(long long a, long long b) { return (a + b - 1) / b; }
-
-// Most window chunks a launch may use (chunks of kWindowChunkMin tokens); bounds the workspace.
-inline int window_chunk_cap(const innerq_config_t& c) {
-  return (int)ceil_div((long long)c.w_sink + c.w_recent + 2LL * c.group, kWindowChunkMin) + 1;
-}
-// Most token splits a launch may use for the quantised range; bounds the workspace.  Never below
-// the window chunk count plus one: the fused inner kernel needs one wavefront beyond those that
-// carry a window chunk.
-inline int split_cap(const innerq_config_t& c) {
-  long long s = ceil_div(4096, (long long)c.batch * c.n_kv_heads);
-  if (s < 4) s = 4;
-  if (s > 512) s = 512;
-  if (s < window_chunk_cap(c) + 1) s = window_chunk_cap(c) + 1;
-  return (int)s;
-}
-
-// Bytes at the start of the workspace for one int per sequence: the fused kernel of a ragged step leaves
-// the sequences' token counts there for the append that follows it -- and, for batches that share the launch's
-// wavefronts by length, behind them how many partial results each sequence has (these fit the first 256 bytes).
-constexpr int kSharedBatchMost = 32;
-constexpr int kRaggedWaves = 1;          // wavefronts of a work-group there (20 heads x 25k tokens 21.9 us, with two 24.3)
-inline size_t seq_bytes(const innerq_config_t& c) { return (((size_t)c.batch * sizeof(int) + 255) / 256) * 256; }
-static_assert(2 * kSharedBatchMost * sizeof(int) <= 256, "both counts of a sequence in the first 256 bytes");
 
 int check_config(const innerq_config_t* c) {
   if (!c) return INNERQ_E_NULL;
@@ -404,181 +379,32 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
     const long long most = (long long)c.w_sink + c.w_recent + c.group;
     win_tokens = N < most ? N : most;
   }
-  const int r = c.n_q_heads / c.n_kv_heads;
-  int n_splits = 0, win_chunk_len = kWindowChunk, waves = 1;
-  // which fused kernel serves this cache (0 = none: the fp32 kernel)
-  const int fused_kind =
-      attention_inner_supported(a) ? 1 : attention_fp16_supported(a) ? 2 : attention_outer_supported(a) ? 3 : 0;
-  const bool fused = fused_kind != 0;
-  bool joins = fused_kind == 1 && n_both > 0 && !n_dev && attention_inner_joins(a);
-  const long long BH = (long long)c.batch * c.n_kv_heads;
-  const size_t heads = (size_t)c.batch * c.n_q_heads;
-  // Partial results a head may have where the launch joins them itself (they are larger there: kJoinBytes each).
-  const long long most_groups = (long long)(split_cap(c) + window_chunk_cap(c)) * (kHeadDim + 2) * (long long)sizeof(float) / kJoinBytes;
-  if (n_both > 0 && fused) {
-    // one wavefront per split; every wavefront of the launch resident at once, no tail round
-    // (the window wavefronts of the same launch take their share of the slots)
-    const long long slots = (long long)compute_units() *
-                            (fused_kind == 1   ? attention_inner_waves_per_cu(a)
-                             : fused_kind == 2 ? attention_fp16_waves_per_cu(a)
-                                               : attention_outer_waves_per_cu(a));
-    const long long n_tiles = ceil_div(n_both, 64);
-    long long per_head = slots / ((long long)c.batch * c.n_kv_heads);
-    // Short contexts: with fewer than about four tiles per wavefront, a launch of half as many
-    // wavefronts (one per SIMD instead of two) is the faster one -- every wavefront pays its query
-    // set-up once, and the launch itself costs time per wavefront (measured on the 32-head 4k-token
-    // configuration: 17.8 -> 14.3 us per step; the two meet at four tiles per wavefront).
-    const bool few_tiles = n_tiles < 4 * per_head;
-    if (fused_kind == 1 && few_tiles && per_head >= 8) per_head /= 2;
-    // Window chunk length and the number of plain wavefronts.
-    bool one_group = false;
-    long long best_len = kWindowChunk, best_cost = -1, best_plain = 1;
-    auto plain_for = [&](long long len) {
-      const long long nw = ceil_div(win_tokens, len);
-      long long plain = per_head - nw;
-      if (plain > n_tiles) plain = n_tiles;
-      // the workspace holds split_cap + window_chunk_cap partials; the inner kernel's wavefronts
-      // that carry a window chunk count as splits too
-      const long long most = fused_kind == 1 ? split_cap(c) - nw : split_cap(c);
-      if (plain > most) plain = most;
-      return plain < 1 ? 1 : plain;
-    };
-    if (fused_kind == 1) {
-      // Inner kernel, as measured (a window chunk costs its wavefront about as much whatever its
-      // length, so short chunks pay only where wavefront slots go begging): 16 tokens while the
-      // whole launch fills at most a quarter of the SIMDs (4-head 512-token configuration: 10.4 us
-      // per step against 10.8 at 64); 32 tokens for short contexts on a busy chip (8 x 8 heads at 2k
-      // tokens: 12.5 us against 13.0 at 64 and 14.1 at 16); 64 tokens from about 3k tokens on
-      // (32 heads at 4k tokens: 13.4 us against 14.1 at 32 and 15.0 at 16) and wherever the slots
-      // are all needed for tiles.
-      const long long simds = (long long)compute_units() * 4;
-      const long long waves16 = (long long)c.batch * c.n_kv_heads * (plain_for(kWindowChunkMin) + ceil_div(win_tokens, kWindowChunkMin));
-      best_len = waves16 * 4 <= simds ? kWindowChunkMin : (n_tiles < 48 ? 32 : kWindowChunk);
-      best_plain = plain_for(best_len);
-      // A short context: one work-group per sequence-head, its wavefronts a window chunk or a tile or two each.
-      const long long chunks32 = ceil_div(win_tokens, 32);
-      if (joins && n_tiles + chunks32 <= 12 && chunks32 <= 7 && BH <= compute_units()) {
-        one_group = true;
-        best_len = 32;
-        best_plain = plain_for(32);
-      }
-    } else {
-      // Comparison kernels: 64 tokens when the wavefront slots are all needed for tiles (long
-      // contexts: a chunk then hides behind the tile work), shorter when slots are to spare and the
-      // window chunk would be the longest wavefront of the launch.  Costs in units of one tile of
-      // one wavefront: a chunk of L tokens about 4 + 14 L / 64.
-      for (long long len = kWindowChunk; len >= kWindowChunkMin; len /= 2) {
-        const long long nw = ceil_div(win_tokens, len);
-        const long long plain = plain_for(len);
-        const long long tile_cost = ceil_div(n_tiles, plain) * 8, win_cost = nw ? 32 + 14 * len / 8 : 0;   // x 8
-        const long long cost = tile_cost > win_cost ? tile_cost : win_cost;
-        if (best_cost < 0 || cost < best_cost) { best_cost = cost; best_len = len; best_plain = plain; }
-      }
-    }
-    win_chunk_len = (int)best_len;
-    const long long n_win_chunks = ceil_div(win_tokens, best_len);
-    // the inner kernel's first wavefronts each carry a window chunk besides their tiles; the
-    // comparison kernels run the window chunks as extra wavefronts of the same launch
-    n_splits = (int)(fused_kind == 1 ? best_plain + n_win_chunks : best_plain);
-    if (joins) {
-      // Wavefronts per work-group and work-groups per sequence-head, all resident at once.  The join costs the same for
-      // two work-groups and for eight, and more beyond (another round of loads, and more that arrive at once).
-      const long long cus = compute_units();
-      const bool heavy = a.bits == 3 || a.v_bits == 3;
-      long long groups = 1, most_joining = 8;
-      if (one_group) {
-        waves = n_splits < 8 ? n_splits : 8;
-      } else if (few_tiles) {
-        // A chip that is not full, up to 192 tiles: eight work-groups at most, wavefronts with one to three tiles each (us per
-        // step, with the merge -> now; kv heads x tokens: 1 x 4k 11.3 -> 9.6, 8 x 4k 12.6 -> 10.2, 8 x 8k 13.6 -> 10.9,
-        // 16 x 8k 13.1 -> 11.1, 32 x 8k 13.6 -> 12.5, 64 x 3k 13.2 -> 11.6).  More tiles want more wavefronts a head than
-        // that: 8 x 16k 13.6 with the merge, 13.7 with eight work-groups, 8 x 32k 13.7 against 16.7 with sixteen.
-        const long long full = slots / BH, half = 4 * cus / BH;
-        const long long most = full < 64 ? full : 64;
-        long long want = n_tiles * 2 / 3 + n_win_chunks;
-        if (want > most) want = most;
-        if (want <= n_win_chunks) want = n_win_chunks + 1;
-        waves = 8;
-        // (a wavefront a SIMD where that is two and a half tiles each at most: 32 x 4k tokens at 4 bits 11.4, with more 12.2; 8k 13.8, 12.5)
-        if (half <= 32 && n_win_chunks < half && 2 * n_tiles <= 5 * half) want = want < half ? want : half;
-        if (want <= 32 && (BH * want <= 4 * cus || want / 4 * 4 > want / 8 * 8)) waves = 4;
-        if (waves > want) waves = (int)want;
-        groups = ceil_div(want, waves);
-        while (groups > 1 && groups * waves > most && (groups - 1) * waves > n_win_chunks) --groups;
-        if (n_tiles > 192 || (n_tiles > 96 && a.bits + a.v_bits > 4)) {
-          // ... but for a few heads (1 x 32k 15.4 with the merge, 13.8; 4 x 32k 14.7, 14.4)
-          joins = BH <= 4 && n_tiles > 192 && n_tiles <= 512 && r <= 4 && a.bits + a.v_bits == 4;
-          waves = 8;
-          groups = ceil_div(n_tiles / 2, 8);
-          most_joining = 32;
-        } else if (BH * groups > cus * (8 / waves) || (a.bits + a.v_bits > 4 && BH * groups * waves > 4 * cus) ||
-                   (groups > 1 && (heavy || r > 4))) {
-          // Not where a second round would begin, nor for wider codes two wavefronts a SIMD (96 heads x 1.3k at 4 bits 13.6 with
-          // the merge, 16.1).  Eight heads' outputs are twice the join (72 heads x 2k tokens 17.3, 19.8; 96 x 0.9k 16.8,
-          // 19.0); 3-bit tiles want a SIMD to themselves (10 heads x 0.9k 12.2, 14.8; 64 heads x 8k 23.1, 25.1).
-          joins = false;
-        }
-      } else {
-        long long best = 0;
-        for (int w = 8; w >= 4; w /= 2) {                // (of fewer, every one of the launch would take part in the join)
-          const long long fit = cus * (8 / w) / BH, all = ceil_div(n_splits, w), g = fit < all ? fit : all;
-          if (g * w <= n_win_chunks) continue;
-          const long long got = g * w < n_splits ? g * w : n_splits;
-          if (got * 10 > best * 11) { best = got; waves = w; groups = g; }
-        }
-        if (best == 0) {
-          // more wavefronts than fit at once: in rounds, where they are many (1024 heads x 4k tokens 85.3 -> 75.2; 320 heads x 3k
-          // tokens 35.8 and 52.2) and the window chunks not most of it (1024 x 1k 39.8 and 50.1)
-          waves = n_splits < 8 ? n_splits : 8;
-          groups = ceil_div(n_splits, waves);
-          if (n_tiles < 32 || BH < 4 * cus) joins = false;
-          best = n_splits;
-        }
-        // Work-groups of several wavefronts may leave slots empty: not where that is two fifths of a tile more for each of them (208
-        // heads, eight wavefronts a head instead of nine: 16k tokens, 3.4 tiles more, 51.9 us -> 59.3; 112 heads, 16 instead of
-        // 18: 6.5k tokens, 0.7 more, 18.5 -> 19.5).
-        if (10 * n_tiles * (n_splits - best) > 4 * best * n_splits) joins = false;
-      }
-      if (groups > most_joining || groups > most_groups) joins = false;
-      // An attention call by itself gains less (there is no append to save) and keeps the merge on a chip that is not full
-      // (4 heads x 9k tokens 11.7 us, joined 12.5) and with work-groups of four (160 heads x 3.6k tokens 18.8, 20.2).
-      if (groups > 1 && (few_tiles || waves < 8) && !append) joins = false;
-      if (joins) {
-        n_splits = (int)(groups * waves);
-        a.n_partials = (int)groups;
-      } else {
-        // (sharing the query tables is worth it for eight heads, 8 x 32k tokens 18.3 us -> 17.0, while every work-group has a
-        // compute unit to itself)
-        waves = r > 4 && BH * ceil_div(n_splits, 4) <= cus ? 4 : 1;
-      }
-    }
-    // Token counts on the device: the wavefronts planned for sequences of the bound's length go to the sequences by
-    // their lengths, as many to one as it has partial slots, where there is something to gain: 16 sequences of 1k to
-    // 16k tokens, 35.3 us per step with the same number each, 29.9 shared.  The sharing itself costs 1 to 1.7 us in
-    // front of the first load, and packs the wavefronts of short sequences onto fewer compute units, so it wants
-    // several tiles per wavefront (8 sequences x 8 heads, bound 2000 tokens: 13.8 against 14.9 shared; 8000 tokens,
-    // lengths spread 16-fold: 18.2 against 15.9) and several wavefronts per head (16 x 32 heads, bound 4000: 28.8 against 38.2).
-    const long long shared = (long long)n_splits * c.batch / kRaggedWaves, least = ceil_div(n_win_chunks + 1, kRaggedWaves);
-    if (n_dev && c.batch > 1 && c.batch <= kSharedBatchMost && least * c.batch <= shared && n_tiles >= 6 * per_head && per_head >= 10) {
-      waves = kRaggedWaves;
-      a.shared_groups = (int)shared;
-      a.n_valid = static_cast<int*>(workspace) + c.batch;
-      n_splits = split_cap(c) / waves * waves;
-    }
-  } else if (n_both > 0) {
-    const long long blocks_per_split = (long long)c.batch * c.n_kv_heads * ceil_div(r, kHeadTile);
-    long long s = ceil_div(2048, blocks_per_split);
-    const long long by_len = ceil_div(n_both, 128);
-    if (s > by_len) s = by_len;
-    if (s > split_cap(c)) s = split_cap(c);
-    if (s < 1) s = 1;
-    n_splits = (int)s;
-  }
-  const int n_win = (int)ceil_div(win_tokens, win_chunk_len);
+  // which fused kernel serves this cache
+  const int fused_kind = attention_inner_supported(a)   ? kInnerKernel
+                         : attention_fp16_supported(a)  ? kFp16Kernel
+                         : attention_outer_supported(a) ? kOuterKernel
+                                                        : kFp32Kernel;
+  const bool fused = fused_kind != kFp32Kernel;
+  PlanInput in;
+  in.fused_kind = fused_kind;
+  in.compute_units = compute_units();
+  in.waves_per_cu = fused_kind == kInnerKernel   ? attention_inner_waves_per_cu(a)
+                    : fused_kind == kFp16Kernel  ? attention_fp16_waves_per_cu(a)
+                    : fused_kind == kOuterKernel ? attention_outer_waves_per_cu(a)
+                                                 : 1;
+  in.may_join = fused_kind == kInnerKernel && attention_inner_joins(a);
+  in.appends = append != nullptr;
+  in.ragged = n_dev != nullptr;
+  in.n_both = n_both; in.win_tokens = win_tokens;
+  const LaunchPlan plan = plan_attention(c, in);
+  const int n_splits = plan.n_splits, n_win = plan.n_win;
+  const bool joins = plan.joins;
   if (n_win > window_chunk_cap(c)) return INNERQ_E_ARG;
-  if (!joins) a.n_partials = n_splits + n_win;
-  const size_t partial_bytes = joins ? (size_t)kJoinBytes : (kHeadDim + 2) * sizeof(float);
-  if (seq_bytes(c) + heads * (size_t)a.n_partials * partial_bytes + 64 > workspace_bytes) return INNERQ_E_WORKSPACE;
+  if (plan.workspace_bytes > workspace_bytes) return INNERQ_E_WORKSPACE;
+  a.n_partials = plan.n_partials;
+  a.shared_groups = plan.shared_groups;
+  if (plan.shared_groups > 0) a.n_valid = static_cast<int*>(workspace) + c.batch;
+  const size_t heads = (size_t)c.batch * c.n_q_heads;
   if (joins) {
     a.join = reinterpret_cast<unsigned long long*>(static_cast<char*>(workspace) + seq_bytes(c));
     a.join_tag = next_join_tag();
@@ -593,8 +419,8 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
     if (fused) {
       // the events take the timestamps of the dispatch itself
       const WindowSet win = {n_sink, win_b0, win_b1 - win_b0, n_win};
-      e = fused_kind == 1   ? launch_attention_inner(a, n_both, n_splits, win, waves, joins ? append : nullptr, stream, prof_start, prof_stop)
-          : fused_kind == 2 ? launch_attention_fp16(a, n_both, n_splits, win, stream, prof_start, prof_stop)
+      e = fused_kind == kInnerKernel ? launch_attention_inner(a, n_both, n_splits, win, plan.waves, joins ? append : nullptr, stream, prof_start, prof_stop)
+          : fused_kind == kFp16Kernel ? launch_attention_fp16(a, n_both, n_splits, win, stream, prof_start, prof_stop)
                             : launch_attention_outer(a, n_both, n_splits, win, stream, prof_start, prof_stop);
     } else {
       if (prof_start) (void)hipEventRecord(prof_start, stream);

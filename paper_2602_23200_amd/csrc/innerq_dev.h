@@ -9,14 +9,10 @@
 
 #include <atomic>
 
-#include "../../include/innerq.h"
+#include "plan.h"
 
 namespace innerq {
 
-constexpr int kHeadDim = 128;          // the only head_dim built
-constexpr int kWindowChunk = 64;       // most window tokens per wavefront / work-group chunk
-constexpr int kWindowChunkMin = 16;    // fewest (short contexts, slots to spare)
-constexpr int kHeadTile = 4;           // query heads served by one work-group pass
 constexpr int kPageTokens = 64;        // tokens per page of a paged store (= one tile of the fused kernels)
 
 // A paged store (no counterpart in the paper, which leaves memory management to future work): the six

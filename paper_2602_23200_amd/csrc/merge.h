@@ -141,11 +141,6 @@ inline bool merge_is_shared(const AttnArgs& a) {
 // states and publishing, 0.3 until the stores are performed, 1.3 for the words, 0.5 for the sums -- against 4.7 us for a
 // launch of any size behind one that fills the chip.  Arrivals counted in a word per sequence-head, the last one
 // joining, take a third memory round trip and contend (32 heads x 4k tokens, attention and append 16.7 us against 14.5).
-constexpr int kJoinWaves = 8;            // most wavefronts of a work-group that joins its own
-constexpr int kJoinGroups = 64;          // most work-groups of a sequence-head that join
-// bytes of one partial of one head: 128 channels, and level and sum for each half of them
-constexpr int kJoinBytes = (kHeadDim + 4) * 8;
-
 typedef unsigned long long join_word;
 __device__ __forceinline__ void publish(join_word* p, float x, uint32_t tag) {
   __hip_atomic_store(p, (join_word)tag << 32 | __float_as_uint(x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
