@@ -201,6 +201,8 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
         if (10 * n_tiles * (n_splits - best) > 4 * best * n_splits) joins = false;
       }
       if (groups > most_joining || groups > most_groups) joins = false;
+      // (a wide recent window may have more chunks than a branch above has wavefronts: one must be left without)
+      if (groups * waves <= n_win_chunks) joins = false;
       // An attention call by itself gains less (there is no append to save) and keeps the merge on a chip that is not full
       // (4 heads x 9k tokens 11.7 us, joined 12.5) and with work-groups of four (160 heads x 3.6k tokens 18.8, 20.2).
       if (groups > 1 && (few_tiles || waves < 8) && !in.appends) joins = false;

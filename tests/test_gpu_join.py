@@ -49,6 +49,24 @@ def test_steps(batch, q_heads, kv_heads, tokens, recent, group, bits):
     assert_cache_equal(g, want, o, bsel=slice(0, 1) if one else slice(None))
 
 
+@pytest.mark.parametrize("batch,q_heads,kv_heads,recent,quantised", [(1, 4, 1, 8192, 12416), (2, 2, 1, 7168, 12800), (1, 4, 4, 6144, 12352)])
+def test_windows_of_more_chunks_than_wavefronts_joined(batch, q_heads, kv_heads, recent, quantised):
+    """A recent window as long as the quantised range: the plan has to keep a wavefront without a window chunk."""
+    import torch
+    from paper_2602_23200_amd import binding as iq
+    n = 4 + recent + quantised
+    w = wl.Workload("w", batch, q_heads, kv_heads, 128, n + 1, 2, 32, 4, recent, seed=recent)
+    o = oracle_config(w)
+    K, V = wl.kv_full(w)
+    q = wl.query(w)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    g = iq.allocate_cache(gpu_config(o))
+    iq.innerq_quantize_append(g, dev(K[:, :, :n]), dev(V[:, :, :n]))
+    iq.innerq_quantize_ahead(g)
+    out = iq.innerq_decode_step(g, dev(K[:, :, n:]), dev(V[:, :, n:]), dev(q), iq.allocate_workspace(g.cfg)).cpu().numpy()
+    assert max_rel_err(out, orc.decode_attention(o, orc.cache_init_prefill(o, K, V), q)) <= TOL
+
+
 def test_replays_from_a_graph_start_from_nothing():
     """A recorded launch keeps its tag: what a replay publishes must not be taken for the next one's."""
     import torch
