@@ -363,6 +363,7 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
   a.join = nullptr;
   a.join_tag = 0;
   a.pages = pages_of(c, *cache);
+  a.f4 = attention_inner_wants_f4(a);
 
   // Tokens [w_sink, w_sink + n_both) are in the quantised store for both K and V: the split-K
   // range.  Everything else (sink window, recent windows, and the < G tokens quantised in only
@@ -392,7 +393,7 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
                     : fused_kind == kFp16Kernel  ? attention_fp16_waves_per_cu(a)
                     : fused_kind == kOuterKernel ? attention_outer_waves_per_cu(a)
                                                  : 1;
-  in.may_join = fused_kind == kInnerKernel && attention_inner_joins(a);
+  in.may_join = fused_kind == kInnerKernel && !a.f4;
   in.appends = append != nullptr;
   in.ragged = n_dev != nullptr;
   in.n_both = n_both; in.win_tokens = win_tokens;

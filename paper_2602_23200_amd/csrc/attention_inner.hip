@@ -1113,22 +1113,22 @@ bool attention_inner_supported(const AttnArgs& a) {
 
 std::atomic<int> g_inner_variant{0};
 
-// Whether the fp8 x fp4 form was asked for and applies.
-static bool uses_f4(const AttnArgs& a) {
+bool attention_inner_wants_f4(const AttnArgs& a) {
   return !a.pages.table && g_inner_variant.load(std::memory_order_relaxed) == 1 && attention_inner_f4_supported(a);
 }
 
-bool attention_inner_joins(const AttnArgs& a) { return !uses_f4(a); }
-
 int attention_inner_waves_per_cu(const AttnArgs& a) {
-  if (uses_f4(a)) return attention_inner_f4_waves_per_cu(a);
+  if (a.f4) return attention_inner_f4_waves_per_cu(a);
   return 8;                                            // two per SIMD, by the kernel's register bound
 }
 
 hipError_t launch_attention_inner(const AttnArgs& a, long long n_both, int n_splits, const WindowSet& win, int waves,
                                   const QuantArgs* append, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
   if (!attention_inner_supported(a)) return hipErrorInvalidValue;
-  if (uses_f4(a)) return launch_attention_inner_f4(a, n_both, n_splits, win, stream, ev_start, ev_stop);
+  if (a.f4) {
+    if (a.join || append) return hipErrorInvalidValue;
+    return launch_attention_inner_f4(a, n_both, n_splits, win, stream, ev_start, ev_stop);
+  }
   const Launch L = {stream, ev_start, ev_stop, waves, append};
   if (a.pages.table)
     return a.group == 32 ? launch_inner_paged_g32(a, (int)n_both, n_splits, win, L) : launch_inner_paged_g64(a, (int)n_both, n_splits, win, L);

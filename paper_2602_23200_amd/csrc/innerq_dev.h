@@ -168,6 +168,7 @@ struct AttnArgs {
   // (odd); null: the partials are joined by a later launch
   unsigned long long* join;
   uint32_t join_tag;
+  int f4;                   // this call runs the fp8 x fp4 form (decided once a call: the plan and the launch must agree)
   PageMap pages;
 };
 
@@ -187,7 +188,7 @@ hipError_t launch_attention_merge(const AttnArgs& a, hipStream_t stream);
 struct WindowSet { long long na, b0, nb; int n_chunks; };
 bool attention_inner_supported(const AttnArgs& a);
 int attention_inner_waves_per_cu(const AttnArgs& a);   // resident wavefronts per compute unit
-bool attention_inner_joins(const AttnArgs& a);         // the launch can write the output itself (not the fp8 x fp4 form)
+bool attention_inner_wants_f4(const AttnArgs& a);      // the fp8 x fp4 form was asked for and applies (for AttnArgs::f4)
 // append (may be null; only where the launch joins): the append of the step's token rides in the launch, but for a value
 // group that leaves its ring.
 // ev_start / ev_stop (may be null) take the begin and end timestamps of the kernel dispatch itself.
@@ -204,7 +205,7 @@ hipError_t launch_inner_paged_g64(const AttnArgs& a, int n_both, int n_splits, c
 // The same partial results for 2-bit codes from the block-scaled fp8 x fp4 matrix instruction
 // (128-token tiles).  Parity-green but slower than the fp16 matrix form (see the file header), so it runs
 // only on request: launch_attention_inner and attention_inner_waves_per_cu route to it when
-// g_inner_variant == 1 and it applies.
+// AttnArgs::f4 is set (g_inner_variant == 1 when the call began, and it applies).
 bool attention_inner_f4_supported(const AttnArgs& a);
 int attention_inner_f4_waves_per_cu(const AttnArgs& a);
 hipError_t launch_attention_inner_f4(const AttnArgs& a, long long n_both, int n_splits, const WindowSet& win,

@@ -67,6 +67,45 @@ def test_windows_of_more_chunks_than_wavefronts_joined(batch, q_heads, kv_heads,
     assert max_rel_err(out, orc.decode_attention(o, orc.cache_init_prefill(o, K, V), q)) <= TOL
 
 
+def test_kernel_choice_changed_by_another_thread():
+    """innerq_select_inner_kernel from a second thread: every step is planned for the kernel that runs it."""
+    import threading
+
+    import torch
+    from paper_2602_23200_amd import binding as iq
+    w = wl.Workload("t", 1, 4, 1, 128, 1500, 2, 32, 4, 128, seed=9)              # joined by the default kernel, not by the other
+    o = oracle_config(w)
+    K, V = wl.kv_full(w)
+    q = wl.query(w)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    n = w.n_tokens - 1
+    g = iq.allocate_cache(gpu_config(o))
+    iq.innerq_quantize_append(g, dev(K[:, :, :n]), dev(V[:, :, :n]))
+    iq.innerq_quantize_ahead(g)
+    k1, v1, qd = dev(K[:, :, n:]), dev(V[:, :, n:]), dev(q)
+    ws, outs = iq.allocate_workspace(g.cfg), torch.empty(2000, 1, 4, 128, device="cuda")
+    done = threading.Event()
+
+    def change():
+        while not done.is_set():
+            iq.innerq_select_inner_kernel(1)
+            iq.innerq_select_inner_kernel(0)
+
+    other = threading.Thread(target=change)
+    outs.fill_(float("nan"))
+    other.start()
+    try:
+        for i in range(outs.shape[0]):
+            g.c.n_tokens, g.c.store_ahead_tokens = n, n + 1
+            iq.innerq_decode_step(g, k1, v1, qd, ws, out=outs[i])
+    finally:
+        done.set()
+        other.join()
+        iq.innerq_select_inner_kernel(0)
+    want = orc.decode_attention(o, orc.cache_init_prefill(o, K, V), q)
+    assert max_rel_err(outs.cpu().numpy(), np.broadcast_to(want, outs.shape)) <= TOL
+
+
 def test_replays_from_a_graph_start_from_nothing():
     """A recorded launch keeps its tag: what a replay publishes must not be taken for the next one's."""
     import torch
