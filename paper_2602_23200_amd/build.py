@@ -22,11 +22,16 @@ SOURCES = {
     "stream_probe.hip": [],
     "attention_fp16.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
     "attention_outer.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
-    # MFMA results straight into VGPRs (with no NaN canonicalisation around fmax above; these also quantise, where NaN counts)
-    "attention_inner.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-    "attention_inner_g64.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-    "attention_inner_paged.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
-    "attention_inner_paged_g64.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    # no NaN canonicalisation around fmax; MFMA results straight into VGPRs
+    "attention_inner.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "attention_inner_g64.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "attention_inner_paged.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "attention_inner_paged_g64.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
+    # (these also quantise, where NaN counts)
+    "attention_join.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "attention_join_g64.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "attention_join_paged.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "attention_join_paged_g64.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "attention_inner_f4.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 

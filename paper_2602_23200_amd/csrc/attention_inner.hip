@@ -42,22 +42,24 @@
 //     launch for merge and append behind this one takes 3.4 us after a short kernel and 4.7 after a long one, whatever it
 //     does.  Per step, before -> now: 1 head x 512 tokens 12.2 us -> 9.4, 32 heads x 4k 12.9 -> 11.6, 8 x 8 x 32k
 //     40.3 -> 38.3, 32 x 8 x 8k 42.0 -> 39.6, 4 x 8 x 128k 72.2 -> 69.1, 3-bit 8 x 8 x 32k 56.9 -> 54.8.
-//   * paged store: this file is compiled for both stores (and, to build in parallel, for both group sizes).
-//     attention_inner_paged*.hip include it with INNERQ_PAGED_STORE set and get the kernels that look every tile up in
-//     the page table (a page is one 64-token tile); the builds for the contiguous store carry no trace of that.
+//   * paged store: this file is compiled for both stores, for launches that join and for those that do not (and, to build in
+//     parallel, for both group sizes).  attention_inner_paged*.hip include it with INNERQ_PAGED_STORE set and get the kernels
+//     that look every tile up in the page table (a page is one 64-token tile); the builds for the contiguous store carry no
+//     trace of that.  attention_join*.hip get the kernels that join and append, compiled with NaN honoured, as the quantiser
+//     wants it; the others need no NaN canonicalisation around their maxima.
 #include "innerq_dev.h"
-#define INNERQ_CONTRACTED
-#include "quantize_rows.h"
-#include "window_pass.h"
-#include "merge.h"
-
-#ifndef INNERQ_PAGED_STORE
-#define INNERQ_PAGED_STORE 0
-#endif
 #ifndef INNERQ_INNER_LAUNCH
+#define INNERQ_PAGED_STORE 0
+#define INNERQ_INNER_JOIN 0
 #define INNERQ_INNER_LAUNCH launch_inner_g32
 #define INNERQ_INNER_GROUP 32
 #endif
+#if INNERQ_INNER_JOIN
+#define INNERQ_CONTRACTED
+#include "quantize_rows.h"
+#endif
+#include "window_pass.h"
+#include "merge.h"
 
 namespace innerq {
 namespace {
@@ -245,17 +247,24 @@ struct Lds {
 // zero-points of its two channels only if one of the two groups is flagged asymmetric (the flag is the
 // sign bit of the scale it already holds), at the start of the tile that needs them, so a 128-byte line
 // of zero-points (64 channels of one token-group) that holds no asymmetric group is never fetched.
-// (a launch that cannot append has no use for its arguments)
-template <bool JOIN> struct AppendArgsOf { typedef int type; };
-template <> struct AppendArgsOf<true> { typedef QuantArgs type; };
-template <bool JOIN> using AppendArgs = typename AppendArgsOf<JOIN>::type;
-
 // JOIN: the launch joins its own partial results and may append a step's token; else it leaves them to the merge, and the token
 // counts may live on the device.  (One kernel for both had worse code in the tile loop: 3-bit keys, 8 x 8 heads x 8k tokens,
 // attention call 19.7 us before, 21.1, 19.9 with the two apart.)
-template <int KB, int VB, int G, int NH4, bool ZK, int ZV, bool JOIN>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) attention_inner_kernel(AttnArgs a_in, int n_both_in, int n_splits, WindowSet win_in, int win_tiles_in, int base_t_in,
-                                                                                                 int rem_t_in, int r, int waves, int groups_in, int appends, AppendArgs<JOIN> append) {
+constexpr bool JOIN = INNERQ_INNER_JOIN != 0;
+// (a launch that cannot append has no use for its arguments)
+#if INNERQ_INNER_JOIN
+typedef QuantArgs AppendArgs;
+#else
+typedef int AppendArgs;
+#endif
+
+// ALONE: one wavefront a work-group, as most launches are that leave their partials to the merge.  It shares nothing: no
+// barrier, no second copy of the query set-up, constants of the heads straight from lane to lane, and a wavefront without a tile has no tables.  (Against
+// kernels for any number of wavefronts, us: 16 paged sequences of 1k to 16k tokens 28.5 -> 28.1; attention calls, eight query
+// heads per kv head, 4 x 8 x 16k, 3-bit keys 25.5 -> 23.6, 8 heads x 0.9k at 4 bits 12.5 -> 11.7.)
+template <int KB, int VB, int G, int NH4, bool ZK, int ZV, bool ALONE>
+__global__ void __launch_bounds__(ALONE ? 64 : 512) __attribute__((amdgpu_waves_per_eu(2, 2))) attention_inner_kernel(AttnArgs a_in, int n_both_in, int n_splits, WindowSet win_in, int win_tiles_in, int base_t_in,
+                                                                                                 int rem_t_in, int r, int waves_in, int groups_in, int appends, AppendArgs append) {
   constexpr int LBK = KB == 3 ? 2 : KB, LBV = VB == 3 ? 2 : VB;   // field width of the (low) plane
   constexpr bool HIK = KB == 3, HIV = VB == 3;                     // a plane of high bits follows it
   using FK = Fields<LBK>;
@@ -281,10 +290,11 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   // No division on the way to the first load: the grid is (splits, kv heads, batch), and the
   // host passes the quotients (heads per kv head; tiles per plain wavefront and their remainder).
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // (waves, groups: of a work-group / launch, as arguments: the built-in sizes are loads of their own)
+  const int waves = ALONE ? 1 : waves_in;
+  const int wave = ALONE ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // (waves, groups: of a work-group / launch, as arguments: the built-in sizes are loads of their own)
   const int hk = (int)blockIdx.y;
   int b = (int)blockIdx.z, group = (int)blockIdx.x;      // sequence; work-group of its (b, hk)
-  int n_groups = groups_in;
+  const int n_groups = groups_in;
   // The host's plan holds for every sequence -- unless the token counts live on the device
   // (a.n_dev: one count per sequence, the tokens cached BEFORE this step; attention runs over them
   // plus the new token).  Then the launch shape and the window chunks are the
@@ -296,7 +306,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   AttnArgs a = a_in;
   int n_both = n_both_in, win_tiles = win_tiles_in, base_t = base_t_in, rem_t = rem_t_in;
   WindowSet win = win_in;
-  if (!JOIN && a_in.n_dev) {
+  if (ALONE && a_in.n_dev) {
     const int w_recent = a.k.slots - 1;                  // (the per-token key ring has w_recent + 1 slots)
     const int n_chunks = win.n_chunks;
     // counts fit 24 bits (capacity * head_dim <= 2^31); outside their bounds they are clamped
@@ -321,34 +331,33 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
       // sequences' wavefronts fit the launch: the smallest one below 8, at most an eighth above it beyond (every try is a
       // scan of the lengths, in front of the first load).  No fewer than four tiles (a wavefront pays its query set-up
       // once).
-      const int total = groups_in, most = n_splits / waves, least = (n_chunks + waves) / waves;   // (at least one wavefront without a chunk)
+      const int total = groups_in;
       const int n_lane = clamped(lane < a.batch ? a_in.n_dev[lane] : 0);
       const Length x = length(n_lane);
       const int work = lane < a.batch ? x.tiles + n_chunks * x.cost : 0;
-      int quota = (wave_scan(work).total + total * waves - 1) / (total * waves);
+      int quota = (wave_scan(work).total + total - 1) / total;
       quota = quota < 4 ? 4 : quota;
       int mine;
       Scan sc;
       for (;;) {
-        mine = (work + quota * waves - 1) / (quota * waves);
-        mine = mine < least ? least : mine;
-        mine = mine > most ? most : mine;
+        mine = (work + quota - 1) / quota;
+        mine = mine < n_chunks + 1 ? n_chunks + 1 : mine;
+        mine = mine > n_splits ? n_splits : mine;
         mine = lane < a.batch ? mine : 0;
         sc = wave_scan(mine);
-        if (sc.total <= total) break;                    // (the host: batch * least <= total)
+        if (sc.total <= total) break;                    // (the host: batch * (n_chunks + 1) <= total)
         quota += 1 + (quota >> 3);
       }
       b = __popcll(__builtin_amdgcn_ballot_w64(lane < a.batch && group >= sc.upto));
       if (b >= a.batch) return;                            // (wave-uniform)
-      n_groups = __builtin_amdgcn_readlane(mine, b);
-      group -= __builtin_amdgcn_readlane(sc.upto, b) - n_groups;
-      n_splits = n_groups * waves;
+      n_splits = __builtin_amdgcn_readlane(mine, b);
+      group -= __builtin_amdgcn_readlane(sc.upto, b) - n_splits;
       n = __builtin_amdgcn_readlane(n_lane, b);            // (not read again: a memory round trip)
     } else {
       n = clamped(a_in.n_dev[b]);
     }
     const Length x = length(n);
-    if (group == 0 && hk == 0 && wave == 0 && lane == 0) {
+    if (group == 0 && hk == 0 && lane == 0) {
       if (a.n_copy) a.n_copy[b] = x.n - 1;                 // for the append that follows
       if (a.n_valid) a.n_valid[b] = n_splits + n_chunks;   // partial results of this sequence's heads
     }
@@ -376,9 +385,9 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   // also serve one chunk of the fp16 windows each (after their tiles) and get win_tiles tiles;
   // the others share the remaining tiles evenly.
   const int n_tiles = (n_both + TILE - 1) / TILE;
-  const int s_idx = wave * n_groups + group;             // (the chunks go to different work-groups first)
+  const int s_idx = ALONE ? group : wave * n_groups + group;   // (the chunks go to different work-groups first)
   int t0 = 0, t1 = 0;
-  if (s_idx >= n_splits) {                               // (a launch that leaves its partials to the merge: beyond the plan)
+  if (!ALONE && s_idx >= n_splits) {                     // (a launch that leaves its partials to the merge: beyond the plan)
   } else if (s_idx < win.n_chunks) {
     t0 = s_idx * win_tiles;
     t1 = t0 + win_tiles;
@@ -502,7 +511,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     u32x4 raw[NH4];
     float4_t fac[NH4][2];                              // per-channel query factors, when given
   };
-  auto sets_up = [&](int rnd) { return wave == waves - 1 - (waves > rnd ? rnd : 0); };
+  auto sets_up = [&](int rnd) { return ALONE || wave == waves - 1 - (waves > rnd ? rnd : 0); };
   auto load_query = [&](Query& q) {
 #pragma unroll
   for (int rnd = 0; rnd < NH4; ++rnd) {
@@ -520,6 +529,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   // ---- query: fp16 (optionally rescaled), offset factors folded in.  A lane takes 8
   // consecutive channels of one head (one 16-byte load); the channels of one key group sit in
   // G/8 neighbouring lanes, so the group sums of q come from a few DPP adds.
+  float q_coef[4];                                       // the score's constants of this lane's four heads
   auto set_up = [&](const Query& q) {
 #pragma unroll
   for (int rnd = 0; rnd < NH4; ++rnd) {
@@ -548,7 +558,15 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     const float q_pow = __uint_as_float((uint32_t)(127 + 8 - q_exp) << 23);
     // per-head constant of the score, log2e/sqrt(d) * 2^(24 - CK) / (the head's factor)
     const float coef = (kSmScale * kLog2e * (float)(1 << (24 - CK))) * __uint_as_float((uint32_t)(127 - 8 + q_exp) << 23);
-    if (lane % 16 == 0) coef_lds[h] = coef;
+    if constexpr (ALONE) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float of_head = from_lane(coef, 16 * j);
+        q_coef[j] = rnd == 0 || (lane & 16) ? of_head : q_coef[j];
+      }
+    } else if (lane % 16 == 0) {
+      coef_lds[h] = coef;
+    }
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int c = c0 + e;
@@ -570,21 +588,28 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     if ((idx % (G / 8)) == 0) qsum[h / 4][c0 / G][h % 4] = part * (kSmScale * kLog2e);
   }
   };
+  auto meet = [] {
+    if constexpr (ALONE) wave_fence();
+    else __syncthreads();
+  };
   int* arrivals = reinterpret_cast<int*>(lds + L::COUNT);
-  if (wave == 0) {
-    if (lane == 0) *arrivals = 0;
+  auto clear = [&] {
+    if (JOIN && lane == 0) *arrivals = 0;
     for (int i = 2 * lane; i < ZEROS; i += 128) *reinterpret_cast<uint32_t*>(&tables[ZERO + i]) = 0u;
-  }
+  };
+  if (!ALONE && wave == 0) clear();
   // A wavefront without a tile (a launch with more wavefronts than tiles gives the window chunks wavefronts of their own)
   // meets the others behind the loads of its window chunk.
   const bool has_tiles = t1 > t0, has_chunk = s_idx < win.n_chunks;
   Query query;
   if (!has_tiles) {
-    if (waves > 1) {                                     // (alone, it needs no tables)
-      load_query(query);
-      set_up(query);
+    if constexpr (!ALONE) {                              // (alone, it needs no tables)
+      if (waves > 1) {
+        load_query(query);
+        set_up(query);
+      }
+      if (!has_chunk) __syncthreads();
     }
-    if (!has_chunk) __syncthreads();
   } else {
   // (the first tile's loads and their use in one branch: brought together from two, they were waited for at the barrier,
   // 0.9 us of a launch of 1024 wavefronts with a few tiles each)
@@ -592,12 +617,13 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
   load_query(query);
   load_tile(t0, bufA);
   set_up(query);
-  __syncthreads();
+  if constexpr (ALONE) clear();
+  meet();
   // Four results a lane: heads 4 par .. 4 par + 3 (see CH below); their constants of the score.
   const int par = NH4 == 2 ? (lane >> 4) & 1 : 0;
-  float q_coef[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
+    if constexpr (ALONE) continue;
     q_coef[i] = coef_lds[4 * par + i];
     if constexpr (NH4 == 1) q_coef[i] = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, q_coef[i])));
   }
@@ -992,7 +1018,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
     __builtin_amdgcn_s_setprio(0);
     WaveState<NH> w;
     window_pass<NH4, KB, G, true, false, kPagedStore>(a, bh, win.na, win.b0, win.nb, s_idx, win.n_chunks, 0, lds + own_lds, w,
-                                                      [&] { if (!has_tiles) __syncthreads(); });
+                                                      [&] { if (!ALONE && !has_tiles) __syncthreads(); });
     if (!JOIN) store_partial(a, w, bh, r, n_splits + s_idx, lane);
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
@@ -1008,11 +1034,13 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))
 
   // ---- the append of the step's token: disjoint memory.  The wavefront of one work-group that is through first takes it,
   // while the others still have tiles.
-  if constexpr (JOIN) if (appends && group == n_groups - 1) {
+#if INNERQ_INNER_JOIN
+  if (appends && group == n_groups - 1) {
     int at = 0;
     if (lane == 0) at = __hip_atomic_fetch_add(arrivals, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (__builtin_amdgcn_readfirstlane(at) == 0) append_keys_and_copies<G, KB>(append, bh, a.n_tokens - 1, lane);
   }
+#endif
 
   if constexpr (!JOIN) {                                 // partials for a later launch (the tiles' after the chunk's: nothing reuses its registers)
     if (s_idx < n_splits) store_partial(a, part, bh, r, s_idx, lane);
@@ -1033,6 +1061,7 @@ hipError_t launch_z(const AttnArgs& a, int n_both, int n_splits, const WindowSet
   int win_tiles = quota > cost ? quota - cost : 0;
   if (win.n_chunks > 0 && win_tiles > n_tiles / win.n_chunks) win_tiles = n_tiles / win.n_chunks;
   if (L.waves < 1 || L.waves > kJoinWaves || (a.join && n_splits > kJoinGroups * L.waves) || (!a.join && L.append)) return hipErrorInvalidValue;
+  if (!JOIN && L.waves > 1 && (r <= 4 || a.n_dev)) return hipErrorInvalidValue;   // (not built)
   if (n_splits <= win.n_chunks) return hipErrorInvalidValue;      // the host gives at least one plain wavefront
   if (a.batch > 65535 || a.n_kv_heads > 65535) return hipErrorInvalidValue;
   const int rest = n_tiles - win.n_chunks * win_tiles, others = n_splits - win.n_chunks;
@@ -1052,13 +1081,14 @@ hipError_t launch_z(const AttnArgs& a, int n_both, int n_splits, const WindowSet
       hipLaunchKernelGGL(kernel, grid, dim3(64u * L.waves), lds_bytes, L.stream, a, n_both, n_splits, win, win_tiles, base_t, rem_t, r,
                          L.waves, (int)grid.x, appends, q);
   };
-  if (a.join) {
-    if (r <= 4) go(attention_inner_kernel<KB, VB, G, 1, ZK, ZV, true>, L.append ? *L.append : QuantArgs{});
-    else go(attention_inner_kernel<KB, VB, G, 2, ZK, ZV, true>, L.append ? *L.append : QuantArgs{});
-  } else {
-    if (r <= 4) go(attention_inner_kernel<KB, VB, G, 1, ZK, ZV, false>, 0);
-    else go(attention_inner_kernel<KB, VB, G, 2, ZK, ZV, false>, 0);
-  }
+#if INNERQ_INNER_JOIN
+  const QuantArgs append = L.append ? *L.append : QuantArgs{};
+#else
+  const int append = 0;
+#endif
+  if (r <= 4) go(attention_inner_kernel<KB, VB, G, 1, ZK, ZV, !JOIN>, append);
+  else if (!JOIN && L.waves == 1) go(attention_inner_kernel<KB, VB, G, 2, ZK, ZV, !JOIN>, append);
+  else go(attention_inner_kernel<KB, VB, G, 2, ZK, ZV, false>, append);
   return hipGetLastError();
 }
 
@@ -1089,10 +1119,10 @@ inline int width_pair(const AttnArgs& a) {
 
 }  // namespace
 
-// The launch of this build (contiguous or paged store, one group size).
+// The launch of this build (contiguous or paged store, one group size, joining or not).
 hipError_t INNERQ_INNER_LAUNCH(const AttnArgs& a, int n_both, int n_splits, const WindowSet& win, const Launch& L) {
   constexpr int G = INNERQ_INNER_GROUP;
-  if (a.group != G || (a.pages.table != nullptr) != kPagedStore) return hipErrorInvalidValue;
+  if (a.group != G || (a.pages.table != nullptr) != kPagedStore || (a.join != nullptr) != JOIN) return hipErrorInvalidValue;
   switch (width_pair(a)) {
     case 0: return launch_t<2, 2, G>(a, n_both, n_splits, win, L);
     case 1: return launch_t<3, 3, G>(a, n_both, n_splits, win, L);
@@ -1102,7 +1132,7 @@ hipError_t INNERQ_INNER_LAUNCH(const AttnArgs& a, int n_both, int n_splits, cons
   }
 }
 
-#if !INNERQ_PAGED_STORE && INNERQ_INNER_GROUP == 32
+#if !INNERQ_PAGED_STORE && INNERQ_INNER_GROUP == 32 && !INNERQ_INNER_JOIN
 
 bool attention_inner_supported(const AttnArgs& a) {
   const int r = a.n_q_heads / a.n_kv_heads;
@@ -1130,9 +1160,10 @@ hipError_t launch_attention_inner(const AttnArgs& a, long long n_both, int n_spl
     return launch_attention_inner_f4(a, n_both, n_splits, win, stream, ev_start, ev_stop);
   }
   const Launch L = {stream, ev_start, ev_stop, waves, append};
-  if (a.pages.table)
-    return a.group == 32 ? launch_inner_paged_g32(a, (int)n_both, n_splits, win, L) : launch_inner_paged_g64(a, (int)n_both, n_splits, win, L);
-  return a.group == 32 ? launch_inner_g32(a, (int)n_both, n_splits, win, L) : launch_inner_g64(a, (int)n_both, n_splits, win, L);
+  const bool paged = a.pages.table != nullptr, wide = a.group != 32;
+  const auto go = a.join ? (paged ? (wide ? launch_join_paged_g64 : launch_join_paged_g32) : (wide ? launch_join_g64 : launch_join_g32))
+                         : (paged ? (wide ? launch_inner_paged_g64 : launch_inner_paged_g32) : (wide ? launch_inner_g64 : launch_inner_g32));
+  return go(a, (int)n_both, n_splits, win, L);
 }
 
 #endif

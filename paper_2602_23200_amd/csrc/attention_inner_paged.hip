@@ -1,5 +1,6 @@
 // The fused inner-grouped kernels for a paged store, groups of 32 (see attention_inner.hip).
 #define INNERQ_PAGED_STORE 1
+#define INNERQ_INNER_JOIN 0
 #define INNERQ_INNER_LAUNCH launch_inner_paged_g32
 #define INNERQ_INNER_GROUP 32
 #include "attention_inner.hip"

@@ -163,7 +163,7 @@ struct AttnArgs {
   const int* n_dev;
   int* n_copy;
   int* n_valid;             // with n_dev: partial results per head of every sequence (workspace, [B]), left by the fused kernel for the merge; else null
-  int shared_groups;        // with n_dev: work-groups of a kv head that the sequences share by their lengths; 0: the same number each
+  int shared_groups;        // with n_dev: wavefronts of a kv head (a work-group each) that the sequences share by their lengths; 0: the same number each
   // a launch that joins its own partial results (merge.h): where its work-groups publish them (workspace) and its tag
   // (odd); null: the partials are joined by a later launch
   unsigned long long* join;
@@ -196,11 +196,16 @@ struct Launch { hipStream_t stream; hipEvent_t ev_start, ev_stop; int waves; con
 hipError_t launch_attention_inner(const AttnArgs& a, long long n_both, int n_splits, const WindowSet& win, int waves,
                                   const QuantArgs* append, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 
-// One build of the kernel each: contiguous or paged store (a.pages.table set), groups of 32 or 64.
+// One build of the kernel each: contiguous or paged store (a.pages.table set), groups of 32 or 64, partials left to the merge or
+// joined (a.join set).
 hipError_t launch_inner_g32(const AttnArgs& a, int n_both, int n_splits, const WindowSet& win, const Launch& L);
 hipError_t launch_inner_g64(const AttnArgs& a, int n_both, int n_splits, const WindowSet& win, const Launch& L);
 hipError_t launch_inner_paged_g32(const AttnArgs& a, int n_both, int n_splits, const WindowSet& win, const Launch& L);
 hipError_t launch_inner_paged_g64(const AttnArgs& a, int n_both, int n_splits, const WindowSet& win, const Launch& L);
+hipError_t launch_join_g32(const AttnArgs& a, int n_both, int n_splits, const WindowSet& win, const Launch& L);
+hipError_t launch_join_g64(const AttnArgs& a, int n_both, int n_splits, const WindowSet& win, const Launch& L);
+hipError_t launch_join_paged_g32(const AttnArgs& a, int n_both, int n_splits, const WindowSet& win, const Launch& L);
+hipError_t launch_join_paged_g64(const AttnArgs& a, int n_both, int n_splits, const WindowSet& win, const Launch& L);
 
 // The same partial results for 2-bit codes from the block-scaled fp8 x fp4 matrix instruction
 // (128-token tiles).  Parity-green but slower than the fp16 matrix form (see the file header), so it runs

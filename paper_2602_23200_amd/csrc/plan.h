@@ -41,7 +41,6 @@ inline int split_cap(const innerq_config_t& c) {
 // the sequences' token counts there for the append that follows it -- and, for batches that share the launch's
 // wavefronts by length, behind them how many partial results each sequence has (these fit the first 256 bytes).
 constexpr int kSharedBatchMost = 32;
-constexpr int kRaggedWaves = 1;          // wavefronts of a work-group there (20 heads x 25k tokens 21.9 us, with two 24.3)
 inline size_t seq_bytes(const innerq_config_t& c) { return (((size_t)c.batch * sizeof(int) + 255) / 256) * 256; }
 static_assert(2 * kSharedBatchMost * sizeof(int) <= 256, "both counts of a sequence in the first 256 bytes");
 
@@ -210,9 +209,13 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
         n_splits = (int)(groups * waves);
         n_partials = (int)groups;
       } else {
-        // (sharing the query tables is worth it for eight heads, 8 x 32k tokens 18.3 us -> 17.0, while every work-group has a
-        // compute unit to itself)
-        waves = r > 4 && BH * ceil_div(n_splits, 4) <= cus ? 4 : 1;
+        // Four wavefronts that share the query tables are worth it for eight heads of narrow codes on a chip of one wavefront a
+        // SIMD, from as many tiles and chunks as wavefronts up to three tiles each, one and a half from 33 heads on (attention
+        // calls, four together over one alone, by tiles a SIMD, 8, 16 and 32 heads: 0.7 1.00 to 1.09; 1 to 2.9 0.91 to 0.95,
+        // 3-bit keys 0.94 to 1.02; 3.4 0.98 to 1.05; 3.9 and more 0.99 to 1.12; 64 heads 1.3 0.97, 2.8 1.08; 4 and 3 bits 1 to
+        // 1.2 0.96 to 0.98, 2 and more 1.01 to 1.10).
+        const int most_a_cu = kb + vb > 5 ? 0 : 8 * BH <= cus ? 12 : 4 * BH <= cus ? 6 : 0;
+        waves = r > 4 && few_tiles && n_tiles + n_win_chunks >= per_head && BH * n_tiles <= most_a_cu * cus ? 4 : 1;
       }
     }
     // Token counts on the device: the wavefronts planned for sequences of the bound's length go to the sequences by
@@ -221,11 +224,11 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
     // front of the first load, and packs the wavefronts of short sequences onto fewer compute units, so it wants
     // several tiles per wavefront (8 sequences x 8 heads, bound 2000 tokens: 13.8 against 14.9 shared; 8000 tokens,
     // lengths spread 16-fold: 18.2 against 15.9) and several wavefronts per head (16 x 32 heads, bound 4000: 28.8 against 38.2).
-    const long long shared = (long long)n_splits * c.batch / kRaggedWaves, least = ceil_div(n_win_chunks + 1, kRaggedWaves);
-    if (ragged && c.batch > 1 && c.batch <= kSharedBatchMost && least * c.batch <= shared && n_tiles >= 6 * per_head && per_head >= 10) {
-      waves = kRaggedWaves;
+    // (Work-groups of one wavefront: 20 heads x 25k tokens 21.9 us, of two 24.3.)
+    const long long shared = (long long)n_splits * c.batch;
+    if (ragged && c.batch > 1 && c.batch <= kSharedBatchMost && (n_win_chunks + 1) * c.batch <= shared && n_tiles >= 6 * per_head && per_head >= 10) {
       shared_groups = (int)shared;
-      n_splits = split_cap(c) / waves * waves;
+      n_splits = split_cap(c);
     }
   } else if (n_both > 0) {
     const long long blocks_per_split = (long long)c.batch * c.n_kv_heads * ceil_div(r, kHeadTile);
