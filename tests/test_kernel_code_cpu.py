@@ -35,7 +35,7 @@ def test_merge_keeping_kernels_carry_no_work_group_code(tmp_path):
         elif name:
             if name in alone and "s_barrier" in line:
                 alone[name] += 1
-            if re.search(r"v_(pk_)?max(_num)?_f(16|32)(_e32|_e64)? (v\d+), (v\d+), \4\b", line):
+            if re.search(r"v_(pk_)?max(_num)?_f(16|32)(_e32|_e64)? v\d+, (v\d+), \5\b", line):
                 canonical[name] += 1
     assert len(alone) >= 24 and len(canonical) > len(alone)
     assert not any(alone.values()), {k: v for k, v in alone.items() if v}
