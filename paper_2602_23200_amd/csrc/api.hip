@@ -395,6 +395,7 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
                                                  : 1;
   in.may_join = fused_kind == kInnerKernel && !a.f4;
   in.appends = append != nullptr;
+  in.spills = !n_dev && partition_of(c, 1, N < c.capacity_tokens ? N + 1 : N).n_quant > partition_of(c, 1, N).n_quant;
   in.ragged = n_dev != nullptr;
   in.n_both = n_both; in.win_tokens = win_tokens;
   const LaunchPlan plan = plan_attention(c, in);

@@ -51,6 +51,7 @@ struct PlanInput {
   int compute_units, waves_per_cu;
   bool may_join;                // the kernel can join its own partials
   bool appends;                 // the launch would take a decode step's append along
+  bool spills;                  // the append of a step over these tokens moves a value group out of its ring
   bool ragged;                  // token counts on the device: n_both, win_tokens hold for the longest sequence allowed
   long long n_both;             // tokens of the quantised range
   long long win_tokens;         // tokens outside it
@@ -74,8 +75,13 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
   const int r = c.n_q_heads / c.n_kv_heads;
   int n_splits = 0, win_chunk_len = kWindowChunk, waves = 1;
   const bool fused = fused_kind != 0;
-  bool joins = fused_kind == 1 && n_both > 0 && !ragged && may_join;
   const long long BH = (long long)c.batch * c.n_kv_heads;
+  const bool can_join = fused_kind == kInnerKernel && n_both > 0 && !ragged && may_join;
+  // A value group that leaves its ring (one step of G) takes a launch that the merge can share: there it is kept until the join
+  // saves more than that (us of such a step, joined and with the merge: 2 heads x 6k tokens at 4 bits 17.7, 11.6, 8 x 8 x 4k 15.4,
+  // 12.7, 16 x 8 x 8k 25.4, 23.9; 32 x 8 x 1k 19.5, 22.8).
+  const bool with_the_group = in.spills && BH < in.compute_units;
+  bool joins = can_join && !(with_the_group && in.appends);
   // Partial results a head may have where the launch joins them itself (they are larger there: kJoinBytes each).
   const long long most_groups = (long long)(split_cap(c) + window_chunk_cap(c)) * (kHeadDim + 2) * (long long)sizeof(float) / kJoinBytes;
   if (n_both > 0 && fused) {
@@ -115,12 +121,16 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
       const long long waves16 = (long long)c.batch * c.n_kv_heads * (plain_for(kWindowChunkMin) + ceil_div(win_tokens, kWindowChunkMin));
       best_len = waves16 * 4 <= simds ? kWindowChunkMin : (n_tiles < 48 ? 32 : kWindowChunk);
       best_plain = plain_for(best_len);
-      // A short context: one work-group per sequence-head, its wavefronts a window chunk or a tile or two each.
+      // A short context: one work-group per sequence-head, its wavefronts a window chunk or a tile or two each.  Whether it is one
+      // does not depend on the append: a step and the separate calls that it replaces give the same bits there.
       const long long chunks32 = ceil_div(win_tokens, 32);
       if (joins && n_tiles + chunks32 <= 12 && chunks32 <= 7 && BH <= in.compute_units) {
-        one_group = true;
-        best_len = 32;
-        best_plain = plain_for(32);
+        one_group = !with_the_group;
+        joins = one_group;
+        if (one_group) {
+          best_len = 32;
+          best_plain = plain_for(32);
+        }
       }
     } else {
       // Comparison kernels: 64 tokens when the wavefront slots are all needed for tiles (long
@@ -140,10 +150,10 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
     // the inner kernel's first wavefronts each carry a window chunk besides their tiles; the
     // comparison kernels run the window chunks as extra wavefronts of the same launch
     n_splits = (int)(fused_kind == 1 ? best_plain + n_win_chunks : best_plain);
+    const long long cus = in.compute_units;
     if (joins) {
       // Wavefronts per work-group and work-groups per sequence-head, all resident at once.  The join costs the same for
       // two work-groups and for eight, and more beyond (another round of loads, and more that arrive at once).
-      const long long cus = in.compute_units;
       const bool heavy = kb == 3 || vb == 3;
       long long groups = 1, most_joining = 8;
       if (one_group) {
@@ -208,15 +218,16 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
       if (joins) {
         n_splits = (int)(groups * waves);
         n_partials = (int)groups;
-      } else {
-        // Four wavefronts that share the query tables are worth it for eight heads of narrow codes on a chip of one wavefront a
-        // SIMD, from as many tiles and chunks as wavefronts up to three tiles each, one and a half from 33 heads on (attention
-        // calls, four together over one alone, by tiles a SIMD, 8, 16 and 32 heads: 0.7 1.00 to 1.09; 1 to 2.9 0.91 to 0.95,
-        // 3-bit keys 0.94 to 1.02; 3.4 0.98 to 1.05; 3.9 and more 0.99 to 1.12; 64 heads 1.3 0.97, 2.8 1.08; 4 and 3 bits 1 to
-        // 1.2 0.96 to 0.98, 2 and more 1.01 to 1.10).
-        const int most_a_cu = kb + vb > 5 ? 0 : 8 * BH <= cus ? 12 : 4 * BH <= cus ? 6 : 0;
-        waves = r > 4 && few_tiles && n_tiles + n_win_chunks >= per_head && BH * n_tiles <= most_a_cu * cus ? 4 : 1;
       }
+    }
+    if (can_join && !joins) {
+      // Four wavefronts that share the query tables are worth it for eight heads of narrow codes on a chip of one wavefront a
+      // SIMD, from as many tiles and chunks as wavefronts up to three tiles each, one and a half from 33 heads on (attention
+      // calls, four together over one alone, by tiles a SIMD, 8, 16 and 32 heads: 0.7 1.00 to 1.09; 1 to 2.9 0.91 to 0.95,
+      // 3-bit keys 0.94 to 1.02; 3.4 0.98 to 1.05; 3.9 and more 0.99 to 1.12; 64 heads 1.3 0.97, 2.8 1.08; 4 and 3 bits 1 to
+      // 1.2 0.96 to 0.98, 2 and more 1.01 to 1.10).
+      const int most_a_cu = kb + vb > 5 ? 0 : 8 * BH <= cus ? 12 : 4 * BH <= cus ? 6 : 0;
+      waves = r > 4 && few_tiles && n_tiles + n_win_chunks >= per_head && BH * n_tiles <= most_a_cu * cus ? 4 : 1;
     }
     // Token counts on the device: the wavefronts planned for sequences of the bound's length go to the sequences by
     // their lengths, as many to one as it has partial slots, where there is something to gain: 16 sequences of 1k to
