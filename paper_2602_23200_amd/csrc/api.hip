@@ -545,7 +545,7 @@ int innerq_decode_step_ragged(const innerq_config_t* cfg, const innerq_cache_t* 
     j.row_end = j.form == kPerChannel ? cfg->group : 1;
     j.ring_from = 0;
   }
-  return launch_quantize(a, static_cast<hipStream_t>(hip_stream), merge.join ? nullptr : &merge) == hipSuccess ? INNERQ_OK : INNERQ_E_HIP;
+  return launch_quantize(a, static_cast<hipStream_t>(hip_stream), &merge) == hipSuccess ? INNERQ_OK : INNERQ_E_HIP;
 }
 
 int innerq_decode_step(const innerq_config_t* cfg, innerq_cache_t* cache, const void* k_new, const void* v_new,

@@ -188,10 +188,11 @@ __device__ __forceinline__ float from_lane(float x, int k) {
 }
 
 // The published partials of UNITS half heads, if all are there (false for the whole wavefront else); half head u is half
-// u & 1 of head u >> 1.  Up to eight of each, so that one round of loads brings everything.
+// u & 1 of head u >> 1.  Up to kJoinGroups of each, so that one round of loads brings everything.
 template <int UNITS>
-__device__ __forceinline__ void join_few(const AttnArgs& a, long long head0, int unit, int step, int lane, int n, uint32_t tag) {
-  constexpr int H = kHeadDim / 2, NB = 8;
+__device__ __forceinline__ void join_published(const AttnArgs& a, long long head0, int unit, int step, int lane, int n, uint32_t tag) {
+  constexpr int H = kHeadDim / 2, NB = kJoinGroups;
+  static_assert(NB == 8, "a level a lane, in eight neighbouring lanes");
   const uint32_t mine = tag ^ (uint32_t)(lane << 1);
   join_word lv[UNITS], sv[UNITS], w[UNITS][NB];
 #pragma unroll
@@ -224,41 +225,6 @@ __device__ __forceinline__ void join_few(const AttnArgs& a, long long head0, int
       clear_word(words + a.n_partials * H + lane);
       clear_word(words + a.n_partials * (H + 1) + lane);
     }
-  }
-}
-
-// The same for one half head and more of them: the levels first (most work-groups are not the last one), then the
-// channels, 32 partials a round of loads.
-__device__ __forceinline__ void join_many(const AttnArgs& a, long long bhq, int half, int lane, int n, uint32_t tag) {
-  constexpr int H = kHeadDim / 2, NB = 32;
-  join_word* words = join_words(a, bhq, half);
-  join_word* levels = words + a.n_partials * H;
-  const uint32_t mine = tag ^ (uint32_t)(lane << 1);
-  // (n <= 64: a lane each)
-  const int at = lane < n ? lane : n - 1;
-  const join_word lv = look(levels + at), sv = look(levels + a.n_partials + at);
-  if (__builtin_amdgcn_ballot_w64(lane < n && (word_tag(lv) != mine || word_tag(sv) != mine)) != 0) return;
-  const float level = lane < n ? word_value(lv) : -INFINITY;
-  const float f = level_weight(level, window_wave_max(level));
-  const float den = window_wave_sum(f * (lane < n ? word_value(sv) : 0.f));
-  float num = 0.f;
-  for (int p0 = 0; p0 < n; p0 += NB) {
-    join_word w[NB];
-    bool bad = false;
-#pragma unroll
-    for (int k = 0; k < NB; ++k) w[k] = look(words + (p0 + k < n ? p0 + k : n - 1) * H + lane);
-#pragma unroll
-    for (int k = 0; k < NB; ++k) {
-      bad |= word_tag(w[k]) != mine;
-      num = __builtin_fmaf(from_lane(f, p0 + k), word_value(w[k]), num);       // (weight 0 beyond the last)
-    }
-    if (__builtin_amdgcn_ballot_w64(bad) != 0) return;
-  }
-  store_output(a, bhq, half * H + lane, num / den);
-  for (int p = 0; p < n; ++p) clear_word(words + p * H + lane);
-  if (lane < n) {
-    clear_word(levels + lane);
-    clear_word(levels + a.n_partials + lane);
   }
 }
 
@@ -296,18 +262,14 @@ __device__ __forceinline__ void join_and_store(const AttnArgs& a, const WaveStat
       join_word* words = join_words(a, bhq, u & 1);
       publish(words + (long long)group * H + lane, num, tag ^ (uint32_t)(lane << 1));
       if (lane < 2)
-        publish(words + (long long)a.n_partials * (H + lane) + group, lane == 0 ? top : den, tag ^ (uint32_t)((group & 63) << 1));
+        publish(words + (long long)a.n_partials * (H + lane) + group, lane == 0 ? top : den, tag ^ (uint32_t)(group << 1));
     }
   }
   if (n_groups == 1) return;
   stores_done();
-  if (n_groups <= 8) {
-    int u = wave;
-    for (; u + waves < 2 * r; u += 2 * waves) join_few<2>(a, bh * r, u, waves, lane, n_groups, tag);
-    if (u < 2 * r) join_few<1>(a, bh * r, u, waves, lane, n_groups, tag);
-  } else {
-    for (int u = wave; u < 2 * r; u += waves) join_many(a, bh * r + (u >> 1), u & 1, lane, n_groups, tag);
-  }
+  int u = wave;
+  for (; u + waves < 2 * r; u += 2 * waves) join_published<2>(a, bh * r, u, waves, lane, n_groups, tag);
+  if (u < 2 * r) join_published<1>(a, bh * r, u, waves, lane, n_groups, tag);
 }
 
 }  // namespace innerq

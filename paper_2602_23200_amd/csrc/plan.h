@@ -16,7 +16,7 @@ constexpr int kWindowChunkMin = 16;    // fewest (short contexts, slots to spare
 constexpr int kHeadTile = 4;           // query heads served by one work-group pass
 
 constexpr int kJoinWaves = 8;            // most wavefronts of a work-group that joins its own
-constexpr int kJoinGroups = 64;          // most work-groups of a sequence-head that join
+constexpr int kJoinGroups = 8;           // most work-groups of a sequence-head that join (one round of loads brings eight partials)
 // bytes of one partial of one head: 128 channels, and level and sum for each half of them
 constexpr int kJoinBytes = (kHeadDim + 4) * 8;
 
@@ -84,6 +84,7 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
   bool joins = can_join && !(with_the_group && in.appends);
   // Partial results a head may have where the launch joins them itself (they are larger there: kJoinBytes each).
   const long long most_groups = (long long)(split_cap(c) + window_chunk_cap(c)) * (kHeadDim + 2) * (long long)sizeof(float) / kJoinBytes;
+  const bool heavy = kb == 3 || vb == 3;
   if (n_both > 0 && fused) {
     // one wavefront per split; every wavefront of the launch resident at once, no tail round
     // (the window wavefronts of the same launch take their share of the slots)
@@ -121,11 +122,14 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
       const long long waves16 = (long long)c.batch * c.n_kv_heads * (plain_for(kWindowChunkMin) + ceil_div(win_tokens, kWindowChunkMin));
       best_len = waves16 * 4 <= simds ? kWindowChunkMin : (n_tiles < 48 ? 32 : kWindowChunk);
       best_plain = plain_for(best_len);
-      // A short context: one work-group per sequence-head, its wavefronts a window chunk or a tile or two each.  Whether it is one
-      // does not depend on the append: a step and the separate calls that it replaces give the same bits there.
+      // A short context: one work-group per sequence-head, its wavefronts a window chunk or a tile or two each.  Not on an idle
+      // chip for eight heads (8 heads x 0.5k tokens, 4 bits: attention call 11.8 us with the merge, 13.1 joined) nor with more than
+      // two 3-bit tiles for a wavefront (8 x 0.5k, G = 64 9.6 and 11.0): these keep the merge.  Whether it is one work-group does not
+      // depend on the append: a step and the separate calls that it replaces give the same bits there.
       const long long chunks32 = ceil_div(win_tokens, 32);
       if (joins && n_tiles + chunks32 <= 12 && chunks32 <= 7 && BH <= in.compute_units) {
-        one_group = !with_the_group;
+        one_group = 2 * BH >= in.compute_units || !(heavy && n_tiles > 2 * (8 - chunks32));
+        if (with_the_group || (r > 4 && 4 * BH < in.compute_units)) one_group = false;
         joins = one_group;
         if (one_group) {
           best_len = 32;
@@ -154,54 +158,60 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
     if (joins) {
       // Wavefronts per work-group and work-groups per sequence-head, all resident at once.  The join costs the same for
       // two work-groups and for eight, and more beyond (another round of loads, and more that arrive at once).
-      const bool heavy = kb == 3 || vb == 3;
-      long long groups = 1, most_joining = 8;
+      long long groups = 1;
       if (one_group) {
         waves = n_splits < 8 ? n_splits : 8;
       } else if (few_tiles) {
-        // A chip that is not full, up to 192 tiles: eight work-groups at most, wavefronts with one to three tiles each (us per
+        // A chip that is not full, up to 160 tiles: eight work-groups at most, wavefronts with one to three tiles each (us per
         // step, with the merge -> now; kv heads x tokens: 1 x 4k 11.3 -> 9.6, 8 x 4k 12.6 -> 10.2, 8 x 8k 13.6 -> 10.9,
-        // 16 x 8k 13.1 -> 11.1, 32 x 8k 13.6 -> 12.5, 64 x 3k 13.2 -> 11.6).  More tiles want more wavefronts a head than
-        // that: 8 x 16k 13.6 with the merge, 13.7 with eight work-groups, 8 x 32k 13.7 against 16.7 with sixteen.
+        // 16 x 8k 13.1 -> 11.1, 32 x 8k 13.6 -> 12.5; captured in a graph, without the host's time for a second launch, 1 x 4k
+        // 10.0 -> 10.2, 8 x 8k 12.5 -> 11.5).  More tiles want more wavefronts a head than that (in a graph: 4 x 11k 12.1 -> 13.2,
+        // 8 x 16k 13.6 -> 13.7).
         const long long full = slots / BH, half = 4 * cus / BH;
         const long long most = full < 64 ? full : 64;
         long long want = n_tiles * 2 / 3 + n_win_chunks;
         if (want > most) want = most;
         if (want <= n_win_chunks) want = n_win_chunks + 1;
         waves = 8;
-        // (a wavefront a SIMD where that is two and a half tiles each at most: 32 x 4k tokens at 4 bits 11.4, with more 12.2; 8k 13.8, 12.5)
-        if (half <= 32 && n_win_chunks < half && 2 * n_tiles <= 5 * half) want = want < half ? want : half;
+        // (a wavefront a SIMD where that is two tiles each at most: 32 x 4k tokens at 4 bits 11.4, with more 12.2; 8k 13.8, 12.5)
+        if (half <= 32 && n_win_chunks < half && n_tiles <= 2 * half) want = want < half ? want : half;
         if (want <= 32 && (BH * want <= 4 * cus || want / 4 * 4 > want / 8 * 8)) waves = 4;
         if (waves > want) waves = (int)want;
         groups = ceil_div(want, waves);
         while (groups > 1 && groups * waves > most && (groups - 1) * waves > n_win_chunks) --groups;
-        if (n_tiles > 192 || (n_tiles > 96 && kb + vb > 4)) {
-          // ... but for a few heads (1 x 32k 15.4 with the merge, 13.8; 4 x 32k 14.7, 14.4)
-          joins = BH <= 4 && n_tiles > 192 && n_tiles <= 512 && r <= 4 && kb + vb == 4;
-          waves = 8;
-          groups = ceil_div(n_tiles / 2, 8);
-          most_joining = 32;
-        } else if (BH * groups > cus * (8 / waves) || (kb + vb > 4 && BH * groups * waves > 4 * cus) ||
-                   (groups > 1 && (heavy || r > 4))) {
+        if (groups > 1) {
           // Not where a second round would begin, nor for wider codes two wavefronts a SIMD (96 heads x 1.3k at 4 bits 13.6 with
           // the merge, 16.1).  Eight heads' outputs are twice the join (72 heads x 2k tokens 17.3, 19.8; 96 x 0.9k 16.8,
           // 19.0); 3-bit tiles want a SIMD to themselves (10 heads x 0.9k 12.2, 14.8; 64 heads x 8k 23.1, 25.1).
-          joins = false;
+          const long long launched = BH * groups, tiles = BH * n_tiles;
+          const bool narrow = kb + vb <= 4;
+          if (launched > cus * (8 / waves) || (!narrow && launched * waves > 4 * cus) || heavy || r > 4) joins = false;
+          // Work-groups of four must not leave some compute units with two and others with one (56 heads x 2k, 280 work-groups: 1.12
+          // of the time with the merge; 40 x 4k 1.16; 72 x 6k, two each, 1.09; from 128 heads on two each are 0.90 to 0.95).
+          if (waves == 4 && launched > cus && (2 * BH < cus || 8 * launched < 14 * cus)) joins = false;
+          // ... nor their window chunks be most of the wavefronts (128 heads x 0.9k 1.08)
+          if (waves == 4 && 2 * n_win_chunks > want) joins = false;
+          // The merge is the faster one where wavefronts have little to do on a busier chip (24 to 32 heads x 0.8k to 1.4k 1.02) and
+          // where they have more than two (wider codes) or three tiles a SIMD (32 x 5k at 4 bits 1.07, 32 x 7k 1.03, 24 x 9k 1.02).
+          if ((n_tiles < 24 && 12 * BH > cus) || n_tiles > (narrow ? 160 : 96) || tiles > (narrow ? 12 : 8) * cus) joins = false;
         }
       } else {
         long long best = 0;
         for (int w = 8; w >= 4; w /= 2) {                // (of fewer, every one of the launch would take part in the join)
           const long long fit = cus * (8 / w) / BH, all = ceil_div(n_splits, w), g = fit < all ? fit : all;
           if (g * w <= n_win_chunks) continue;
+          // (several work-groups of four: 72 heads x 6k to 9k 1.08 of the time with the merge, 96 x 6k 1.06, eight query heads 1.13;
+          // 160 heads 0.95 to 1.00)
+          if (w == 4 && g > 1 && (2 * BH < cus || r > 4)) continue;
           const long long got = g * w < n_splits ? g * w : n_splits;
           if (got * 10 > best * 11) { best = got; waves = w; groups = g; }
         }
         if (best == 0) {
           // more wavefronts than fit at once: in rounds, where they are many (1024 heads x 4k tokens 85.3 -> 75.2; 320 heads x 3k
-          // tokens 35.8 and 52.2) and the window chunks not most of it (1024 x 1k 39.8 and 50.1)
+          // tokens 35.8 and 52.2) and the window chunks not most of it (1024 x 1k 39.8 and 50.1, x 3k 1.03 to 1.08 of the time)
           waves = n_splits < 8 ? n_splits : 8;
           groups = ceil_div(n_splits, waves);
-          if (n_tiles < 32 || BH < 4 * cus) joins = false;
+          if (n_tiles < 48 || BH < 4 * cus) joins = false;
           best = n_splits;
         }
         // Work-groups of several wavefronts may leave slots empty: not where that is two fifths of a tile more for each of them (208
@@ -209,9 +219,7 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
         // 18: 6.5k tokens, 0.7 more, 18.5 -> 19.5).
         if (10 * n_tiles * (n_splits - best) > 4 * best * n_splits) joins = false;
       }
-      if (groups > most_joining || groups > most_groups) joins = false;
-      // (a wide recent window may have more chunks than a branch above has wavefronts: one must be left without)
-      if (groups * waves <= n_win_chunks) joins = false;
+      if (groups > kJoinGroups || groups > most_groups) joins = false;
       // An attention call by itself gains less (there is no append to save) and keeps the merge on a chip that is not full
       // (4 heads x 9k tokens 11.7 us, joined 12.5) and with work-groups of four (160 heads x 3.6k tokens 18.8, 20.2).
       if (groups > 1 && (few_tiles || waves < 8) && !in.appends) joins = false;
@@ -225,9 +233,9 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
       // SIMD, from as many tiles and chunks as wavefronts up to three tiles each, one and a half from 33 heads on (attention
       // calls, four together over one alone, by tiles a SIMD, 8, 16 and 32 heads: 0.7 1.00 to 1.09; 1 to 2.9 0.91 to 0.95,
       // 3-bit keys 0.94 to 1.02; 3.4 0.98 to 1.05; 3.9 and more 0.99 to 1.12; 64 heads 1.3 0.97, 2.8 1.08; 4 and 3 bits 1 to
-      // 1.2 0.96 to 0.98, 2 and more 1.01 to 1.10).
+      // 1.2 0.96 to 0.98, 2 and more 1.01 to 1.10), and a compute unit for each (24 heads x 6k, 264 work-groups, 1.14).
       const int most_a_cu = kb + vb > 5 ? 0 : 8 * BH <= cus ? 12 : 4 * BH <= cus ? 6 : 0;
-      waves = r > 4 && few_tiles && n_tiles + n_win_chunks >= per_head && BH * n_tiles <= most_a_cu * cus ? 4 : 1;
+      waves = r > 4 && few_tiles && n_tiles + n_win_chunks >= per_head && BH * n_tiles <= most_a_cu * cus && BH * ceil_div(n_splits, 4) <= cus ? 4 : 1;
     }
     // Token counts on the device: the wavefronts planned for sequences of the bound's length go to the sequences by
     // their lengths, as many to one as it has partial slots, where there is something to gain: 16 sequences of 1k to

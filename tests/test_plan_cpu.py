@@ -58,7 +58,7 @@ int main() {
       }
   }
   printf("%lld plans, %lld joined, %lld bad\n", plans, joined, bad);
-  return bad || joined * 30 < plans;
+  return bad || joined * 40 < plans;
 }
 """
 
