@@ -179,13 +179,15 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
         if (waves > want) waves = (int)want;
         groups = ceil_div(want, waves);
         while (groups > 1 && groups * waves > most && (groups - 1) * waves > n_win_chunks) --groups;
+        // Not where a second round would begin, nor for wider codes two wavefronts a SIMD (96 heads x 1.3k at 4 bits 13.6 with
+        // the merge, 16.1).
+        const long long launched = BH * groups, tiles = BH * n_tiles;
+        const bool narrow = kb + vb <= 4;
+        if (launched > cus * (8 / waves) || (!narrow && launched * waves > 4 * cus)) joins = false;
         if (groups > 1) {
-          // Not where a second round would begin, nor for wider codes two wavefronts a SIMD (96 heads x 1.3k at 4 bits 13.6 with
-          // the merge, 16.1).  Eight heads' outputs are twice the join (72 heads x 2k tokens 17.3, 19.8; 96 x 0.9k 16.8,
-          // 19.0); 3-bit tiles want a SIMD to themselves (10 heads x 0.9k 12.2, 14.8; 64 heads x 8k 23.1, 25.1).
-          const long long launched = BH * groups, tiles = BH * n_tiles;
-          const bool narrow = kb + vb <= 4;
-          if (launched > cus * (8 / waves) || (!narrow && launched * waves > 4 * cus) || heavy || r > 4) joins = false;
+          // Eight heads' outputs are twice the join (72 heads x 2k tokens 17.3, 19.8; 96 x 0.9k 16.8, 19.0); 3-bit tiles want a
+          // SIMD to themselves (10 heads x 0.9k 12.2, 14.8; 64 heads x 8k 23.1, 25.1).
+          if (heavy || r > 4) joins = false;
           // Work-groups of four must not leave some compute units with two and others with one (56 heads x 2k, 280 work-groups: 1.12
           // of the time with the merge; 40 x 4k 1.16; 72 x 6k, two each, 1.09; from 128 heads on two each are 0.90 to 0.95).
           if (waves == 4 && launched > cus && (2 * BH < cus || 8 * launched < 14 * cus)) joins = false;

@@ -46,6 +46,7 @@ int main() {
           if (p.waves < 1 || p.waves > kJoinWaves) why = "wavefronts of a work-group";
           if (!p.joins && p.waves > 1 && (r <= 4 || in.ragged)) why = "wavefronts that no kernel is built for";
           if (p.n_splits <= p.n_win) why = "no wavefront without a window chunk";
+          if (p.joins && bh < 4 * in.compute_units && (long long)bh * p.n_partials > in.compute_units * (8 / p.waves)) why = "joined in more than one round";
           if (p.joins && in.spills && bh < in.compute_units) why = "joined although a value group leaves";
           if (p.joins && (p.n_splits != p.n_partials * p.waves || p.n_partials > kJoinGroups)) why = "joined launch";
           if (p.shared_groups && (p.joins || c.batch > kSharedBatchMost || (long long)(p.n_win + 1) * c.batch > p.shared_groups)) why = "shared wavefronts";
