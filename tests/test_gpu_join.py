@@ -1,6 +1,10 @@
-"""Launches that join their own partial results: one work-group per sequence-head and several (up to eight, and more than
-eight, which take another path), work-groups of few and of eight wavefronts, more of them than fit the chip at once, and
-windows of many chunks; steps at which a value group leaves its ring; a workspace of any content; replays from a graph.
+"""Launches that join their own partial results: one work-group per sequence-head and two to eight, of few and of eight
+wavefronts, for two to eight query heads and all widths, more of them than fit the chip at once, and windows of many chunks;
+steps at which a value group leaves its ring; a workspace of any content; replays from a graph.
+
+Which launch ran is read back from the workspace, since it depends on the planner and sizes that miss a path would prove nothing: a
+work-group by itself writes none of it, joined work-groups leave the words that they published cleared, and a launch that keeps
+the merge leaves its partial results.
 """
 import numpy as np
 import pytest
@@ -11,15 +15,35 @@ from tests.helpers import assert_cache_equal, gpu_config, max_rel_err, oracle_co
 
 pytestmark = pytest.mark.gpu
 TOL = 2e-3
+MERGE = 0                                                # (else: work-groups of a sequence-head; a pair: before and after the value group leaves)
 
 
-@pytest.mark.parametrize("batch,q_heads,kv_heads,tokens,recent,group,bits", [
-    (1, 4, 1, 200, 32, 32, 4), (2, 8, 2, 440, 48, 64, 2),                             # one work-group
-    (1, 3, 1, 900, 32, 32, 2), (1, 32, 8, 1500, 128, 32, 4), (2, 16, 2, 3000, 128, 64, 2), (3, 15, 3, 2000, 48, 32, 3),
-    (1, 4, 1, 9000, 128, 32, 2),                                                      # more than eight
-    (1, 4, 1, 1500, 900, 32, 2), (300, 1, 1, 700, 32, 32, 2), (2100, 2, 1, 250, 40, 32, 2),
+def joined_groups(ws, batch, heads):
+    """Work-groups of a sequence-head that joined in the last call, from a workspace that held nothing but 0xFF before it."""
+    import torch
+    words = ws[-(-4 * batch // 256) * 256:].view(torch.int32)
+    written = words != -1
+    n = int(written.sum())
+    if n == 0:
+        return 1
+    if int((words[written] != 0).sum()) > 0:
+        assert n % (130 * batch * heads) == 0
+        return MERGE
+    assert n % (264 * batch * heads) == 0                # (a half head: 64 channels, a level and a sum of 64 bits)
+    return n // (264 * batch * heads)
+
+
+@pytest.mark.parametrize("batch,q_heads,kv_heads,tokens,recent,group,bits,groups", [
+    (1, 4, 1, 200, 32, 32, 4, 1), (2, 8, 2, 440, 48, 64, 2, 1), (64, 8, 1, 440, 64, 32, 3, 1),      # one work-group
+    (1, 3, 1, 900, 32, 32, 2, (4, 3)), (1, 32, 8, 1500, 128, 32, 4, (7, 6)), (1, 4, 1, 6000, 128, 32, 2, 8), (1, 4, 1, 9000, 128, 32, 2, 8),
+    (1, 4, 1, 1500, 900, 32, 2, 8),                                                  # window chunks for most of the wavefronts
+    (64, 4, 1, 9000, 128, 32, 2, 4), (64, 8, 1, 9000, 128, 32, 2, 4), (64, 5, 1, 9000, 48, 64, 2, 4),       # a full chip
+    (64, 4, 1, 9000, 48, 32, 3, 4), (64, 8, 1, 9000, 128, 64, 3, 4), (128, 8, 1, 5000, 32, 32, 4, 2),
+    (256, 2, 1, 2500, 32, 32, 2, 1), (300, 1, 1, 700, 32, 32, 2, 1), (1024, 1, 1, 3700, 500, 32, 2, 2),              # ... and more than fit it at once
+    (2, 16, 2, 3000, 128, 64, 2, MERGE), (3, 15, 3, 2000, 48, 32, 3, MERGE), (1, 4, 1, 12000, 128, 32, 2, MERGE),
+    (2100, 2, 1, 250, 40, 32, 2, MERGE), (40, 4, 1, 3000, 128, 32, 2, MERGE),
 ])
-def test_steps(batch, q_heads, kv_heads, tokens, recent, group, bits):
+def test_steps(batch, q_heads, kv_heads, tokens, recent, group, bits, groups):
     import torch
     from paper_2602_23200_amd import binding as iq
     assert torch.cuda.is_available(), "these tests need the MI355X"
@@ -30,21 +54,36 @@ def test_steps(batch, q_heads, kv_heads, tokens, recent, group, bits):
     w = wl.Workload("j", 1 if one else batch, q_heads, kv_heads, 128, n + steps, bits, group, 4, recent, seed=tokens)
     o = oracle_config(w)
     K, V = wl.kv_full(w)
-    spread = lambda a: torch.from_numpy(np.ascontiguousarray(np.broadcast_to(a, (batch,) + a.shape[1:]) if one else a)).cuda()  # noqa: E731
+
+    def spread(a):
+        t = torch.from_numpy(np.ascontiguousarray(a)).cuda()
+        return t.expand(batch, *t.shape[1:]).contiguous() if one else t
+
     g = iq.allocate_cache(gpu_config(oracle_config(w.with_(batch=batch))))
     iq.innerq_quantize_append(g, spread(K[:, :, :n]), spread(V[:, :, :n]))
     iq.innerq_quantize_ahead(g)
     want = orc.cache_init_prefill(o, K[:, :, :n], V[:, :, :n])
     ws = iq.allocate_workspace(g.cfg)
     for i in range(steps):
-        ws.fill_((0xFF, 0x00, 0x3F)[i])
         q = wl.query(w, 0, i)
-        out = iq.innerq_decode_step(g, spread(K[:, :, n + i:n + i + 1]), spread(V[:, :, n + i:n + i + 1]), spread(q), ws).cpu().numpy()
+        k1, v1, qd = spread(K[:, :, n + i:n + i + 1]), spread(V[:, :, n + i:n + i + 1]), spread(q)
+        leaves = (n + i + 2 - 4 - recent) % group == 0            # (the merge takes the group along on a chip that is not full)
+        out = None
+        for content in (0x00, 0x3F, 0xFF):                        # (its contents must not matter)
+            ws.fill_(content)
+            g.c.n_tokens, g.c.store_ahead_tokens = n + i, n + i + 1
+            again = iq.innerq_decode_step(g, k1, v1, qd, ws).cpu().numpy()
+            assert out is None or np.array_equal(out, again)
+            out = again
+        left = (n + i + 1 - 4 - recent) % group <= i              # ... or has left in these steps
+        expect = MERGE if leaves and batch * kv_heads < 256 else groups[left] if isinstance(groups, tuple) else groups
+        got = joined_groups(ws, batch, q_heads)
+        assert got == expect, f"step {i}: {got} work-groups"
         orc.quantize_append(o, want, K[:, :, n + i:n + i + 1], V[:, :, n + i:n + i + 1])
         ref = orc.decode_attention(o, want, q)
         for b in range(0, batch, max(1, batch // 7)):
             assert max_rel_err(out[b:b + 1], ref[:1] if one else ref[b:b + 1]) <= TOL, f"step {i} sequence {b}"
-        again = iq.innerq_decode_attention(g, spread(q), ws).cpu().numpy()      # the same tokens, now appended
+        again = iq.innerq_decode_attention(g, qd, ws).cpu().numpy()   # the same tokens, now appended
         assert max_rel_err(again, out) <= TOL
     assert_cache_equal(g, want, o, bsel=slice(0, 1) if one else slice(None))
 
