@@ -47,8 +47,8 @@ def parse():
     p.add_argument("--prewarm-ms", type=float, default=25.0,
                    help="untimed device pre-warm before the warm-up steps, in ms of the same work (0: none)")
     p.add_argument("--step-mode", default="fused", choices=["fused", "serial", "two-stream"],
-                   help="fused (default): innerq_decode_step, i.e. attention over the cache plus the new token, then "
-                        "one launch that merges the partials, appends the token and quantises one step ahead; "
+                   help="fused (default): innerq_decode_step, i.e. attention over the cache plus the new token with the "
+                        "token's append and the quantisation one step ahead, in one launch or two; "
                         "serial: innerq_quantize_append, then innerq_decode_attention (three launches); two-stream: "
                         "the deferred append on a side stream next to the attention")
     p.add_argument("--inner-kernel", type=int, default=0, choices=[0, 1],
@@ -191,7 +191,7 @@ def make_instance(torch, iq, w, cfg, layer, n_prefill, gen, asym_frac=None, shuf
     return cache
 
 
-KERNEL_SOURCES = {"inner": ["attention_inner.hip", "window_pass.h", "innerq_dev.h"],
+KERNEL_SOURCES = {"inner": ["attention_inner.hip", "window_pass.h", "innerq_dev.h", "merge.h", "plan.h", "quantize_rows.h"],
                   "outer": ["attention_outer.hip", "window_pass.h", "innerq_dev.h"],
                   "fp16": ["attention_fp16.hip", "window_pass.h", "innerq_dev.h"]}
 
@@ -478,8 +478,8 @@ def main():
             pending[j] = True
 
     def step_fused(profile=None):
-        """The same work per layer in two launches: attention (new token read from its input), then
-        merge + append + quantisation one step ahead."""
+        """The same work per layer in one call: one launch where the fused inner kernel joins its partials and appends,
+        else attention (new token read from its input), then merge + append + quantisation one step ahead."""
         for layer in range(n_layers):
             i = state["i"]
             state["i"] += 1
@@ -638,7 +638,8 @@ def main():
                      **({"traffic_GBps": traffic / (kern_ms * 1e-3) / 1e9,
                          "traffic_frac_of_peak": traffic / (kern_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
                          "traffic_bytes_per_token_kvhead": traffic / units} if traffic else {}),
-                     "kernel": "fused dequant score+value pass over the quantised range",
+                     # (a launch that joins its partial results and appends has both in its time)
+                     "kernel": "fused dequant score+value pass over the quantised range, with what rides in its launch",
                      "kernel_ms_mean": kern_ms, "kernel_ms_median": kern_ms_median,
                      "algorithmic_bytes_per_launch": alg_bytes, "bytes_per_token_kvhead": per_unit,
                      "token_kvheads_per_launch": units,

@@ -261,7 +261,8 @@ int innerq_decode_attention(const innerq_config_t *cfg, const innerq_cache_t *ca
  * make that first call outside a graph capture).
  *   - INNERQ_E_WORKSPACE if innerq_workspace_bytes(cfg) exceeds INNERQ_STATIC_WORKSPACE_BYTES
  *     (nothing is launched); INNERQ_E_HIP if the address lookup fails.
- *   - The partials need no clearing: every slot a call reads was written by that call.
+ *   - The partials need no clearing: a call reads slots that it wrote itself, or words that carry the
+ *     tag of its own launch.
  *   - All calls on one GPU share the one array: two calls that overlap in time on the same GPU
  *     (different streams or host threads) race on it and give undefined outputs.  Calls on one
  *     stream are ordered and safe. */
@@ -311,8 +312,9 @@ int innerq_append_deferred(const innerq_config_t *cfg, innerq_cache_t *cache, co
 
 /* One decode step in one or two launches instead of three: innerq_decode_attention_next followed by
  * innerq_append_deferred on the same stream (they touch disjoint memory).  Where the fused inner kernel
- * joins its partial results itself, the append rides in the same launch, but for the value group that
- * leaves its ring in one step of G; else the log-sum-exp merge and the append share the second launch.
+ * joins its partial results itself, the append rides in the same launch (but for the value group that
+ * leaves its ring in one step of G, which takes the second one); else the log-sum-exp merge and the
+ * append share the second launch.  Which it is follows from the sizes and the token count alone.
  * Same preconditions and errors as those two calls (INNERQ_E_ARG unless store_ahead_tokens ==
  * n_tokens + 1), the same cache bit for bit, the same output to the rounding of its sums, whose order
  * follows from how the launch is cut; on success n_tokens += 1 and the store already holds what the next
@@ -357,8 +359,9 @@ int innerq_decode_step_ragged(const innerq_config_t *cfg, const innerq_cache_t *
  * The next attention call made by the calling host thread (innerq_decode_attention,
  * innerq_decode_attention_static, innerq_decode_attention_next or innerq_decode_step) attaches
  * ev_start and ev_stop to the dispatch of its dominant kernel (the fused dequantise +
- * score + value pass over the quantised range) on that call's stream: they take the
- * begin and end timestamps of that dispatch, so their difference is the kernel's own
+ * score + value pass over the quantised range, and whatever else rides in that launch: the join of
+ * its partial results and a step's append, where the plan has them there) on that call's stream:
+ * they take the begin and end timestamps of that dispatch, so their difference is the kernel's own
  * duration as a profiler reports it.  Both are hipEvent_t created by the caller with
  * timing enabled; the request is consumed by that one call.  Passing NULL for either
  * cancels a pending request. */

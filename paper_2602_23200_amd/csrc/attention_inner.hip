@@ -34,14 +34,15 @@
 //   * softmax probabilities are rounded to fp16 for the value pass and the
 //     normaliser is the MFMA sum of those same rounded values (an extra all-ones B
 //     operand), so the weights stay consistent.
-//   * schedule: n_splits wavefronts per (batch, kv-head), all resident at once at two per SIMD, in work-groups of up to
-//     eight that share the query tables; contiguous tile ranges; two register buffers in ping-pong; the wavefront that is
-//     behind its SIMD partner gets the higher issue priority, so both finish together.
-//   * one launch: a work-group's wavefronts meet in LDS at the end, the work-groups of a (batch, kv-head) through the
-//     workspace (merge.h), and the append of a decode step's token is taken by the first wavefront that is through.  A
-//     launch for merge and append behind this one takes 3.4 us after a short kernel and 4.7 after a long one, whatever it
-//     does.  Per step, before -> now: 1 head x 512 tokens 12.2 us -> 9.4, 32 heads x 4k 12.9 -> 11.6, 8 x 8 x 32k
-//     40.3 -> 38.3, 32 x 8 x 8k 42.0 -> 39.6, 4 x 8 x 128k 72.2 -> 69.1, 3-bit 8 x 8 x 32k 56.9 -> 54.8.
+//   * schedule: n_splits wavefronts per (batch, kv-head), all resident at once at two per SIMD, by themselves or (launches that
+//     join, some with eight heads) in work-groups of up to eight that share the query tables; contiguous tile ranges; two
+//     register buffers in ping-pong; the wavefront that is behind its SIMD partner gets the higher issue priority, so both
+//     finish together.
+//   * one launch, where the plan (plan.h) says so: a work-group's wavefronts meet in LDS at the end, the work-groups of a (batch,
+//     kv-head) through the workspace (merge.h), and the append of a decode step's token is taken by the first wavefront
+//     that is through.  A launch for merge and append behind this one takes 3.4 us after a short kernel and 4.7 after a
+//     long one, whatever it does.  Per step, with the merge -> joined: 1 head x 512 tokens 11.8 us -> 9.0, 32 heads x 4k
+//     12.8 -> 11.6, 8 x 8 x 32k 40.0 -> 37.9, 32 x 8 x 8k 41.8 -> 38.7, 4 x 8 x 128k 72.7 -> 70.3, 3-bit 8 x 8 x 32k 56.9 -> 54.6.
 //   * paged store: this file is compiled for both stores, for launches that join and for those that do not (and, to build in
 //     parallel, for both group sizes).  attention_inner_paged*.hip include it with INNERQ_PAGED_STORE set and get the kernels
 //     that look every tile up in the page table (a page is one 64-token tile); the builds for the contiguous store carry no
@@ -259,9 +260,9 @@ typedef int AppendArgs;
 #endif
 
 // ALONE: one wavefront a work-group, as most launches are that leave their partials to the merge.  It shares nothing: no
-// barrier, no second copy of the query set-up, constants of the heads straight from lane to lane, and a wavefront without a tile has no tables.  (Against
-// kernels for any number of wavefronts, us: 16 paged sequences of 1k to 16k tokens 28.5 -> 28.1; attention calls, eight query
-// heads per kv head, 4 x 8 x 16k, 3-bit keys 25.5 -> 23.6, 8 heads x 0.9k at 4 bits 12.5 -> 11.7.)
+// barrier, no second copy of the query set-up, constants of the heads straight from lane to lane, and a wavefront without a
+// tile has no tables.  (Against kernels for any number of wavefronts, us: 16 paged sequences of 1k to 16k tokens 28.4 -> 27.8;
+// attention calls, eight query heads per kv head, 4 x 8 x 16k, 3-bit keys 25.6 -> 23.5, 8 heads x 0.9k at 4 bits 12.4 -> 11.6.)
 template <int KB, int VB, int G, int NH4, bool ZK, int ZV, bool ALONE>
 __global__ void __launch_bounds__(ALONE ? 64 : 512) __attribute__((amdgpu_waves_per_eu(2, 2))) attention_inner_kernel(AttnArgs a_in, int n_both_in, int n_splits, WindowSet win_in, int win_tiles_in, int base_t_in,
                                                                                                  int rem_t_in, int r, int waves_in, int groups_in, int appends, AppendArgs append) {
@@ -679,7 +680,7 @@ __global__ void __launch_bounds__(ALONE ? 64 : 512) __attribute__((amdgpu_waves_
   // and lane l's result are heads 4 par .. 4 par + 3 of its chain's column.  Half the matrix instructions of eight
   // heads as twice four, and a quarter of the operand reads; the halves of two columns change places by one lane swap a word.
   // (Eight query heads per kv head, step before -> now: 8 x 8 x 32k tokens, 2-bit 51.8 us -> 45.5, 4-bit 86.3 -> 77.1; 32 x 8 x
-  // 8k, G = 64 51.6 -> 39.9; 4 x 8 x 16k, 3-bit keys 28.1 -> 26.4.)
+  // 8k, G = 64 51.6 -> 39.9; attention call, 4 x 8 x 16k, 3-bit keys 27.5 -> 23.6.)
   // Lanes off the diagonal read the zeros.
   const bool diagonal = CH == 1 ? ((lane >> 2) & 3) == (lane >> 4) : ((lane >> 3) & 1) == (lane >> 5);
   const int head_row = lane & (NH - 1), half_at = CH == 1 ? 0 : par * (G / 2);

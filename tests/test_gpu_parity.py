@@ -743,8 +743,9 @@ def test_deferred_append_on_a_side_stream(env):
 @pytest.mark.parametrize("kind", KINDS)
 @pytest.mark.parametrize("n_prompt,n_steps,group", [(0, 120, 32), (300, 140, 64)])
 def test_decode_step_two_launches(env, kind, n_prompt, n_steps, group):
-    """innerq_decode_step (merge and append in one launch) against the separate deferred calls:
-    same outputs bit for bit, same cache as the oracle."""
+    """innerq_decode_step against the separate deferred calls: same cache as the oracle, and the same outputs bit for
+    bit, since a short context has one plan (one work-group, or the merge in both); where a step joins several
+    work-groups and the attention call by itself does not, they differ by the rounding of their sums."""
     torch, iq = env
     w = small(n_tokens=n_prompt + n_steps, group=group)
     o = oracle_config(w, kind=kind)
