@@ -129,7 +129,7 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
       const long long chunks32 = ceil_div(win_tokens, 32);
       if (joins && n_tiles + chunks32 <= 12 && chunks32 <= 7 && BH <= in.compute_units) {
         one_group = 2 * BH >= in.compute_units || !(heavy && n_tiles > 2 * (8 - chunks32));
-        if (with_the_group || (r > 4 && 4 * BH < in.compute_units)) one_group = false;
+        if (with_the_group || (r > 4 && 4 * BH < in.compute_units && !in.appends)) one_group = false;
         joins = one_group;
         if (one_group) {
           best_len = 32;
@@ -179,6 +179,9 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
         if (waves > want) waves = (int)want;
         groups = ceil_div(want, waves);
         while (groups > 1 && groups * waves > most && (groups - 1) * waves > n_win_chunks) --groups;
+        // Work-groups of four for a wavefront a SIMD: a compute unit each, not two for some and one for others (56 heads x 2k, 280
+        // work-groups: 1.12 of the time with the merge; 40 x 4k 1.16).
+        if (waves == 4 && BH * groups > cus && BH * want <= 4 * cus && 4 * (cus / BH) > n_win_chunks) groups = cus / BH;
         // Not where a second round would begin, nor for wider codes two wavefronts a SIMD (96 heads x 1.3k at 4 bits 13.6 with
         // the merge, 16.1).
         const long long launched = BH * groups, tiles = BH * n_tiles;
@@ -188,14 +191,18 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
           // Eight heads' outputs are twice the join (72 heads x 2k tokens 17.3, 19.8; 96 x 0.9k 16.8, 19.0); 3-bit tiles want a
           // SIMD to themselves (10 heads x 0.9k 12.2, 14.8; 64 heads x 8k 23.1, 25.1).
           if (heavy || r > 4) joins = false;
-          // Work-groups of four must not leave some compute units with two and others with one (56 heads x 2k, 280 work-groups: 1.12
-          // of the time with the merge; 40 x 4k 1.16; 72 x 6k, two each, 1.09; from 128 heads on two each are 0.90 to 0.95).
-          if (waves == 4 && launched > cus && (2 * BH < cus || 8 * launched < 14 * cus)) joins = false;
-          // ... nor their window chunks be most of the wavefronts (128 heads x 0.9k 1.08)
-          if (waves == 4 && 2 * n_win_chunks > want) joins = false;
-          // The merge is the faster one where wavefronts have little to do on a busier chip (24 to 32 heads x 0.8k to 1.4k 1.02) and
-          // where they have more than two (wider codes) or three tiles a SIMD (32 x 5k at 4 bits 1.07, 32 x 7k 1.03, 24 x 9k 1.02).
-          if ((n_tiles < 24 && 12 * BH > cus) || n_tiles > (narrow ? 160 : 96) || tiles > (narrow ? 12 : 8) * cus) joins = false;
+          const long long plain = groups * waves - n_win_chunks;
+          if (waves == 4) {
+            // (two work-groups of four for a compute unit: 72 heads x 6k 1.09 of the time with the merge, for one or two query heads
+            // 0.87 to 1.01; from 128 heads on 0.90 to 0.95)
+            if (launched > cus && (2 * BH < cus ? r > 2 : 8 * launched < 14 * cus)) joins = false;
+            // ... nor on a busy chip where the window chunks are most of it (128 heads x 0.9k 1.08, x 0.6k 0.87, G = 64 0.93) or leave the
+            // others more than three tiles each (72 and 80 heads x 1.6k 1.07)
+            if (4 * BH >= cus && ((c.group == 32 && n_tiles >= 10 && plain < n_win_chunks) || (2 * BH < cus && n_tiles > 3 * plain))) joins = false;
+          }
+          // Up to 50 heads the merge is the faster one where a SIMD has more than four tiles, two of wider codes (32 x 5k at 4 bits 1.07,
+          // 32 x 9k 1.02), and everywhere beyond 160 (96) tiles a head.
+          if (n_tiles > (narrow ? 160 : 96) || (5 * BH < cus && tiles > (narrow ? 16 : 8) * cus)) joins = false;
         }
       } else {
         long long best = 0;

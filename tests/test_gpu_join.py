@@ -39,9 +39,9 @@ def joined_groups(ws, batch, heads):
     (1, 4, 1, 1500, 900, 32, 2, 8),                                                  # window chunks for most of the wavefronts
     (64, 4, 1, 9000, 128, 32, 2, 4), (64, 8, 1, 9000, 128, 32, 2, 4), (64, 5, 1, 9000, 48, 64, 2, 4),       # a full chip
     (64, 4, 1, 9000, 48, 32, 3, 4), (64, 8, 1, 9000, 128, 64, 3, 4), (128, 8, 1, 5000, 32, 32, 4, 2),
-    (256, 2, 1, 2500, 32, 32, 2, 1), (300, 1, 1, 700, 32, 32, 2, 1), (1024, 1, 1, 3700, 500, 32, 2, 2),              # ... and more than fit it at once
+    (40, 4, 1, 3000, 128, 32, 2, 6), (256, 2, 1, 2500, 32, 32, 2, 1), (300, 1, 1, 700, 32, 32, 2, 1), (1024, 1, 1, 3700, 500, 32, 2, 2),              # ... and more than fit it at once
     (2, 16, 2, 3000, 128, 64, 2, MERGE), (3, 15, 3, 2000, 48, 32, 3, MERGE), (1, 4, 1, 12000, 128, 32, 2, MERGE),
-    (2100, 2, 1, 250, 40, 32, 2, MERGE), (40, 4, 1, 3000, 128, 32, 2, MERGE),
+    (2100, 2, 1, 250, 40, 32, 2, MERGE), (72, 4, 1, 6000, 128, 32, 2, MERGE),
 ])
 def test_steps(batch, q_heads, kv_heads, tokens, recent, group, bits, groups):
     import torch
