@@ -122,9 +122,9 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
       const long long waves16 = (long long)c.batch * c.n_kv_heads * (plain_for(kWindowChunkMin) + ceil_div(win_tokens, kWindowChunkMin));
       best_len = waves16 * 4 <= simds ? kWindowChunkMin : (n_tiles < 48 ? 32 : kWindowChunk);
       best_plain = plain_for(best_len);
-      // A short context: one work-group per sequence-head, its wavefronts a window chunk or a tile or two each.  Not on an idle
-      // chip for eight heads (8 heads x 0.5k tokens, 4 bits: attention call 11.8 us with the merge, 13.1 joined) nor with more than
-      // two 3-bit tiles for a wavefront (8 x 0.5k, G = 64 9.6 and 11.0): these keep the merge.  Whether it is one work-group does not
+      // A short context: one work-group per sequence-head, its wavefronts a window chunk or a tile or two each.  On an idle chip not with
+      // more than two 3-bit tiles for a wavefront (8 heads x 0.5k tokens, G = 64 9.6 us with the merge, 11.0), nor an attention call
+      // by itself for eight query heads (8 x 0.5k, 4 bits 11.8, 13.1): these keep the merge.  Up to four query heads it does not
       // depend on the append: a step and the separate calls that it replaces give the same bits there.
       const long long chunks32 = ceil_div(win_tokens, 32);
       if (joins && n_tiles + chunks32 <= 12 && chunks32 <= 7 && BH <= in.compute_units) {
