@@ -326,7 +326,7 @@ int innerq_append_deferred(const innerq_config_t* cfg, innerq_cache_t* cache, co
 
 // Attention over the first N tokens of the cache.  k_newest / v_newest (both or neither): fp16 rows
 // [B][Hk][d] of token N - 1 when that token has not been copied into its window yet.
-// defer_merge (may be null): the final merge is not launched; its arguments are returned instead.
+// defer_merge (may be null): the final merge is not launched; its arguments are returned instead (n_partials 0, or join set: there is none).
 // append, appended (may be null): the append of the step's token but for a value group, which a launch that joins its own partials takes along
 // (*appended says whether it did).
 // n_dev (may be null): per-sequence token counts on the device (the count before this step); N is then
@@ -380,6 +380,21 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
     const long long most = (long long)c.w_sink + c.w_recent + c.group;
     win_tokens = N < most ? N : most;
   }
+  // A short cache, nothing quantised in both tensors yet: one launch, with the append of a step's token in the inner layout.  Not
+  // for the count at which a value group leaves its ring: that append is the longer launch, and the merge rides in it
+  // (2 x 8 heads, 162 tokens 12.5 us; attention in one launch and the append in one 13.0).  Nor an attention call by itself
+  // there: a step and the separate calls that it replaces give the same bits.
+  const bool spills = !n_dev && partition_of(c, 1, N < c.capacity_tokens ? N + 1 : N).n_quant > partition_of(c, 1, N).n_quant;
+  const bool inner = c.kind == INNERQ_KIND_INNER;
+  if (n_both == 0 && !n_dev && N <= kShortTokens && !(inner && spills) && (long long)c.batch * c.n_q_heads < (1LL << 30)) {
+    const QuantArgs* rides = inner ? append : nullptr;
+    a.n_partials = 0;                                    // (nothing to merge)
+    g_prof_start = g_prof_stop = nullptr;                // (events are for the kernel of the quantised range)
+    if (launch_attention_short(a, rides, stream) != hipSuccess) return INNERQ_E_HIP;
+    if (defer_merge) *defer_merge = a;
+    if (appended) *appended = rides != nullptr;
+    return INNERQ_OK;
+  }
   // which fused kernel serves this cache
   const int fused_kind = attention_inner_supported(a)   ? kInnerKernel
                          : attention_fp16_supported(a)  ? kFp16Kernel
@@ -395,7 +410,7 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
                                                  : 1;
   in.may_join = fused_kind == kInnerKernel && !a.f4;
   in.appends = append != nullptr;
-  in.spills = !n_dev && partition_of(c, 1, N < c.capacity_tokens ? N + 1 : N).n_quant > partition_of(c, 1, N).n_quant;
+  in.spills = spills;
   in.ragged = n_dev != nullptr;
   in.n_both = n_both; in.win_tokens = win_tokens;
   const LaunchPlan plan = plan_attention(c, in);
@@ -584,7 +599,7 @@ int innerq_decode_step(const innerq_config_t* cfg, innerq_cache_t* cache, const 
   }
   // second launch: the merge of this step together with the append of its token and the
   // quantisation the next step needs
-  if (launch_quantize(append, static_cast<hipStream_t>(hip_stream), merge.join ? nullptr : &merge) != hipSuccess) return INNERQ_E_HIP;
+  if (launch_quantize(append, static_cast<hipStream_t>(hip_stream), merge.join || merge.n_partials == 0 ? nullptr : &merge) != hipSuccess) return INNERQ_E_HIP;
   cache->n_tokens = n + 1;
   cache->store_ahead_tokens = to;
   return INNERQ_OK;

@@ -1,12 +1,15 @@
-// Generic partial attention and the split-K merge.
+// Attention in fp32 (any form), the short caches in one launch, and the split-K merge.
 //
-// attention_generic_kernel takes any grouping form and any window in fp32 (weights included).  It
-// serves the caches that hold no token quantised in both tensors yet (the first w_sink + w_recent + G
-// tokens of every sequence), and is the fallback for shapes the fused kernels do not cover.
+// attention_generic_kernel takes any grouping form and any window in fp32 (weights included).  It is the fallback for shapes
+// the fused kernels do not cover, and serves the caches that hold no token quantised in both tensors yet (the first
+// w_sink + w_recent + G tokens of every sequence) beyond kShortTokens tokens and in the step at which their first value group leaves.
+// attention_short_kernel serves the other ones, the append of a decode step included.
 // attention_merge_kernel joins all partial results by log-sum-exp: the
 // quantised part and the window parts are concatenated before the softmax is
 // normalised (Eq. att:1-3; Figure "quantization_overall").
 #include "innerq_dev.h"
+#define INNERQ_CONTRACTED
+#include "quantize_rows.h"
 #include "window_pass.h"
 #include "merge.h"
 
@@ -16,8 +19,6 @@ namespace {
 constexpr int D = kHeadDim;
 constexpr int RT = kHeadTile;
 constexpr int TILE = 64;          // tokens per inner tile
-
-__device__ inline float h2f(__half h) { return __half2float(h); }
 
 // Eight consecutive channels of one token as they are loaded: an fp16 row's 16 bytes, or the packed
 // fields with the scales and zero-points that decode them.  FORM: the form of the rows that may be
@@ -154,7 +155,7 @@ __device__ __forceinline__ void add_row_groups(const float (&o)[RT][8], float (&
 
 // One work-group: up to four query heads, tiles of 64 tokens.  16 lanes share a token row (16 bytes of an
 // fp16 row each, coalesced), ROWS rows a thread, and a tile's key and value loads all go out before the
-// first is used.  On the short caches this kernel is there for, a launch is one tile per work-group and
+// first is used.  Where a launch is one tile per work-group,
 // its time is a memory round trip and the instructions of one thread, so 1024 threads take a row each
 // (ROWS = 1); with several tiles per work-group, or more work-groups than compute units, 256 threads take four
 // (ROWS = 4).  The kernel before this one decoded element by element: 2 x 8 heads x 165 tokens, kernel trace, 27 us (100 tokens) and 36 us
@@ -308,6 +309,184 @@ __global__ void __launch_bounds__(1024 / ROWS) attention_generic_kernel(AttnArgs
   }
 }
 
+// q.x[2 i], q.x[2 i + 1] times the same two of an fp16 row, added to acc: two mixed-precision multiply-adds (exact products).
+__device__ __forceinline__ float add_products(const uint4& q, const uint4& x, float acc) {
+  const uint32_t qw[4] = {q.x, q.y, q.z, q.w}, xw[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    acc = __builtin_fmaf(half_lo(qw[i]), half_lo(xw[i]), acc);
+    acc = __builtin_fmaf(half_hi(qw[i]), half_hi(xw[i]), acc);
+  }
+  return acc;
+}
+
+// A cache of at most kShortTokens tokens, none of them quantised in both tensors, in one launch: a work-group takes all tokens
+// of a sequence-head for up to NH query heads.  16 lanes share a token row as in attention_generic_kernel; a thread has a
+// row of each 64-token tile, and all its loads go out before the first is used.  The append of a decode step's token rides along as
+// work-groups of its own (the last ones, a sequence-head a wavefront): a new token's ring slot is never one that the attention reads.
+//
+// Such a step is a memory round trip and the instructions of one work-group, so what counts is to have one launch instead of
+// one for partials and one for merge and append, and few instructions a thread: products of fp16 rows are mixed-precision
+// multiply-adds (exact products, no conversions), and a work-group has as few heads as the chip has room for.  GPU time of
+// a step in a graph, 4-bit, before -> now: 2 x 8 heads, r = 4, 60 tokens 9.3 us -> 4.7, 128 tokens 9.3 -> 6.0, 150 (packed
+// key rows among them) 10.0 -> 6.7; 32 x 8 heads, 60 9.7 -> 6.6, 150 14.5 -> 11.4; 128 x 8 heads, 60 20.0 -> 15.4, 150 40.6 -> 32.8.
+// Registers: 64 a thread leave room for two work-groups a compute unit (128 x 8 heads x 128 tokens 22.5 us, 26.0 without the bound); with packed
+// rows that bound spills (2 x 8 x 150 7.4 against 6.7).
+template <int KF, int VF, int NH>
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(KF == kFp16 && VF == kFp16 ? 8 : 4, 8), amdgpu_num_sgpr(94))) attention_short_kernel(AttnArgs a, int r, int passes, int attention_groups, QuantArgs append) {
+  constexpr int ROWS = kShortTokens / TILE, WAVES = 16, V = NH * 8;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  if ((int)blockIdx.x >= attention_groups) {
+    // ---- the append of the step's token, a sequence-head a wavefront: memory that the attention does not touch
+    const long long bh = (long long)((int)blockIdx.x - attention_groups) * WAVES + wave;
+    if (bh >= (long long)a.batch * a.n_kv_heads) return;
+    const long long n = a.n_tokens - 1;
+    if (a.group == 32) {
+      if (a.bits == 2) append_keys_and_copies<32, 2>(append, bh, n, lane);
+      else if (a.bits == 3) append_keys_and_copies<32, 3>(append, bh, n, lane);
+      else append_keys_and_copies<32, 4>(append, bh, n, lane);
+    } else {
+      if (a.bits == 2) append_keys_and_copies<64, 2>(append, bh, n, lane);
+      else if (a.bits == 3) append_keys_and_copies<64, 3>(append, bh, n, lane);
+      else append_keys_and_copies<64, 4>(append, bh, n, lane);
+    }
+    return;
+  }
+  const uint32_t bh = blockIdx.x / (uint32_t)passes;
+  const int h0 = (int)(blockIdx.x - bh * passes) * NH, nh = min(NH, r - h0);
+  const uint32_t hk = bh % (uint32_t)a.n_kv_heads;
+  const int n = (int)a.n_tokens;
+  const int cb = tid & 15, tg = tid >> 4;               // channels 8 cb .. 8 cb + 7; token rows 64 k + tg
+
+  __shared__ float s_s[NH][kShortTokens];
+  __shared__ float l_s[NH];
+  __shared__ __attribute__((aligned(16))) float o_s[WAVES][NH][D];
+
+  Octet<KF> ko[ROWS];
+  Octet<VF> vo[ROWS];
+#pragma unroll
+  for (int k = 0; k < ROWS; ++k)
+    if (k == 0 || TILE * k < n) ko[k] = load_octet<KF>(a.k, a, bh, min(TILE * k + tg, n - 1), cb);     // (rows past the end: the last one, weight 0)
+  uint4 q[NH];
+  const long long hq = (long long)bh * r + h0;           // (batch b * n_q_heads + hk r + h0)
+#pragma unroll
+  for (int h = 0; h < NH; ++h) q[h] = *reinterpret_cast<const uint4*>(a.q + (hq + (h < nh ? h : 0)) * D + 8 * cb);
+#pragma unroll
+  for (int k = 0; k < ROWS; ++k)
+    if (k == 0 || TILE * k < n) vo[k] = load_octet<VF>(a.v, a, bh, min(TILE * k + tg, n - 1), cb);
+  if (a.q_scale) {
+    const float4* f = reinterpret_cast<const float4*>(a.q_scale + hk * D + 8 * cb);
+    const float4 f0 = f[0], f1 = f[1];
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+      q[h].x = scaled_pair(q[h].x, f0.x, f0.y);
+      q[h].y = scaled_pair(q[h].y, f0.z, f0.w);
+      q[h].z = scaled_pair(q[h].z, f1.x, f1.y);
+      q[h].w = scaled_pair(q[h].w, f1.z, f1.w);
+    }
+  }
+
+  // ---- scores (Eq. att:1, scaled by 1/sqrt(d))
+  const float sm_scale = 0.08838834764831845f;          // 1 / sqrt(128)
+#pragma unroll
+  for (int k = 0; k < ROWS; ++k) {
+    if (k > 0 && TILE * k >= n) break;
+    float acc[NH];
+    bool packed = false;
+    if constexpr (KF != kFp16) packed = __builtin_amdgcn_ballot_w64(ko[k].packed) != 0;    // (a wavefront's four rows: packed ones among them)
+    if (packed) {
+      float x[8];
+      decode_octet<KF>(ko[k], a.k.bits, x);
+#pragma unroll
+      for (int h = 0; h < NH; ++h) {
+        acc[h] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[h] = __builtin_fmaf(half_at(q[h], e), x[e], acc[h]);
+      }
+    } else {
+#pragma unroll
+      for (int h = 0; h < NH; ++h) acc[h] = add_products(q[h], ko[k].raw, 0.f);
+    }
+#pragma unroll
+    for (int h = 0; h < NH; ++h) acc[h] = row_sum(acc[h]);
+    float mine = acc[0];
+#pragma unroll
+    for (int h = 1; h < NH; ++h) mine = cb == h ? acc[h] : mine;
+    const int t = TILE * k + tg;
+    if (cb < NH) s_s[cb][t] = t < n ? mine * sm_scale : -INFINITY;
+  }
+  __syncthreads();
+  // ---- softmax of head `wave` (Eq. att:2), a token of every tile per lane
+  if (wave < NH) {
+    float s[ROWS], top = -INFINITY, sum = 0.f;
+#pragma unroll
+    for (int k = 0; k < ROWS; ++k) {
+      s[k] = TILE * k < n ? s_s[wave][TILE * k + lane] : -INFINITY;
+      top = fmaxf(top, s[k]);
+    }
+    top = window_wave_max(top);
+#pragma unroll
+    for (int k = 0; k < ROWS; ++k) {
+      if (k > 0 && TILE * k >= n) break;
+      const float p = expf(s[k] - top);
+      s_s[wave][TILE * k + lane] = p;
+      sum += p;
+    }
+    sum = window_wave_sum(sum);
+    if (lane == 0) l_s[wave] = sum;
+  }
+  __syncthreads();
+  // ---- weighted sum of values (Eq. att:3): the thread's channels of its token rows
+  float o[V];
+#pragma unroll
+  for (int i = 0; i < V; ++i) o[i] = 0.f;
+#pragma unroll
+  for (int k = 0; k < ROWS; ++k) {
+    if (k > 0 && TILE * k >= n) break;
+    float x[8];
+    decode_octet<VF>(vo[k], a.v.bits, x);
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+      const float p = s_s[h][TILE * k + tg];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[8 * h + e] = __builtin_fmaf(p, x[e], o[8 * h + e]);
+    }
+  }
+  // ---- the wavefront's four rows, each keeping a quarter of the (head, channel) sums; then the wavefronts
+  {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    float half[V / 2], quarter[V / 4];
+#pragma unroll
+    for (int i = 0; i < V / 2; ++i) {
+      const u32x2 p = __builtin_amdgcn_permlane32_swap(__float_as_uint(o[i]), __float_as_uint(o[V / 2 + i]), false, false);
+      half[i] = __uint_as_float(p.x) + __uint_as_float(p.y);
+    }
+#pragma unroll
+    for (int i = 0; i < V / 4; ++i) {
+      const u32x2 p = __builtin_amdgcn_permlane16_swap(__float_as_uint(half[i]), __float_as_uint(half[V / 4 + i]), false, false);
+      quarter[i] = __uint_as_float(p.x) + __uint_as_float(p.y);
+    }
+    const int at = (lane >> 4) * (V / 4);                // of the V sums of channel block cb: head at / 8, channels at % 8 on
+    float* dst = &o_s[wave][at / 8][8 * cb + at % 8];
+#pragma unroll
+    for (int i = 0; i < V / 4; i += 2) *reinterpret_cast<float2*>(dst + i) = float2{quarter[i], quarter[i + 1]};
+  }
+  __syncthreads();
+  if (wave < nh) {                                      // wavefront = head, lane = channel pair
+    float2 sum = {0.f, 0.f};
+#pragma unroll
+    for (int g = 0; g < WAVES; ++g) {
+      const float2 x = *reinterpret_cast<const float2*>(&o_s[g][wave][2 * lane]);
+      sum.x += x.x;
+      sum.y += x.y;
+    }
+    const float inv = 1.0f / l_s[wave];
+    const long long at = (hq + wave) * D + 2 * lane;
+    if (a.out_is_fp32) *reinterpret_cast<float2*>(reinterpret_cast<float*>(a.out) + at) = float2{sum.x * inv, sum.y * inv};
+    else *reinterpret_cast<__half2*>(reinterpret_cast<__half*>(a.out) + at) = __floats2half2_rn(sum.x * inv, sum.y * inv);
+  }
+}
+
 template <int WAVES>
 __global__ void __launch_bounds__(64 * WAVES) attention_merge_kernel(AttnArgs a) {
   merge_head<WAVES>(a, blockIdx.x, threadIdx.x >> 6, threadIdx.x & 63);
@@ -349,6 +528,28 @@ hipError_t launch_attention_generic(const AttnArgs& a, long long a0, long long a
   }
   if (vf == kFp16) return go(attention_generic_kernel<kPerChannel, kFp16, 1>, attention_generic_kernel<kPerChannel, kFp16, 4>);
   return go(attention_generic_kernel<kPerChannel, kPerToken, 1>, attention_generic_kernel<kPerChannel, kPerToken, 4>);
+}
+
+hipError_t launch_attention_short(const AttnArgs& a, const QuantArgs* append, hipStream_t stream) {
+  const int r = a.n_q_heads / a.n_kv_heads, bh = a.batch * a.n_kv_heads;
+  const bool kp = a.k.form != kFp16 && a.k.n_quant > 0, vp = a.v.form != kFp16 && a.v.n_quant > 0;
+  if ((kp && vp) || (kp && a.k.form != kPerToken) || (vp && a.v.form != kPerToken)) return hipErrorInvalidValue;
+  // One query head a work-group while every work-group, the append's among them, has a compute unit to itself, else two, else four
+  // (us a step, one, two and four heads each: 2 x 8 kv heads, r = 4, 128 tokens 6.0, 6.5, 7.7; 8 x 8, 260, 132 and 68 work-groups, 150
+  // tokens 9.6, 7.5, 8.5; 32 x 8, 128 tokens 15.4, 9.5, 8.6).  Heads that are there: one of one stays one (128 x 8 kv heads, r = 1 12.4, 18.8 in four).
+  const int append_groups = append ? (bh + 15) / 16 : 0;
+  int heads_each = 1;
+  while (heads_each < RT && heads_each < r && (long long)bh * ((r + heads_each - 1) / heads_each) + append_groups > compute_units()) heads_each *= 2;
+  const int passes = (r + heads_each - 1) / heads_each, groups = bh * passes;
+  const dim3 grid((unsigned)(groups + append_groups));
+  auto go = [&](auto kernel) {
+    kernel<<<grid, 1024, 0, stream>>>(a, r, passes, groups, append ? *append : QuantArgs{});
+    return hipGetLastError();
+  };
+  auto heads = [&](auto k1, auto k2, auto k4) { return heads_each == 1 ? go(k1) : heads_each == 2 ? go(k2) : go(k4); };
+  if (kp) return heads(attention_short_kernel<kPerToken, kFp16, 1>, attention_short_kernel<kPerToken, kFp16, 2>, attention_short_kernel<kPerToken, kFp16, 4>);
+  if (vp) return heads(attention_short_kernel<kFp16, kPerToken, 1>, attention_short_kernel<kFp16, kPerToken, 2>, attention_short_kernel<kFp16, kPerToken, 4>);
+  return heads(attention_short_kernel<kFp16, kFp16, 1>, attention_short_kernel<kFp16, kFp16, 2>, attention_short_kernel<kFp16, kFp16, 4>);
 }
 
 hipError_t launch_attention_merge(const AttnArgs& a, hipStream_t stream) {

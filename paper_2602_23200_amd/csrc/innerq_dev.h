@@ -178,6 +178,10 @@ struct AttnArgs {
 hipError_t launch_attention_generic(const AttnArgs& a, long long a0, long long a1, long long b0, long long b1,
                                     int n_chunks, int first_slot, hipStream_t stream);
 hipError_t launch_attention_merge(const AttnArgs& a, hipStream_t stream);
+// The whole attention call over a cache of at most kShortTokens tokens, none of them quantised in both tensors, in one
+// launch: partials, workspace and merge are not used.  append (may be null): the append of the step's token, but for a value
+// group, rides along (inner layout, a ring of at least two tokens).
+hipError_t launch_attention_short(const AttnArgs& a, const QuantArgs* append, hipStream_t stream);
 
 // Fused MFMA kernel for the inner-grouped layout: tokens [w_sink, w_sink + n_both) cut into
 // n_splits contiguous ranges of 64-token tiles, one wavefront each, partial slots 0 .. n_splits.

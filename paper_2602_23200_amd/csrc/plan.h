@@ -14,6 +14,7 @@ constexpr int kHeadDim = 128;          // the only head_dim built
 constexpr int kWindowChunk = 64;       // most window tokens per wavefront / work-group chunk
 constexpr int kWindowChunkMin = 16;    // fewest (short contexts, slots to spare)
 constexpr int kHeadTile = 4;           // query heads served by one work-group pass
+constexpr int kShortTokens = 256;      // most tokens of a cache that one work-group attends to by itself (attention_generic.hip)
 
 constexpr int kJoinWaves = 8;            // most wavefronts of a work-group that joins its own
 constexpr int kJoinGroups = 8;           // most work-groups of a sequence-head that join (one round of loads brings eight partials)
