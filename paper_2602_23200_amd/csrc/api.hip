@@ -413,6 +413,7 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
   in.spills = spills;
   in.ragged = n_dev != nullptr;
   in.n_both = n_both; in.win_tokens = win_tokens;
+  if (fused_kind == kOuterKernel) in.tile_tokens = attention_outer_tile_tokens(a);
   const LaunchPlan plan = plan_attention(c, in);
   const int n_splits = plan.n_splits, n_win = plan.n_win;
   const bool joins = plan.joins;

@@ -245,6 +245,7 @@ hipError_t launch_attention_fp16(const AttnArgs& a, long long n_rows, int n_spli
 // Comparison kernel over an outer-grouped cache, same launch shape.
 bool attention_outer_supported(const AttnArgs& a);
 int attention_outer_waves_per_cu(const AttnArgs& a);
+int attention_outer_tile_tokens(const AttnArgs& a);   // of a tile
 hipError_t launch_attention_outer(const AttnArgs& a, long long n_both, int n_splits, const WindowSet& win,
                                   hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 

@@ -56,6 +56,7 @@ struct PlanInput {
   bool ragged;                  // token counts on the device: n_both, win_tokens hold for the longest sequence allowed
   long long n_both;             // tokens of the quantised range
   long long win_tokens;         // tokens outside it
+  int tile_tokens = 64;         // of a tile of the kernel
 };
 
 struct LaunchPlan {
@@ -90,7 +91,7 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
     // one wavefront per split; every wavefront of the launch resident at once, no tail round
     // (the window wavefronts of the same launch take their share of the slots)
     const long long slots = (long long)in.compute_units * in.waves_per_cu;
-    const long long n_tiles = ceil_div(n_both, 64);
+    const long long n_tiles = ceil_div(n_both, in.tile_tokens);
     long long per_head = slots / ((long long)c.batch * c.n_kv_heads);
     // Short contexts: with fewer than about four tiles per wavefront, a launch of half as many
     // wavefronts (one per SIMD instead of two) is the faster one -- every wavefront pays its query
@@ -141,11 +142,12 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
       // Comparison kernels: 64 tokens when the wavefront slots are all needed for tiles (long
       // contexts: a chunk then hides behind the tile work), shorter when slots are to spare and the
       // window chunk would be the longest wavefront of the launch.  Costs in units of one tile of
-      // one wavefront: a chunk of L tokens about 4 + 14 L / 64.
+      // one wavefront: a chunk of L tokens about 4 + 14 L / 64 (outer-grouped kernel, tiles of 2.9 us: 5 / 8 + 3 L / 128; 8 heads x
+      // 8k tokens 11.0 us a call with chunks of 16, 12.3 of 32, 14.2 of 64; 16 x 8 heads x 6k, eight query heads, 188.5, 73.5, 53.1).
       for (long long len = kWindowChunk; len >= kWindowChunkMin; len /= 2) {
         const long long nw = ceil_div(win_tokens, len);
         const long long plain = plain_for(len);
-        const long long tile_cost = ceil_div(n_tiles, plain) * 8, win_cost = nw ? 32 + 14 * len / 8 : 0;   // x 8
+        const long long tile_cost = ceil_div(n_tiles, plain) * 8, win_cost = !nw ? 0 : fused_kind == kOuterKernel ? 5 + 12 * len / 64 : 32 + 14 * len / 8;   // x 8
         const long long cost = tile_cost > win_cost ? tile_cost : win_cost;
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; best_len = len; best_plain = plain; }
       }
