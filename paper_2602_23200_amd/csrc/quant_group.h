@@ -34,10 +34,23 @@ __device__ inline float code_quotient(float num, float S, float r) {
 // is the code the formula assigns when the scale is 0.
 __device__ inline float group_reciprocal(float S) { return S == 0.f ? 0.f : 1.0f / S; }
 
-// ---- a group in one lane: the form of prompts and chunks, which are bound by vector instructions, and of all
-// per-channel groups.
+// The same number in half the instructions, for an fp16 value S: one Newton step from the instruction's approximation (one
+// ulp) rounds correctly for each of the 1024 significands that S can have; an infinite or NaN S is set right at the end.
+__device__ inline float fp16_reciprocal(float S) {
+  const float r = __builtin_amdgcn_rcpf(S);
+  const float q = __builtin_fmaf(__builtin_fmaf(-S, r, 1.0f), r, r);
+  return S == 0.f ? 0.f : __builtin_amdgcn_div_fixupf(q, S, 1.0f);
+}
+// The correctly rounded x / d for a denominator d of the scales (1, 3, 7 or 15; r = fl(1 / d)): the division step of
+// code_quotient, an infinite or NaN x set right at the end.
+__device__ inline float scale_quotient(float x, float d, float r) {
+  return __builtin_amdgcn_div_fixupf(code_quotient(x, d, r), d, x);
+}
+
+// ---- a group in one lane: the form of prompts and chunks, and of all per-channel groups.  Long prompts are bound by memory, at
+// the rate of a copy (8 x 8 heads x 32k tokens, 2 bits: 1.24 GB in 250 us), with the vector units busy for three quarters of it.
 //
-// It uses three facts, each exact, so that codes, flags and scales keep every bit:
+// It uses these facts, so that codes, flags and scales keep every bit:
 //   * rint(fl(num / S)) is the exact quotient rounded to nearest-even.  A tie k + 1/2 of the quotient is
 //     num = T = S (k + 1/2), a number of at most 16 bits and so an fp32 number; any other num is at least one
 //     fp32 step from T, which leaves num / S further from k + 1/2 than half an fp32 step there.
@@ -50,7 +63,10 @@ __device__ inline float group_reciprocal(float S) { return S == 0.f ? 0.f : 1.0f
 // Values stay packed as they were loaded: every use is a mixed-precision multiply-add that reads its half.
 // A code cannot leave its range unless the scale is an fp16 denormal (whose rounding is coarse) or the
 // symmetric denominator is the literal one: wavefronts with such a group run the form that clamps.
-// Instructions per element of a 2-bit hybrid group, minimum and maximum included: 14 against 28.
+// The competition of the two variants is decided on a shorter error sum where its rounding cannot matter (bulk_codes).
+// Instructions per element of a 2-bit hybrid group, minimum and maximum included: 12 (14 with the oracle's own sum, 28 with
+// divisions and conversions); 14 and 10 more a group for its scales and their reciprocals (45 with divisions).  Appends of 8 x 8
+// heads x 32k tokens: 2 bits 259 us -> 250, 4 bits 287 -> 277, G = 64 256 -> 244.
 
 // One value of a group: a half of a register.
 struct HalfRef { uint32_t w; bool hi; };
@@ -80,7 +96,7 @@ __device__ __forceinline__ float half_times(HalfRef x, float r) {
 struct Reciprocal { float hi, lo; };
 __device__ inline Reciprocal split_reciprocal(float S) {
   Reciprocal r;
-  r.hi = group_reciprocal(S);
+  r.hi = fp16_reciprocal(S);
   r.lo = __builtin_fmaf(-S, r.hi, S == 0.f ? 0.f : 1.0f) * r.hi;    // 1 - S r_hi is exact
   return r;
 }
@@ -145,12 +161,26 @@ struct TernaryPacker {
   __device__ __forceinline__ uint32_t word(int i) const { return w[i]; }
 };
 
+// Distances |x - S code| of symmetric 2-bit groups as packed fp16 pairs: min(|x|, S - |x|) with S = max |x|.  Exact: S - |x| is where it
+// is the smaller one.  The error sum takes them with one mixed-precision addition each.
+__device__ __forceinline__ uint32_t ternary_distances(uint32_t x, uint32_t scales) {
+  typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+  const f16x2 a = __builtin_bit_cast(f16x2, x & 0x7fff7fffu), b = __builtin_bit_cast(f16x2, scales) - a;
+  uint32_t d;                                            // (the builtin makes the minimum of a number and itself first)
+  asm("v_pk_min_f16 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+  return d;
+}
+struct NoDistances {};                                   // (the sum forms its own)
+
 // CLAMP: codes are clamped, and `mode` (else: MODE) is what chooses between the two variants.
-template <int G, int BITS, int MODE, bool CLAMP, typename X>
-__device__ __forceinline__ void bulk_codes(X x, float mn, __half Sa, __half Ss, int mode,
+// Where both variants compete and no code is clamped, the asymmetric differences are taken as (x - mn) - Sa code, one operation
+// less than x - (Sa code + mn).  Their sum differs in its last bits, and is only compared with the other one: the result says
+// whether that could change the answer (the codes of both variants are right in any case).  most: the largest magnitude.
+template <int G, int BITS, int MODE, bool CLAMP, typename X, typename Dist>
+__device__ __forceinline__ bool bulk_codes(X x, Dist dist, float mn, float most, __half Sa, __half Ss, int mode,
                                            uint32_t (&words)[G * BITS / 32], __half& scale, __half& zero) {
   constexpr bool ASYM = MODE != INNERQ_SYM, SYM = MODE != INNERQ_ASYM, BOTH = ASYM && SYM;
-  constexpr bool TERNARY = BITS == 2 && !CLAMP;
+  constexpr bool TERNARY = BITS == 2 && !CLAMP, SHORT = BOTH && !CLAMP;
   constexpr int HALF = 1 << (BITS - 1), QMAX = (1 << BITS) - 1;
   const float Saf = h2f(Sa), Ssf = h2f(Ss);
   Reciprocal ra = {0.f, 0.f}, rs = {0.f, 0.f};
@@ -168,16 +198,22 @@ __device__ __forceinline__ void bulk_codes(X x, float mn, __half Sa, __half Ss, 
   for (int i = 0; i < G; ++i) {
     const HalfRef v = x(i);
     if constexpr (ASYM) {
-      float c = exact_code(half_minus(v, mn, one), ra);
+      const float num = half_minus(v, mn, one);
+      float c = exact_code(num, ra);
       if constexpr (CLAMP) c = __builtin_amdgcn_fmed3f(c, 0.f, (float)QMAX);
       pa.add(i, c);
-      if constexpr (BOTH) ea = ea + fabsf(half_minus(v, __builtin_fmaf(Saf, c, mn), one));
+      if constexpr (SHORT) ea = ea + fabsf(__builtin_fmaf(-Saf, c, num));
+      else if constexpr (BOTH) ea = ea + fabsf(half_minus(v, __builtin_fmaf(Saf, c, mn), one));
     }
     if constexpr (SYM) {
       float c;
       if constexpr (TERNARY) {
         const float t = half_times_plus(v, r_tern, 12582912.0f);
         pt.add(i, t);
+        if constexpr (SHORT && !__is_same(Dist, NoDistances)) {
+          es = __builtin_fmaf(value_of(dist(i)), one, es);
+          continue;
+        }
         c = t - 12582912.0f;
       } else {
         c = exact_code(v, rs);
@@ -197,17 +233,26 @@ __device__ __forceinline__ void bulk_codes(X x, float mn, __half Sa, __half Ss, 
   }
   scale = asym ? __hneg(Sa) : Ss;
   zero = asym ? __float2half_rn(mn) : __float2half_rn(0.f);
+  if constexpr (!SHORT) return false;
+  // With u = 2^-24 and M = most: x - mn, Sa code + mn and the differences round by at most (2 + 1.001 + 2 x 0.67) u M an element, and
+  // the sum of each of the two ways by G u times itself.
+  constexpr float u = 0x1p-24f;
+  return fabsf(ea - es) < __builtin_fmaf(ea, 2.1f * G * u, most * (4.4f * G * u));
 }
 
-// The group's fields, scale and zero-point from its values x(i) and their minimum and maximum.
-template <int G, int BITS, typename X>
-__device__ __forceinline__ void quantize_group_bulk(X x, float mn, float mx, int mode, int sym_den_literal,
+// The group's fields, scale and zero-point from its values x(i) and their minimum and maximum.  dist: the distances of a symmetric 2-bit
+// group whose denominator is 1 (others make no use of them), or NoDistances.
+template <int G, int BITS, typename X, typename Dist>
+__device__ __forceinline__ void quantize_group_bulk(X x, Dist dist, float mn, float mx, int mode, int sym_den_literal,
                                                     uint32_t (&words)[G * BITS / 32], __half& scale, __half& zero) {
   constexpr int QMAX = (1 << BITS) - 1;
   constexpr int HALF = 1 << (BITS - 1);
-  auto asym_scale = [&] { return __float2half_rn((mx - mn) / (float)QMAX); };
+  auto asym_scale = [&] { return __float2half_rn(scale_quotient(mx - mn, (float)QMAX, 1.0f / (float)QMAX)); };
   auto sym_scale = [&] {
-    return __float2half_rn(fmaxf(fabsf(mn), fabsf(mx)) / (sym_den_literal ? (float)QMAX : (float)(HALF - 1)));
+    const float most = fmaxf(fabsf(mn), fabsf(mx));
+    return __float2half_rn(sym_den_literal ? scale_quotient(most, (float)QMAX, 1.0f / (float)QMAX)
+                           : HALF == 2     ? most
+                                           : scale_quotient(most, (float)(HALF - 1), 1.0f / (float)(HALF - 1)));
   };
   __half Sa = asym_scale(), Ss = sym_scale();
   // a scale that is an fp16 denormal but not 0 (for 2-bit symmetric groups it is max |x| itself: exact),
@@ -218,7 +263,8 @@ __device__ __forceinline__ void quantize_group_bulk(X x, float mn, float mx, int
   };
   bool clamp = (mode != INNERQ_SYM && coarse(Sa, true)) || (mode != INNERQ_ASYM && coarse(Ss, BITS != 2));
   if (sym_den_literal && mode != INNERQ_ASYM) clamp = true;
-  if (__builtin_amdgcn_ballot_w64(clamp) != 0) {          // (wave-uniform)
+  bool redo = __builtin_amdgcn_ballot_w64(clamp) != 0;    // (wave-uniform)
+  if (redo) {
     if (__builtin_amdgcn_ballot_w64(mn != mn) != 0) {
       // the packed minimum and maximum hand a NaN on; the form of eight lanes passes it over, and a token's bytes
       // do not depend on the call it came with
@@ -233,10 +279,25 @@ __device__ __forceinline__ void quantize_group_bulk(X x, float mn, float mx, int
       Sa = asym_scale();
       Ss = sym_scale();
     }
-    bulk_codes<G, BITS, INNERQ_HYBRID, true>(x, mn, Sa, Ss, mode, words, scale, zero);
-  } else if (mode == INNERQ_HYBRID) bulk_codes<G, BITS, INNERQ_HYBRID, false>(x, mn, Sa, Ss, mode, words, scale, zero);
-  else if (mode == INNERQ_SYM) bulk_codes<G, BITS, INNERQ_SYM, false>(x, mn, Sa, Ss, mode, words, scale, zero);
-  else bulk_codes<G, BITS, INNERQ_ASYM, false>(x, mn, Sa, Ss, mode, words, scale, zero);
+  }
+  if (!redo && mode == INNERQ_HYBRID)
+    redo = __builtin_amdgcn_ballot_w64(bulk_codes<G, BITS, INNERQ_HYBRID, false>(x, dist, mn, fmaxf(fabsf(mn), fabsf(mx)), Sa, Ss, mode, words, scale, zero)) != 0;
+  else if (!redo && mode == INNERQ_SYM) bulk_codes<G, BITS, INNERQ_SYM, false>(x, NoDistances{}, mn, 0.f, Sa, Ss, mode, words, scale, zero);
+  else if (!redo) bulk_codes<G, BITS, INNERQ_ASYM, false>(x, NoDistances{}, mn, 0.f, Sa, Ss, mode, words, scale, zero);
+  if (redo) {
+    // The general form: clamped codes, the sums as the oracle takes them (on normal draws one wavefront in a hundred to a
+    // thousand gets here).  Its inputs are opaque: whatever the compiler shared with the forms above, conversions first
+    // of all, would hold registers through them (108 in the owners' kernel; 128 and 89 to 250 spilled).
+    uint32_t scales = (uint32_t)__half_as_ushort(Sa) | (uint32_t)__half_as_ushort(Ss) << 16;
+    asm volatile("" : "+v"(mn), "+v"(scales));
+    auto again = [&](int i) {
+      HalfRef v = x(i);
+      asm volatile("" : "+v"(v.w));
+      return v;
+    };
+    bulk_codes<G, BITS, INNERQ_HYBRID, true>(again, NoDistances{}, mn, 0.f, __ushort_as_half((unsigned short)(scales & 0xffffu)),
+                                             __ushort_as_half((unsigned short)(scales >> 16)), mode, words, scale, zero);
+  }
 }
 
 // Minimum / maximum of three fp16 pairs, half by half.
@@ -392,8 +453,14 @@ __device__ __forceinline__ void per_token_group(const QuantArgs& a, const QuantT
   mx = pair_max(mx, mx >> 16, mx >> 16);
   uint32_t words[W];
   __half s, z;
-  quantize_group_bulk<G, BITS>([&](int i) { return HalfRef{x[i / 2], (i & 1) != 0}; }, half_lo(mn), half_lo(mx), j.mode,
-                               a.sym_den_literal, words, s, z);
+  auto value = [&](int i) { return HalfRef{x[i / 2], (i & 1) != 0}; };
+  if constexpr (BITS == 2) {
+    const uint32_t less = mn ^ 0x80008000u, most = pair_max(mx, less, less) & 0xffffu, scales = most | most << 16;
+    quantize_group_bulk<G, BITS>(value, [&](int i) { return HalfRef{ternary_distances(x[i / 2], scales), (i & 1) != 0}; }, half_lo(mn), half_lo(mx), j.mode,
+                                 a.sym_den_literal, words, s, z);
+  } else {
+    quantize_group_bulk<G, BITS>(value, NoDistances{}, half_lo(mn), half_lo(mx), j.mode, a.sym_den_literal, words, s, z);
+  }
   // a row is one plane of LB-bit fields over all channels (3-bit: followed by the plane of high bits)
   constexpr int LB = BITS == 3 ? 2 : BITS;
   constexpr int WL = G * LB / 32;                        // words of the (low) plane of one group

@@ -101,9 +101,9 @@ __device__ __forceinline__ void per_channel_unit(const QuantArgs& a, const Quant
   pair_range(x, mn, mx);
   uint32_t words[2][W];
   __half s[2], z[2];
-  quantize_group_bulk<G, BITS>([&](int i) { return HalfRef{x[i], false}; }, half_lo(mn), half_lo(mx), j.mode,
+  quantize_group_bulk<G, BITS>([&](int i) { return HalfRef{x[i], false}; }, NoDistances{}, half_lo(mn), half_lo(mx), j.mode,
                                a.sym_den_literal, words[0], s[0], z[0]);
-  quantize_group_bulk<G, BITS>([&](int i) { return HalfRef{x[i], true}; }, half_hi(mn), half_hi(mx), j.mode,
+  quantize_group_bulk<G, BITS>([&](int i) { return HalfRef{x[i], true}; }, NoDistances{}, half_hi(mn), half_hi(mx), j.mode,
                                a.sym_den_literal, words[1], s[1], z[1]);
   long long go = ((long long)bh * a.capacity / G + tg) * D;            // (capacity is a multiple of G)
   uint32_t dc = dt * D + c;

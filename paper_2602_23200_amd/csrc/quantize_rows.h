@@ -192,7 +192,7 @@ __device__ __forceinline__ void per_channel_group(const QuantArgs& a, const Quan
   uint32_t mn, mx, words[W];
   pair_range(x, mn, mx);
   __half s, z;
-  quantize_group_bulk<G, BITS>([&](int i) { return HalfRef{x[i], false}; }, half_lo(mn), half_lo(mx), j.mode,
+  quantize_group_bulk<G, BITS>([&](int i) { return HalfRef{x[i], false}; }, NoDistances{}, half_lo(mn), half_lo(mx), j.mode,
                                a.sym_den_literal, words, s, z);
   const long long go = (store_row(a.pages, a.n_kv_heads, a.capacity, bh, tg * G) / G) * kHeadDim + c;
   uint32_t* dst = reinterpret_cast<uint32_t*>(j.codes) + go * W;

@@ -163,3 +163,67 @@ def test_zero_scale_gives_code_zero_without_a_select():
     q0 = num * r
     rem = num - S * q0
     assert np.array_equal(q0 + rem * r, np.zeros(4, dtype=f32))
+
+
+@pytest.mark.skipif(np.finfo(ld).nmant < 63, reason="needs an extended-precision long double")
+def test_reciprocal_of_a_scale_from_any_start_within_an_ulp():
+    """r0 is the instruction's 1 / S, within one ulp; e = fl(1 - S r0), r = fl(e r0 + r0) is the correctly rounded 1 / S from
+    every such start, for every positive finite fp16 S."""
+    S = np.arange(1, 0x7C00, dtype=np.uint16).view(np.float16).astype(f32)
+    want = (f32(1) / S).astype(f32)
+    for ulps in (-1, 0, 1):
+        r0 = (want.view(np.int32) + ulps).view(f32)
+        e = (ld(1) - S.astype(ld) * r0.astype(ld)).astype(f32)
+        got = (e.astype(ld) * r0.astype(ld) + r0.astype(ld)).astype(f32)
+        assert np.array_equal(got, want)
+
+
+@pytest.mark.skipif(np.finfo(ld).nmant < 63, reason="needs an extended-precision long double")
+@pytest.mark.parametrize("den", [3, 7, 15])
+def test_scale_quotient_equals_ieee_division(den):
+    """Scales: x / (2^b - 1) and x / (2^(b-1) - 1) by the correction step with r = fl(1 / den), for every fp16 magnitude and for
+    differences of fp16 values."""
+    rng = np.random.default_rng(den)
+    every = np.arange(0, 0x7C00, dtype=np.uint16).view(np.float16).astype(f32)
+    ranges = np.abs(fp16_values(rng, 3_000_000) - fp16_values(rng, 3_000_000) * rng.choice(f32([-1, 1]), 3_000_000)).astype(f32)
+    x = np.concatenate([every, ranges])
+    assert np.array_equal(correction_step_quotient(x, np.full_like(x, f32(den))), (x / f32(den)).astype(f32))
+
+
+def test_distances_of_a_symmetric_two_bit_group():
+    """min(|x|, S - |x|) in fp16 is |x - S code| with S = max |x|, exactly, for every fp16 x up to S."""
+    rng = np.random.default_rng(31)
+    S = np.concatenate([np.arange(1, 0x7C00, dtype=np.uint16), rng.integers(1, 0x7C00, 2_000_000).astype(np.uint16)])
+    x = (rng.integers(0, S.astype(np.int64) + 1)).astype(np.uint16)
+    half = (S.view(np.float16).astype(f32) / 2).astype(np.float16).view(np.uint16)
+    for pick in (x, S, np.minimum(half, S), np.minimum(half + 1, S), half - (half > 0)):
+        a, s = pick.astype(np.uint16).view(np.float16), S.view(np.float16)
+        code = np.rint((a.astype(f32) / s.astype(f32)).astype(f32))
+        want = np.abs(a.astype(f64) - s.astype(f64) * code)
+        assert np.array_equal(np.minimum(a, (s - a).astype(np.float16)).astype(f64), want)
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("G", [32, 64])
+def test_bound_of_the_short_error_sum(bits, G):
+    """sum |(x - mn) - S code| against sum |x - (S code + mn)|, every operation rounded to fp32: they differ by less than the bound
+    2.1 G u sum + 4.4 G u max |x| below which the kernel takes the comparison again, on groups whose values span many binades."""
+    rng = np.random.default_rng(bits * G)
+    n, u, top = 30_000, 2.0 ** -24, (1 << bits) - 1
+    x = (rng.standard_normal((n, G)) * np.exp2(rng.integers(-12, 3, (n, G)) * (rng.random((n, 1)) < 0.5))).astype(np.float16)
+    x[:2000] += np.float16(1000)
+    x[2000:4000] = np.abs(x[2000:4000])
+    x = x.astype(f32)
+    mn, mx = x.min(1, keepdims=True), x.max(1, keepdims=True)
+    S = ((mx - mn) / f32(top)).astype(np.float16).astype(f32)
+    num = (x - mn).astype(f32)
+    with np.errstate(all="ignore"):
+        c = np.rint(np.where(S == 0, f32(0), num / S)).astype(f32).clip(0, top)
+    fma = lambda a, b, d: (a.astype(f64) * b.astype(f64) + d.astype(f64)).astype(f32)  # noqa: E731  (11 x 4 bits: the sum is exact in fp64)
+    exact, short = np.zeros(n, f32), np.zeros(n, f32)
+    for i in range(G):
+        exact = exact + np.abs(x[:, i] - fma(S[:, 0], c[:, i], mn[:, 0]))
+        short = short + np.abs(fma(-S[:, 0], c[:, i], num[:, i]))
+    bound = 2.1 * G * u * short + 4.4 * G * u * np.abs(x).max(1)
+    assert (np.abs(exact.astype(f64) - short) <= 0.5 * bound).all()          # (the bound is a worst case: half of it is never reached here)
+    assert (exact != short).any()
