@@ -6,11 +6,10 @@
 // New tokens that do not stay in a window are units of one wavefront each:
 //   * per-token form: 64 consecutive groups of one sequence-head, one a lane (its G channels are 2 G contiguous bytes,
 //     and the 64 lanes' loads and packed stores are contiguous too);
-//   * per-channel form: one group of G tokens, a lane a pair of channels (a token's row is one coalesced 256-byte load).
+//   * per-channel form: half of the channels of one group of G tokens, a lane a channel (a token's row is coalesced 128-byte loads).
 //
 // What bounds it is the chain of an owner: the rounds of loads of the rows that leave, one lane's whole group, the
-// rounds of copies.  It pays while the owners fit the chip and their rings are short, and for the longest prompts with
-// key factors (append_form): 512 tokens onto 500 of 8 heads, G = 32, 7.9 us against 8.7 in two launches; 32 heads 9.0
+// rounds of copies.  It pays while the owners fit the chip and their rings are short (append_form): 512 tokens onto 500 of 8 heads, G = 32, 5.9 us against 8.7 in two launches; 32 heads 8.1
 // against 10.5; but with a window of 1024 tokens 19 against 10, and 157 against 13 with 8192 (1 head, G = 64): a ring's
 // rows are one work-group's serial rounds.
 #include "innerq_dev.h"
@@ -57,70 +56,61 @@ __device__ __forceinline__ void per_token_unit(const QuantArgs& a, const QuantTe
 }
 
 // ---- per-channel form ----------------------------------------------------------------------
-// One group of G tokens (tg) of sequence-head bh, all channels; or (RING) 128 / G groups from tg on, one channel
-// slice.  Groups from tg_end on are not there: their lanes repeat the last one, store included.
+// One group of G tokens (tg) of sequence-head bh, half of the channels (part), a lane each; or (RING) 64 / G groups from tg on, one
+// channel slice (part).  Groups from tg_end on are not there: their lanes repeat the last one, store included.
+// (A channel a lane: with two, one after the other, a lane's chain was the longest of a chunk, 512 tokens onto 500 of 32 heads at
+// 4 bits 9.4 us a chunk, 8.1 now; 250 of 32 heads, 3-bit keys, 8.6, 6.6; chunks of 8192 tokens of 32 heads 39.5, 38.8.)
 template <int BITS, bool RING>
 __device__ __forceinline__ void per_channel_unit(const QuantArgs& a, const QuantTensorJob& j, uint32_t bh, uint32_t tg,
-                                                 uint32_t tg_end, uint32_t slice) {
+                                                 uint32_t tg_end, uint32_t part) {
   constexpr int W = G * BITS / 32;
   const uint32_t lane = threadIdx.x & 63u;
-  uint32_t c = 2u * lane, dt = 0u;                       // channel pair; group, counted from tg
+  uint32_t c = 64u * part + lane, dt = 0u;               // channel; group, counted from tg
   if (RING) {
-    c = slice * G + 2u * (lane % (G / 2));
-    dt = lane / (G / 2);
+    c = part * G + lane % G;
+    dt = lane / G;
     dt = tg + dt < tg_end ? dt : tg_end - 1u - tg;
   }
   const long long t0 = (long long)a.w_sink + (long long)(tg + dt) * G;
-  const uint32_t* base = reinterpret_cast<const uint32_t*>(
-      j.x_new + ((long long)bh * a.t_new + ((long long)a.w_sink + (long long)tg * G - a.n_old)) * D);      // (uniform)
-  const uint32_t* src = base + (dt * (G * D / 2) + c / 2);
-  uint32_t x[G];
+  const __half* src = j.x_new + ((long long)bh * a.t_new + ((long long)a.w_sink + (long long)tg * G - a.n_old)) * D      // (uniform)
+                      + (dt * (G * D) + c);
+  uint32_t x[G];                                         // a value each, in the low half
   if constexpr (!RING) {
 #pragma unroll
-    for (int i = 0; i < G; ++i) x[i] = src[i * (D / 2)];
+    for (int i = 0; i < G; ++i) x[i] = __half_as_ushort(src[i * D]);
   } else {
-    const uint32_t* ring = reinterpret_cast<const uint32_t*>(j.ring + (long long)bh * j.slots * D + c);
+    const __half* ring = j.ring + (long long)bh * j.slots * D + c;
     uint32_t slot = (uint32_t)t0 % (uint32_t)j.slots;
 #pragma unroll
     for (int i = 0; i < G; ++i) {
-      const uint32_t* p = t0 + i >= a.n_old ? src + i * (D / 2) : ring + slot * (D / 2);
-      x[i] = *p;
+      x[i] = __half_as_ushort(*(t0 + i >= a.n_old ? src + i * D : ring + slot * D));
       slot = slot + 1u == (uint32_t)j.slots ? 0u : slot + 1u;
     }
   }
   if (j.normalise) {
-    const float* inv = a.inv_norm + (bh % (uint32_t)a.n_kv_heads) * D + c;
-    const float f0 = inv[0], f1 = inv[1];
+    const float f = a.inv_norm[(bh % (uint32_t)a.n_kv_heads) * D + c];
 #pragma unroll
     for (int i = 0; i < G; ++i) {
-      const uint32_t y = scaled_pair(x[i], f0, f1);
+      const uint32_t y = scaled_pair(x[i], f, 0.f);
       x[i] = !RING || t0 + i >= a.n_old ? y : x[i];      // (ring rows already are)
     }
   }
-  uint32_t mn, mx;
+  uint32_t mn, mx, words[W];
   pair_range(x, mn, mx);
-  uint32_t words[2][W];
-  __half s[2], z[2];
+  __half s, z;
   quantize_group_bulk<G, BITS>([&](int i) { return HalfRef{x[i], false}; }, NoDistances{}, half_lo(mn), half_lo(mx), j.mode,
-                               a.sym_den_literal, words[0], s[0], z[0]);
-  quantize_group_bulk<G, BITS>([&](int i) { return HalfRef{x[i], true}; }, NoDistances{}, half_hi(mn), half_hi(mx), j.mode,
-                               a.sym_den_literal, words[1], s[1], z[1]);
+                               a.sym_den_literal, words, s, z);
   long long go = ((long long)bh * a.capacity / G + tg) * D;            // (capacity is a multiple of G)
   uint32_t dc = dt * D + c;
   if (a.pages.table) {
     go = (store_row(a.pages, a.n_kv_heads, a.capacity, bh, (long long)(tg + dt) * G) / G) * D;
     dc = c;
   }
-  uint32_t* dst = reinterpret_cast<uint32_t*>(j.codes) + go * W + dc * W;   // 2 W words from an even channel: 8-byte aligned
+  uint32_t* dst = reinterpret_cast<uint32_t*>(j.codes) + go * W + dc * W;
 #pragma unroll
-  for (int i = 0; i < W; ++i) {
-    const uint32_t w0 = 2 * i < W ? words[0][2 * i] : words[1][2 * i - W];
-    const uint32_t w1 = 2 * i + 1 < W ? words[0][2 * i + 1] : words[1][2 * i + 1 - W];
-    *reinterpret_cast<uint2*>(dst + 2 * i) = uint2{w0, w1};
-  }
-  auto pair = [](__half lo, __half hi) { return (uint32_t)__half_as_ushort(lo) | ((uint32_t)__half_as_ushort(hi) << 16); };
-  *reinterpret_cast<uint32_t*>(j.scales + go + dc) = pair(s[0], s[1]);
-  if (j.zeros) *reinterpret_cast<uint32_t*>(j.zeros + go + dc) = pair(z[0], z[1]);
+  for (int i = 0; i < W; ++i) dst[i] = words[i];
+  (j.scales + go)[dc] = s;
+  if (j.zeros) (j.zeros + go)[dc] = z;
 }
 
 // Rows (store rows) of a job that come from the ring and from the new tokens.
@@ -182,7 +172,7 @@ __device__ __forceinline__ void ring_units(const QuantArgs& a, const QuantTensor
   if (j.form == kPerToken) {
     for (uint32_t r = 64u * wave; r < rows; r += 256u) per_token_unit<BITS, true>(a, j, bh, row0 + r, row0 + rows, slice);
   } else {
-    constexpr uint32_t PER = 128u / G;                   // groups a wavefront takes
+    constexpr uint32_t PER = 64u / G;                    // groups a wavefront takes
     const uint32_t tg0 = row0 / G, n = rows / G;
     for (uint32_t t = PER * wave; t < n; t += 4u * PER) per_channel_unit<BITS, true>(a, j, bh, tg0 + t, tg0 + n, slice);
   }
@@ -218,10 +208,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 3
   u -= BH * p.per_bh_t;
   if (u < BH * p.per_bh_c) {
     const QuantTensorJob j = pick_job(a, INNER ? 1 : 0);
-    const uint32_t bh = u / p.per_bh_c, tg = (uint32_t)((j.row_begin + split_rows(a, j).ring) / G) + (u - bh * p.per_bh_c);
-    if (j.bits == 2) per_channel_unit<2, false>(a, j, bh, tg, tg + 1u, 0u);
-    else if (j.bits == 3) per_channel_unit<3, false>(a, j, bh, tg, tg + 1u, 0u);
-    else per_channel_unit<4, false>(a, j, bh, tg, tg + 1u, 0u);
+    const uint32_t bh = u / p.per_bh_c, at = u - bh * p.per_bh_c, part = at & 1u;
+    const uint32_t tg = (uint32_t)((j.row_begin + split_rows(a, j).ring) / G) + (at >> 1);
+    if (j.bits == 2) per_channel_unit<2, false>(a, j, bh, tg, tg + 1u, part);
+    else if (j.bits == 3) per_channel_unit<3, false>(a, j, bh, tg, tg + 1u, part);
+    else per_channel_unit<4, false>(a, j, bh, tg, tg + 1u, part);
   }
 }
 
@@ -229,7 +220,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 3
 
 #if INNERQ_OWNERS_GROUP == 32
 // One chunk measured in all forms, 2800 shapes of 1 to 2048 sequence-heads, 2 to 32768 tokens, windows of 32 to 16384, both
-// group sizes: the rule is 0.7 % (geometric mean) behind the best form of each.
+// group sizes (before the owners took a channel a lane): the rule was 0.7 % (geometric mean) behind the best form of each.
 AppendForm append_form(const QuantArgs& a) {
   if (a.n_dev) return AppendForm::kLanes8;
   long long most = 0, slice_rows = 0;
@@ -257,18 +248,12 @@ AppendForm append_form(const QuantArgs& a) {
   }
   // Owners of ring slices: where per-channel groups leave a ring (a chunk that only moves keys on is a short chain in
   // either form: 16 heads, 8 tokens 5.0 us in two launches of eight lanes a group, 5.3 here), at most two owners a
-  // compute unit (64 x 8 heads, 8 tokens 17 us here, 7.7 there) and rings of up to 448 rows (above).  At G = 64 one
-  // lane's chain through both variants of a group is longer than the second launch it saves while the chip has room
-  // (8 heads, 512 tokens 12.5 us against 11.3; 32 heads 13.2 against 13.1), and behind a large chunk it is the tail
-  // (128 heads, 3000 tokens 75 against 60): hybrid groups from 32 sequence-heads on and up to 131072 groups only.
+  // compute unit (64 x 8 heads, 8 tokens 17 us here, 7.7 there) and rings of up to 448 rows (above).  At G = 64 a lane's chain
+  // through both variants of a group is the tail behind a large chunk (128 heads, 3000 tokens 65 us here, 50 there; 32 heads, 4000
+  // 28 and 23; 8 heads, 4000 10.8 and 11.9; 100 8.0 and 10.6; 512 8.5 and 10.3): hybrid groups up to 131072 groups only.
   const long long heads = (long long)a.batch * a.n_kv_heads, owners = 2 * heads * (D / a.group);
   const bool few_short = narrow && owners <= 2LL * compute_units() && slice_rows <= 448;
-  if (few_short && shared && ring_values && (a.group == 32 || !hybrid || (heads >= 32 && most <= 131072)))
-    return AppendForm::kRingOwners;
-  // Long prompts with key factors, G = 32: the units of new rows here take 2 to 5 % less than consecutive groups in
-  // consecutive lanes (8 heads x 131072 tokens, 2 bits 153 us against 159; 8 x 8 x 32768 294 against 302, 4 bits 317 against
-  // 327; 32 x 16384 (2 M groups) 82.4 against 82.1; 8 x 8 x 4096 38.7 against 37.2; G = 64 5 to 20 % more).
-  if (few_short && a.group == 32 && a.job[0].form == kPerToken && a.job[0].normalise && most >= (1LL << 22))
+  if (few_short && shared && ring_values && (a.group == 32 || !hybrid || most <= 131072))
     return AppendForm::kRingOwners;
   // A group a lane, or spread over eight: the chain of a lane's group is the longer one, but the per-channel groups
   // beside it are in one lane each anyway, so eight lanes only pay while the chip is nearly empty (a first prompt of 8
@@ -289,7 +274,7 @@ hipError_t launch_quantize_owners_g64(const QuantArgs& a, hipStream_t stream) {
   const bool inner = a.job[0].form == kPerToken;
   const long long BH = (long long)a.batch * a.n_kv_heads;
   const QuantTensorJob &jt = a.job[inner ? 0 : 1], &jc = a.job[inner ? 1 : 0];
-  const long long per_bh_t = (split_rows(a, jt).fresh + kUnitRows - 1) / kUnitRows, per_bh_c = split_rows(a, jc).fresh / G;
+  const long long per_bh_t = (split_rows(a, jt).fresh + kUnitRows - 1) / kUnitRows, per_bh_c = split_rows(a, jc).fresh / G * 2;
   const long long ring_groups = 2 * BH * kSlices, blocks = (BH * (per_bh_t + per_bh_c) + 3) / 4;
   const OwnersPlan p = {(uint32_t)ring_groups, (uint32_t)per_bh_t, (uint32_t)per_bh_c};
   const unsigned grid = (unsigned)(ring_groups + blocks);

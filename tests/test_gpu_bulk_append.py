@@ -243,3 +243,23 @@ def test_bytes_do_not_depend_on_the_call(env, kind, bits, group, mode, bad):
     for name, buf in chunk.buffers.items():
         if buf is not None and not name.endswith("recent"):               # (a ring's spare slots hold older tokens)
             assert torch.equal(buf, steps.buffers[name]), name
+
+
+@pytest.mark.parametrize("kind,bits,heads,chunks", [
+    (orc.KIND_INNER, 4, 1, (150, 64, 200)), (orc.KIND_INNER, 3, 9, (200, 70, 131)), (orc.KIND_OUTER, 2, 5, (133, 100, 300)),
+    (orc.KIND_INNER, 2, 64, (150, 1024, 1025)),           # 131072 groups and 128 more: owners, then two launches
+])
+def test_owners_of_hybrid_groups_of_64(env, kind, bits, heads, chunks):
+    torch, iq = env
+    n = sum(chunks)
+    w = wl.Workload("b", 1, heads, heads, 128, n, bits, 64, 4, 64, k_mode=orc.HYBRID, v_mode=orc.HYBRID)
+    o = oracle_config(w, kind=kind)
+    rng = np.random.default_rng(n + bits)
+    K, V = (rng.standard_normal((1, heads, n, 128)).astype(np.float16) for _ in range(2))
+    g = iq.allocate_cache(gpu_config(o))
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    at = 0
+    for c in chunks:
+        iq.innerq_quantize_append(g, dev(K[:, :, at:at + c]), dev(V[:, :, at:at + c]))
+        at += c
+    assert_cache_equal(g, orc.cache_init_prefill(o, K, V), o)
