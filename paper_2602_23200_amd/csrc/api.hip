@@ -225,6 +225,7 @@ static QuantArgs quant_args(const innerq_config_t* cfg, const innerq_cache_t* ca
   a.inv_norm = k_inv_norm;
   a.batch = cfg->batch; a.n_kv_heads = cfg->n_kv_heads; a.group = cfg->group;
   a.w_sink = cfg->w_sink; a.sym_den_literal = cfg->sym_denominator;
+  a.channel_lanes = 1;
   a.capacity = cfg->capacity_tokens; a.n_old = n0; a.t_new = t_new;
   a.w_recent = cfg->w_recent; a.n_dev = nullptr; a.n_dev_out = nullptr;
   a.pages = pages_of(*cfg, *cache);

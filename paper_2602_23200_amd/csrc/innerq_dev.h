@@ -116,6 +116,7 @@ struct QuantArgs {
   QuantTensorJob job[2];          // K, V
   const float* inv_norm;          // [Hk][d] or null
   int batch, n_kv_heads, group, w_sink, sym_den_literal;
+  int channel_lanes;              // lanes that share a per-channel group: 1, or 8 (set by the launch)
   long long capacity, n_old, t_new;
   // per-sequence token counts (device, [B], the count before the step), or null: a.n_old holds for all;
   // n_dev_out: the caller's counters, advanced by one per sequence by the append

@@ -173,14 +173,14 @@ __device__ __forceinline__ uint32_t ternary_distances(uint32_t x, uint32_t scale
 struct NoDistances {};                                   // (the sum forms its own)
 
 // CLAMP: codes are clamped, and `mode` (else: MODE) is what chooses between the two variants.
-// Where both variants compete and no code is clamped, the asymmetric differences are taken as (x - mn) - Sa code, one operation
+// FAST, where both variants compete and no code is clamped: the asymmetric differences are taken as (x - mn) - Sa code, one operation
 // less than x - (Sa code + mn).  Their sum differs in its last bits, and is only compared with the other one: the result says
 // whether that could change the answer (the codes of both variants are right in any case).  most: the largest magnitude.
-template <int G, int BITS, int MODE, bool CLAMP, typename X, typename Dist>
+template <int G, int BITS, int MODE, bool CLAMP, bool FAST, typename X, typename Dist>
 __device__ __forceinline__ bool bulk_codes(X x, Dist dist, float mn, float most, __half Sa, __half Ss, int mode,
                                            uint32_t (&words)[G * BITS / 32], __half& scale, __half& zero) {
   constexpr bool ASYM = MODE != INNERQ_SYM, SYM = MODE != INNERQ_ASYM, BOTH = ASYM && SYM;
-  constexpr bool TERNARY = BITS == 2 && !CLAMP, SHORT = BOTH && !CLAMP;
+  constexpr bool TERNARY = BITS == 2 && !CLAMP, SHORT = BOTH && !CLAMP && FAST;
   constexpr int HALF = 1 << (BITS - 1), QMAX = (1 << BITS) - 1;
   const float Saf = h2f(Sa), Ssf = h2f(Ss);
   Reciprocal ra = {0.f, 0.f}, rs = {0.f, 0.f};
@@ -210,7 +210,7 @@ __device__ __forceinline__ bool bulk_codes(X x, Dist dist, float mn, float most,
       if constexpr (TERNARY) {
         const float t = half_times_plus(v, r_tern, 12582912.0f);
         pt.add(i, t);
-        if constexpr (SHORT && !__is_same(Dist, NoDistances)) {
+        if constexpr (BOTH && !__is_same(Dist, NoDistances)) {
           es = __builtin_fmaf(value_of(dist(i)), one, es);
           continue;
         }
@@ -242,7 +242,9 @@ __device__ __forceinline__ bool bulk_codes(X x, Dist dist, float mn, float most,
 
 // The group's fields, scale and zero-point from its values x(i) and their minimum and maximum.  dist: the distances of a symmetric 2-bit
 // group whose denominator is 1 (others make no use of them), or NoDistances.
-template <int G, int BITS, typename X, typename Dist>
+// FAST: the shorter error sum, for launches that fill the chip many times over.  (One wavefront in a few hundred goes through the
+// general form too, the tail of a short launch: 1 M groups of 4 bits 19.6 us and 19.8 with it, 64000 5.4 and 6.4, G = 64 8.1 and 10.2.)
+template <int G, int BITS, bool FAST, typename X, typename Dist>
 __device__ __forceinline__ void quantize_group_bulk(X x, Dist dist, float mn, float mx, int mode, int sym_den_literal,
                                                     uint32_t (&words)[G * BITS / 32], __half& scale, __half& zero) {
   constexpr int QMAX = (1 << BITS) - 1;
@@ -281,9 +283,9 @@ __device__ __forceinline__ void quantize_group_bulk(X x, Dist dist, float mn, fl
     }
   }
   if (!redo && mode == INNERQ_HYBRID)
-    redo = __builtin_amdgcn_ballot_w64(bulk_codes<G, BITS, INNERQ_HYBRID, false>(x, dist, mn, fmaxf(fabsf(mn), fabsf(mx)), Sa, Ss, mode, words, scale, zero)) != 0;
-  else if (!redo && mode == INNERQ_SYM) bulk_codes<G, BITS, INNERQ_SYM, false>(x, NoDistances{}, mn, 0.f, Sa, Ss, mode, words, scale, zero);
-  else if (!redo) bulk_codes<G, BITS, INNERQ_ASYM, false>(x, NoDistances{}, mn, 0.f, Sa, Ss, mode, words, scale, zero);
+    redo = __builtin_amdgcn_ballot_w64(bulk_codes<G, BITS, INNERQ_HYBRID, false, FAST>(x, dist, mn, fmaxf(fabsf(mn), fabsf(mx)), Sa, Ss, mode, words, scale, zero)) != 0;
+  else if (!redo && mode == INNERQ_SYM) bulk_codes<G, BITS, INNERQ_SYM, false, false>(x, NoDistances{}, mn, 0.f, Sa, Ss, mode, words, scale, zero);
+  else if (!redo) bulk_codes<G, BITS, INNERQ_ASYM, false, false>(x, NoDistances{}, mn, 0.f, Sa, Ss, mode, words, scale, zero);
   if (redo) {
     // The general form: clamped codes, the sums as the oracle takes them (on normal draws one wavefront in a hundred to a
     // thousand gets here).  Its inputs are opaque: whatever the compiler shared with the forms above, conversions first
@@ -295,7 +297,7 @@ __device__ __forceinline__ void quantize_group_bulk(X x, Dist dist, float mn, fl
       asm volatile("" : "+v"(v.w));
       return v;
     };
-    bulk_codes<G, BITS, INNERQ_HYBRID, true>(again, NoDistances{}, mn, 0.f, __ushort_as_half((unsigned short)(scales & 0xffffu)),
+    bulk_codes<G, BITS, INNERQ_HYBRID, true, false>(again, NoDistances{}, mn, 0.f, __ushort_as_half((unsigned short)(scales & 0xffffu)),
                                              __ushort_as_half((unsigned short)(scales >> 16)), mode, words, scale, zero);
   }
 }
@@ -429,7 +431,7 @@ __device__ __forceinline__ void window_copy(const QuantArgs& a, const QuantTenso
 
 // Group g of one row of the per-token form in one lane: its values at src (scaled if they are new ones and the job
 // says so), its packed fields, scale and zero-point to store row lin + dr (dr apart: lin may be uniform).
-template <int G, int BITS>
+template <int G, int BITS, bool FAST>
 __device__ __forceinline__ void per_token_group(const QuantArgs& a, const QuantTensorJob& j, const __half* src, bool fresh,
                                                 uint32_t bh, uint32_t g, long long lin, uint32_t dr) {
   constexpr int GPR = kHeadDim / G, W = G * BITS / 32;
@@ -454,12 +456,12 @@ __device__ __forceinline__ void per_token_group(const QuantArgs& a, const QuantT
   uint32_t words[W];
   __half s, z;
   auto value = [&](int i) { return HalfRef{x[i / 2], (i & 1) != 0}; };
-  if constexpr (BITS == 2) {
+  if constexpr (BITS == 2 && FAST) {
     const uint32_t less = mn ^ 0x80008000u, most = pair_max(mx, less, less) & 0xffffu, scales = most | most << 16;
-    quantize_group_bulk<G, BITS>(value, [&](int i) { return HalfRef{ternary_distances(x[i / 2], scales), (i & 1) != 0}; }, half_lo(mn), half_lo(mx), j.mode,
+    quantize_group_bulk<G, BITS, FAST>(value, [&](int i) { return HalfRef{ternary_distances(x[i / 2], scales), (i & 1) != 0}; }, half_lo(mn), half_lo(mx), j.mode,
                                  a.sym_den_literal, words, s, z);
   } else {
-    quantize_group_bulk<G, BITS>(value, NoDistances{}, half_lo(mn), half_lo(mx), j.mode, a.sym_den_literal, words, s, z);
+    quantize_group_bulk<G, BITS, FAST>(value, NoDistances{}, half_lo(mn), half_lo(mx), j.mode, a.sym_den_literal, words, s, z);
   }
   // a row is one plane of LB-bit fields over all channels (3-bit: followed by the plane of high bits)
   constexpr int LB = BITS == 3 ? 2 : BITS;

@@ -16,8 +16,9 @@ __global__ void __launch_bounds__(256) window_copy_kernel(QuantArgs a) {
   window_copy(a, j, (long long)blockIdx.x * blockDim.x + threadIdx.x);
 }
 
-template <int G, int LANES>
-__global__ void __launch_bounds__(256) quantize_kernel(QuantArgs a, long long copy_from) {
+// (Registers: a long prompt waits for memory, and the copies into the windows in a short one for room beside the quantising work-groups.)
+template <int G, int LANES, bool FAST>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 32 ? 6 : 4))) quantize_kernel(QuantArgs a, long long copy_from) {
   // Thread indices below copy_from quantise evicted tokens, those from copy_from on write the
   // new tokens into the windows (one launch; only used when no new token lands in a ring slot
   // that this call still has to read).  copy_from < 0: no copy work in this launch.
@@ -27,9 +28,9 @@ __global__ void __launch_bounds__(256) quantize_kernel(QuantArgs a, long long co
     window_copy(a, j, idx - copy_from);
     return;
   }
-  if (j.bits == 2) quantize_rows<G, 2, LANES, false>(a, j, idx);
-  else if (j.bits == 3) quantize_rows<G, 3, LANES, false>(a, j, idx);
-  else quantize_rows<G, 4, LANES, false>(a, j, idx);
+  if (j.bits == 2) quantize_rows<G, 2, LANES, false, FAST>(a, j, idx);
+  else if (j.bits == 3) quantize_rows<G, 3, LANES, false, FAST>(a, j, idx);
+  else quantize_rows<G, 4, LANES, false, FAST>(a, j, idx);
 }
 
 // The same launch with the log-sum-exp merge of an attention call riding along: the last
@@ -51,9 +52,9 @@ __global__ void __launch_bounds__(256) quantize_merge_kernel(QuantArgs a, long l
     window_copy(a, j, idx - copy_from);
     return;
   }
-  if (j.bits == 2) quantize_rows<G, 2, 8, true>(a, j, idx);
-  else if (j.bits == 3) quantize_rows<G, 3, 8, true>(a, j, idx);
-  else quantize_rows<G, 4, 8, true>(a, j, idx);
+  if (j.bits == 2) quantize_rows<G, 2, 8, true, false>(a, j, idx);
+  else if (j.bits == 3) quantize_rows<G, 3, 8, true, false>(a, j, idx);
+  else quantize_rows<G, 4, 8, true, false>(a, j, idx);
 }
 
 // Threads the quantise work of one tensor job needs.
@@ -63,7 +64,7 @@ long long quantize_threads(const QuantArgs& a, const QuantTensorJob& j) {
   const long long rows = j.row_end - j.row_begin;
   if (rows <= 0) return 0;
   if (j.form == kPerToken) return BH * rows * (kHeadDim / G) * LANES;
-  if (j.form == kPerChannel) return BH * (rows / G) * kHeadDim;
+  if (j.form == kPerChannel) return BH * (rows / G) * kHeadDim * a.channel_lanes;
   return BH * rows * (kHeadDim / 8);
 }
 
@@ -75,8 +76,18 @@ hipError_t window_copies(const QuantArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <int G, int LANES>
-hipError_t launch_quantize_t(const QuantArgs& a, hipStream_t stream, const AttnArgs* merge) {
+template <int G, int LANES, bool FAST = false>
+hipError_t launch_quantize_t(QuantArgs a, hipStream_t stream, const AttnArgs* merge) {
+  // Per-channel groups of the form of eight lanes, spread over eight too: a lane's chain of a group is the longest of a short launch (us, one
+  // lane -> eight: one value group of 8 heads G = 32 6.0 -> 3.8, G = 64 9.1 -> 4.2; steps at which one leaves its ring, 8 x 8 heads, 13.8 ->
+  // 12.2, G = 64 16.7 -> 12.3; 3 bits, symmetric, 14.6 -> 13.2), up to 256 sequence-heads (512: 34.0 -> 36.9), 64 of groups of one variant, whose
+  // chain is half as long (128: 18.2 -> 20.4).  Where the counts live on the device the launch holds a group of every sequence, and mostly
+  // none leaves: 16 sequences of 8 heads 27.6 -> 26.5 where some do, 19.7 -> 20.1 where none does; 4 sequences 14.2 -> 14.4, 32 at G = 64
+  // 23.4 -> 24.9.
+  const int mode = a.job[a.job[0].form == kPerChannel ? 0 : 1].mode;
+  const long long bh = (long long)a.batch * a.n_kv_heads;
+  const bool spread = bh <= (mode == INNERQ_HYBRID ? 256 : 64) && (!a.n_dev || (a.batch >= 16 && G == 32));
+  a.channel_lanes = LANES == 8 && spread ? 8 : 1;
   const long long kthreads = quantize_threads<G, LANES>(a, a.job[0]), vthreads = quantize_threads<G, LANES>(a, a.job[1]);
   const long long threads = kthreads > vthreads ? kthreads : vthreads, cthreads = copy_threads(a);
   if (threads >= (1LL << 32)) return hipErrorInvalidValue;   // (device index arithmetic is 32-bit)
@@ -101,12 +112,12 @@ hipError_t launch_quantize_t(const QuantArgs& a, hipStream_t stream, const AttnA
   if (threads > 0 && disjoint) {
     const long long qthreads = ((threads + 255) / 256) * 256;
     dim3 grid((unsigned)((qthreads + cthreads + 255) / 256), 2);
-    quantize_kernel<G, LANES><<<grid, 256, 0, stream>>>(a, qthreads);
+    quantize_kernel<G, LANES, FAST><<<grid, 256, 0, stream>>>(a, qthreads);
     return hipGetLastError();
   }
   if (threads > 0) {
     dim3 grid((unsigned)((threads + 255) / 256), 2);
-    quantize_kernel<G, LANES><<<grid, 256, 0, stream>>>(a, -1);
+    quantize_kernel<G, LANES, FAST><<<grid, 256, 0, stream>>>(a, -1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -250,7 +261,17 @@ hipError_t launch_quantize(const QuantArgs& a, hipStream_t stream, const AttnArg
   if (a.group != 32 && a.group != 64) return hipErrorInvalidValue;
   const AppendForm form = merge ? AppendForm::kLanes8 : append_form(a);
   if (form == AppendForm::kRingOwners) return launch_quantize_owners(a, stream);
-  if (form == AppendForm::kLane) return a.group == 32 ? launch_quantize_t<32, 1>(a, stream, nullptr) : launch_quantize_t<64, 1>(a, stream, nullptr);
+  if (form == AppendForm::kLane) {
+    // (the shorter error sum from 2 M groups on: 8 x 8 heads x 32k tokens (8.4 M) 2 bits 259 us -> 250, 16k 131 -> 128, 8k (1 M) the same)
+    long long most = 0;
+    for (int w = 0; w < 2; ++w) {
+      const long long groups = (long long)a.batch * a.n_kv_heads * (a.job[w].row_end - a.job[w].row_begin) * (kHeadDim / a.group);
+      most = groups > most ? groups : most;
+    }
+    const bool fast = most >= (1LL << 21);
+    if (a.group == 32) return fast ? launch_quantize_t<32, 1, true>(a, stream, nullptr) : launch_quantize_t<32, 1>(a, stream, nullptr);
+    return fast ? launch_quantize_t<64, 1, true>(a, stream, nullptr) : launch_quantize_t<64, 1>(a, stream, nullptr);
+  }
   return a.group == 32 ? launch_quantize_t<32, 8>(a, stream, merge) : launch_quantize_t<64, 8>(a, stream, merge);
 }
 

@@ -52,7 +52,7 @@ __device__ __forceinline__ void per_token_unit(const QuantArgs& a, const QuantTe
     lin = store_row(a.pages, a.n_kv_heads, a.capacity, bh, row0 + r);
     dr = 0u;
   }
-  per_token_group<G, BITS>(a, j, src, !RING || fresh, bh, g, lin, dr);
+  per_token_group<G, BITS, false>(a, j, src, !RING || fresh, bh, g, lin, dr);
 }
 
 // ---- per-channel form ----------------------------------------------------------------------
@@ -98,7 +98,7 @@ __device__ __forceinline__ void per_channel_unit(const QuantArgs& a, const Quant
   uint32_t mn, mx, words[W];
   pair_range(x, mn, mx);
   __half s, z;
-  quantize_group_bulk<G, BITS>([&](int i) { return HalfRef{x[i], false}; }, NoDistances{}, half_lo(mn), half_lo(mx), j.mode,
+  quantize_group_bulk<G, BITS, false>([&](int i) { return HalfRef{x[i], false}; }, NoDistances{}, half_lo(mn), half_lo(mx), j.mode,
                                a.sym_den_literal, words, s, z);
   long long go = ((long long)bh * a.capacity / G + tg) * D;            // (capacity is a multiple of G)
   uint32_t dc = dt * D + c;
@@ -255,13 +255,13 @@ AppendForm append_form(const QuantArgs& a) {
   const bool few_short = narrow && owners <= 2LL * compute_units() && slice_rows <= 448;
   if (few_short && shared && ring_values && (a.group == 32 || !hybrid || most <= 131072))
     return AppendForm::kRingOwners;
-  // A group a lane, or spread over eight: the chain of a lane's group is the longer one, but the per-channel groups
-  // beside it are in one lane each anyway, so eight lanes only pay while the chip is nearly empty (a first prompt of 8
-  // heads, 133 tokens 3.3 us against 3.9; 700 (18176 groups) 5.5 against 4.9; 4000 15.8 against 7.7), or, with nothing
-  // but keys, as long as there are wavefronts to spare: a single token of 8192 heads (32768 groups) 7.0 against 5.9, of
-  // 2048 heads the same; beside the second launch of a chunk longer (2048 heads, 2 tokens (16384 groups) 7.5 against
+  // A group a lane, or spread over eight: the chain of a lane's group is the longer one, but eight lanes are eight times the
+  // wavefronts (a first prompt of hybrid groups, G = 32, 4 bits: 4 heads, 600 tokens (7488 groups) 4.2 us against 4.7, 16 heads, 300
+  // (10752) 5.1 against 4.8; G = 64: 8 heads, 600 (7488) 4.8 against 6.4, 1000 (13888) 6.3 against 6.0; 3-bit symmetric ones 4.2 against 4.0 at
+  // 5376), or, with nothing but keys, as long as there are wavefronts to spare: a single token of 8192 heads (32768 groups) 7.0
+  // against 5.9, of 2048 heads the same; beside the second launch of a chunk longer (2048 heads, 2 tokens (16384 groups) 7.5 against
   // 9; 8 tokens 10.2 against 10.5).
-  return most < (values ? 4096 : shared ? 65536 : 16384) ? AppendForm::kLanes8 : AppendForm::kLane;
+  return most < (values ? (hybrid ? 8192 : 4096) : shared ? 65536 : 16384) ? AppendForm::kLanes8 : AppendForm::kLane;
 }
 
 hipError_t launch_quantize_owners_g64(const QuantArgs& a, hipStream_t stream);

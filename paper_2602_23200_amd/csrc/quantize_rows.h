@@ -94,7 +94,8 @@ __device__ inline uint32_t quantize_group_lanes(const float (&x)[G / 8], int sub
   const int last = ((int)(threadIdx.x & 63u) & ~7) + 7;
   ea = __shfl(ea, last);
   es = __shfl(es, last);
-  const bool asym = (mode == INNERQ_ASYM) || (mode == INNERQ_HYBRID && ea < es);
+  const bool asym = (mode == INNERQ_ASYM) | ((mode == INNERQ_HYBRID) & (ea < es));
+  // (bitwise: from the form with a branch clang 22 made code that kept the symmetric scale of asymmetric groups, per-channel form, G = 64)
   scale = asym ? __hneg(Sa) : Ss;
   zero = asym ? __float2half_rn(mn) : __float2half_rn(0.f);
   constexpr int LB = BITS == 3 ? 2 : BITS;             // bits per field of the (low) plane
@@ -159,7 +160,7 @@ __device__ __forceinline__ void per_token_group_lanes(const QuantArgs& a, const 
 }
 
 // Channel c of token-group tg of the store (per-channel form).  STEP: of a call with at most one new token.
-template <int G, int BITS, bool STEP>
+template <int G, int BITS, bool STEP, bool FAST>
 __device__ __forceinline__ void per_channel_group(const QuantArgs& a, const QuantTensorJob& j, long long bh, long long tg,
                                                   int c, long long n_old) {
   constexpr int W = G * BITS / 32;
@@ -192,7 +193,7 @@ __device__ __forceinline__ void per_channel_group(const QuantArgs& a, const Quan
   uint32_t mn, mx, words[W];
   pair_range(x, mn, mx);
   __half s, z;
-  quantize_group_bulk<G, BITS>([&](int i) { return HalfRef{x[i], false}; }, NoDistances{}, half_lo(mn), half_lo(mx), j.mode,
+  quantize_group_bulk<G, BITS, FAST>([&](int i) { return HalfRef{x[i], false}; }, NoDistances{}, half_lo(mn), half_lo(mx), j.mode,
                                a.sym_den_literal, words, s, z);
   const long long go = (store_row(a.pages, a.n_kv_heads, a.capacity, bh, tg * G) / G) * kHeadDim + c;
   uint32_t* dst = reinterpret_cast<uint32_t*>(j.codes) + go * W;
@@ -202,9 +203,45 @@ __device__ __forceinline__ void per_channel_group(const QuantArgs& a, const Quan
   if (j.zeros) j.zeros[go] = z;
 }
 
+// Lane `sub` of the eight of channel c of token-group tg of the store (per-channel form): tokens G / 8 sub on.
+template <int G, int BITS>
+__device__ __forceinline__ void per_channel_group_lanes(const QuantArgs& a, const QuantTensorJob& j, long long bh, long long tg,
+                                                        int c, int sub, long long n_old) {
+  constexpr int E = G / 8, W = G * BITS / 32;
+  constexpr int LB = BITS == 3 ? 2 : BITS, LPW = 32 / (E * LB);
+  const float inv = j.normalise ? a.inv_norm[mod32(bh, a.n_kv_heads) * kHeadDim + c] : 1.f;
+  const long long t0 = a.w_sink + tg * G + sub * E;    // the lane's first token
+  const __half* fresh = j.x_new + ((bh * a.t_new) + (t0 - n_old)) * kHeadDim + c;     // (meaningful from token n_old on)
+  const __half* ring = j.ring + bh * j.slots * kHeadDim + c;
+  uint32_t slot = mod32(t0, j.slots);
+  __half raw[E];
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    raw[i] = *(t0 + i >= n_old ? fresh + i * kHeadDim : ring + slot * kHeadDim);
+    slot = slot + 1u == (uint32_t)j.slots ? 0u : slot + 1u;
+  }
+  float x[E];
+#pragma unroll
+  for (int i = 0; i < E; ++i) x[i] = h2f(t0 + i >= n_old && j.normalise ? scaled_half(h2f(raw[i]), inv) : raw[i]);
+  __half s, z;
+  uint32_t word_hi;
+  const uint32_t word = quantize_group_lanes<G, BITS>(x, sub, j.mode, a.sym_den_literal, s, z, word_hi);
+  const long long go = (store_row(a.pages, a.n_kv_heads, a.capacity, bh, tg * G) / G) * kHeadDim + c;
+  uint32_t* dst = reinterpret_cast<uint32_t*>(j.codes) + go * W;
+  if (sub % LPW == 0) dst[sub / LPW] = word;
+  if constexpr (BITS == 3) {
+    constexpr int LPH = 32 / E;
+    if (sub % LPH == 0) dst[G / 16 + sub / LPH] = word_hi;
+  }
+  if (sub == 0) {
+    j.scales[go] = s;
+    if (j.zeros) j.zeros[go] = z;
+  }
+}
+
 // The quantise work of thread idx of tensor job j (keys and values may have different widths).  LANES: that share a
-// per-token group (8, or 1).  STEP: of a call with at most one new token.
-template <int G, int BITS, int LANES, bool STEP>
+// per-token group (8, or 1).  STEP: of a call with at most one new token.  FAST: see quantize_group_bulk.
+template <int G, int BITS, int LANES, bool STEP, bool FAST>
 __device__ __forceinline__ void quantize_rows(const QuantArgs& a, const QuantTensorJob& j, long long idx) {
   const long long n_rows = j.row_end - j.row_begin;
   if (n_rows <= 0) return;
@@ -220,7 +257,7 @@ __device__ __forceinline__ void quantize_rows(const QuantArgs& a, const QuantTen
     const long long bh = div32(idx / GPR, n_rows), row = j.row_begin + (idx / GPR - bh * n_rows);
     bool from_new;
     const __half* src = token_row(j, a, a.n_old, bh, a.w_sink + row, from_new) + g * G;
-    per_token_group<G, BITS>(a, j, src, from_new, (uint32_t)bh, g, store_row(a.pages, a.n_kv_heads, a.capacity, bh, row), 0u);
+    per_token_group<G, BITS, FAST>(a, j, src, from_new, (uint32_t)bh, g, store_row(a.pages, a.n_kv_heads, a.capacity, bh, row), 0u);
   } else if (j.form == kPerToken) {
     // 8 lanes per group, G/8 consecutive channels each
     constexpr int GPR = kHeadDim / G;                    // groups per row
@@ -237,13 +274,22 @@ __device__ __forceinline__ void quantize_rows(const QuantArgs& a, const QuantTen
     per_token_group_lanes<G, BITS>(a, j, bh, row, g, sub, token, from_new);
   } else if (j.form == kPerChannel) {
     const long long n_groups = n_rows / G;
+    if (LANES == 8 && a.channel_lanes == 8) {
+      if (idx >= BH * n_groups * kHeadDim * 8) return;
+      const int sub = (int)(idx % 8), c = (int)(idx / 8 % kHeadDim);
+      const long long bh = div32(idx / (8 * kHeadDim), n_groups);
+      long long n_old = a.n_old, row_begin = j.row_begin;
+      if (a.n_dev && !sequence_rows(a, j, bh, n_old, row_begin)) return;
+      per_channel_group_lanes<G, BITS>(a, j, bh, row_begin / G + (idx / (8 * kHeadDim) - bh * n_groups), c, sub, n_old);
+      return;
+    }
     if (idx >= BH * n_groups * kHeadDim) return;
     const int c = (int)(idx % kHeadDim);
     const long long bh = div32(idx / kHeadDim, n_groups);
     long long n_old = a.n_old, row_begin = j.row_begin;
     if (a.n_dev && !sequence_rows(a, j, bh, n_old, row_begin)) return;
     const long long tg = row_begin / G + (idx / kHeadDim - bh * n_groups);   // token-group index in the store
-    per_channel_group<G, BITS, STEP>(a, j, bh, tg, c, n_old);
+    per_channel_group<G, BITS, STEP, FAST>(a, j, bh, tg, c, n_old);
   } else {
     // fp16 "store": copy the rows, 8 halfs per thread
     constexpr int CPR = kHeadDim / 8;

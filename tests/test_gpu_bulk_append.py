@@ -263,3 +263,28 @@ def test_owners_of_hybrid_groups_of_64(env, kind, bits, heads, chunks):
         iq.innerq_quantize_append(g, dev(K[:, :, at:at + c]), dev(V[:, :, at:at + c]))
         at += c
     assert_cache_equal(g, orc.cache_init_prefill(o, K, V), o)
+
+
+@pytest.mark.parametrize("kind,bits,group,modes,heads", [
+    (orc.KIND_INNER, 2, 32, (orc.HYBRID, orc.HYBRID), 3), (orc.KIND_INNER, 3, 32, (orc.SYM, orc.HYBRID), 256), (orc.KIND_INNER, 4, 64, (orc.HYBRID, orc.ASYM), 64),
+    (orc.KIND_INNER, 3, 64, (orc.HYBRID, orc.HYBRID), 257), (orc.KIND_INNER, 2, 32, (orc.HYBRID, orc.SYM), 65),       # beyond the lines: a group a lane
+    (orc.KIND_OUTER, 4, 32, (orc.HYBRID, orc.SYM), 5), (orc.KIND_OUTER, 3, 64, (orc.ASYM, orc.HYBRID), 2),
+])
+@pytest.mark.parametrize("dist", ["normal", "ties", "denormal"])
+def test_channel_groups_over_eight_lanes(env, kind, bits, group, modes, heads, dist):
+    """Short appends and steps in which per-channel groups leave their ring: the groups spread over eight lanes, and in one."""
+    torch, iq = env
+    chunks = (4 + 32 + group - 1, 1, 2, group, 1)            # up to a group short of one token, then one at a time and a group at once
+    n = sum(chunks)
+    w = wl.Workload("c", 1, heads, heads, 128, n, bits, group, 4, 32, k_mode=modes[0], v_mode=modes[1])
+    o = oracle_config(w, kind=kind)
+    rng = np.random.default_rng(n + bits)
+    K, V = (values(rng, (1, heads, n, 128), dist) for _ in range(2))
+    inv = rng.uniform(0.3, 1.0, (heads, 128)).astype(np.float32)
+    g = iq.allocate_cache(gpu_config(o))
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    at = 0
+    for c in chunks:
+        iq.innerq_quantize_append(g, dev(K[:, :, at:at + c]), dev(V[:, :, at:at + c]), dev(inv))
+        at += c
+    assert_cache_equal(g, orc.cache_init_prefill(o, K, V, k_inv_norm=inv), o)
