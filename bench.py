@@ -216,7 +216,7 @@ def compare_kinds(torch, iq, hip, w, cfg, args, gen, inner_kernel_ms, stream):
            "outer_kernel_note": "the outer-grouped kernel is built like the inner-grouped one (stored fields masked in "
                                 "place as matrix operands, scales folded into the other operand once per group, "
                                 "zero-point terms as per-group constants): what separates the two is what the grouping "
-                                "forces (tables rebuilt per tile, the transposes)"}
+                                "forces (operands folded anew for every tile, the transposes)"}
     B, Hq, d = w.batch, w.n_q_heads, w.head_dim
     q = torch.randn((B, Hq, d), device="cuda", generator=gen).half()
     o = torch.empty((B, Hq, d), dtype=torch.float32, device="cuda")

@@ -137,8 +137,9 @@ struct AttnArgs;
 // this stream rides in the same launch (or, for the rare two-launch appends, goes first).
 hipError_t launch_quantize(const QuantArgs& a, hipStream_t stream, const AttnArgs* merge = nullptr);
 // How an append runs (the rule: append_form in quantize_owners.hip; launch_quantize routes by it):
-//   kLanes8      a per-token group spread over eight lanes (a decode step, short calls); the window copies in the same
-//                launch, or in a second one where a new token lands in a ring slot that the call still reads
+//   kLanes8      a per-token group spread over eight lanes (a decode step, short calls), a per-channel group too where it
+//                leaves a ring and the heads are few (QuantArgs::channel_lanes); the window copies in the same launch,
+//                or in a second one where a new token lands in a ring slot that the call still reads
 //   kLane        the same launches with a group a lane (prompts and large chunks)
 //   kRingOwners  a group a lane, and a work-group that owns a slice of a ring reads what leaves it and then writes what
 //                enters: one launch although slots are shared
