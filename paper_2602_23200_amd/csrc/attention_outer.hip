@@ -358,7 +358,7 @@ attention_outer_kernel(AttnArgs a, int n_both, int n_splits, WindowSet win) {
       if constexpr (ZV) vrange.add(cur.vz[t][0], cur.vz[t][NG / 2 - 1]);
     }
     const int shk = tile_shift(krange.magnitudes()), shv_tile = tile_shift(vrange.magnitudes());
-    const half2_t fk = pow2_half2(shk), fk_level = fk * level2;
+    const half2_t fk = pow2_half2(shk);
 
     // ---- scores (Eq. att:1)
     float4_t su[HWT][NH4], sz[NH4];
@@ -377,16 +377,17 @@ attention_outer_kernel(AttnArgs a, int n_both, int n_splits, WindowSet win) {
       u32x4 sw, zw;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const half2_t sn = as_half2(cur.ks[ks][i] & 0x7fff7fffu) * fk;
+        // (the level meets the normalised scale: 2^(b-1) 2^shk by itself is no fp16 number where a tile's scales are tiny or zero)
+        const half2_t signed_scale = as_half2(cur.ks[ks][i]) * fk;
         half2_t zn;
         if constexpr (ZK) {
           // the sign bit of a scale marks an asymmetric group, whose zero-point is stored; a symmetric
           // group stores +0 there and has Zeff = -2^(b-1) S
-          zn = __builtin_elementwise_fma(as_half2(cur.kz[ks][i]), fk, __builtin_elementwise_max(as_half2(cur.ks[ks][i]), zero2) * fk_level);
+          zn = __builtin_elementwise_fma(as_half2(cur.kz[ks][i]), fk, __builtin_elementwise_max(signed_scale, zero2) * level2);
         } else {
-          zn = as_half2(cur.ks[ks][i]) * fk_level;       // (no flags: the scales are not negative)
+          zn = signed_scale * level2;                    // (no flags: the scales are not negative)
         }
-        sw[i] = as_u32(sn);
+        sw[i] = as_u32(signed_scale) & 0x7fff7fffu;
         zw[i] = as_u32(zn);
       }
 #pragma unroll

@@ -47,3 +47,35 @@ def test_outer_attention(bits, group, batch, heads, quantised, modes, ramp):
     out = iq.innerq_decode_attention(g, spread(q), iq.allocate_workspace(g.cfg)).cpu().numpy()
     want = orc.decode_attention(o, orc.cache_init_prefill(o, K, V), q)
     assert max_rel_err(out, np.repeat(want, batch, 0) if one else want) <= TOL
+
+
+@pytest.mark.parametrize("what", ["keys all zero", "a tile of zero keys", "keys x 2^-12", "keys x 2^-16", "a tile of zero values", "values x 2^-12"])
+@pytest.mark.parametrize("k_mode", [orc.SYM, orc.ASYM, orc.HYBRID])
+@pytest.mark.parametrize("group,heads", [(32, (4, 1)), (64, (8, 1))])
+@pytest.mark.parametrize("bits", [2, 4])
+def test_zero_and_tiny_groups(bits, group, heads, k_mode, what):
+    """Tiles whose scales are all zero, or fp16 denormals: the power of two that normalises them is at its upper end (2^14, and
+    2^14 times the level 2^(b-1) is no fp16 number at 4 bits)."""
+    import torch
+    from paper_2602_23200_amd import binding as iq
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    n = 4 + 32 + 512 + 5
+    w = wl.Workload("z", 1, heads[0], heads[1], 128, n, bits, group, 4, 32, seed=bits + group, k_mode=k_mode, v_mode=orc.HYBRID)
+    o = oracle_config(w, kind=orc.KIND_OUTER)
+    K, V = wl.kv_full(w)
+    if what == "keys all zero":
+        K[:] = 0
+    elif what == "a tile of zero keys":
+        K[:, :, 4 + 128:4 + 256] = 0                         # one tile of 128 tokens, two of 64
+    elif what == "a tile of zero values":
+        V[:, :, 4 + 128:4 + 256] = 0
+    else:
+        x, shift = what.split(" x 2^")
+        (K if x == "keys" else V)[:] *= np.float16(2.0 ** int(shift))
+    q = wl.query(w)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    g = iq.allocate_cache(gpu_config(o))
+    iq.innerq_quantize_append(g, dev(K), dev(V))
+    out = iq.innerq_decode_attention(g, dev(q), iq.allocate_workspace(g.cfg)).cpu().numpy()
+    assert np.isfinite(out).all()
+    assert max_rel_err(out, orc.decode_attention(o, orc.cache_init_prefill(o, K, V), q)) <= TOL
