@@ -166,14 +166,16 @@ attention_outer_kernel(AttnArgs a, int n_both, int n_splits, WindowSet win) {
   __shared__ __attribute__((aligned(16))) unsigned char lds[kLdsBytes];
   // (The grid is (sequence-heads, window chunks and then token ranges): ranges next to each other in it would meet on the same
   // dies where chunks and ranges together are a multiple of four or eight, 1024 heads x 4k tokens, 3 chunks and 1 range each, 331 us.)
-  if ((int)blockIdx.y < win.n_chunks) {
+  const int part = (int)(blockIdx.z * kGridParts + blockIdx.y);
+  if (part >= win.n_chunks + n_splits) return;           // (a part that is not there: heads_by_parts)
+  if (part < win.n_chunks) {
     WaveState<NH> st;
-    window_pass<NH4, BITS, G, false, true, false>(a, bh, win.na, win.b0, win.nb, (int)blockIdx.y, win.n_chunks, n_splits + (int)blockIdx.y, lds, st, [] {});
+    window_pass<NH4, BITS, G, false, true, false>(a, bh, win.na, win.b0, win.nb, part, win.n_chunks, n_splits + part, lds, st, [] {});
     return;
   }
   const int n_tiles = (n_both + TT - 1) / TT;
   const int base_t = n_tiles / n_splits, rem_t = n_tiles % n_splits;
-  const int s_idx = (int)blockIdx.y - win.n_chunks;
+  const int s_idx = part - win.n_chunks;
   const int t0 = s_idx * base_t + (s_idx < rem_t ? s_idx : rem_t);
   const int t1 = t0 + base_t + (s_idx < rem_t ? 1 : 0);
 
@@ -565,7 +567,8 @@ attention_outer_kernel(AttnArgs a, int n_both, int n_splits, WindowSet win) {
 template <int BITS, int G, bool ZK, bool ZV>
 hipError_t launch_z(const AttnArgs& a, int n_both, int n_splits, const WindowSet& win, const Launch& L) {
   const int r = a.n_q_heads / a.n_kv_heads;
-  dim3 grid((unsigned)(a.batch * a.n_kv_heads), (unsigned)(n_splits + win.n_chunks));
+  const HeadsByParts g = heads_by_parts((long long)a.batch * a.n_kv_heads, (long long)n_splits + win.n_chunks);
+  const dim3 grid(g.x, g.y, g.z);
   if (r <= 4)
     hipExtLaunchKernelGGL((attention_outer_kernel<BITS, G, 1, ZK, ZV>), grid, dim3(64), 0, L.stream, L.ev_start,
                           L.ev_stop, 0, a, n_both, n_splits, win);

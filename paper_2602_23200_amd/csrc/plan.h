@@ -59,6 +59,15 @@ struct PlanInput {
   int tile_tokens = 64;         // of a tile of the kernel
 };
 
+// Grid of the outer-grouped kernel: sequence-heads, then the parts of one (window chunks and token ranges), which are more than a
+// grid's second dimension can be (65536) where the window is longer than a million tokens: the rest goes to the third.  A part is
+// z * kGridParts + y; of the last layer some are not there.
+constexpr int kGridParts = 32768;
+struct HeadsByParts { unsigned x, y, z; };
+inline HeadsByParts heads_by_parts(long long heads, long long parts) {
+  return {(unsigned)heads, (unsigned)(parts < kGridParts ? parts : kGridParts), (unsigned)ceil_div(parts, kGridParts)};
+}
+
 struct LaunchPlan {
   int n_splits;                 // wavefronts (fp32 kernel: work-groups) of a sequence-head that share the quantised range; 0: there is none
   int n_win;                    // window chunks

@@ -79,3 +79,26 @@ def test_zero_and_tiny_groups(bits, group, heads, k_mode, what):
     out = iq.innerq_decode_attention(g, dev(q), iq.allocate_workspace(g.cfg)).cpu().numpy()
     assert np.isfinite(out).all()
     assert max_rel_err(out, orc.decode_attention(o, orc.cache_init_prefill(o, K, V), q)) <= TOL
+
+
+def test_window_of_a_million_tokens():
+    """68754 window chunks of a sequence-head: more than the second dimension of a grid.  (The quantised tokens are zeros, which every
+    width holds exactly, so that the inputs themselves are what is attended to.)"""
+    import torch
+    from paper_2602_23200_amd import binding as iq
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    recent, quantised = 1_100_000, 64
+    n = 4 + quantised + recent
+    cfg = iq.make_config(1, 2, 1, 128, 4, 32, 4, recent, kind=orc.KIND_OUTER, capacity_tokens=-(-n // 64) * 64)
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    K, V = (torch.randn(1, 1, n, 128, device="cuda", generator=gen).half() for _ in range(2))
+    K[:, :, 4:4 + quantised] = 0
+    V[:, :, 4:4 + quantised] = 0
+    q = 2 * torch.randn(1, 2, 128, device="cuda", generator=gen).half()
+    g = iq.allocate_cache(cfg)
+    iq.innerq_quantize_append(g, K, V)
+    assert iq.innerq_partition(cfg, 0, n)[1] == quantised
+    out = iq.innerq_decode_attention(g, q, iq.allocate_workspace(cfg))
+    s = (K[0, 0].double() @ q[0].double().T) / 128 ** 0.5
+    want = torch.softmax(s, 0).T @ V[0, 0].double()
+    assert ((out[0].double() - want).abs().amax(-1) / want.abs().amax(-1)).max().item() <= TOL

@@ -63,6 +63,47 @@ int main() {
 }
 """
 
+GRIDS = r"""
+#include <stdio.h>
+#include <initializer_list>
+#include "paper_2602_23200_amd/csrc/plan.h"
+using namespace innerq;
+
+int main() {
+  long long bad = 0, most = 0;
+  for (long long recent : {32LL, 4096LL, 500000LL, 1048000LL, 1100000LL, 5000000LL, 16000000LL}) for (int n_both : {32, 64, 4096}) for (int tile = 64; tile <= 128; tile *= 2) {
+    innerq_config_t c = {};
+    c.batch = 1; c.n_kv_heads = 1; c.n_q_heads = 1; c.head_dim = 128; c.bits = tile == 64 ? 4 : 2; c.group = 32; c.w_sink = 4;
+    c.w_recent = (int)recent; c.capacity_tokens = 1 << 24; c.kind = INNERQ_KIND_OUTER;
+    PlanInput in = {};
+    in.fused_kind = kOuterKernel; in.compute_units = 256; in.waves_per_cu = 8; in.n_both = n_both; in.win_tokens = c.w_sink + recent; in.tile_tokens = tile;
+    const LaunchPlan p = plan_attention(c, in);
+    const long long parts = (long long)p.n_splits + p.n_win;
+    most = parts > most ? parts : most;
+    const HeadsByParts g = heads_by_parts(1, parts);
+    if (g.y > 65536 || g.z > 65536 || (long long)g.y * g.z < parts || (g.z > 1 && g.y != kGridParts) || (parts <= kGridParts && g.z != 1)) ++bad;
+  }
+  printf("%lld parts at most, %lld bad\n", most, bad);
+  return bad || most <= 65536;
+}
+"""
+
+
+def run(tmp_path, text):
+    gxx = shutil.which("g++") or shutil.which("clang++")
+    if not gxx:
+        pytest.skip("no C++ compiler")
+    (tmp_path / "grids.cpp").write_text(text)
+    exe = str(tmp_path / "grids")
+    subprocess.run([gxx, "-std=c++17", "-O2", "-Wall", "-Werror", "-I", ROOT, str(tmp_path / "grids.cpp"), "-o", exe], check=True)
+    return subprocess.run([exe], stdout=subprocess.PIPE, text=True, timeout=100)
+
+
+def test_grids_of_long_windows(tmp_path):
+    """The outer-grouped kernel's parts of a sequence-head (window chunks and token ranges) fit a grid's dimensions of 65536 each."""
+    done = run(tmp_path, GRIDS)
+    assert done.returncode == 0, done.stdout
+
 
 def test_every_plan_can_be_launched(tmp_path):
     gxx = shutil.which("g++") or shutil.which("clang++")
