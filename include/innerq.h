@@ -313,7 +313,8 @@ int innerq_append_deferred(const innerq_config_t *cfg, innerq_cache_t *cache, co
 /* One decode step in one or two launches instead of three: innerq_decode_attention_next followed by
  * innerq_append_deferred on the same stream (they touch disjoint memory).  Where the fused inner kernel
  * joins its partial results itself, and while a short cache (up to 256 tokens, none of them quantised in both
- * tensors) is attended to by one work-group a sequence-head, the append rides in the same launch (but for
+ * tensors) is attended to by one work-group a sequence-head (all but 64 tokens and fewer of many heads with
+ * quantised keys among them), the append rides in the same launch (but for
  * the steps, one in G, in which a value group leaves its ring); else the log-sum-exp merge and the
  * append share the second launch.  Which it is follows from the sizes and the token count alone.
  * Same preconditions and errors as those two calls (INNERQ_E_ARG unless store_ahead_tokens ==

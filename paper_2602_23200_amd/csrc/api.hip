@@ -387,7 +387,13 @@ static int attention_impl(const innerq_config_t* cfg, const innerq_cache_t* cach
   // there: a step and the separate calls that it replaces give the same bits.
   const bool spills = !n_dev && partition_of(c, 1, N < c.capacity_tokens ? N + 1 : N).n_quant > partition_of(c, 1, N).n_quant;
   const bool inner = c.kind == INNERQ_KIND_INNER;
-  if (n_both == 0 && !n_dev && N <= kShortTokens && !(inner && spills) && (long long)c.batch * c.n_q_heads < (1LL << 30)) {
+  // Nor a single tile with packed key rows in it (recent windows of less than a tile) over more work-groups than two a compute unit:
+  // the kernel for packed rows has room for one of them there, and small ones of 256 threads are the faster ones (us a step, in one
+  // launch and in two: 300 x 8 heads, r = 5, 9 tokens 76.5, 56.1; 711 x 8, 49 182, 137; 1889 heads 64.0, 49.9; r = 1 and 4 by
+  // work-groups a compute unit: 1 to 2 0.90 of the time, 3 to 8 1.04, more 1.10).  Rows of values, or a second tile: one launch 0.5 to 0.95.
+  const long long short_groups = (long long)c.batch * c.n_kv_heads * ceil_div(c.n_q_heads / c.n_kv_heads, kHeadTile);
+  const bool crowded = inner && a.k.n_quant > 0 && N <= 64 && short_groups > 2 * compute_units();
+  if (n_both == 0 && !n_dev && N <= kShortTokens && !(inner && spills) && !crowded && (long long)c.batch * c.n_q_heads < (1LL << 30)) {
     const QuantArgs* rides = inner ? append : nullptr;
     a.n_partials = 0;                                    // (nothing to merge)
     g_prof_start = g_prof_stop = nullptr;                // (events are for the kernel of the quantised range)

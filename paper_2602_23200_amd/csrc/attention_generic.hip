@@ -2,8 +2,8 @@
 //
 // attention_generic_kernel takes any grouping form and any window in fp32 (weights included).  It is the fallback for shapes
 // the fused kernels do not cover, and serves the caches that hold no token quantised in both tensors yet (the first
-// w_sink + w_recent + G tokens of every sequence) beyond kShortTokens tokens and in the step at which their first value group leaves.
-// attention_short_kernel serves the other ones, the append of a decode step included.
+// w_sink + w_recent + G tokens of every sequence) beyond kShortTokens tokens, in the step at which their first value group leaves, and
+// for a tile with packed keys of many heads.  attention_short_kernel serves the other ones, the append of a decode step included.
 // attention_merge_kernel joins all partial results by log-sum-exp: the
 // quantised part and the window parts are concatenated before the softmax is
 // normalised (Eq. att:1-3; Figure "quantization_overall").
