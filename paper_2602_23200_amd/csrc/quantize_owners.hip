@@ -6,11 +6,12 @@
 // New tokens that do not stay in a window are units of one wavefront each:
 //   * per-token form: 64 consecutive groups of one sequence-head, one a lane (its G channels are 2 G contiguous bytes,
 //     and the 64 lanes' loads and packed stores are contiguous too);
-//   * per-channel form: half of the channels of one group of G tokens, a lane a channel (a token's row is coalesced 128-byte loads).
+//   * per-channel form: half of the channels of one group of G tokens, a lane a channel (a token's row is coalesced 128-byte loads);
+//     all of them, a lane a pair, where G is 64 and the mode is not the hybrid one.
 //
 // What bounds it is the chain of an owner: the rounds of loads of the rows that leave, one lane's whole group, the
-// rounds of copies.  It pays while the owners fit the chip and their rings are short (append_form): 512 tokens onto 500 of 8 heads, G = 32, 5.9 us against 8.7 in two launches; 32 heads 8.1
-// against 10.5; but with a window of 1024 tokens 19 against 10, and 157 against 13 with 8192 (1 head, G = 64): a ring's
+// rounds of copies.  It pays while the owners fit the chip and their rings are short (append_form): 512 tokens onto 500 of 8 heads, G = 32, 6.2 us against 8.6 in two launches; 32 heads 7.8
+// against 10.3; but with a window of 1024 tokens 19 against 10, and 157 against 13 with 8192 (1 head, G = 64): a ring's
 // rows are one work-group's serial rounds.
 #include "innerq_dev.h"
 #include "quant_group.h"
@@ -57,49 +58,58 @@ __device__ __forceinline__ void per_token_unit(const QuantArgs& a, const QuantTe
 
 // ---- per-channel form ----------------------------------------------------------------------
 // One group of G tokens (tg) of sequence-head bh, half of the channels (part), a lane each; or (RING) 64 / G groups from tg on, one
-// channel slice (part).  Groups from tg_end on are not there: their lanes repeat the last one, store included.
-// (A channel a lane: with two, one after the other, a lane's chain was the longest of a chunk, 512 tokens onto 500 of 32 heads at
-// 4 bits 9.4 us a chunk, 8.1 now; 250 of 32 heads, 3-bit keys, 8.6, 6.6; chunks of 8192 tokens of 32 heads 39.5, 38.8.)
-template <int BITS, bool RING>
+// channel slice (part).  PAIR: two channels a lane, one after the other: all channels, or twice the groups.  Groups from tg_end
+// on are not there: their lanes repeat the last one, store included.
+// A channel a lane is the shorter chain: 512 tokens onto 500 of 32 heads at 4 bits 7.8 us a chunk, with pairs alone 9.5; 250 of 32 heads,
+// 3 bits, 7.3, 9.6; chunks of 8192 tokens of 32 heads 37, 39.  A pair is half the loads, which is what counts where a lane has 64 of
+// them and one variant to compute (G = 64, 2 bits: 110 heads, 8583 tokens 161 us a channel a lane, 94 a pair), and one
+// round of a ring's wavefronts where a channel a lane takes two (4 heads, 330 tokens, a window of 416, G = 32 8.3, 7.0; 1 head, 395, G = 64
+// 12.7, 10.4).  (What each path has of its own goes on the others' registers: 44 heads, 1358 tokens, G = 64, 2 bits 12.1 with pairs alone, 13.0.)
+template <int BITS, bool RING, bool PAIR>
 __device__ __forceinline__ void per_channel_unit(const QuantArgs& a, const QuantTensorJob& j, uint32_t bh, uint32_t tg,
                                                  uint32_t tg_end, uint32_t part) {
-  constexpr int W = G * BITS / 32;
+  constexpr int W = G * BITS / 32, C = PAIR ? 2 : 1;
   const uint32_t lane = threadIdx.x & 63u;
-  uint32_t c = 64u * part + lane, dt = 0u;               // channel; group, counted from tg
+  uint32_t c = PAIR ? 2u * lane : 64u * part + lane, dt = 0u;   // (first) channel; group, counted from tg
   if (RING) {
-    c = part * G + lane % G;
-    dt = lane / G;
+    c = part * G + C * (lane % (G / C));
+    dt = lane / (G / C);
     dt = tg + dt < tg_end ? dt : tg_end - 1u - tg;
   }
   const long long t0 = (long long)a.w_sink + (long long)(tg + dt) * G;
   const __half* src = j.x_new + ((long long)bh * a.t_new + ((long long)a.w_sink + (long long)tg * G - a.n_old)) * D      // (uniform)
                       + (dt * (G * D) + c);
-  uint32_t x[G];                                         // a value each, in the low half
+  auto load = [](const __half* p) { return PAIR ? *reinterpret_cast<const uint32_t*>(p) : (uint32_t)__half_as_ushort(*p); };
+  uint32_t x[G];                                         // one value, in the low half, or two
   if constexpr (!RING) {
 #pragma unroll
-    for (int i = 0; i < G; ++i) x[i] = __half_as_ushort(src[i * D]);
+    for (int i = 0; i < G; ++i) x[i] = load(src + i * D);
   } else {
     const __half* ring = j.ring + (long long)bh * j.slots * D + c;
     uint32_t slot = (uint32_t)t0 % (uint32_t)j.slots;
 #pragma unroll
     for (int i = 0; i < G; ++i) {
-      x[i] = __half_as_ushort(*(t0 + i >= a.n_old ? src + i * D : ring + slot * D));
+      x[i] = load(t0 + i >= a.n_old ? src + i * D : ring + slot * D);
       slot = slot + 1u == (uint32_t)j.slots ? 0u : slot + 1u;
     }
   }
   if (j.normalise) {
-    const float f = a.inv_norm[(bh % (uint32_t)a.n_kv_heads) * D + c];
+    const float* f = a.inv_norm + (bh % (uint32_t)a.n_kv_heads) * D + c;
+    const float f0 = f[0], f1 = PAIR ? f[1] : 0.f;
 #pragma unroll
     for (int i = 0; i < G; ++i) {
-      const uint32_t y = scaled_pair(x[i], f, 0.f);
+      const uint32_t y = scaled_pair(x[i], f0, f1);
       x[i] = !RING || t0 + i >= a.n_old ? y : x[i];      // (ring rows already are)
     }
   }
-  uint32_t mn, mx, words[W];
+  uint32_t mn, mx, words[C][W];
   pair_range(x, mn, mx);
-  __half s, z;
+  __half s[C], z[C];
   quantize_group_bulk<G, BITS, false>([&](int i) { return HalfRef{x[i], false}; }, NoDistances{}, half_lo(mn), half_lo(mx), j.mode,
-                               a.sym_den_literal, words, s, z);
+                               a.sym_den_literal, words[0], s[0], z[0]);
+  if constexpr (PAIR)
+    quantize_group_bulk<G, BITS, false>([&](int i) { return HalfRef{x[i], true}; }, NoDistances{}, half_hi(mn), half_hi(mx), j.mode,
+                                 a.sym_den_literal, words[1], s[1], z[1]);
   long long go = ((long long)bh * a.capacity / G + tg) * D;            // (capacity is a multiple of G)
   uint32_t dc = dt * D + c;
   if (a.pages.table) {
@@ -108,9 +118,12 @@ __device__ __forceinline__ void per_channel_unit(const QuantArgs& a, const Quant
   }
   uint32_t* dst = reinterpret_cast<uint32_t*>(j.codes) + go * W + dc * W;
 #pragma unroll
-  for (int i = 0; i < W; ++i) dst[i] = words[i];
-  (j.scales + go)[dc] = s;
-  if (j.zeros) (j.zeros + go)[dc] = z;
+  for (int i = 0; i < C * W; ++i) dst[i] = words[i / W][i % W];
+#pragma unroll
+  for (int i = 0; i < C; ++i) {
+    (j.scales + go)[dc + i] = s[i];
+    if (j.zeros) (j.zeros + go)[dc + i] = z[i];
+  }
 }
 
 // Rows (store rows) of a job that come from the ring and from the new tokens.
@@ -163,6 +176,7 @@ constexpr uint32_t kUnitRows = 64u / kSlices;            // rows of a per-token 
 struct OwnersPlan {
   uint32_t ring_groups;                                  // work-groups in front that own a ring slice each: 2 BH kSlices
   uint32_t per_bh_t, per_bh_c;                           // units per sequence-head of the per-token / per-channel tensor
+  uint32_t pairs;                                        // G = 64: a lane of the per-channel tensor's units takes two channels
 };
 
 template <int BITS>
@@ -174,7 +188,12 @@ __device__ __forceinline__ void ring_units(const QuantArgs& a, const QuantTensor
   } else {
     constexpr uint32_t PER = 64u / G;                    // groups a wavefront takes
     const uint32_t tg0 = row0 / G, n = rows / G;
-    for (uint32_t t = PER * wave; t < n; t += 4u * PER) per_channel_unit<BITS, true>(a, j, bh, tg0 + t, tg0 + n, slice);
+    if (n <= 4u * PER) {
+      // (no loop: 8 heads, 512 tokens onto 500, G = 32 6.2 us a chunk, with one 6.7)
+      if (PER * wave < n) per_channel_unit<BITS, true, false>(a, j, bh, tg0 + PER * wave, tg0 + n, slice);
+    } else {
+      for (uint32_t t = 2u * PER * wave; t < n; t += 8u * PER) per_channel_unit<BITS, true, true>(a, j, bh, tg0 + t, tg0 + n, slice);
+    }
   }
 }
 
@@ -208,22 +227,30 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 3
   u -= BH * p.per_bh_t;
   if (u < BH * p.per_bh_c) {
     const QuantTensorJob j = pick_job(a, INNER ? 1 : 0);
-    const uint32_t bh = u / p.per_bh_c, at = u - bh * p.per_bh_c, part = at & 1u;
-    const uint32_t tg = (uint32_t)((j.row_begin + split_rows(a, j).ring) / G) + (at >> 1);
-    if (j.bits == 2) per_channel_unit<2, false>(a, j, bh, tg, tg + 1u, part);
-    else if (j.bits == 3) per_channel_unit<3, false>(a, j, bh, tg, tg + 1u, part);
-    else per_channel_unit<4, false>(a, j, bh, tg, tg + 1u, part);
+    const uint32_t bh = u / p.per_bh_c, at = u - bh * p.per_bh_c;
+    const uint32_t first = (uint32_t)((j.row_begin + split_rows(a, j).ring) / G);
+    if (G == 64 && p.pairs) {
+      const uint32_t tg = first + at;
+      if (j.bits == 2) per_channel_unit<2, false, true>(a, j, bh, tg, tg + 1u, 0u);
+      else if (j.bits == 3) per_channel_unit<3, false, true>(a, j, bh, tg, tg + 1u, 0u);
+      else per_channel_unit<4, false, true>(a, j, bh, tg, tg + 1u, 0u);
+      return;
+    }
+    const uint32_t tg = first + (at >> 1), part = at & 1u;
+    if (j.bits == 2) per_channel_unit<2, false, false>(a, j, bh, tg, tg + 1u, part);
+    else if (j.bits == 3) per_channel_unit<3, false, false>(a, j, bh, tg, tg + 1u, part);
+    else per_channel_unit<4, false, false>(a, j, bh, tg, tg + 1u, part);
   }
 }
 
 }  // namespace
 
 #if INNERQ_OWNERS_GROUP == 32
-// One chunk measured in all forms, 2800 shapes of 1 to 2048 sequence-heads, 2 to 32768 tokens, windows of 32 to 16384, both
-// group sizes (before the owners took a channel a lane): the rule was 0.7 % (geometric mean) behind the best form of each.
+// One chunk measured in its form and without owners, 23000 drawn shapes that meet the first line of the rule below (sequence-heads,
+// tokens and windows over their ranges, all widths and modes, both group sizes).
 AppendForm append_form(const QuantArgs& a) {
   if (a.n_dev) return AppendForm::kLanes8;
-  long long most = 0, slice_rows = 0;
+  long long most = 0, slice_rows = 0, ring_groups = 0;
   bool shared = false, values = false, ring_values = false, hybrid = false;
   bool narrow = a.n_old + a.t_new < (1LL << 31);         // (the owners' row arithmetic is 32-bit)
   for (int w = 0; w < 2; ++w) {
@@ -241,6 +268,7 @@ AppendForm append_form(const QuantArgs& a) {
     // rows that an owner reads from its ring, tokens that it writes
     long long old = a.n_old - a.w_sink - j.row_begin;
     old = old < 0 ? 0 : old > rows ? rows : old;
+    if (j.form == kPerChannel) ring_groups = (old + a.group - 1) / a.group;
     const CopySpan sp = copy_span(a, j);
     const long long in = sp.n_a + (a.t_new - sp.i_b);
     slice_rows = old > slice_rows ? old : slice_rows;
@@ -248,13 +276,15 @@ AppendForm append_form(const QuantArgs& a) {
   }
   // Owners of ring slices: where per-channel groups leave a ring (a chunk that only moves keys on is a short chain in
   // either form: 16 heads, 8 tokens 5.0 us in two launches of eight lanes a group, 5.3 here), at most two owners a
-  // compute unit (64 x 8 heads, 8 tokens 17 us here, 7.7 there) and rings of up to 448 rows (above).  At G = 64 a lane's chain
-  // through both variants of a group is the tail behind a large chunk (128 heads, 3000 tokens 65 us here, 50 there; 32 heads, 4000
-  // 28 and 23; 8 heads, 4000 10.8 and 11.9; 100 8.0 and 10.6; 512 8.5 and 10.3): hybrid groups up to 131072 groups only.
+  // compute unit (64 x 8 heads, 8 tokens 17 us here, 7.7 there) and rings of up to 448 rows (above).  The time without them, by groups (ratio
+  // of geometric means): G = 32, both variants to 8192 1.03, to 32768 1.30, to 131072 1.23, to 512k 1.16, to 2 M 1.06, beyond 1.01; one
+  // variant 1.20, 1.35, 1.31, 1.18, 1.08, 1.02.  At G = 64 a lane's chain is twice as long.  One variant: 1.01, 1.30, 1.24, to 262144 1.02,
+  // beyond 0.90: up to 262144 groups.  Both: 0.81, 1.26, 1.11, and 1.02 beyond (128 heads, 3000 tokens 65 us here, 50 there): from 8192 to
+  // 131072, and not where the groups of a ring want a second round of its wavefronts (0.96; 1.02 from 32768 groups on).
   const long long heads = (long long)a.batch * a.n_kv_heads, owners = 2 * heads * (D / a.group);
   const bool few_short = narrow && owners <= 2LL * compute_units() && slice_rows <= 448;
-  if (few_short && shared && ring_values && (a.group == 32 || !hybrid || most <= 131072))
-    return AppendForm::kRingOwners;
+  const bool pays = a.group == 32 ? true : hybrid ? most >= 8192 && most <= 131072 && ring_groups <= 4 : most <= 262144;
+  if (few_short && shared && ring_values && pays) return AppendForm::kRingOwners;
   // A group a lane, or spread over eight: the chain of a lane's group is the longer one, but eight lanes are eight times the
   // wavefronts (a first prompt of hybrid groups, G = 32, 4 bits: 4 heads, 600 tokens (7488 groups) 4.2 us against 4.7, 16 heads, 300
   // (10752) 5.1 against 4.8; G = 64: 8 heads, 600 (7488) 4.8 against 6.4, 1000 (13888) 6.3 against 6.0; 3-bit symmetric ones 4.2 against 4.0 at
@@ -274,9 +304,10 @@ hipError_t launch_quantize_owners_g64(const QuantArgs& a, hipStream_t stream) {
   const bool inner = a.job[0].form == kPerToken;
   const long long BH = (long long)a.batch * a.n_kv_heads;
   const QuantTensorJob &jt = a.job[inner ? 0 : 1], &jc = a.job[inner ? 1 : 0];
-  const long long per_bh_t = (split_rows(a, jt).fresh + kUnitRows - 1) / kUnitRows, per_bh_c = split_rows(a, jc).fresh / G * 2;
+  const bool pairs = G == 64 && jc.mode != INNERQ_HYBRID;
+  const long long per_bh_t = (split_rows(a, jt).fresh + kUnitRows - 1) / kUnitRows, per_bh_c = split_rows(a, jc).fresh / G * (pairs ? 1 : 2);
   const long long ring_groups = 2 * BH * kSlices, blocks = (BH * (per_bh_t + per_bh_c) + 3) / 4;
-  const OwnersPlan p = {(uint32_t)ring_groups, (uint32_t)per_bh_t, (uint32_t)per_bh_c};
+  const OwnersPlan p = {(uint32_t)ring_groups, (uint32_t)per_bh_t, (uint32_t)per_bh_c, pairs ? 1u : 0u};
   const unsigned grid = (unsigned)(ring_groups + blocks);
   if (inner) quantize_owners_kernel<true><<<grid, 256, 0, stream>>>(a, p);
   else quantize_owners_kernel<false><<<grid, 256, 0, stream>>>(a, p);

@@ -65,9 +65,12 @@ def test_bulk_append_bit_exact(env, kind, bits, group, modes, literal, recent, c
 
 
 @pytest.mark.parametrize("heads,group,recent,chunks", [
-    (33, 64, 64, (200, 140, 300)),                        # owners of hybrid groups of 64: from 32 sequence-heads on
-    (31, 64, 64, (200, 140, 300)),                        # ... below it two launches
-    (2, 32, 416, (900, 448, 449, 447, 480)),              # rings of 448 rows and more
+    (33, 64, 64, (200, 140, 300)),                        # owners of hybrid groups of 64: 9240 and 19800 groups
+    (31, 64, 64, (200, 140, 300)),                        # ... 8680 and 18600
+    (29, 64, 64, (200, 140, 300)),                        # ... 8120: two launches of eight lanes a group, then 17400
+    (64, 64, 64, (200, 64, 1024, 1025)),                  # ... 8192, 131072, and beyond: two launches of a group a lane
+    (33, 64, 300, (500, 200, 400)),                       # ... a second round of groups in a ring: two launches
+    (2, 32, 416, (900, 448, 449, 447, 480)),              # rings of 448 rows and more, a second round of their groups
     (40, 32, 32, (70, 2, 3, 130, 27, 4)),                 # keys only, few groups, 4096 groups and more
 ])
 def test_lines_between_the_forms(env, heads, group, recent, chunks):
@@ -103,12 +106,13 @@ def test_long_prompt_with_key_factors(env):
             assert torch.equal(buf, parts.buffers[name]), name
 
 
-def append_us(torch, iq, heads, group, recent, cached, t):
+def append_us(torch, iq, heads, group, recent, cached, t, mode=orc.HYBRID):
     """GPU time of one append of t tokens onto `cached` ones, from a replayed graph of ten."""
-    cfg = iq.make_config(1, heads, heads, 128, 2, group, 4, recent, capacity_tokens=-(-(cached + t) // 64) * 64)
+    cfg = iq.make_config(1, heads, heads, 128, 2, group, 4, recent, mode, mode, capacity_tokens=-(-(cached + t) // 64) * 64)
     c = iq.allocate_cache(cfg)
     x = torch.randn(1, heads, max(cached, t), 128, device="cuda").half()
-    iq.innerq_quantize_append(c, x[:, :, :cached].contiguous(), x[:, :, :cached].contiguous())
+    if cached:
+        iq.innerq_quantize_append(c, x[:, :, :cached].contiguous(), x[:, :, :cached].contiguous())
     x = x[:, :, :t].contiguous()
 
     def again():
@@ -146,6 +150,15 @@ def test_many_heads_use_the_whole_chip(env):
     torch, iq = env
     few, many = append_us(torch, iq, 256, 32, 128, 1000, 2), append_us(torch, iq, 2048, 32, 128, 1000, 2)
     assert many < 3 * few, (few, many)
+
+
+@pytest.mark.parametrize("heads,t", [(110, 8583), (60, 17635)])
+def test_chunk_takes_what_a_prompt_takes(env, heads, t):
+    """Groups of 64 of one variant: a chunk onto a cache reads and packs what a first prompt of as many tokens does (86 us, 81); with a
+    channel of two bytes a lane and load, owners of ring slices took 163."""
+    torch, iq = env
+    chunk, prompt = (append_us(torch, iq, heads, 64, 16, cached, t, orc.ASYM) for cached in (64, 0))
+    assert chunk < 1.3 * prompt, (chunk, prompt)
 
 
 @pytest.mark.parametrize("kind,bits,group", [(orc.KIND_INNER, 2, 32), (orc.KIND_INNER, 4, 64), (orc.KIND_OUTER, 3, 32)])
@@ -248,6 +261,7 @@ def test_bytes_do_not_depend_on_the_call(env, kind, bits, group, mode, bad):
 @pytest.mark.parametrize("kind,bits,heads,chunks", [
     (orc.KIND_INNER, 4, 1, (150, 64, 200)), (orc.KIND_INNER, 3, 9, (200, 70, 131)), (orc.KIND_OUTER, 2, 5, (133, 100, 300)),
     (orc.KIND_INNER, 2, 64, (150, 1024, 1025)),           # 131072 groups and 128 more: owners, then two launches
+    (orc.KIND_INNER, 3, 40, (150, 200, 131)), (orc.KIND_OUTER, 4, 48, (133, 100, 300)),                     # owners: 8192 groups and more
 ])
 def test_owners_of_hybrid_groups_of_64(env, kind, bits, heads, chunks):
     torch, iq = env
@@ -288,3 +302,46 @@ def test_channel_groups_over_eight_lanes(env, kind, bits, group, modes, heads, d
         iq.innerq_quantize_append(g, dev(K[:, :, at:at + c]), dev(V[:, :, at:at + c]), dev(inv))
         at += c
     assert_cache_equal(g, orc.cache_init_prefill(o, K, V, k_inv_norm=inv), o)
+
+
+@pytest.mark.parametrize("kind,bits,group,mode,heads,recent,chunks", [
+    (orc.KIND_INNER, 2, 64, orc.ASYM, 1, 64, (150, 64, 200)), (orc.KIND_INNER, 3, 64, orc.SYM, 9, 64, (200, 70, 131)), (orc.KIND_OUTER, 4, 64, orc.ASYM, 5, 64, (133, 100, 300)),
+    (orc.KIND_INNER, 2, 64, orc.SYM, 64, 16, (150, 2048, 2049)),          # 262144 groups and 128 more: owners, then two launches
+    (orc.KIND_INNER, 4, 64, orc.ASYM, 2, 384, (700, 320, 447, 64)), (orc.KIND_OUTER, 3, 64, orc.SYM, 1, 300, (600, 400)),       # five groups of a ring and more
+    (orc.KIND_INNER, 2, 32, orc.HYBRID, 3, 416, (800, 288, 300, 447)), (orc.KIND_OUTER, 3, 32, orc.HYBRID, 1, 280, (600, 400)),   # nine and more, at G = 32
+    (orc.KIND_INNER, 4, 32, orc.ASYM, 2, 256, (300, 287, 513, 40)),
+])
+@pytest.mark.parametrize("paged", [False, True])
+def test_owners_with_a_pair_of_channels_a_lane(env, kind, bits, group, mode, heads, recent, chunks, paged):
+    """New groups of one variant at G = 64, and rings with more groups than one round of a work-group takes; the same bytes in a paged store."""
+    torch, iq = env
+    n = sum(chunks)
+    w = wl.Workload("p", 1, heads, heads, 128, n, bits, group, 4, recent, k_mode=mode, v_mode=mode)
+    cap = -(-n // 64) * 64
+    o = oracle_config(w, kind=kind, capacity=cap)
+    rng = np.random.default_rng(n + bits)
+    K, V = values(rng, (1, heads, n, 128), "normal"), values(rng, (1, heads, n, 128), "ties")
+    inv = rng.uniform(0.3, 1.0, (heads, 128)).astype(np.float32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()  # noqa: E731
+    pages, caches = cap // 64, [iq.allocate_cache(gpu_config(o))]
+    if paged:
+        cfg = gpu_config(o)
+        cfg.page_pool_pages = pages
+        caches.append(iq.allocate_cache(cfg, page_table=torch.arange(pages - 1, -1, -1, dtype=torch.int32, device="cuda")[None].contiguous()))
+    for g in caches:
+        at = 0
+        for c in chunks:
+            iq.innerq_quantize_append(g, dev(K[:, :, at:at + c]), dev(V[:, :, at:at + c]), dev(inv))
+            at += c
+    if not paged:
+        assert_cache_equal(caches[0], orc.cache_init_prefill(o, K, V, k_inv_norm=inv), o)
+        return
+    # page by page (64 rows of every head): the pages lie in the pool in reverse
+    for name in ("k_codes", "k_scales", "k_zeros", "v_codes", "v_scales", "v_zeros"):
+        a, b = (c.buffers[name] for c in caches)
+        if a is None:
+            continue
+        rows = a.view(heads, pages, -1)
+        got = b.view(pages, heads, -1).flip(0).permute(1, 0, 2)
+        full = min(orc.partition(o, x, n)[1] for x in "kv") // 64                # (whole pages of quantised rows)
+        assert torch.equal(rows[:, :full], got[:, :full]), name
