@@ -143,9 +143,10 @@ hipError_t launch_quantize(const QuantArgs& a, hipStream_t stream, const AttnArg
 //   kLane        the same launches with a group a lane (prompts and large chunks)
 //   kRingOwners  a group a lane, and a work-group that owns a slice of a ring reads what leaves it and then writes what
 //                enters: one launch although slots are shared
-enum class AppendForm { kLanes8, kLane, kRingOwners };
+//   kRingOwnersPairs  the same, two channels of per-channel groups a lane (G = 64)
+enum class AppendForm { kLanes8, kLane, kRingOwners, kRingOwnersPairs };
 AppendForm append_form(const QuantArgs& a);
-hipError_t launch_quantize_owners(const QuantArgs& a, hipStream_t stream);
+hipError_t launch_quantize_owners(const QuantArgs& a, bool pairs, hipStream_t stream);
 hipError_t launch_calibrate(const __half* k, int batch, int n_kv_heads, long long n_tokens, int per_head,
                             float* norm_out, float* inv_out, hipStream_t stream);
 

@@ -260,7 +260,7 @@ hipError_t launch_quantize(const QuantArgs& a, hipStream_t stream, const AttnArg
     if (a.job[w].form != kFp16 && (a.job[w].bits < 2 || a.job[w].bits > 4)) return hipErrorInvalidValue;
   if (a.group != 32 && a.group != 64) return hipErrorInvalidValue;
   const AppendForm form = merge ? AppendForm::kLanes8 : append_form(a);
-  if (form == AppendForm::kRingOwners) return launch_quantize_owners(a, stream);
+  if (form == AppendForm::kRingOwners || form == AppendForm::kRingOwnersPairs) return launch_quantize_owners(a, form == AppendForm::kRingOwnersPairs, stream);
   if (form == AppendForm::kLane) {
     // (the shorter error sum from 2 M groups on: 8 x 8 heads x 32k tokens (8.4 M) 2 bits 259 us -> 250, 16k 131 -> 128, 8k (1 M) the same)
     long long most = 0;

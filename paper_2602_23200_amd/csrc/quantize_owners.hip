@@ -7,7 +7,7 @@
 //   * per-token form: 64 consecutive groups of one sequence-head, one a lane (its G channels are 2 G contiguous bytes,
 //     and the 64 lanes' loads and packed stores are contiguous too);
 //   * per-channel form: half of the channels of one group of G tokens, a lane a channel (a token's row is coalesced 128-byte loads);
-//     all of them, a lane a pair, where G is 64 and the mode is not the hybrid one.
+//     or, in a kernel of its own for G = 64 (PAIRS), all of them, a lane a pair.
 //
 // What bounds it is the chain of an owner: the rounds of loads of the rows that leave, one lane's whole group, the
 // rounds of copies.  It pays while the owners fit the chip and their rings are short (append_form): 512 tokens onto 500 of 8 heads, G = 32, 6.2 us against 8.6 in two launches; 32 heads 7.8
@@ -62,9 +62,9 @@ __device__ __forceinline__ void per_token_unit(const QuantArgs& a, const QuantTe
 // on are not there: their lanes repeat the last one, store included.
 // A channel a lane is the shorter chain: 512 tokens onto 500 of 32 heads at 4 bits 7.8 us a chunk, with pairs alone 9.5; 250 of 32 heads,
 // 3 bits, 7.3, 9.6; chunks of 8192 tokens of 32 heads 37, 39.  A pair is half the loads, which is what counts where a lane has 64 of
-// them and one variant to compute (G = 64, 2 bits: 110 heads, 8583 tokens 161 us a channel a lane, 94 a pair), and one
+// them and one variant to compute (G = 64, 2 bits: 110 heads, 8583 tokens 162 us a channel a lane, 84 a pair), and one
 // round of a ring's wavefronts where a channel a lane takes two (4 heads, 330 tokens, a window of 416, G = 32 8.3, 7.0; 1 head, 395, G = 64
-// 12.7, 10.4).  (What each path has of its own goes on the others' registers: 44 heads, 1358 tokens, G = 64, 2 bits 12.1 with pairs alone, 13.0.)
+// 12.7, 10.4).
 template <int BITS, bool RING, bool PAIR>
 __device__ __forceinline__ void per_channel_unit(const QuantArgs& a, const QuantTensorJob& j, uint32_t bh, uint32_t tg,
                                                  uint32_t tg_end, uint32_t part) {
@@ -117,12 +117,17 @@ __device__ __forceinline__ void per_channel_unit(const QuantArgs& a, const Quant
     dc = c;
   }
   uint32_t* dst = reinterpret_cast<uint32_t*>(j.codes) + go * W + dc * W;
+  if constexpr (PAIR) {                                                  // 2 W words from an even channel: 8-byte aligned
 #pragma unroll
-  for (int i = 0; i < C * W; ++i) dst[i] = words[i / W][i % W];
+    for (int i = 0; i < C * W; i += 2) *reinterpret_cast<uint2*>(dst + i) = uint2{words[i / W][i % W], words[(i + 1) / W][(i + 1) % W]};
+    auto both = [](const __half (&x)[C]) { return (uint32_t)__half_as_ushort(x[0]) | (uint32_t)__half_as_ushort(x[C - 1]) << 16; };
+    *reinterpret_cast<uint32_t*>(j.scales + go + dc) = both(s);
+    if (j.zeros) *reinterpret_cast<uint32_t*>(j.zeros + go + dc) = both(z);
+  } else {
 #pragma unroll
-  for (int i = 0; i < C; ++i) {
-    (j.scales + go)[dc + i] = s[i];
-    if (j.zeros) (j.zeros + go)[dc + i] = z[i];
+    for (int i = 0; i < W; ++i) dst[i] = words[0][i];
+    (j.scales + go)[dc] = s[0];
+    if (j.zeros) (j.zeros + go)[dc] = z[0];
   }
 }
 
@@ -176,10 +181,11 @@ constexpr uint32_t kUnitRows = 64u / kSlices;            // rows of a per-token 
 struct OwnersPlan {
   uint32_t ring_groups;                                  // work-groups in front that own a ring slice each: 2 BH kSlices
   uint32_t per_bh_t, per_bh_c;                           // units per sequence-head of the per-token / per-channel tensor
-  uint32_t pairs;                                        // G = 64: a lane of the per-channel tensor's units takes two channels
 };
 
-template <int BITS>
+// PAIRS: two channels a lane in every unit of the per-channel tensor; else one, in a ring of G = 64 of at most four groups
+// (the launch sees to it).
+template <int BITS, bool PAIRS>
 __device__ __forceinline__ void ring_units(const QuantArgs& a, const QuantTensorJob& j, uint32_t bh, uint32_t slice,
                                            uint32_t row0, uint32_t rows) {
   const uint32_t wave = threadIdx.x >> 6;
@@ -188,7 +194,7 @@ __device__ __forceinline__ void ring_units(const QuantArgs& a, const QuantTensor
   } else {
     constexpr uint32_t PER = 64u / G;                    // groups a wavefront takes
     const uint32_t tg0 = row0 / G, n = rows / G;
-    if (n <= 4u * PER) {
+    if (!PAIRS && (G == 64 || n <= 4u * PER)) {
       // (no loop: 8 heads, 512 tokens onto 500, G = 32 6.2 us a chunk, with one 6.7)
       if (PER * wave < n) per_channel_unit<BITS, true, false>(a, j, bh, tg0 + PER * wave, tg0 + n, slice);
     } else {
@@ -197,7 +203,7 @@ __device__ __forceinline__ void ring_units(const QuantArgs& a, const QuantTensor
   }
 }
 
-template <bool INNER>
+template <bool INNER, bool PAIRS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 32 ? 4 : 3))) quantize_owners_kernel(QuantArgs a, OwnersPlan p) {
   if (blockIdx.x < p.ring_groups) {
     // ---- a ring slice: what leaves it, then what enters
@@ -205,9 +211,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 3
     const QuantTensorJob j = pick_job(a, (int)tensor);
     const uint32_t rows = (uint32_t)split_rows(a, j).ring;
     if (rows > 0u) {
-      if (j.bits == 2) ring_units<2>(a, j, bh, slice, (uint32_t)j.row_begin, rows);
-      else if (j.bits == 3) ring_units<3>(a, j, bh, slice, (uint32_t)j.row_begin, rows);
-      else ring_units<4>(a, j, bh, slice, (uint32_t)j.row_begin, rows);
+      if (j.bits == 2) ring_units<2, PAIRS>(a, j, bh, slice, (uint32_t)j.row_begin, rows);
+      else if (j.bits == 3) ring_units<3, PAIRS>(a, j, bh, slice, (uint32_t)j.row_begin, rows);
+      else ring_units<4, PAIRS>(a, j, bh, slice, (uint32_t)j.row_begin, rows);
     }
     __syncthreads();                                     // every row of this slice has been read
     copy_slice(a, j, bh, slice);
@@ -229,17 +235,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 3
     const QuantTensorJob j = pick_job(a, INNER ? 1 : 0);
     const uint32_t bh = u / p.per_bh_c, at = u - bh * p.per_bh_c;
     const uint32_t first = (uint32_t)((j.row_begin + split_rows(a, j).ring) / G);
-    if (G == 64 && p.pairs) {
-      const uint32_t tg = first + at;
-      if (j.bits == 2) per_channel_unit<2, false, true>(a, j, bh, tg, tg + 1u, 0u);
-      else if (j.bits == 3) per_channel_unit<3, false, true>(a, j, bh, tg, tg + 1u, 0u);
-      else per_channel_unit<4, false, true>(a, j, bh, tg, tg + 1u, 0u);
-      return;
-    }
-    const uint32_t tg = first + (at >> 1), part = at & 1u;
-    if (j.bits == 2) per_channel_unit<2, false, false>(a, j, bh, tg, tg + 1u, part);
-    else if (j.bits == 3) per_channel_unit<3, false, false>(a, j, bh, tg, tg + 1u, part);
-    else per_channel_unit<4, false, false>(a, j, bh, tg, tg + 1u, part);
+    const uint32_t tg = first + (PAIRS ? at : at >> 1), part = PAIRS ? 0u : at & 1u;
+    if (j.bits == 2) per_channel_unit<2, false, PAIRS>(a, j, bh, tg, tg + 1u, part);
+    else if (j.bits == 3) per_channel_unit<3, false, PAIRS>(a, j, bh, tg, tg + 1u, part);
+    else per_channel_unit<4, false, PAIRS>(a, j, bh, tg, tg + 1u, part);
   }
 }
 
@@ -251,7 +250,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 3
 AppendForm append_form(const QuantArgs& a) {
   if (a.n_dev) return AppendForm::kLanes8;
   long long most = 0, slice_rows = 0, ring_groups = 0;
-  bool shared = false, values = false, ring_values = false, hybrid = false;
+  int channel_bits = 2;
+  bool shared = false, values = false, ring_values = false, hybrid = false, both = false;
   bool narrow = a.n_old + a.t_new < (1LL << 31);         // (the owners' row arithmetic is 32-bit)
   for (int w = 0; w < 2; ++w) {
     const QuantTensorJob& j = a.job[w];
@@ -263,6 +263,8 @@ AppendForm append_form(const QuantArgs& a) {
     hybrid = hybrid || j.mode == INNERQ_HYBRID;
     if (j.form == kPerChannel) {
       values = rows > 0;
+      channel_bits = j.bits;
+      both = j.mode == INNERQ_HYBRID;
       ring_values = rows > 0 && a.w_sink + j.row_begin < a.n_old;
     }
     // rows that an owner reads from its ring, tokens that it writes
@@ -278,13 +280,28 @@ AppendForm append_form(const QuantArgs& a) {
   // either form: 16 heads, 8 tokens 5.0 us in two launches of eight lanes a group, 5.3 here), at most two owners a
   // compute unit (64 x 8 heads, 8 tokens 17 us here, 7.7 there) and rings of up to 448 rows (above).  The time without them, by groups (ratio
   // of geometric means): G = 32, both variants to 8192 1.03, to 32768 1.30, to 131072 1.23, to 512k 1.16, to 2 M 1.06, beyond 1.01; one
-  // variant 1.20, 1.35, 1.31, 1.18, 1.08, 1.02.  At G = 64 a lane's chain is twice as long.  One variant: 1.01, 1.30, 1.24, to 262144 1.02,
-  // beyond 0.90: up to 262144 groups.  Both: 0.81, 1.26, 1.11, and 1.02 beyond (128 heads, 3000 tokens 65 us here, 50 there): from 8192 to
-  // 131072, and not where the groups of a ring want a second round of its wavefronts (0.96; 1.02 from 32768 groups on).
+  // variant 1.20, 1.35, 1.31, 1.18, 1.08, 1.02.
+  // At G = 64 a lane's chain is twice as long.  Time relative to the best of three forms (two launches / owners, a channel a lane / owners,
+  // pairs), geometric means of 6000 drawn chunks, by groups of the larger tensor up to
+  //                                        2048            8192            65536           131072          262144          512k            more
+  //   one variant, 2 bits             1.00 1.06 1.35  1.23 1.02 1.30  1.43 1.00 1.21  1.24 1.08 1.00  1.16 1.25 1.00  1.07 1.31 1.00  1.00 1.45 1.01
+  //   one variant, 3 bits             1.00 1.13 1.49  1.22 1.05 1.37  1.41 1.00 1.24  1.19 1.00 1.06  1.04 1.05 1.00  1.00 1.12 1.03  1.00 1.32 1.09
+  //   one variant, 4 bits             1.00 1.10 1.37  1.21 1.04 1.29  1.43 1.00 1.21  1.27 1.00 1.07  1.01 1.00 1.04  1.00 1.12 1.10  1.00 1.28 1.21
+  //   both variants, 2 bits           1.00 1.28 1.79  1.00 1.23 1.72  1.34 1.00 1.30  1.02 1.00 1.02  1.00 1.12 1.01  1.00 1.19 1.02  1.00 1.44 1.04
+  //   both variants, 3 and 4 bits     1.00 1.35 1.90  1.00 1.29 1.81  1.32 1.00 1.32  1.06 1.00 1.16  1.00 1.00 1.10  1.00 1.06 1.08  1.00 1.19 1.08
+  // and, of pairs alone, where a ring's groups are more than one round of its wavefronts (two launches over pairs): one variant 1.08 to 1.20
+  // from 8192 groups to 512k, beyond 1.02 at 2 bits and 0.93 at 3 and 4; both, from 24 heads on, 1.06 to 1.12 up to 196608, fewer heads 0.99.
   const long long heads = (long long)a.batch * a.n_kv_heads, owners = 2 * heads * (D / a.group);
   const bool few_short = narrow && owners <= 2LL * compute_units() && slice_rows <= 448;
-  const bool pays = a.group == 32 ? true : hybrid ? most >= 8192 && most <= 131072 && ring_groups <= 4 : most <= 262144;
-  if (few_short && shared && ring_values && pays) return AppendForm::kRingOwners;
+  if (few_short && shared && ring_values) {
+    if (a.group == 32) return AppendForm::kRingOwners;
+    const bool one_round = ring_groups <= 4;
+    const long long from = one_round && !both ? 3072 : 8192;
+    const long long single_to = !one_round ? 0 : both ? (channel_bits == 2 ? 98304 : 163840) : 65536 * (channel_bits - 1);
+    const long long pairs_to = both ? (!one_round && heads >= 24 ? 196608 : 0) : channel_bits == 2 ? 1048576 : !one_round ? 524288 : channel_bits == 3 ? 262144 : 0;
+    if (most >= from && most < single_to) return AppendForm::kRingOwners;
+    if (most >= from && most < pairs_to) return AppendForm::kRingOwnersPairs;
+  }
   // A group a lane, or spread over eight: the chain of a lane's group is the longer one, but eight lanes are eight times the
   // wavefronts (a first prompt of hybrid groups, G = 32, 4 bits: 4 heads, 600 tokens (7488 groups) 4.2 us against 4.7, 16 heads, 300
   // (10752) 5.1 against 4.8; G = 64: 8 heads, 600 (7488) 4.8 against 6.4, 1000 (13888) 6.3 against 6.0; 3-bit symmetric ones 4.2 against 4.0 at
@@ -294,23 +311,31 @@ AppendForm append_form(const QuantArgs& a) {
   return most < (values ? (hybrid ? 8192 : 4096) : shared ? 65536 : 16384) ? AppendForm::kLanes8 : AppendForm::kLane;
 }
 
-hipError_t launch_quantize_owners_g64(const QuantArgs& a, hipStream_t stream);
-hipError_t launch_quantize_owners(const QuantArgs& a, hipStream_t stream) {
-  if (a.group == 64) return launch_quantize_owners_g64(a, stream);
+hipError_t launch_quantize_owners_g64(const QuantArgs& a, bool pairs, hipStream_t stream);
+hipError_t launch_quantize_owners(const QuantArgs& a, bool pairs, hipStream_t stream) {
+  if (a.group == 64) return launch_quantize_owners_g64(a, pairs, stream);
+  if (pairs) return hipErrorInvalidValue;
 #else
-hipError_t launch_quantize_owners_g64(const QuantArgs& a, hipStream_t stream) {
+hipError_t launch_quantize_owners_g64(const QuantArgs& a, bool pairs, hipStream_t stream) {
 #endif
   if (a.group != G) return hipErrorInvalidValue;
   const bool inner = a.job[0].form == kPerToken;
   const long long BH = (long long)a.batch * a.n_kv_heads;
   const QuantTensorJob &jt = a.job[inner ? 0 : 1], &jc = a.job[inner ? 1 : 0];
-  const bool pairs = G == 64 && jc.mode != INNERQ_HYBRID;
+  if (G == 64 && !pairs && split_rows(a, jc).ring > 4 * G) return hipErrorInvalidValue;      // (see ring_units)
   const long long per_bh_t = (split_rows(a, jt).fresh + kUnitRows - 1) / kUnitRows, per_bh_c = split_rows(a, jc).fresh / G * (pairs ? 1 : 2);
   const long long ring_groups = 2 * BH * kSlices, blocks = (BH * (per_bh_t + per_bh_c) + 3) / 4;
-  const OwnersPlan p = {(uint32_t)ring_groups, (uint32_t)per_bh_t, (uint32_t)per_bh_c, pairs ? 1u : 0u};
+  const OwnersPlan p = {(uint32_t)ring_groups, (uint32_t)per_bh_t, (uint32_t)per_bh_c};
   const unsigned grid = (unsigned)(ring_groups + blocks);
-  if (inner) quantize_owners_kernel<true><<<grid, 256, 0, stream>>>(a, p);
-  else quantize_owners_kernel<false><<<grid, 256, 0, stream>>>(a, p);
+#if INNERQ_OWNERS_GROUP == 64
+  if (pairs) {
+    if (inner) quantize_owners_kernel<true, true><<<grid, 256, 0, stream>>>(a, p);
+    else quantize_owners_kernel<false, true><<<grid, 256, 0, stream>>>(a, p);
+    return hipGetLastError();
+  }
+#endif
+  if (inner) quantize_owners_kernel<true, false><<<grid, 256, 0, stream>>>(a, p);
+  else quantize_owners_kernel<false, false><<<grid, 256, 0, stream>>>(a, p);
   return hipGetLastError();
 }
 

@@ -64,20 +64,31 @@ def test_bulk_append_bit_exact(env, kind, bits, group, modes, literal, recent, c
     assert_cache_equal(g, want, o)
 
 
-@pytest.mark.parametrize("heads,group,recent,chunks", [
-    (33, 64, 64, (200, 140, 300)),                        # owners of hybrid groups of 64: 9240 and 19800 groups
-    (31, 64, 64, (200, 140, 300)),                        # ... 8680 and 18600
-    (29, 64, 64, (200, 140, 300)),                        # ... 8120: two launches of eight lanes a group, then 17400
-    (64, 64, 64, (200, 64, 1024, 1025)),                  # ... 8192, 131072, and beyond: two launches of a group a lane
-    (33, 64, 300, (500, 200, 400)),                       # ... a second round of groups in a ring: two launches
-    (2, 32, 416, (900, 448, 449, 447, 480)),              # rings of 448 rows and more, a second round of their groups
-    (40, 32, 32, (70, 2, 3, 130, 27, 4)),                 # keys only, few groups, 4096 groups and more
+@pytest.mark.parametrize("heads,group,recent,bits,mode,chunks", [
+    # both variants, groups of 64: owners of a channel a lane from 8192 groups to 98304 (2 bits) or 163840
+    (33, 64, 64, 2, orc.HYBRID, (200, 140, 300)),         # 9240 and 19800 groups
+    (31, 64, 64, 2, orc.HYBRID, (200, 140, 300)),         # 8680 and 18600
+    (29, 64, 64, 2, orc.HYBRID, (200, 140, 300)),         # 8120: two launches of eight lanes a group, then 17400
+    (64, 64, 64, 2, orc.HYBRID, (200, 64, 767, 768)),     # 8192, 98176, and 98304: two launches of a group a lane
+    (64, 64, 64, 4, orc.HYBRID, (200, 1279, 1280)),       # 163712, 163840
+    # ... where a ring's groups are more than one round: of pairs, from 24 heads on
+    (33, 64, 300, 2, orc.HYBRID, (500, 200, 400)),
+    (23, 64, 300, 2, orc.HYBRID, (500, 200, 400)),
+    # one variant: from 3072 groups on, a channel a lane up to 65536 (131072, 196608), then pairs
+    (64, 64, 64, 2, orc.ASYM, (236, 24, 40, 511, 512)),   # 3072, no values, 65408, 65536
+    (63, 64, 64, 2, orc.SYM, (236, 24)),                  # 3024: two launches
+    (64, 64, 64, 3, orc.SYM, (200, 1023, 1024, 2048)),    # 130944, 131072, 262144: two launches
+    (64, 64, 64, 4, orc.ASYM, (200, 1535, 1536)),         # 196480, 196608
+    (33, 64, 300, 4, orc.ASYM, (500, 100, 400)),          # more rounds: 6600 groups, 26400
+    (2, 32, 416, 2, orc.HYBRID, (900, 448, 449, 447, 480)),   # rings of 448 rows and more, a second round of their groups
+    (40, 32, 32, 2, orc.HYBRID, (70, 2, 3, 130, 27, 4)),      # keys only, few groups, 4096 groups and more
 ])
-def test_lines_between_the_forms(env, heads, group, recent, chunks):
+@pytest.mark.parametrize("kind", [orc.KIND_INNER, orc.KIND_OUTER])
+def test_lines_between_the_forms(env, kind, heads, group, recent, bits, mode, chunks):
     torch, iq = env
     n = sum(chunks)
-    w = wl.Workload("l", 1, heads, heads, 128, n, 2, group, 4, recent)
-    o = oracle_config(w)
+    w = wl.Workload("l", 1, heads, heads, 128, n, bits, group, 4, recent, k_mode=mode, v_mode=mode)
+    o = oracle_config(w, kind=kind)
     rng = np.random.default_rng(n)
     K, V = values(rng, (1, heads, n, 128), "normal"), values(rng, (1, heads, n, 128), "ties")
     g = iq.allocate_cache(gpu_config(o))
@@ -152,12 +163,14 @@ def test_many_heads_use_the_whole_chip(env):
     assert many < 3 * few, (few, many)
 
 
-@pytest.mark.parametrize("heads,t", [(110, 8583), (60, 17635)])
-def test_chunk_takes_what_a_prompt_takes(env, heads, t):
-    """Groups of 64 of one variant: a chunk onto a cache reads and packs what a first prompt of as many tokens does (86 us, 81); with a
-    channel of two bytes a lane and load, owners of ring slices took 163."""
+@pytest.mark.parametrize("heads,t,recent,cached,mode", [
+    (110, 8583, 16, 64, orc.ASYM), (60, 17635, 16, 64, orc.ASYM), (32, 5226, 128, 285, orc.ASYM), (16, 9040, 128, 611, orc.SYM),
+])
+def test_chunk_takes_what_a_prompt_takes(env, heads, t, recent, cached, mode):
+    """Groups of 64 of one variant: a chunk onto a cache reads and packs what a first prompt of as many tokens does (84 us, 79; 22, 19);
+    with a channel of two bytes a lane and load, owners of ring slices took 162, in two launches the smaller ones 29."""
     torch, iq = env
-    chunk, prompt = (append_us(torch, iq, heads, 64, 16, cached, t, orc.ASYM) for cached in (64, 0))
+    chunk, prompt = (append_us(torch, iq, heads, 64, recent, c, t, mode) for c in (cached, 0))
     assert chunk < 1.3 * prompt, (chunk, prompt)
 
 
