@@ -87,6 +87,51 @@ def run(name, lengths, heads, group, bound, steps=3, bits=2, v_bits=0, scaled=Fa
         assert_cache_equal(g, want[b], o1, bsel=slice(b, b + 1), what=f"{name} sequence {b}", per_sequence=True)
 
 
+def replayed_us(call):
+    """GPU time of one call, from a replayed graph of twenty."""
+    import torch
+    call()
+    graph, best = torch.cuda.CUDAGraph(), []
+    with torch.cuda.graph(graph):
+        for _ in range(20):
+            call()
+    for _ in range(8):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        graph.replay()
+        b.record()
+        b.synchronize()
+        best.append(a.elapsed_time(b) * 50)
+    return min(best)
+
+
+def ragged_step_us(iq, batch):
+    import torch
+    lengths = [1024 + 977 * i % 6000 for i in range(batch)]
+    lengths = [n + ((n + 2 - 132) % 32 == 0) for n in lengths]                 # no value group leaves a ring
+    cfg = iq.make_config(batch, 32, 8, 128, 2, 32, 4, 128, capacity_tokens=8192)
+    g, ws = iq.allocate_cache(cfg), iq.allocate_workspace(cfg)
+    x = torch.randn(batch, 8, 7100, 128, device="cuda").half()
+    iq.innerq_quantize_append(g, x, x)
+    one, q = x[:, :, :1].contiguous(), torch.randn(batch, 32, 128, device="cuda").half()
+    first = torch.tensor(lengths, dtype=torch.int32, device="cuda")
+    counts, out = first.clone(), torch.empty(batch, 32, 128, device="cuda")
+
+    def step():
+        counts.copy_(first)
+        iq.innerq_decode_step_ragged(g, counts, max(lengths) + 1, one, one, q, ws, out=out)
+
+    return replayed_us(step)
+
+
+def test_groups_that_do_not_leave_cost_little():
+    """The launch holds a value group of every sequence, and mostly none leaves: 32 sequences of 8 kv heads 1.21 times the step of
+    24, with those groups over eight lanes 1.29 times."""
+    from paper_2602_23200_amd import binding as iq
+    t24, t32 = ragged_step_us(iq, 24), ragged_step_us(iq, 32)
+    assert t32 < 1.25 * t24, (t24, t32)
+
+
 def test_short_sequences_keep_their_wavefronts():
     """Four sequences of 750 tokens behind a bound of 1500 have a wavefront per tile, as in a plain step: a few
     tenths longer for reading the counts, not half as long again for sharing wavefronts (12.5 and 18.5 us, plain 10.5)."""
@@ -111,20 +156,5 @@ def test_short_sequences_keep_their_wavefronts():
         counts.copy_(first)
         iq.innerq_decode_step_ragged(g, counts, bound, one, one, q, ws, out=out)
 
-    def us(call):
-        call()
-        graph, best = torch.cuda.CUDAGraph(), []
-        with torch.cuda.graph(graph):
-            for _ in range(20):
-                call()
-        for _ in range(8):
-            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            a.record()
-            graph.replay()
-            b.record()
-            b.synchronize()
-            best.append(a.elapsed_time(b) * 50)
-        return min(best)
-
-    t_plain, t_ragged = us(plain), us(ragged)
+    t_plain, t_ragged = replayed_us(plain), replayed_us(ragged)
     assert t_ragged < 1.4 * t_plain, (t_plain, t_ragged)
