@@ -223,7 +223,8 @@ __device__ __forceinline__ bool bulk_codes(X x, Dist dist, float mn, float most,
       if constexpr (BOTH) es = es + fabsf(half_minus_product(v, Ssf, c));
     }
   }
-  const bool asym = CLAMP ? mode == INNERQ_ASYM || (mode == INNERQ_HYBRID && ea < es) : BOTH ? ea < es : ASYM;
+  // (one condition, bitwise: entered from two tests, the arm "asymmetric" may lose the negation of its scale; see quantize_group_lanes)
+  const bool asym = CLAMP ? (mode == INNERQ_ASYM) | ((mode == INNERQ_HYBRID) & (ea < es)) : BOTH ? ea < es : ASYM;
 #pragma unroll
   for (int w = 0; w < G * BITS / 32; ++w) {
     uint32_t s = 0u, t = 0u;

@@ -94,8 +94,10 @@ __device__ inline uint32_t quantize_group_lanes(const float (&x)[G / 8], int sub
   const int last = ((int)(threadIdx.x & 63u) & ~7) + 7;
   ea = __shfl(ea, last);
   es = __shfl(es, last);
+  // One condition, bitwise: with || and && the arm "asymmetric" is entered from two tests, and clang 22 (structurizecfg) moves the
+  // negation of its scale, an instruction that costs nothing to its reckoning, in front of the first test and uses it on that edge only; lanes
+  // that entered over the second one kept Ss (per-channel form, G = 64).
   const bool asym = (mode == INNERQ_ASYM) | ((mode == INNERQ_HYBRID) & (ea < es));
-  // (bitwise: from the form with a branch clang 22 made code that kept the symmetric scale of asymmetric groups, per-channel form, G = 64)
   scale = asym ? __hneg(Sa) : Ss;
   zero = asym ? __float2half_rn(mn) : __float2half_rn(0.f);
   constexpr int LB = BITS == 3 ? 2 : BITS;             // bits per field of the (low) plane
