@@ -146,7 +146,10 @@ def _stream(stream) -> Optional[int]:
     import torch
     if stream is not None:
         return stream.cuda_stream or None
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+    except AttributeError:                                # (private names: where a torch does not have them)
+        return torch.cuda.current_stream().cuda_stream or None
 
 
 @dataclass

@@ -189,3 +189,17 @@ def test_paged_store_sizes_and_rejections():
     c.page_pool_pages = 7
     c.capacity_tokens = 1280 + 32                                   # not a whole number of pages
     assert iq.innerq_validate_config(c) == iq.E_ARG
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_where_torch_lacks_the_private_names(monkeypatch, missing):
+    import types
+
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.setattr(torch._C, name, lambda *a: 5, raising=False)
+    assert iq._stream(None) == 5
+    monkeypatch.delattr(torch._C, missing)
+    assert iq._stream(None) == 77
+    assert iq._stream(types.SimpleNamespace(cuda_stream=9)) == 9
