@@ -100,21 +100,62 @@ def test_lines_between_the_forms(env, kind, heads, group, recent, bits, mode, ch
     assert_cache_equal(g, orc.cache_init_prefill(o, K, V), o)
 
 
+def device_values(torch, gen, shape, dist):
+    x = torch.randn(shape, generator=gen, device="cuda")
+    if dist == "ties":
+        x = torch.round(x * 6) / 4
+    elif dist == "denormal":
+        x = x * 2.0 ** -17
+    elif dist == "wide":
+        x = x * torch.exp2(torch.randint(-20, 14, shape, generator=gen, device="cuda").float())
+    elif dist == "offset":                                # differences small against the values: the bound's largest term
+        x = x + 1000 * torch.randint(-1, 2, shape[:3] + (1,), generator=gen, device="cuda")
+    x = x.clamp(-60000, 60000).half()
+    if dist == "special":
+        m = torch.rand(shape, generator=gen, device="cuda")
+        x[m < 1e-4], x[(m > 1e-4) & (m < 2e-4)], x[(m > 2e-4) & (m < 3e-4)] = float("nan"), float("inf"), float("-inf")
+        x[(m > .3) & (m < .4)] = -0.0
+    return x
+
+
+def same_bytes_whole_and_in_parts(torch, iq, cfg, K, V, inv, cuts):
+    whole, parts = iq.allocate_cache(cfg), iq.allocate_cache(cfg)
+    iq.innerq_quantize_append(whole, K, V, inv)
+    for a, b in zip(cuts, cuts[1:]):
+        iq.innerq_quantize_append(parts, K[:, :, a:b].contiguous(), V[:, :, a:b].contiguous(), inv)
+    for name, buf in whole.buffers.items():
+        if buf is not None and not name.endswith("recent"):               # (a ring's spare slots hold older tokens)
+            assert torch.equal(buf, parts.buffers[name]), name
+
+
+@pytest.mark.parametrize("dist", ["normal", "ties", "denormal", "wide", "offset", "special"])
+@pytest.mark.parametrize("kind,bits,group,modes", [
+    (orc.KIND_INNER, 2, 32, (orc.HYBRID, orc.HYBRID)), (orc.KIND_INNER, 2, 64, (orc.HYBRID, orc.HYBRID)),
+    (orc.KIND_INNER, 3, 32, (orc.HYBRID, orc.HYBRID)), (orc.KIND_INNER, 3, 64, (orc.SYM, orc.HYBRID)),
+    (orc.KIND_INNER, 4, 32, (orc.HYBRID, orc.ASYM)), (orc.KIND_INNER, 4, 64, (orc.HYBRID, orc.HYBRID)),
+    (orc.KIND_OUTER, 2, 32, (orc.HYBRID, orc.HYBRID)), (orc.KIND_OUTER, 4, 64, (orc.HYBRID, orc.SYM)),
+])
+def test_shorter_error_sum(env, kind, bits, group, modes, dist):
+    """From 2 M groups on a prompt decides between the variants on a shorter error sum (2.1 M here); the same tokens in parts below that
+    line, which the tests above hold against the oracle, leave the same bytes."""
+    torch, iq = env
+    H, n = 8, (1 << 21) // 8 * group // 128 + 200
+    cfg = iq.make_config(1, H, H, 128, bits, group, 4, 128, modes[0], modes[1], 0, kind, capacity_tokens=-(-n // 64) * 64)
+    gen = torch.Generator(device="cuda").manual_seed(bits * group)
+    K, V = (device_values(torch, gen, (1, H, n, 128), dist) for _ in range(2))
+    inv = torch.rand(H, 128, device="cuda", generator=gen) + 0.5 if group == 32 else None
+    same_bytes_whole_and_in_parts(torch, iq, cfg, K, V, inv, (0, n // 3, n // 3 * 2 - 5, n))
+
+
 def test_long_prompt_with_key_factors(env):
-    """From 4 M groups on a prompt runs as units of new rows; in chunks of any length it leaves the same bytes."""
+    """A prompt of 4 M groups, and in parts of at most 1.95 M; they leave the same bytes."""
     torch, iq = env
     n, H = 131400, 8
     cfg = iq.make_config(1, H, H, 128, 2, 32, 4, 128, capacity_tokens=131456)
     gen = torch.Generator(device="cuda").manual_seed(5)
     K, V = (torch.randn(1, H, n, 128, device="cuda", generator=gen).half() for _ in range(2))
     inv = torch.rand(H, 128, device="cuda", generator=gen) + 0.5
-    whole, parts = iq.allocate_cache(cfg), iq.allocate_cache(cfg)
-    iq.innerq_quantize_append(whole, K, V, inv)
-    for a, b in ((0, 70000), (70000, 70601), (70601, n)):
-        iq.innerq_quantize_append(parts, K[:, :, a:b].contiguous(), V[:, :, a:b].contiguous(), inv)
-    for name, buf in whole.buffers.items():
-        if buf is not None and not name.endswith("recent"):               # (a ring's spare slots hold older tokens)
-            assert torch.equal(buf, parts.buffers[name]), name
+    same_bytes_whole_and_in_parts(torch, iq, cfg, K, V, inv, (0, 40000, 70000, 70601, n))
 
 
 def append_us(torch, iq, heads, group, recent, cached, t, mode=orc.HYBRID):
