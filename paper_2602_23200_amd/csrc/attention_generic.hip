@@ -333,7 +333,7 @@ __device__ __forceinline__ float add_products(const uint4& q, const uint4& x, fl
 // Registers: 64 a thread leave room for two work-groups a compute unit (128 x 8 heads x 128 tokens 22.5 us, 26.0 without the bound); with packed
 // rows that bound spills (2 x 8 x 150 7.4 against 6.7).
 template <int KF, int VF, int NH>
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(KF == kFp16 && VF == kFp16 ? 8 : 4, 8), amdgpu_num_sgpr(94))) attention_short_kernel(AttnArgs a, int r, int passes, int attention_groups, QuantArgs append) {
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(KF == kFp16 && VF == kFp16 ? 8 : 4, 8))) attention_short_kernel(AttnArgs a, int r, int passes, int attention_groups, QuantArgs append) {
   constexpr int ROWS = kShortTokens / TILE, WAVES = 16, V = NH * 8;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   if ((int)blockIdx.x >= attention_groups) {
