@@ -143,7 +143,7 @@ hipError_t launch_quantize(const QuantArgs& a, hipStream_t stream, const AttnArg
 //   kLane        the same launches with a group a lane (prompts and large chunks)
 //   kRingOwners  a group a lane, and a work-group that owns a slice of a ring reads what leaves it and then writes what
 //                enters: one launch although slots are shared
-//   kRingOwnersPairs  the same, two channels of per-channel groups a lane (G = 64)
+//   kRingOwnersPairs  the same, two channels of per-channel groups a lane (half the loads)
 enum class AppendForm { kLanes8, kLane, kRingOwners, kRingOwnersPairs };
 AppendForm append_form(const QuantArgs& a);
 hipError_t launch_quantize_owners(const QuantArgs& a, bool pairs, hipStream_t stream);

@@ -7,7 +7,7 @@
 //   * per-token form: 64 consecutive groups of one sequence-head, one a lane (its G channels are 2 G contiguous bytes,
 //     and the 64 lanes' loads and packed stores are contiguous too);
 //   * per-channel form: half of the channels of one group of G tokens, a lane a channel (a token's row is coalesced 128-byte loads);
-//     or, in a kernel of its own for G = 64 (PAIRS), all of them, a lane a pair.
+//     or, in a kernel of its own (PAIRS), all of them, a lane a pair.
 //
 // What bounds it is the chain of an owner: the rounds of loads of the rows that leave, one lane's whole group, the
 // rounds of copies.  It pays while the owners fit the chip and their rings are short (append_form): 512 tokens onto 500 of 8 heads, G = 32, 6.2 us against 8.6 in two launches; 32 heads 7.8
@@ -279,8 +279,10 @@ AppendForm append_form(const QuantArgs& a) {
   // Owners of ring slices: where per-channel groups leave a ring (a chunk that only moves keys on is a short chain in
   // either form: 16 heads, 8 tokens 5.0 us in two launches of eight lanes a group, 5.3 here), at most two owners a
   // compute unit (64 x 8 heads, 8 tokens 17 us here, 7.7 there) and rings of up to 448 rows (above).  The time without them, by groups (ratio
-  // of geometric means): G = 32, both variants to 8192 1.03, to 32768 1.30, to 131072 1.23, to 512k 1.16, to 2 M 1.06, beyond 1.01; one
-  // variant 1.20, 1.35, 1.31, 1.18, 1.08, 1.02.
+  // of geometric means): G = 32, both variants to 8192 1.03, to 32768 1.30, to 131072 1.23, to 512k 1.16, to 2 M 1.06; one
+  // variant 1.20, 1.35, 1.31, 1.18, 1.08.  Beyond, to 3 M, 4 M, 8 M and more, two launches and a channel a lane over pairs: both, 2 bits 1.05 1.02, 1.04 1.04,
+  // 1.00 1.05, 0.99 1.05; 3 bits 1.06 1.01, 1.05 1.02, 1.04 1.02, 1.05 1.03; 4 bits 1.03 1.02, 0.99 1.05, 0.98 1.05, 1.00 1.08; one, 2 bits 1.05 0.97,
+  // 1.01 0.99, 1.01 0.97, 1.01 0.97; 3 bits 1.02 1.02, 0.97 1.06, 1.01 0.99, 1.02 0.98; 4 bits 1.04 0.99, 1.01 1.01, 1.03 0.98, 1.02 0.98.
   // At G = 64 a lane's chain is twice as long.  Time relative to the best of three forms (two launches / owners, a channel a lane / owners,
   // pairs), geometric means of 6000 drawn chunks, by groups of the larger tensor up to
   //                                        2048            8192            65536           131072          262144          512k            more
@@ -293,8 +295,9 @@ AppendForm append_form(const QuantArgs& a) {
   // from 8192 groups to 512k, beyond 1.02 at 2 bits and 0.93 at 3 and 4; both, from 24 heads on, 1.06 to 1.12 up to 196608, fewer heads 0.99.
   const long long heads = (long long)a.batch * a.n_kv_heads, owners = 2 * heads * (D / a.group);
   const bool few_short = narrow && owners <= 2LL * compute_units() && slice_rows <= 448;
-  if (few_short && shared && ring_values) {
-    if (a.group == 32) return AppendForm::kRingOwners;
+  if (few_short && shared && ring_values && a.group == 32) {
+    return most >= 2097152 && (hybrid || channel_bits == 3) ? AppendForm::kRingOwnersPairs : AppendForm::kRingOwners;
+  } else if (few_short && shared && ring_values) {
     const bool one_round = ring_groups <= 4;
     const long long from = one_round && !both ? 3072 : 8192;
     const long long single_to = !one_round ? 0 : both ? (channel_bits == 2 ? 98304 : 163840) : 65536 * (channel_bits - 1);
@@ -314,7 +317,6 @@ AppendForm append_form(const QuantArgs& a) {
 hipError_t launch_quantize_owners_g64(const QuantArgs& a, bool pairs, hipStream_t stream);
 hipError_t launch_quantize_owners(const QuantArgs& a, bool pairs, hipStream_t stream) {
   if (a.group == 64) return launch_quantize_owners_g64(a, pairs, stream);
-  if (pairs) return hipErrorInvalidValue;
 #else
 hipError_t launch_quantize_owners_g64(const QuantArgs& a, bool pairs, hipStream_t stream) {
 #endif
@@ -327,13 +329,11 @@ hipError_t launch_quantize_owners_g64(const QuantArgs& a, bool pairs, hipStream_
   const long long ring_groups = 2 * BH * kSlices, blocks = (BH * (per_bh_t + per_bh_c) + 3) / 4;
   const OwnersPlan p = {(uint32_t)ring_groups, (uint32_t)per_bh_t, (uint32_t)per_bh_c};
   const unsigned grid = (unsigned)(ring_groups + blocks);
-#if INNERQ_OWNERS_GROUP == 64
   if (pairs) {
     if (inner) quantize_owners_kernel<true, true><<<grid, 256, 0, stream>>>(a, p);
     else quantize_owners_kernel<false, true><<<grid, 256, 0, stream>>>(a, p);
     return hipGetLastError();
   }
-#endif
   if (inner) quantize_owners_kernel<true, false><<<grid, 256, 0, stream>>>(a, p);
   else quantize_owners_kernel<false, false><<<grid, 256, 0, stream>>>(a, p);
   return hipGetLastError();
