@@ -47,7 +47,7 @@ __device__ inline float scale_quotient(float x, float d, float r) {
   return __builtin_amdgcn_div_fixupf(code_quotient(x, d, r), d, x);
 }
 
-// ---- a group in one lane: the form of prompts and chunks, and of all per-channel groups.  Long prompts are bound by memory, at
+// ---- a group in one lane: the form of prompts and chunks, and of per-channel groups but for those of short calls.  Long prompts are bound by memory, at
 // the rate of a copy (8 x 8 heads x 32k tokens, 2 bits: 1.24 GB in 250 us), with the vector units busy for three quarters of it.
 //
 // It uses these facts, so that codes, flags and scales keep every bit:
@@ -63,7 +63,7 @@ __device__ inline float scale_quotient(float x, float d, float r) {
 // Values stay packed as they were loaded: every use is a mixed-precision multiply-add that reads its half.
 // A code cannot leave its range unless the scale is an fp16 denormal (whose rounding is coarse) or the
 // symmetric denominator is the literal one: wavefronts with such a group run the form that clamps.
-// The competition of the two variants is decided on a shorter error sum where its rounding cannot matter (bulk_codes).
+// The competition of the two variants is decided on a shorter error sum where its rounding cannot matter (bulk_codes; in long prompts).
 // Instructions per element of a 2-bit hybrid group, minimum and maximum included: 12 (14 with the oracle's own sum, 28 with
 // divisions and conversions); 14 and 10 more a group for its scales and their reciprocals (45 with divisions).  Appends of 8 x 8
 // heads x 32k tokens: 2 bits 259 us -> 250, 4 bits 287 -> 277, G = 64 256 -> 244.
@@ -243,7 +243,7 @@ __device__ __forceinline__ bool bulk_codes(X x, Dist dist, float mn, float most,
 
 // The group's fields, scale and zero-point from its values x(i) and their minimum and maximum.  dist: the distances of a symmetric 2-bit
 // group whose denominator is 1 (others make no use of them), or NoDistances.
-// FAST: the shorter error sum, for launches that fill the chip many times over.  (One wavefront in a few hundred goes through the
+// FAST: the shorter error sum, for launches that fill the chip many times over, where it gains (launch_quantize).  (One wavefront in a few hundred goes through the
 // general form too, the tail of a short launch: 1 M groups of 4 bits 19.6 us and 19.8 with it, 64000 5.4 and 6.4, G = 64 8.1 and 10.2.)
 template <int G, int BITS, bool FAST, typename X, typename Dist>
 __device__ __forceinline__ void quantize_group_bulk(X x, Dist dist, float mn, float mx, int mode, int sym_den_literal,

@@ -29,8 +29,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G == 3
     return;
   }
   if (j.bits == 2) quantize_rows<G, 2, LANES, false, FAST>(a, j, idx);
-  else if (j.bits == 3) quantize_rows<G, 3, LANES, false, FAST>(a, j, idx);
-  else quantize_rows<G, 4, LANES, false, FAST>(a, j, idx);
+  else if (j.bits == 3) quantize_rows<G, 3, LANES, false, false>(a, j, idx);
+  else quantize_rows<G, 4, LANES, false, FAST && G == 64>(a, j, idx);
 }
 
 // The same launch with the log-sum-exp merge of an attention call riding along: the last
@@ -263,13 +263,17 @@ hipError_t launch_quantize(const QuantArgs& a, hipStream_t stream, const AttnArg
   const AppendForm form = merge ? AppendForm::kLanes8 : append_form(a);
   if (form == AppendForm::kRingOwners || form == AppendForm::kRingOwnersPairs) return launch_quantize_owners(a, form == AppendForm::kRingOwnersPairs, stream);
   if (form == AppendForm::kLane) {
-    // (the shorter error sum from 2 M groups on: 8 x 8 heads x 32k tokens (8.4 M) 2 bits 259 us -> 250, 16k 131 -> 128, 8k (1 M) the same)
+    // The shorter error sum for hybrid groups of 2 bits, and of 4 at G = 64, from 2 M groups on: 8 x 8 heads x 32k tokens (8.4 M) 259 us -> 250, 16k 131 -> 128, 8k
+    // (1 M) the same; of the time without it 0.974 to 1.002 at G = 32 and 0.979 to 0.993 at G = 64, at 4 bits 1.01 to 1.04 and 0.98
+    // to 1.00, at 3 bits 1.00 to 1.04.
     long long most = 0;
+    bool gains = false;
     for (int w = 0; w < 2; ++w) {
       const long long groups = (long long)a.batch * a.n_kv_heads * (a.job[w].row_end - a.job[w].row_begin) * (kHeadDim / a.group);
       most = groups > most ? groups : most;
+      gains = gains || (a.job[w].mode == INNERQ_HYBRID && (a.job[w].bits == 2 || (a.job[w].bits == 4 && a.group == 64)));
     }
-    const bool fast = most >= (1LL << 21);
+    const bool fast = gains && most >= (1LL << 21);
     if (a.group == 32) return fast ? launch_quantize_t<32, 1, true>(a, stream, nullptr) : launch_quantize_t<32, 1>(a, stream, nullptr);
     return fast ? launch_quantize_t<64, 1, true>(a, stream, nullptr) : launch_quantize_t<64, 1>(a, stream, nullptr);
   }
