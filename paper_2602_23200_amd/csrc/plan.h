@@ -105,7 +105,8 @@ inline LaunchPlan plan_attention(const innerq_config_t& c, const PlanInput& in) 
     // Short contexts: with fewer than about four tiles per wavefront, a launch of half as many
     // wavefronts (one per SIMD instead of two) is the faster one -- every wavefront pays its query
     // set-up once, and the launch itself costs time per wavefront (measured on the 32-head 4k-token
-    // configuration: 17.8 -> 14.3 us per step; the two meet at four tiles per wavefront).
+    // configuration, 4 bits: 17.8 -> 14.3 us per step; the two meet at four tiles per wavefront.  Eight query heads and 3-bit keys
+    // go by the same line; they have not been measured apart).
     const bool few_tiles = n_tiles < 4 * per_head;
     if (fused_kind == 1 && few_tiles && per_head >= 8) per_head /= 2;
     // Window chunk length and the number of plain wavefronts.

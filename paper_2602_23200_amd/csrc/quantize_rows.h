@@ -1,5 +1,5 @@
-// The quantise work of a thread: a per-token group spread over eight lanes, a per-channel group in a lane, and the rows of
-// one launch shared out over its threads.  Compiled without contraction (see quant_group.h); a translation unit that is
+// The quantise work of a thread: a per-token group spread over eight lanes, a per-channel group in a lane or spread likewise,
+// and the rows of one launch shared out over its threads.  Compiled without contraction (see quant_group.h); a translation unit that is
 // not sets INNERQ_CONTRACTED, and the pragma below holds for this file alone.
 #pragma once
 

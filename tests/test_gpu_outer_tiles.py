@@ -1,6 +1,6 @@
 """The outer-grouped kernel around its tiles (16 half-words: 128 tokens of 2 bits, 64 of 4): quantised ranges that end inside one,
 token groups and channel groups of 32 and 64, one to eight query heads, every combination of zero-point arrays, several
-tiles a wavefront, and scales whose magnitudes force another normalisation in every tile, against the oracle.
+tiles a wavefront, scales whose magnitudes force another normalisation in every tile, and tiles of zero and tiny ones, against the oracle.
 
 Softmax weights and their products with the value scales are fp16 numbers (relative 2^-12 each), the bound that the other parity tests use.
 """
