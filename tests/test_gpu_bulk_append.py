@@ -148,6 +148,22 @@ def test_shorter_error_sum(env, kind, bits, group, modes, dist):
     same_bytes_whole_and_in_parts(torch, iq, cfg, K, V, inv, (0, n // 3, n // 3 * 2 - 5, n))
 
 
+@pytest.mark.parametrize("dist", ["normal", "ties", "denormal", "special"])
+@pytest.mark.parametrize("kind,bits,modes", [
+    (orc.KIND_INNER, 2, (orc.HYBRID, orc.HYBRID)), (orc.KIND_INNER, 3, (orc.SYM, orc.SYM)), (orc.KIND_INNER, 4, (orc.SYM, orc.HYBRID)),
+    (orc.KIND_OUTER, 2, (orc.HYBRID, orc.ASYM)), (orc.KIND_OUTER, 3, (orc.ASYM, orc.HYBRID)),
+])
+def test_large_chunks_of_groups_of_32(env, kind, bits, modes, dist):
+    """A chunk of 2.1 M groups onto 300 tokens: owners of ring slices with two channels a lane."""
+    torch, iq = env
+    H, n = 8, 66200
+    cfg = iq.make_config(1, H, H, 128, bits, 32, 4, 128, modes[0], modes[1], 0, kind, capacity_tokens=-(-n // 64) * 64)
+    gen = torch.Generator(device="cuda").manual_seed(bits)
+    K, V = (device_values(torch, gen, (1, H, n, 128), dist) for _ in range(2))
+    inv = torch.rand(H, 128, device="cuda", generator=gen) + 0.5
+    same_bytes_whole_and_in_parts(torch, iq, cfg, K, V, inv, (0, 300, n))
+
+
 def test_long_prompt_with_key_factors(env):
     """A prompt of 4 M groups, and in parts of at most 1.95 M; they leave the same bytes."""
     torch, iq = env
