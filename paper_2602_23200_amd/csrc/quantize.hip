@@ -80,14 +80,16 @@ template <int G, int LANES, bool FAST = false>
 hipError_t launch_quantize_t(QuantArgs a, hipStream_t stream, const AttnArgs* merge) {
   // Per-channel groups of the form of eight lanes, spread over eight too: a lane's chain of a group is the longest of a short launch (us, one
   // lane -> eight: one value group of 8 heads G = 32 6.0 -> 3.8, G = 64 9.1 -> 4.2; steps at which one leaves its ring, 8 x 8 heads, 13.8 ->
-  // 12.2, G = 64 16.7 -> 12.3; 3 bits, symmetric, 14.6 -> 13.2), up to 256 sequence-heads (512: 34.0 -> 36.9), 64 of groups of one variant, whose
+  // 12.2, G = 64 16.7 -> 12.3; 3 bits, symmetric, 14.6 -> 13.2), up to 192 sequence-heads, 256 at G = 64 (steps with a spill, time of eight lanes over one:
+  // 128 heads 0.92 to 0.95, 256 0.99 to 1.00, single shapes to 1.11, and 0.96 at G = 64; 512 1.08), 64 of groups of one variant, whose
   // chain is half as long (128: 18.2 -> 20.4).  Where the counts live on the device the launch holds a group of every sequence, and mostly
   // none leaves (us a step of sequences of 8 heads, G = 32, in which none, one and all have one leave: 16 of them 19.2 21.6 21.9 -> 19.6
   // 19.7 20.9, 24 25.7 28.0 29.4 -> 26.1 26.1 28.0, 32 30.5 33.8 33.9 -> 34.4 34.4 36.5, 8 16.6 19.8 19.9 -> 18.2 18.8 19.0): in the mean
   // over independent lengths 0.92 to 0.97 of the time from 16 sequences up to 192 heads, 1.02 to 1.10 from 256 heads on.
   const int mode = a.job[a.job[0].form == kPerChannel ? 0 : 1].mode;
   const long long bh = (long long)a.batch * a.n_kv_heads;
-  const bool spread = bh <= (mode == INNERQ_HYBRID ? 256 : 64) && (!a.n_dev || (a.batch >= 16 && bh <= 192 && G == 32));
+  const long long most_heads = mode != INNERQ_HYBRID ? 64 : G == 64 ? 256 : 192;
+  const bool spread = bh <= most_heads && (!a.n_dev || (a.batch >= 16 && G == 32));
   a.channel_lanes = LANES == 8 && spread ? 8 : 1;
   const long long kthreads = quantize_threads<G, LANES>(a, a.job[0]), vthreads = quantize_threads<G, LANES>(a, a.job[1]);
   const long long threads = kthreads > vthreads ? kthreads : vthreads, cthreads = copy_threads(a);

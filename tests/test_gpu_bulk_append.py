@@ -351,8 +351,10 @@ def test_owners_of_hybrid_groups_of_64(env, kind, bits, heads, chunks):
 
 
 @pytest.mark.parametrize("kind,bits,group,modes,heads", [
-    (orc.KIND_INNER, 2, 32, (orc.HYBRID, orc.HYBRID), 3), (orc.KIND_INNER, 3, 32, (orc.SYM, orc.HYBRID), 256), (orc.KIND_INNER, 4, 64, (orc.HYBRID, orc.ASYM), 64),
+    (orc.KIND_INNER, 2, 32, (orc.HYBRID, orc.HYBRID), 3), (orc.KIND_INNER, 3, 32, (orc.SYM, orc.HYBRID), 192), (orc.KIND_INNER, 4, 64, (orc.HYBRID, orc.ASYM), 64),
+    (orc.KIND_INNER, 2, 64, (orc.HYBRID, orc.HYBRID), 256),
     (orc.KIND_INNER, 3, 64, (orc.HYBRID, orc.HYBRID), 257), (orc.KIND_INNER, 2, 32, (orc.HYBRID, orc.SYM), 65),       # beyond the lines: a group a lane
+    (orc.KIND_INNER, 3, 32, (orc.SYM, orc.HYBRID), 193), (orc.KIND_INNER, 3, 32, (orc.SYM, orc.HYBRID), 256),
     (orc.KIND_OUTER, 4, 32, (orc.HYBRID, orc.SYM), 5), (orc.KIND_OUTER, 3, 64, (orc.ASYM, orc.HYBRID), 2),
 ])
 @pytest.mark.parametrize("dist", ["normal", "ties", "denormal"])
